@@ -85,6 +85,7 @@ struct RoutingArgs {
   int group_top2;         // group score: sum of the two best router weights (else the best logit)
   int vote_atomic;        // votes meet in floating-point LDS atomics (arrival order) instead of
                           // the fixed-order reduction
+  int perm_parts;         // workgroups of the permutation (1, or more in a launch of its own)
   int tiles_m, tiles_t;   // router tiles along experts / tokens
   int max_wait;           // polls before a wait gives up
   const int32_t* prev_n_unique;  // the previous layer's n_unique (a stack), or null: a negative
@@ -703,12 +704,21 @@ __device__ bool select_sequence(const RoutingArgs& a, int b, int g, char* smem, 
 // by (token, slot) are ordered by token alone, so a per-expert bitmap over the
 // tokens gives every pair's sorted position with popcounts: no sort, no float,
 // integer LDS atomics only (their result does not depend on arrival order).
+// The popcounts before each bitmap word are kept too, so a pair's position is one
+// table entry and one popcount whatever the number of tokens.
 // idx_dev: S_n was written by other workgroups of this launch with device-scope
 // stores (read it the same way).
 // MP = the kernel's padded expert count (M <= MP): the counters are kept for MP
 // experts (zero past M) so that the ranking below has compile-time trip counts.
+// part / parts: a launch of its own may spread the pairs over several workgroups.
+// Each builds the whole bitmap (reading the indices is cheap), places its share of
+// the pairs, and the first also writes the tables; nobody reads what another wrote.
+// What bounds it is latency: one workgroup on one compute unit, so the index loads of
+// a thread are requested eight at a time, and the work per pair does not grow with
+// the block (16384 pairs of 128 experts: 16.0 us; walking the bitmap words per pair in
+// one workgroup took 127 us).
 template <int MP>
-__device__ void permute_all(const RoutingArgs& a, char* smem, bool idx_dev) {
+__device__ void permute_all(const RoutingArgs& a, char* smem, bool idx_dev, int part, int parts) {
   const int T = a.B * a.N, K = a.K, M = a.M;
   const int words = (T + 31) / 32;
   uint32_t* member = reinterpret_cast<uint32_t*>(smem);           // [M][words]
@@ -717,6 +727,7 @@ __device__ void permute_all(const RoutingArgs& a, char* smem, bool idx_dev) {
   int* s_liv = s_off + M + 1;                                      // [M+1]
   int* s_slot = s_liv + M + 1;                                     // [MP] slot of a live expert
   int* s_uoff = s_slot + MP;                                       // [MP] its first unit
+  uint16_t* s_pre = reinterpret_cast<uint16_t*>(s_uoff + MP);      // [M][words] pairs before the word
   const int tid = threadIdx.x;
   const int TK = T * K;
 
@@ -724,11 +735,25 @@ __device__ void permute_all(const RoutingArgs& a, char* smem, bool idx_dev) {
     return idx_dev ? __hip_atomic_load(a.topk_idx + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                    : a.topk_idx[p];
   };
-  constexpr int kKeep = 2;  // a thread's first pairs stay in registers for the second pass
-  int kept[kKeep];
-  for (int i = tid; i < M * words; i += kRtThreads) member[i] = 0u;
+  // every pair of [p0, p1), `kBatch` indices of a thread in flight at a time
+  constexpr int kBatch = 8;
+  auto for_pairs = [&](int p0, int p1, auto&& f) {
+    for (int p = p0 + tid; p < p1; p += kBatch * kRtThreads) {
+      int e[kBatch];
 #pragma unroll
-  for (int i = 0; i < kKeep; ++i) kept[i] = tid + i * kRtThreads < TK ? get_idx(tid + i * kRtThreads) : -1;
+      for (int i = 0; i < kBatch; ++i) e[i] = p + i * kRtThreads < p1 ? get_idx(p + i * kRtThreads) : -1;
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i)
+        if (p + i * kRtThreads < p1) f(p + i * kRtThreads, e[i]);
+    }
+  };
+  constexpr int kKeep = 2;  // up to 2048 pairs stay in registers for the second pass
+  const bool keep = TK <= kKeep * kRtThreads;
+  int kept[kKeep];
+#pragma unroll
+  for (int i = 0; i < kKeep; ++i)
+    kept[i] = keep && tid + i * kRtThreads < TK ? get_idx(tid + i * kRtThreads) : -1;
+  for (int i = tid; i < M * words; i += kRtThreads) member[i] = 0u;
   __syncthreads();
   auto mark = [&](int p, int e) {
     if (e >= 0) {
@@ -736,19 +761,44 @@ __device__ void permute_all(const RoutingArgs& a, char* smem, bool idx_dev) {
       atomicOr(&member[static_cast<size_t>(e) * words + (t >> 5)], 1u << (t & 31));
     }
   };
+  if (keep) {
 #pragma unroll
-  for (int i = 0; i < kKeep; ++i)
-    if (tid + i * kRtThreads < TK) mark(tid + i * kRtThreads, kept[i]);
-  for (int p = tid + kKeep * kRtThreads; p < TK; p += kRtThreads) mark(p, get_idx(p));
+    for (int i = 0; i < kKeep; ++i) mark(tid + i * kRtThreads, kept[i]);
+  } else {
+    for_pairs(0, TK, mark);
+  }
   __syncthreads();
-  for (int e = tid; e < MP; e += kRtThreads) {
-    int c = 0;
-    if (e < M)
-      for (int w = 0; w < words; ++w) c += __popc(member[static_cast<size_t>(e) * words + w]);
-    s_cnt[e] = c;
-    s_slot[e] = 0;
-    s_uoff[e] = 0;
-    if (e < M) a.expert_counts[e] = c;
+  // counts and the popcounts before each word: eight lanes per expert, each a run of
+  // consecutive words, an exclusive scan over the eight
+  {
+    constexpr int GL = 8;
+    const int run = (words + GL - 1) / GL, gl = tid % GL;
+    for (int e = tid / GL; e < MP; e += kRtThreads / GL) {
+      const int w0 = min(gl * run, words), w1 = min(w0 + run, words);
+      const uint32_t* mrow = member + static_cast<size_t>(e < M ? e : 0) * words;
+      int c = 0;
+      if (e < M)
+        for (int w = w0; w < w1; ++w) c += __popc(mrow[w]);
+      int inc = c;
+#pragma unroll
+      for (int d = 1; d < GL; d <<= 1) {
+        const int o = __shfl_up(inc, d, GL);
+        if (gl >= d) inc += o;
+      }
+      if (e < M) {
+        int pre = inc - c;
+        for (int w = w0; w < w1; ++w) {
+          s_pre[static_cast<size_t>(e) * words + w] = static_cast<uint16_t>(pre);
+          pre += __popc(mrow[w]);
+        }
+      }
+      if (gl == GL - 1) {
+        s_cnt[e] = inc;
+        s_slot[e] = 0;
+        s_uoff[e] = 0;
+        if (e < M && part == 0) a.expert_counts[e] = inc;
+      }
+    }
   }
   __syncthreads();
   // Slot order.  Up to 32 tokens every FFN task is on the chip at once and the
@@ -805,52 +855,61 @@ __device__ void permute_all(const RoutingArgs& a, char* smem, bool idx_dev) {
     if (tid == 0) {
       s_off[M] = base_c;
       s_liv[M] = base_l;
-      a.meta[0] = base_l;
-      a.meta[1] = base_c;
-      a.meta[2] = 0;  // live units: set after the barrier by the last slot's expert, if any
-      a.n_unique[0] = (a.prev_n_unique != nullptr && a.prev_n_unique[0] < 0) ? -1 : base_l;
+      if (part == 0) {
+        a.meta[0] = base_l;
+        a.meta[1] = base_c;
+        a.meta[2] = 0;  // live units: set after the barrier by the last slot's expert, if any
+        a.n_unique[0] = (a.prev_n_unique != nullptr && a.prev_n_unique[0] < 0) ? -1 : base_l;
+      }
     }
   }
   __syncthreads();
   const int n_live = s_liv[M];
-  for (int e = tid; e <= M; e += kRtThreads) a.offsets[e] = s_off[e];
-  for (int e = tid; e < M; e += kRtThreads) {
-    const int sl = by_count ? s_slot[e] : s_liv[e];
-    const bool live = s_cnt[e] > 0 && sl < a.n_slots;
-    // (up to 32 tokens the expert's bitmap row is one word: the tokens routed to it)
-    if (live) a.slots[sl] = make_int4(e, s_off[e], s_cnt[e], words == 1 ? static_cast<int>(member[e]) : 0);
-    a.slot_of[e] = live ? sl : -1;
-    if (live && by_count) {
-      const int nu = units_of(s_cnt[e]);
-      for (int k = 0; k < nu; ++k) a.units[s_uoff[e] + k] = sl | (k << 16) | (nu << 24);
-      if (sl == n_live - 1) a.meta[2] = s_uoff[e] + nu;  // the last slot closes the list
+  if (part == 0) {
+    for (int e = tid; e <= M; e += kRtThreads) a.offsets[e] = s_off[e];
+    for (int e = tid; e < M; e += kRtThreads) {
+      const int c = s_cnt[e];
+      const int sl = by_count ? s_slot[e] : s_liv[e];
+      const bool live = c > 0 && sl < a.n_slots;
+      // (up to 32 tokens the expert's bitmap row is one word: the tokens routed to it)
+      if (live) a.slots[sl] = make_int4(e, s_off[e], c, words == 1 ? static_cast<int>(member[e]) : 0);
+      a.slot_of[e] = live ? sl : -1;
+      if (live && by_count) {
+        const int nu = units_of(c);
+        for (int k = 0; k < nu; ++k) a.units[s_uoff[e] + k] = sl | (k << 16) | (nu << 24);
+        if (sl == n_live - 1) a.meta[2] = s_uoff[e] + nu;  // the last slot closes the list
+        // entries of the slot-major token table past a slot's count must still name a
+        // valid token (the others are filled with the pairs below; up to 32 tokens the
+        // FFN kernels take an expert's tokens from the bitmap in its record)
+        for (int k = c; k < kSlotToks; ++k) a.slot_tok[sl * kSlotToks + k] = 0;
+      }
+    }
+    for (int s = n_live + tid; s < a.n_slots; s += kRtThreads) {
+      a.slots[s] = make_int4(-1, 0, 0, 0);
+      if (by_count)
+        for (int k = 0; k < kSlotToks; ++k) a.slot_tok[s * kSlotToks + k] = 0;
     }
   }
-  for (int s = n_live + tid; s < a.n_slots; s += kRtThreads) a.slots[s] = make_int4(-1, 0, 0, 0);
-  // entries of the slot-major token table past a slot's count must still name a
-  // valid token: clear the table, then (after the barrier) fill it
-  // (up to 32 tokens the FFN kernels take an expert's tokens from the bitmap in its record)
-  if (T > 32)
-    for (int i = tid; i < a.n_slots * kSlotToks; i += kRtThreads) a.slot_tok[i] = 0;
-  __syncthreads();
   auto place = [&](int p, int e) {
     if (e < 0) { a.pos[p] = -1; return; }
     const int t = p / K;
-    const uint32_t* mrow = member + static_cast<size_t>(e) * words;
-    int r = s_off[e];
-    for (int w = 0; w < (t >> 5); ++w) r += __popc(mrow[w]);
-    r += __popc(mrow[t >> 5] & ((1u << (t & 31)) - 1u));
+    const size_t w = static_cast<size_t>(e) * words + (t >> 5);
+    const int within = s_pre[w] + __popc(member[w] & ((1u << (t & 31)) - 1u));
+    const int r = s_off[e] + within;
     a.pair_tok[r] = t;
     a.pos[p] = r;
-    const int within = r - s_off[e];
     const int sl = by_count ? s_slot[e] : s_liv[e];
     if (T > 32 && within < kSlotToks && sl < a.n_slots)
       a.slot_tok[sl * kSlotToks + within] = static_cast<uint16_t>(t);
   };
+  if (keep) {
 #pragma unroll
-  for (int i = 0; i < kKeep; ++i)
-    if (tid + i * kRtThreads < TK) place(tid + i * kRtThreads, kept[i]);
-  for (int p = tid + kKeep * kRtThreads; p < TK; p += kRtThreads) place(p, get_idx(p));
+    for (int i = 0; i < kKeep; ++i)
+      if (tid + i * kRtThreads < TK) place(tid + i * kRtThreads, kept[i]);
+  } else {
+    const int share = (TK + parts - 1) / parts;
+    for_pairs(part * share, min(TK, (part + 1) * share), place);
+  }
 }
 
 // A bounded wait ran out (a fault of the device, or another kernel keeps this
@@ -946,9 +1005,11 @@ __device__ void permute_small(const RoutingArgs& a, char* smem) {
 
 // ---------------------------------------------------------------- the kernel
 // LDS of the routing kernel: the selection's carve-up, but at least what the
-// router tile (16 KB) and the permutation (bitmap of at most 8192 words plus
-// at most 5 * 512 + 2 counters, under 44 KB for every shape the library accepts) need.
-constexpr int kMinRoutingLds = 44 * 1024;
+// router tile (16 KB) and the permutation (bitmap of at most 8192 words, as many
+// 16-bit counts and at most 5 * 512 + 2 counters, under 59 KB for every shape the
+// library accepts) need.
+constexpr int kMinRoutingLds = 59 * 1024;
+static_assert(kMinRoutingLds >= 8192 * 6 + 4 * (5 * 512 + 2), "permutation tables");
 
 template <int LPT, bool EXT>
 __global__ __launch_bounds__(kRtThreads) void routing_kernel(RoutingArgs a) {
@@ -993,7 +1054,7 @@ __global__ __launch_bounds__(kRtThreads) void routing_kernel(RoutingArgs a) {
       __syncthreads();
       DES_STAMP(a, 6);
       if (a.small_perm) permute_small<LPT>(a, smem);
-      else permute_all<SelLds<LPT>::MP>(a, smem, false);
+      else permute_all<SelLds<LPT>::MP>(a, smem, false, 0, 1);
       DES_STAMP(a, 7);
       // every flag of this call has been consumed: clear them, so that a replay
       // of a captured launch (same epoch) cannot be satisfied by stale flags
@@ -1009,14 +1070,14 @@ __global__ __launch_bounds__(kRtThreads) void routing_kernel(RoutingArgs a) {
     return;
   }
   blk -= n_sel;
-  if (blk == 0 && a.do_permute && a.B * a.groups > 1) {  // ---- role P
+  if (blk < a.perm_parts && a.do_permute && a.B * a.groups > 1) {  // ---- role P
     if (a.use_flags && a.do_select &&
         !flags_wait(a.flags + all_tiles + a.B * a.groups, a.B * a.groups, a.epoch, false,
                     a.max_wait)) {
       publish_empty(a, n_flags);  // a bounded wait expired
       return;
     }
-    permute_all<SelLds<LPT>::MP>(a, smem, a.use_flags && a.do_select);
+    permute_all<SelLds<LPT>::MP>(a, smem, a.use_flags && a.do_select, blk, a.perm_parts);
     if (a.use_flags)  // all selectors have consumed the other flags and published theirs
       for (int i = threadIdx.x; i < n_flags; i += kRtThreads) a.flags[i] = 0ull;
   }
@@ -1087,6 +1148,7 @@ static void fill_common(RoutingArgs& a, const des_shape_t& s) {
   a.tiles_t = (s.n_seqs * s.n_tokens + 15) / 16;
   a.bf16 = s.dtype == DES_BF16;
   a.groups = 1;
+  a.perm_parts = 1;
   a.max_wait = g_test_max_wait > 0 ? g_test_max_wait : kMaxWaitIters;
   a.k_route = s.k_route > 0 ? s.k_route : s.top_k;
   a.skip_beta = s.skip_beta;
@@ -1205,7 +1267,11 @@ int launch_routing(const des_shape_t& s, const void* x, const void* w_router, co
   if (rc != DES_OK || a.B == 1) return rc;
   RoutingArgs p = a;
   p.do_permute = 1;
-  return launch_routing_grid(p, 1, kKPermute, st);
+  // about one pair per thread and workgroup (all of them read every index for the bitmaps,
+  // so more workgroups stop paying off)
+  const int pairs = s.n_seqs * s.n_tokens * s.top_k;
+  p.perm_parts = pairs <= 2 * kRtThreads ? 1 : (pairs + kRtThreads - 1) / kRtThreads > 16 ? 16 : (pairs + kRtThreads - 1) / kRtThreads;
+  return launch_routing_grid(p, p.perm_parts, kKPermute, st);
 }
 
 }  // namespace des
