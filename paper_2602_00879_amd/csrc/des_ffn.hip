@@ -100,11 +100,77 @@ __device__ __forceinline__ bf16x8 zero8() {
   return z;
 }
 
+// The weight stream of one wavefront: `steps` stages in two register sets.  load(st, set)
+// requests stage st, compute(set) multiplies it.  The trips carry no branch, so the
+// compiler waits for exactly the stage it needs and the next one stays in flight (with a
+// test for the end around each load it waited for everything outstanding); the scheduling
+// barriers keep a stage's loads together in front of the multiplies.  More sets do not
+// help: what bounds these kernels is the chip's read rate and its spread over the compute
+// units (128-expert layer, 32 tokens: 34.4 us with two, three or four sets of two k-steps;
+// where fewer wavefronts are in flight the branch-free form pays: 16 of 256 experts 22.3 ->
+// 20.0 us, 4 tokens 20.2 -> 18.6 us, the down projections 12.1 -> 11.1 and 12.0 -> 10.6).
+template <typename Load, typename Compute>
+__device__ __forceinline__ void stream_pipeline(int steps, Load&& load, Compute&& compute) {
+  if (steps > 0) load(0, S0{});
+  int st = 0;
+  for (; st + 3 <= steps; st += 2) {
+    load(st + 1, S1{});
+    __builtin_amdgcn_sched_barrier(0);
+    compute(S0{});
+    __builtin_amdgcn_sched_barrier(0);
+    load(st + 2, S0{});
+    __builtin_amdgcn_sched_barrier(0);
+    compute(S1{});
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (st < steps) {
+    if (st + 1 < steps) load(st + 1, S1{});
+    compute(S0{});
+    if (st + 1 < steps) compute(S1{});
+  }
+}
+
+// Row-major weights.  An MFMA A operand takes 16 rows x 32 elements, 64 bytes of each
+// row: a load in operand order touches 16 half lines, and the kernels then ran at 3.6 TB/s
+// where packed tiles reach 5.8 (33 experts of 2048 x 768: gate/up 58.4 us, down 31.8 us; as
+// below 44.4 and 23.2, packed 42.5 and 21.8).  So row-major tiles are loaded in whole 128-byte lines (a load = 8 rows x 64 elements, lane l has
+// piece l % 8 of row l / 8) and turned into operand order through a few KB of LDS that
+// belong to the wavefront alone: two loads (v[0], v[1]: rows 0-7 and 8-15) become the
+// operands of two k-steps.  16-byte piece p of row r is kept at piece p ^ (r / 2 % 8), so
+// writes and reads both spread over all banks.
+constexpr int kTurnBytes = 2048;  // of LDS per 16 x 64 tile
+__device__ __forceinline__ void turn_write(const bf16x8& v0, const bf16x8& v1, char* tile, int lane) {
+  const int r = lane >> 3, p = lane & 7;
+  *reinterpret_cast<bf16x8*>(tile + r * 128 + ((p ^ (r >> 1)) << 4)) = v0;
+  *reinterpret_cast<bf16x8*>(tile + (r + 8) * 128 + ((p ^ ((r >> 1) + 4)) << 4)) = v1;
+}
+__device__ __forceinline__ bf16x8 turn_read(const char* tile, int u, int lane) {
+  const int r = lane & 15, p = u * 4 + (lane >> 4);
+  return *reinterpret_cast<const bf16x8*>(tile + r * 128 + ((p ^ (r >> 1)) << 4));
+}
+// the wavefront's LDS accesses stay in program order (they execute in order)
+__device__ __forceinline__ void turn_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+// This lane's place in the loads of row tile rt: packed tiles are in operand order already.
+template <bool PACKED>
+__device__ __forceinline__ const uint16_t* load_ptr(const uint16_t* base, int rt, int kd, int lane) {
+  if (PACKED) return frag_ptr<true>(base, rt, kd, lane);
+  return base + (static_cast<size_t>(rt) * 16 + (lane >> 3)) * kd + (lane & 7) * 8;
+}
+// Load i of a tile's stream: k-step i (packed), or half i % 2 of 64-element block i / 2.
+template <bool PACKED>
+__device__ __forceinline__ size_t load_off(int i, int kd) {
+  return PACKED ? static_cast<size_t>(i) * 512 : static_cast<size_t>(i & 1) * 8 * kd + (i >> 1) * 64;
+}
+
 // gate/up for pairs [g0, g0 + 16*NT) of the task, intermediate rows
 // (ft0 .. ft0+FT-1)*16..+15.  The FT row tiles share every token fragment.
 template <int FT, int NT, int U, bool PACKED>
 __device__ __forceinline__ void gateup_group(const FfnArgs& a, const Task& t, int ft0, int g0,
-                                             int lane) {
+                                             int lane, char* turn) {
+  static_assert(PACKED || U % 2 == 0, "row-major stages are whole 64-element blocks");
   const int D = a.D;
   const int nks = D / 32;
   const uint16_t* x = static_cast<const uint16_t*>(a.x);
@@ -112,8 +178,8 @@ __device__ __forceinline__ void gateup_group(const FfnArgs& a, const Task& t, in
   const uint16_t* up[FT];
 #pragma unroll
   for (int f = 0; f < FT; ++f) {
-    gp[f] = frag_ptr<PACKED>(t.w0, ft0 + f, D, lane);
-    up[f] = frag_ptr<PACKED>(t.w1, ft0 + f, D, lane);
+    gp[f] = load_ptr<PACKED>(t.w0, ft0 + f, D, lane);
+    up[f] = load_ptr<PACKED>(t.w1, ft0 + f, D, lane);
   }
   const uint16_t* xp[NT];
 #pragma unroll
@@ -134,32 +200,40 @@ __device__ __forceinline__ void gateup_group(const FfnArgs& a, const Task& t, in
       accu[f][i] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
   bf16x8 ag[2][U][FT], au[2][U][FT], bx[2][U][NT];
-
-  auto load = [&](int ks, auto stage) {
+  auto load = [&](int st, auto stage) {
     constexpr int s = decltype(stage)::value;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (ks + u < nks) {
+      const int ks = st * U + u;
 #pragma unroll
-        for (int f = 0; f < FT; ++f) {
-          ag[s][u][f] = ld8_stream(gp[f] + static_cast<size_t>(ks + u) * frag_step<PACKED>());
-          au[s][u][f] = ld8_stream(up[f] + static_cast<size_t>(ks + u) * frag_step<PACKED>());
-        }
-#pragma unroll
-        for (int i = 0; i < NT; ++i) bx[s][u][i] = ld8(xp[i] + (ks + u) * 32);
-      } else {
-#pragma unroll
-        for (int f = 0; f < FT; ++f) {
-          ag[s][u][f] = zero8();
-          au[s][u][f] = zero8();
-        }
-#pragma unroll
-        for (int i = 0; i < NT; ++i) bx[s][u][i] = zero8();
+      for (int f = 0; f < FT; ++f) {
+        ag[s][u][f] = ld8_stream(gp[f] + load_off<PACKED>(ks, D));
+        au[s][u][f] = ld8_stream(up[f] + load_off<PACKED>(ks, D));
       }
+#pragma unroll
+      for (int i = 0; i < NT; ++i) bx[s][u][i] = ld8(xp[i] + ks * 32);
     }
   };
   auto compute = [&](auto stage) {
     constexpr int s = decltype(stage)::value;
+    if constexpr (!PACKED) {
+      turn_fence();
+#pragma unroll
+      for (int u = 0; u < U; u += 2)
+#pragma unroll
+        for (int f = 0; f < FT; ++f) {
+          turn_write(ag[s][u][f], ag[s][u + 1][f], turn + (u / 2 * 2 * FT + 2 * f) * kTurnBytes, lane);
+          turn_write(au[s][u][f], au[s][u + 1][f], turn + (u / 2 * 2 * FT + 2 * f + 1) * kTurnBytes, lane);
+        }
+      turn_fence();
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int f = 0; f < FT; ++f) {
+          ag[s][u][f] = turn_read(turn + (u / 2 * 2 * FT + 2 * f) * kTurnBytes, u & 1, lane);
+          au[s][u][f] = turn_read(turn + (u / 2 * 2 * FT + 2 * f + 1) * kTurnBytes, u & 1, lane);
+        }
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -170,12 +244,21 @@ __device__ __forceinline__ void gateup_group(const FfnArgs& a, const Task& t, in
           accu[f][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(au[s][u][f], bx[s][u][i], accu[f][i], 0, 0, 0);
         }
   };
-  load(0, S0{});
-  for (int ks = 0; ks < nks; ks += 2 * U) {
-    load(ks + U, S1{});
-    compute(S0{});
-    load(ks + 2 * U, S0{});
-    compute(S1{});
+  stream_pipeline(nks / U, load, compute);
+  for (int ks = nks / U * U; ks < nks; ++ks) {  // k-steps left over by the stages
+    bf16x8 x1[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) x1[i] = ld8(xp[i] + ks * 32);
+#pragma unroll
+    for (int f = 0; f < FT; ++f) {
+      const bf16x8 g1 = ld8_stream(frag_ptr<PACKED>(t.w0, ft0 + f, D, lane) + static_cast<size_t>(ks) * frag_step<PACKED>());
+      const bf16x8 u1 = ld8_stream(frag_ptr<PACKED>(t.w1, ft0 + f, D, lane) + static_cast<size_t>(ks) * frag_step<PACKED>());
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        accg[f][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g1, x1[i], accg[f][i], 0, 0, 0);
+        accu[f][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u1, x1[i], accu[f][i], 0, 0, 0);
+      }
+    }
   }
   uint16_t* h = static_cast<uint16_t*>(a.h);
 #pragma unroll
@@ -289,14 +372,9 @@ __device__ __forceinline__ FfnArgs shared_view(const FfnArgs& a, Task& t, size_t
 constexpr int kFfnWaves = DES_FFN_WAVES;  // wavefronts per workgroup; each is an independent task
 constexpr int kGuTiles = 2;   // gate/up row tiles per task (F % 32 == 0, so F/16 is even)
 
-// MAXNT bounds the token tiles a task can have (the host knows T >= any expert's
-// count), so that small blocks get a kernel with few registers.  U1 / U2 are
-// the k-steps per prefetch stage of the one- and two-token-tile paths; two
-// stages of two k-steps measured best on the 128-expert layer (34.3 us against
-// 36.2 us for four and 34.5 us for one).
 // One gate/up task (see the kernel comment): returns false if the slot is unused.
 template <int MAXNT, bool PACKED, int U1 = 2, int U2 = 2, int GT = kGuTiles>
-__device__ __forceinline__ bool gateup_task(const FfnArgs& a, int task, int lane) {
+__device__ __forceinline__ bool gateup_task(const FfnArgs& a, int task, int lane, char* turn) {
   const int tiles_r = a.F / (16 * GT);
   const int routed = a.n_slots * tiles_r;
   Task t;
@@ -315,31 +393,31 @@ __device__ __forceinline__ bool gateup_task(const FfnArgs& a, int task, int lane
   const int nt = (t.count + 15) / 16;
   bool done = false;
   if (MAXNT == 1 || nt <= 1) {
-    gateup_group<GT, 1, U1, PACKED>(v, t, ft, 0, lane);
+    gateup_group<GT, 1, U1, PACKED>(v, t, ft, 0, lane, turn);
     done = true;
   }
   if constexpr (MAXNT >= 2) {
     if (!done && (MAXNT == 2 || nt <= 2)) {
-      gateup_group<GT, 2, U2, PACKED>(v, t, ft, 0, lane);
+      gateup_group<GT, 2, U2, PACKED>(v, t, ft, 0, lane, turn);
       done = true;
     }
   }
   if constexpr (MAXNT >= 4) {
     if (!done && (MAXNT == 4 || nt <= 4)) {
-      gateup_group<GT, 4, 2, PACKED>(v, t, ft, 0, lane);
+      gateup_group<GT, 4, 2, PACKED>(v, t, ft, 0, lane, turn);
       done = true;
     }
   }
   if constexpr (MAXNT >= 8) {
     if (!done && (MAXNT == 8 || nt <= 8)) {
-      gateup_group<GT, 8, 1, PACKED>(v, t, ft, 0, lane);
+      gateup_group<GT, 8, PACKED ? 1 : 2, PACKED>(v, t, ft, 0, lane, turn);
       done = true;
     }
   }
   if constexpr (MAXNT >= 16) {
     if (!done)
       for (int g0 = 0; g0 < t.count; g0 += 256)
-        for (int f = 0; f < GT; ++f) gateup_group<1, 16, 1, PACKED>(v, t, ft + f, g0, lane);
+        for (int f = 0; f < GT; ++f) gateup_group<1, 16, PACKED ? 1 : 2, PACKED>(v, t, ft + f, g0, lane, turn);
   }
   DES_FSTAMP(task, 2);
 #ifdef DES_FFN_STAMPS
@@ -352,9 +430,7 @@ __device__ __forceinline__ bool gateup_task(const FfnArgs& a, int task, int lane
 
 // MAXNT bounds the token tiles a task can have (the host knows T >= any expert's
 // count), so that small blocks get a kernel with few registers.  U1 / U2 are
-// the k-steps per prefetch stage of the one- and two-token-tile paths; two
-// stages of two k-steps measured best on the 128-expert layer (34.3 us against
-// 36.2 us for four and 34.5 us for one).
+// the k-steps per stage of the one- and two-token-tile paths.
 // GT = row tiles per task: 2 normally, 1 when the launch would otherwise have
 // too few wavefronts to keep enough bytes in flight (small coresets).
 template <int MAXNT, bool PACKED, int U1 = 2, int U2 = 2, int GT = kGuTiles>
@@ -384,19 +460,24 @@ __global__ __launch_bounds__(kFfnWaves* kWave) void gateup_bf16_kernel(FfnArgs a
     }
   }
   const int tasks = a.n_slots * (a.F / (16 * GT)) + a.Fs / (16 * GT);
-  if (task < tasks) gateup_task<MAXNT, PACKED, U1, U2, GT>(a, task, lane);
+  // row-major: the stage's tiles (2 per row tile, U k-steps) in operand order, per wavefront
+  constexpr int kUmax = (U1 > U2 ? U1 : U2) > 2 ? (U1 > U2 ? U1 : U2) : 2;
+  constexpr int kTurn = PACKED ? 16 : kUmax / 2 * 2 * GT * kTurnBytes;
+  __shared__ __align__(16) char s_turn[kFfnWaves * kTurn];
+  if (task < tasks) gateup_task<MAXNT, PACKED, U1, U2, GT>(a, task, lane, s_turn + (threadIdx.x >> 6) * kTurn);
 }
 
 // down for pairs [g0, g0+16*NT), output rows (dt0 .. dt0+RT-1)*16
 template <int RT, int NT, int U, bool PACKED>
 __device__ __forceinline__ void down_group(const FfnArgs& a, const Task& t, int dt0, int g0,
-                                           int lane) {
+                                           int lane, char* turn) {
+  static_assert(PACKED || U % 2 == 0, "row-major stages are whole 64-element blocks");
   const int F = t.fdim;
   const int nks = F / 32;
   const uint16_t* h = static_cast<const uint16_t*>(a.h);
   const uint16_t* ap[RT];
 #pragma unroll
-  for (int r = 0; r < RT; ++r) ap[r] = frag_ptr<PACKED>(t.w0, dt0 + r, F, lane);
+  for (int r = 0; r < RT; ++r) ap[r] = load_ptr<PACKED>(t.w0, dt0 + r, F, lane);
   const uint16_t* hp[NT];
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
@@ -412,33 +493,33 @@ __device__ __forceinline__ void down_group(const FfnArgs& a, const Task& t, int 
 #pragma unroll
     for (int i = 0; i < NT; ++i) acc[r][i] = f32x4{0.f, 0.f, 0.f, 0.f};
   bf16x8 aw[2][U][RT], bh[2][U][NT];
-  auto load_w = [&](int ks, auto stage) {
+  auto load = [&](int st, auto stage) {
     constexpr int s = decltype(stage)::value;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+      const int ks = st * U + u;
 #pragma unroll
       for (int r = 0; r < RT; ++r)
-        aw[s][u][r] = (ks + u < nks)
-                          ? ld8_stream(ap[r] + static_cast<size_t>(ks + u) * frag_step<PACKED>())
-                          : zero8();
-    }
-  };
-  auto load_h = [&](int ks, auto stage) {
-    constexpr int s = decltype(stage)::value;
+        aw[s][u][r] = ld8_stream(ap[r] + load_off<PACKED>(ks, F));
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-#pragma unroll
-      for (int i = 0; i < NT; ++i)
-        bh[s][u][i] = (ks + u < nks) ? ld8(hp[i] + (ks + u) * 32)
-                                     : zero8();
+      for (int i = 0; i < NT; ++i) bh[s][u][i] = ld8(hp[i] + ks * 32);
     }
-  };
-  auto load = [&](int ks, auto stage) {
-    load_w(ks, stage);
-    load_h(ks, stage);
   };
   auto compute = [&](auto stage) {
     constexpr int s = decltype(stage)::value;
+    if constexpr (!PACKED) {
+      turn_fence();
+#pragma unroll
+      for (int u = 0; u < U; u += 2)
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+          turn_write(aw[s][u][r], aw[s][u + 1][r], turn + (u / 2 * RT + r) * kTurnBytes, lane);
+      turn_fence();
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) aw[s][u][r] = turn_read(turn + (u / 2 * RT + r) * kTurnBytes, u & 1, lane);
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -448,12 +529,18 @@ __device__ __forceinline__ void down_group(const FfnArgs& a, const Task& t, int 
           acc[r][i] =
               __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[s][u][r], bh[s][u][i], acc[r][i], 0, 0, 0);
   };
-  load(0, S0{});
-  for (int ks = 0; ks < nks; ks += 2 * U) {
-    load(ks + U, S1{});
-    compute(S0{});
-    load(ks + 2 * U, S0{});
-    compute(S1{});
+  stream_pipeline(nks / U, load, compute);
+  for (int ks = nks / U * U; ks < nks; ++ks) {  // k-steps left over by the stages
+    bf16x8 h1[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) h1[i] = ld8(hp[i] + ks * 32);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      const bf16x8 w1 = ld8_stream(frag_ptr<PACKED>(t.w0, dt0 + r, F, lane) + static_cast<size_t>(ks) * frag_step<PACKED>());
+#pragma unroll
+      for (int i = 0; i < NT; ++i)
+        acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, h1[i], acc[r][i], 0, 0, 0);
+    }
   }
   const size_t orow0 = t.shared ? static_cast<size_t>(a.T) * a.K : static_cast<size_t>(t.pair0);
 #pragma unroll
@@ -478,7 +565,7 @@ __device__ __forceinline__ void down_group(const FfnArgs& a, const Task& t, int 
 
 // One down task: 64 output rows of one expert for all of its pairs.
 template <int MAXNT, bool PACKED, int U1 = 2, int U2 = 2, int RTG = 4>
-__device__ __forceinline__ bool down_task(const FfnArgs& a, int task, int lane) {
+__device__ __forceinline__ bool down_task(const FfnArgs& a, int task, int lane, char* turn) {
   const int dtiles = a.D / 16;
   const int groups = (dtiles + RTG - 1) / RTG;  // 16 * RTG output rows per task
   const int routed = a.n_slots * groups;
@@ -500,25 +587,25 @@ __device__ __forceinline__ bool down_task(const FfnArgs& a, int task, int lane) 
   bool done = false;
   if (dt_end - dt_begin == RTG) {
     if (MAXNT == 1 || nt <= 1) {
-      down_group<RTG, 1, U1, PACKED>(v, t, dt_begin, 0, lane);
+      down_group<RTG, 1, U1, PACKED>(v, t, dt_begin, 0, lane, turn);
       done = true;
     }
     if constexpr (MAXNT >= 2) {
       if (!done && (MAXNT == 2 || nt <= 2)) {
-        down_group<RTG, 2, U2, PACKED>(v, t, dt_begin, 0, lane);
+        down_group<RTG, 2, U2, PACKED>(v, t, dt_begin, 0, lane, turn);
         done = true;
       }
     }
     if constexpr (MAXNT >= 4) {
       if (!done && (MAXNT == 4 || nt <= 4)) {
-        down_group<RTG, 4, 1, PACKED>(v, t, dt_begin, 0, lane);
+        down_group<RTG, 4, PACKED ? 1 : 2, PACKED>(v, t, dt_begin, 0, lane, turn);
         done = true;
       }
     }
     if constexpr (MAXNT >= 8) {
       if (!done && (MAXNT == 8 || nt <= 8)) {
         for (int r2 = 0; r2 < RTG; r2 += 2)
-          down_group<2, 8, 1, PACKED>(v, t, dt_begin + r2, 0, lane);
+          down_group<2, 8, PACKED ? 1 : 2, PACKED>(v, t, dt_begin + r2, 0, lane, turn);
         done = true;
       }
     }
@@ -526,10 +613,10 @@ __device__ __forceinline__ bool down_task(const FfnArgs& a, int task, int lane) 
   if (!done) {  // ragged row group, or more than 128 pairs: one row tile at a time
     for (int dt = dt_begin; dt < dt_end; ++dt) {
       if constexpr (MAXNT <= 4) {
-        down_group<1, MAXNT, 2, PACKED>(v, t, dt, 0, lane);
+        down_group<1, MAXNT, 2, PACKED>(v, t, dt, 0, lane, turn);
       } else {
         for (int g0 = 0; g0 < t.count; g0 += 16 * MAXNT)
-          down_group<1, MAXNT, 1, PACKED>(v, t, dt, g0, lane);
+          down_group<1, MAXNT, PACKED ? 1 : 2, PACKED>(v, t, dt, g0, lane, turn);
       }
     }
   }
@@ -542,7 +629,10 @@ __global__ __launch_bounds__(kFfnWaves* kWave) void down_bf16_kernel(FfnArgs a) 
   const int task = blockIdx.x * kFfnWaves + (threadIdx.x >> 6);
   const int groups = (a.D / 16 + RTG - 1) / RTG;
   const int tasks = a.n_slots * groups + (a.Fs > 0 ? groups : 0);
-  if (task < tasks) down_task<MAXNT, PACKED, U1, U2, RTG>(a, task, lane);
+  constexpr int kUmax = (U1 > U2 ? U1 : U2) > 2 ? (U1 > U2 ? U1 : U2) : 2;
+  constexpr int kTurn = PACKED ? 16 : kUmax / 2 * RTG * kTurnBytes;
+  __shared__ __align__(16) char s_turn[kFfnWaves * kTurn];
+  if (task < tasks) down_task<MAXNT, PACKED, U1, U2, RTG>(a, task, lane, s_turn + (threadIdx.x >> 6) * kTurn);
 }
 
 // ------------------------------------------ larger blocks: activations via LDS
