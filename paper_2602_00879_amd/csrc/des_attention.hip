@@ -7,7 +7,7 @@
 // Three launches per sub-layer:
 //   1. q, k, v = x Wq^T, x Wk^T, x Wv^T     one dense-projection launch over the three
 //                                            weight matrices (bf16 MFMA, fp32 accumulate)
-//   2. softmax(q K^T / sqrt(dh)) V           one workgroup per (sequence, head), bf16 MFMA
+//   2. softmax(q K^T / sqrt(dh)) V           workgroups per (sequence, key/value head), bf16 MFMA
 //   3. y = heads Wo^T (+ x)                  the same projection kernel, residual fused
 // The projections are weight scans like the expert FFN (a 2048 x 2048 matrix is 8 MB for
 // at most a few hundred token rows), so they reuse its streaming building block: weights
@@ -326,32 +326,62 @@ struct AttnArgs {
   const uint16_t *k_cache, *v_cache;   // [B][Hkv][P][dh] cached positions (prefix, then suffix)
   uint16_t* o;                         // [T][H*dh] per-head outputs
   int B, N, H, Hkv, dh, P;
+  int splits, tiles;                   // of a workgroup: parts of the window x query tiles (wavefronts)
   float scale;                         // 1 / sqrt(dh)
 };
 
-// One workgroup (four wavefronts) per (sequence, query head); each wavefront takes tiles
-// of 16 queries.  Scores and the weighted sum of values are bf16 MFMA contractions with
-// fp32 accumulation, laid out so that no operand needs a transpose between them:
+// How the work of one (sequence, key/value head) is cut.  Its query rows - the block's
+// tokens under each query head that shares the keys - form tiles of 16; a wavefront takes
+// one tile and one part of the window, a workgroup up to eight wavefronts that share the
+// transposed values in LDS.  The window is cut further while the launch has fewer than
+// 2048 wavefronts (eight per compute unit), as long as a part keeps 64 positions (what a
+// wavefront requests at once anyway); then the tiles are spread over more workgroups until every compute unit has one (each
+// stages the values again, from L2).
+struct AttnPlan { int splits, tiles, groups; };
+static AttnPlan attn_plan(const AttnArgs& a) {
+  const int rows = a.H / a.Hkv * a.N, tiles = (rows + 15) / 16, steps = (a.P + a.N + 31) / 32;
+  const int heads = a.B * a.Hkv;
+  AttnPlan p{1, 8, 1};
+  while (p.splits < 8 && 4 * p.splits <= steps && heads * tiles * p.splits < 2048) p.splits *= 2;
+  p.tiles = 8 / p.splits;
+  while (p.tiles > 1 && heads * ((tiles + p.tiles - 1) / p.tiles) < 256) p.tiles /= 2;
+  if (p.tiles > tiles) p.tiles = tiles;
+  p.groups = (tiles + p.tiles - 1) / p.tiles;
+  return p;
+}
+
+// Both contractions are bf16 MFMA with fp32 accumulation, laid out so that no operand
+// needs a transpose between them:
 //   S^T = K Q^T    A = keys (16 per tile, straight from global memory), B = the 16 queries
 //                  -> lane l holds query l % 16, keys 4 (l / 16) .. + 3 of the tile
 //   O^T = V^T P^T  B = the weights of two score tiles as they sit in those registers (the
 //                  contraction only needs A and B to agree on which key a slot means),
 //                  A = values transposed in LDS, read with that same key order
 //                  -> lane l holds query l % 16, coordinates 4 (l / 16) .. + 3 of the tile
-// The softmax is two passes over the keys (maximum first, then weights and sums; the
-// scores are recomputed - a handful of MFMAs - when the window exceeds 64 positions)
-// instead of a running rescale; weights are
-// rounded to bf16 for the second contraction, their sum is kept in fp32.  Sums run in a
-// fixed order, so results are reproducible.
-__global__ __launch_bounds__(256) void attention_core_kernel(AttnArgs a) {
+// One pass over the keys, 64 at a time with the next 128 requested ahead, under a running
+// maximum (the accumulators are rescaled when it grows); the parts of a split window are
+// added through LDS in window order.  Weights are rounded to bf16 for the second
+// contraction, their sum is kept in fp32; all sums run in a fixed order.
+// What bounds it is latency - the loads behind one another, then the staging of the
+// values: eight sequences of 32 tokens over 496 positions, 32 heads on 4, take 20 us
+// (one workgroup per query head, half of its wavefronts idle, scores computed twice and
+// values transposed two bytes at a time: 49.6 us); one block over 64 positions 7.0 us
+// (6.9).  Of the 20 us the key loads cost 6 (an MFMA operand takes 64 bytes of 16 rows) and the
+// staging of the values 4.
+// NKS = 32-element steps of the head width.
+template <int NKS>
+__global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
+  constexpr int NDT = 2 * NKS;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   uint16_t* vt = reinterpret_cast<uint16_t*>(smem_raw);  // [ndt * 16][ldv]: values, transposed
   const int N = a.N, dh = a.dh, P = a.P, nk = a.P + a.N;
-  const int nkp = (nk + 31) & ~31, ldv = nkp + 4;
-  const int ndt = (dh + 15) / 16, nks = (dh + 31) / 32, nkt = (nk + 15) / 16;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int b = blockIdx.x / a.H, h = blockIdx.x % a.H;
-  const int g = h / (a.H / a.Hkv);
+  const int nkp = (nk + 31) & ~31, ldv = nkp + 4, steps = nkp / 32;
+  const int ndt = (dh + 15) / 16;
+  const int tid = threadIdx.x, lane = tid & 63, n_threads = blockDim.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = blockIdx.x / a.Hkv, g = blockIdx.x % a.Hkv;
+  const int rep = a.H / a.Hkv, rows = rep * N;
+  const int S = a.splits, part = wave % S;
   const size_t cbase = (static_cast<size_t>(b) * a.Hkv + g) * P * dh;
   const uint16_t* kc = a.k_cache + cbase;  // cached keys / values of this head (unused if P == 0)
   const uint16_t* vc = a.v_cache + cbase;
@@ -361,8 +391,8 @@ __global__ __launch_bounds__(256) void attention_core_kernel(AttnArgs a) {
   const int bstride = a.Hkv * dh;
   const int col = lane & 15, grp = lane >> 4;
   const float neg_inf = -__builtin_inff();
-  auto key_row = [&](int j) -> const uint16_t* {
-    return j < P ? kc + static_cast<size_t>(j) * dh : kb + static_cast<size_t>(j - P) * bstride;
+  auto row_of = [&](const uint16_t* cache, const uint16_t* block, int j) -> const uint16_t* {
+    return j < P ? cache + static_cast<size_t>(j) * dh : block + static_cast<size_t>(j - P) * bstride;
   };
   auto load8 = [&](const uint16_t* row, int s) -> bf16x8 {  // elements 32 s + 8 grp .. + 7, zeros past dh
     const int e = 32 * s + 8 * grp;
@@ -370,138 +400,192 @@ __global__ __launch_bounds__(256) void attention_core_kernel(AttnArgs a) {
     if (e < dh) raw = *reinterpret_cast<const uint4*>(row + e);
     return __builtin_bit_cast(bf16x8, raw);
   };
-  // values -> LDS, transposed; key slots beyond the window hold zeros (their weights are
-  // zero too, but 0 x garbage could be NaN).  A thread's first four pieces are requested
-  // here and written after the first pass over the keys, which does not need them: the
-  // three kinds of loads (values, queries, keys) then share one round trip.
-  const int vec = dh / 8, n_piece = nkp * vec;
-  auto value_piece = [&](int i) -> uint4 {
-    const int j = i / vec, c = (i % vec) * 8;
-    if (i >= n_piece || j >= nk) return make_uint4(0u, 0u, 0u, 0u);
-    const uint16_t* src = j < P ? vc + static_cast<size_t>(j) * dh : vb + static_cast<size_t>(j - P) * bstride;
-    return *reinterpret_cast<const uint4*>(src + c);
-  };
-  auto store_piece = [&](int i, const uint4& raw) {
-    if (i >= n_piece) return;
-    const int j = i / vec, c = (i % vec) * 8;
-    const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+  // this lane's query row (rows past the last repeat it and are not stored)
+  const int row = (blockIdx.y * a.tiles + wave / S) * 16 + col, qrow = min(row, rows - 1);
+  const size_t qoff = (static_cast<size_t>(b) * N + qrow % N) * (a.H * dh) +
+                      static_cast<size_t>(g * rep + qrow / N) * dh;
+  bf16x8 qf[NKS];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      vt[(c + 2 * q) * ldv + j] = static_cast<uint16_t>(w[q] & 0xffffu);
-      vt[(c + 2 * q + 1) * ldv + j] = static_cast<uint16_t>(w[q] >> 16);
-    }
-  };
-  uint4 vraw[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) vraw[q] = value_piece(tid + 256 * q);
-
-  bf16x8 qf[4];
-  f32x4 sc[4];
-  int n = 0;
-  float mx = neg_inf;
-  auto load_queries = [&](int qt) {
-    n = min(qt * 16 + col, N - 1);  // rows past the block repeat the last query, not stored
-    const uint16_t* qrow = a.q + (static_cast<size_t>(b) * N + n) * (a.H * dh) + static_cast<size_t>(h) * dh;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) qf[s] = s < nks ? load8(qrow, s) : bf16x8{};
-  };
-  // scores of four key tiles at once, every key fragment requested before the first is
-  // used (one round trip to L2 instead of sixteen); lane: keys 16 t + 4 grp + r of its query
-  auto score_batch = [&](int t0) {
-    bf16x8 kf[4][4];
+  for (int s = 0; s < NKS; ++s) qf[s] = load8(a.q + qoff, s);
+  // this wavefront's part of the window, in steps of 32 positions
+  const int per = (steps + S - 1) / S;
+  const int s0 = min(part * per, steps), s1 = wave < S * a.tiles ? min(s0 + per, steps) : s0;
+  bf16x8 kf[2][4][NKS];
+  auto load_keys = [&](int st, auto set) {  // four key tiles (two steps); tiles past the part are skipped
+    constexpr int z = decltype(set)::value;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint16_t* krow = key_row(min(16 * (t0 + i) + col, nk - 1));
+      const uint16_t* krow = row_of(kc, kb, min(32 * st + 16 * i + col, nk - 1));
 #pragma unroll
-      for (int s = 0; s < 4; ++s) kf[i][s] = (s < nks && t0 + i < nkt) ? load8(krow, s) : bf16x8{};
+      for (int s = 0; s < NKS; ++s) kf[z][i][s] = st + i / 2 < s1 ? load8(krow, s) : bf16x8{};
     }
+  };
+  if (s0 < s1) load_keys(s0, S0{});
+  if (s0 + 2 < s1) load_keys(s0 + 2, S1{});
+
+  // values -> LDS, transposed: a thread takes 8 coordinates of 4 consecutive positions and
+  // writes 8 bytes per coordinate.  Slots beyond the window hold zeros (their weights are
+  // zero too, but 0 x garbage could be NaN).
+  {
+    const int vec = dh / 8, n_piece = nkp / 4 * vec;
+    auto fetch = [&](int i, uint4 (&raw)[4]) {
+      const int j = i / vec * 4, c = (i % vec) * 8;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        raw[q] = (i < n_piece && j + q < nk) ? *reinterpret_cast<const uint4*>(row_of(vc, vb, j + q) + c)
+                                             : make_uint4(0u, 0u, 0u, 0u);
+    };
+    auto put = [&](int i, const uint4 (&raw)[4]) {
+      if (i >= n_piece) return;
+      uint16_t* dst = vt + (i % vec) * 8 * ldv + i / vec * 4;
+      const uint32_t w[4][4] = {{raw[0].x, raw[1].x, raw[2].x, raw[3].x}, {raw[0].y, raw[1].y, raw[2].y, raw[3].y},
+                                {raw[0].z, raw[1].z, raw[2].z, raw[3].z}, {raw[0].w, raw[1].w, raw[2].w, raw[3].w}};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {  // coordinates 2q (low halves) and 2q + 1 (high halves)
+        *reinterpret_cast<uint2*>(dst + 2 * q * ldv) =
+            make_uint2((w[q][0] & 0xffffu) | (w[q][1] << 16), (w[q][2] & 0xffffu) | (w[q][3] << 16));
+        *reinterpret_cast<uint2*>(dst + (2 * q + 1) * ldv) =
+            make_uint2((w[q][0] >> 16) | (w[q][1] & 0xffff0000u), (w[q][2] >> 16) | (w[q][3] & 0xffff0000u));
+      }
+    };
+    for (int i = tid; i < n_piece; i += 2 * n_threads) {
+      uint4 r0[4], r1[4];
+      fetch(i, r0);
+      fetch(i + n_threads, r1);
+      put(i, r0);
+      put(i + n_threads, r1);
+    }
+  }
+  __syncthreads();
+
+  const int n_waves = S * a.tiles;  // wavefronts past these only helped with the values
+  if (wave >= n_waves) {
+    if (S > 1) {  // the barriers of the exchange below
+      __syncthreads();
+      __syncthreads();
+    }
+    return;
+  }
+  float mx = neg_inf, lsum = 0.f;
+  f32x4 oacc[NDT];
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt) oacc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto consume = [&](int st, auto set) {
+    constexpr int z = decltype(set)::value;
+    f32x4 sc[4];
+    float bm = neg_inf;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
-        if (s < nks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[i][s], qf[s], acc, 0, 0, 0);
+      for (int s = 0; s < NKS; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[z][i][s], qf[s], acc, 0, 0, 0);
       sc[i] = acc;
     }
-  };
-  auto first_pass = [&](int qt) {  // the largest score of each query
-    load_queries(qt);
-    mx = neg_inf;
-    for (int t0 = 0; t0 < nkt; t0 += 4) {
-      score_batch(t0);
+    // positions of this lane that count: inside the window and inside the part
+    const int lim = min(nk, 32 * s1) - (32 * st + 4 * grp);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (16 * (t0 + i) + 4 * grp + r < nk) mx = fmaxf(mx, sc[i][r]);
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-  };
-  auto second_pass = [&](int qt) {  // weights, their sum, the weighted values; store
-    f32x4 oacc[8];
+      for (int r = 0; r < 4; ++r) bm = 16 * i + r < lim ? fmaxf(bm, sc[i][r]) : bm;
+    bm = fmaxf(bm, __shfl_xor(bm, 16));
+    bm = fmaxf(bm, __shfl_xor(bm, 32));
+    const float m_new = fmaxf(mx, bm);  // finite: the first position of a step is in the window
+    const float corr = mx == neg_inf ? 0.f : expf((mx - m_new) * a.scale);
+    mx = m_new;
+    lsum *= corr;
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) oacc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float lsum = 0.f;
-    for (int t0 = 0; t0 < nkt; t0 += 4) {
-      if (nkt > 4) score_batch(t0);  // a window of at most 64 positions still has them
+    for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-      for (int cc = 0; cc < 2; ++cc) {
-        const int c = t0 / 2 + cc;  // 32 keys: tiles 2 c and 2 c + 1
-        if (c * 32 < nkp) {
-          u16x4 pw[2];
+      for (int r = 0; r < 4; ++r) oacc[dt][r] *= corr;
 #pragma unroll
-          for (int half = 0; half < 2; ++half) {
+    for (int c = 0; c < 2; ++c) {
+      if (st + c < s1) {
+        u16x4 pw[2];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const float pr =
-                  16 * (2 * c + half) + 4 * grp + r < nk ? expf((sc[2 * cc + half][r] - mx) * a.scale) : 0.f;
-              lsum += pr;
-              pw[half][r] = f32_to_bf16_bits(pr);
-            }
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int i = 2 * c + half;
+            const float pr = 16 * i + r < lim ? expf((sc[i][r] - m_new) * a.scale) : 0.f;
+            lsum += pr;
+            pw[half][r] = f32_to_bf16_bits(pr);
           }
-          struct { u16x4 lo, hi; } pp = {pw[0], pw[1]};
-          const bf16x8 pb = __builtin_bit_cast(bf16x8, pp);
+        struct { u16x4 lo, hi; } pp = {pw[0], pw[1]};
+        const bf16x8 pb = __builtin_bit_cast(bf16x8, pp);
 #pragma unroll
-          for (int dt = 0; dt < 8; ++dt) {
-            if (dt < ndt) {
-              const uint16_t* vrow = vt + (16 * dt + col) * ldv + 32 * c + 4 * grp;
-              struct { u16x4 lo, hi; } vv = {*reinterpret_cast<const u16x4*>(vrow),
-                                             *reinterpret_cast<const u16x4*>(vrow + 16)};
-              oacc[dt] =
-                  __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vv), pb, oacc[dt], 0, 0, 0);
-            }
+        for (int dt = 0; dt < NDT; ++dt) {
+          if (dt < ndt) {
+            const uint16_t* vrow = vt + (16 * dt + col) * ldv + 32 * (st + c) + 4 * grp;
+            struct { u16x4 lo, hi; } vv = {*reinterpret_cast<const u16x4*>(vrow),
+                                           *reinterpret_cast<const u16x4*>(vrow + 16)};
+            oacc[dt] =
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vv), pb, oacc[dt], 0, 0, 0);
           }
         }
       }
     }
-    lsum += __shfl_xor(lsum, 16);
-    lsum += __shfl_xor(lsum, 32);
-    const float inv = 1.0f / lsum;
-    if (qt * 16 + col < N) {
-      uint16_t* orow = a.o + (static_cast<size_t>(b) * N + n) * (a.H * dh) + static_cast<size_t>(h) * dh;
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt) {
-        const int d0 = 16 * dt + 4 * grp;
-        if (d0 < dh) {
-          u16x4 ob;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) ob[r] = f32_to_bf16_bits(oacc[dt][r] * inv);
-          *reinterpret_cast<u16x4*>(orow + d0) = ob;
-        }
-      }
-    }
   };
+  for (int st = s0; st < s1; st += 4) {
+    consume(st, S0{});
+    if (st + 4 < s1) load_keys(st + 4, S0{});
+    if (st + 2 < s1) consume(st + 2, S1{});
+    if (st + 6 < s1) load_keys(st + 6, S1{});
+  }
+  lsum += __shfl_xor(lsum, 16);
+  lsum += __shfl_xor(lsum, 32);
 
-  const bool has_tile = wave * 16 < N;
-  if (has_tile) first_pass(wave);
+  uint16_t* orow = a.o + qoff;
+  auto store = [&](int dt, const f32x4& o, float inv) {
+    const int d0 = 16 * dt + 4 * grp;
+    if (row < rows && d0 < dh) {
+      u16x4 ob;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) store_piece(tid + 256 * q, vraw[q]);
-  for (int i = tid + 1024; i < n_piece; i += 256) store_piece(i, value_piece(i));
+      for (int r = 0; r < 4; ++r) ob[r] = f32_to_bf16_bits(o[r] * inv);
+      *reinterpret_cast<u16x4*>(orow + d0) = ob;
+    }
+  };
+  if (S == 1) {
+    const float inv = 1.0f / lsum;
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) store(dt, oacc[dt], inv);
+    return;
+  }
+  // the parts of a tile meet in LDS (the values are done with): each wavefront of the tile
+  // finishes its share of the coordinates, adding the parts in window order
   __syncthreads();
-  for (int qt = wave; qt * 16 < N; qt += 4) {
-    if (qt != wave) first_pass(qt);
-    second_pass(qt);
+  float* parts = reinterpret_cast<float*>(smem_raw);         // [wave][NDT][64 lanes][4]
+  float* ml = parts + static_cast<size_t>(n_waves) * NDT * 256;  // [wave][2][16]: maximum, sum
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt) *reinterpret_cast<f32x4*>(parts + ((wave * NDT + dt) * 64 + lane) * 4) = oacc[dt];
+  if (grp == 0) {
+    ml[wave * 32 + col] = mx;
+    ml[wave * 32 + 16 + col] = lsum;
+  }
+  __syncthreads();
+  const int w0 = wave - part;
+  float top = neg_inf, sum = 0.f, f[8];
+  for (int p = 0; p < S; ++p) top = fmaxf(top, ml[(w0 + p) * 32 + col]);
+#pragma unroll
+  for (int p = 0; p < 8; ++p) {
+    f[p] = 0.f;
+    if (p < S) {
+      const float m = ml[(w0 + p) * 32 + col];
+      f[p] = m == neg_inf ? 0.f : expf((m - top) * a.scale);  // (a part without positions)
+      sum += f[p] * ml[(w0 + p) * 32 + 16 + col];
+    }
+  }
+  const float inv = 1.0f / sum;
+  for (int dt = part; dt < ndt; dt += S) {
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      if (p < S) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(parts + (((w0 + p) * NDT + dt) * 64 + lane) * 4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[r] = fmaf(v[r], f[p], o[r]);
+      }
+    }
+    store(dt, o, inv);
   }
 }
 
@@ -647,13 +731,28 @@ int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void
   c.B = s.n_seqs; c.N = s.n_tokens; c.H = t.n_heads; c.Hkv = t.n_kv_heads; c.dh = t.head_dim;
   c.P = attn_cached(t);
   c.scale = 1.0f / sqrtf(static_cast<float>(t.head_dim));
-  const size_t lds = attn_core_lds(s, t);
-  if (lds > 48 * 1024) {  // (a property of the function on the current device; cheap to repeat)
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attention_core_kernel),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return hip_fail(e, "attention LDS size");
+  const AttnPlan pl = attn_plan(c);
+  c.splits = pl.splits;
+  c.tiles = pl.tiles;
+  const int waves = pl.splits * pl.tiles, nks = (t.head_dim + 31) / 32;
+  size_t lds = attn_core_lds(s, t);
+  if (pl.splits > 1) {  // the parts of a split window, after the values
+    const size_t merge = static_cast<size_t>(waves) * (2 * nks * 1024 + 128);
+    if (merge > lds) lds = merge;
   }
-  launch(kKAttnCore, attention_core_kernel, dim3(s.n_seqs * t.n_heads), dim3(256), lds, st, c);
+  const dim3 grid(s.n_seqs * t.n_kv_heads, pl.groups), block((waves < 4 ? 4 : waves) * kWave);  // (four stage faster than one)
+  auto core = [&](auto kernel) -> int {
+    if (lds > 48 * 1024) {  // (a property of the function on the current device; cheap to repeat)
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      if (e != hipSuccess) return hip_fail(e, "attention LDS size");
+    }
+    launch(kKAttnCore, kernel, grid, block, lds, st, c);
+    return DES_OK;
+  };
+  const int rc = nks == 1 ? core(attention_core_kernel<1>) : nks == 2 ? core(attention_core_kernel<2>)
+               : nks == 3 ? core(attention_core_kernel<3>) : core(attention_core_kernel<4>);
+  if (rc != DES_OK) return rc;
 
   LinearArgs o{};
   o.in = c.o;
