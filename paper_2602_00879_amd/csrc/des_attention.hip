@@ -9,11 +9,12 @@
 //                                            weight matrices (bf16 MFMA, fp32 accumulate)
 //   2. softmax(q K^T / sqrt(dh)) V           workgroups per (sequence, key/value head), bf16 MFMA
 //   3. y = heads Wo^T (+ x)                  the same projection kernel, residual fused
-// The projections are weight scans like the expert FFN (a 2048 x 2048 matrix is 8 MB for
-// at most a few hundred token rows), so they reuse its streaming building block: weights
-// from HBM straight into MFMA operands, token rows staged through LDS.
+// For at most 32 token rows the projections are weight scans like the expert FFN: weights
+// from HBM straight into MFMA operands.  Longer blocks use tiles of weight rows and token
+// rows that meet in LDS (des_tile_gemm.h).
 #include "des_common.h"
 #include "des_stream_gemm.h"
+#include "des_tile_gemm.h"
 
 namespace des {
 
@@ -24,7 +25,7 @@ struct LinearArgs {
   const uint16_t* res;   // [T][fout[0]] bf16 added to out[0] before rounding, or null
   int fout[3];
   int n_mats, T, Din;
-  // short blocks, reduction dimension split over two workgroups (ksplit = 2):
+  // reduction dimension split over two workgroups (ksplit = 2):
   int ksplit;
   float* partial;             // [workgroups][tiles of a workgroup][64 lanes][4] fp32 partial tiles
   unsigned long long* flags;  // [workgroup pairs] set to `epoch` by the half that finishes first
@@ -48,10 +49,11 @@ __device__ __forceinline__ int arrive(unsigned long long* word, unsigned long lo
   }
 }
 
+// Very large matrices under 33 to 64 token rows (see stream_linear()) are weight scans:
 // out[m][t][f] = sum_d in[t][d] * w[m][f][d].  A workgroup of LW wavefronts owns LW pairs
-// of 16-row weight tiles of one matrix and up to ROWS (64 or 128) token rows (blockIdx.y
+// of 16-row weight tiles of one matrix and up to ROWS token rows (blockIdx.y
 // names which; the weights are streamed once per ROWS rows).  KD = the reduction length of a workgroup if
-// it is one of the unrolled ones (1024, 2048, 4096), else 0.  With ksplit > 1 the reduction
+// it is the unrolled one, else 0.  With ksplit > 1 the reduction
 // dimension is split over that many workgroups (blockIdx.z): each writes its fp32 partial
 // tiles with device-scope stores and counts itself in; the last to arrive adds all the
 // partials in order of their part of the reduction dimension, whoever finished when.
@@ -166,6 +168,86 @@ __global__ __launch_bounds__(LW* kWave, 2) void linear_lds_kernel(LinearArgs a) 
     else if (kRows <= 64 || nt <= 4) run(std::integral_constant<int, 4>{});
     else if (nt <= 6) run(std::integral_constant<int, kRows <= 64 ? 4 : 6>{});
     else run(std::integral_constant<int, kRows <= 64 ? 4 : 8>{});
+  }
+}
+
+// out[m][t][f] = sum_d in[t][d] * w[m][f][d] for blocks of more than 32 token rows, in tiles
+// of 32 MT weight rows x 32 NT token rows (des_tile_gemm.h).  KW = 2: the two halves of the
+// reduction dimension go to the two halves of the workgroup and meet in LDS, first half +
+// second half.
+// Consecutive workgroups go to the eight XCDs in turn: the grid is walked so that one XCD
+// has all the token tiles of a weight tile (its L2 then reads those weights once).
+template <int MT, int NT, int KW>
+__global__ __launch_bounds__(256 * KW, 2) void linear_tile_kernel(LinearArgs a) {
+  constexpr int BM = 32 * MT, BN = 32 * NT;
+  __shared__ __align__(16) char lds[tile_lds_bytes<MT, NT, KW>()];
+  const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
+  const int part = KW > 1 ? threadIdx.x >> 8 : 0;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int kd = a.Din / KW, k0 = part * kd;
+  const int tok_tiles = (a.T + BN - 1) / BN;
+  const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
+  int mb = seq / tok_tiles * 8 + xcd, m = 0;
+  const int g0 = seq % tok_tiles * BN;
+  for (; m < a.n_mats; ++m) {  // which matrix this workgroup belongs to
+    const int per = (a.fout[m] + BM - 1) / BM;
+    if (mb < per) break;
+    mb -= per;
+  }
+  if (m >= a.n_mats) return;  // (the grid is rounded up to whole rounds of the XCDs)
+  const int fout = a.fout[m], Din = a.Din, f0 = mb * BM;
+  const uint16_t* aptr[MT];
+  const uint16_t* bptr[NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+    aptr[i] = a.w[m] + static_cast<size_t>(min(f0 + i * 32 + (tid >> 3), fout - 1)) * Din + k0 + (tid & 7) * 8;
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+    bptr[i] = a.in + static_cast<size_t>(min(g0 + i * 32 + (tid >> 3), a.T - 1)) * Din + k0 + (tid & 7) * 8;
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  tile_gemm<MT, NT, KW>(aptr, bptr, kd, lds, acc);
+  if constexpr (KW > 1) {  // (everybody is done with the buffers)
+    float* other = reinterpret_cast<float*>(lds);  // [wave][MT x NT][64 lanes][4]
+    if (part == 1) {
+#pragma unroll
+      for (int t = 0; t < MT * NT; ++t)
+        *reinterpret_cast<f32x4*>(other + ((wave * MT * NT + t) * 64 + lane) * 4) = acc[t / NT][t % NT];
+    }
+    __syncthreads();
+    if (part == 1) return;
+#pragma unroll
+    for (int t = 0; t < MT * NT; ++t) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(other + ((wave * MT * NT + t) * 64 + lane) * 4);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[t / NT][t % NT][q] += v[q];
+    }
+  }
+  uint16_t* out = a.out[m];
+  const uint16_t* res = m == 0 ? a.res : nullptr;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int tok = g0 + (wn * NT + j) * 16 + (lane & 15);
+    if (tok >= a.T) continue;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const int f = f0 + (wm * MT + i) * 16 + 4 * (lane >> 4);
+      if (f >= fout) continue;
+      const size_t o = static_cast<size_t>(tok) * fout + f;
+      f32x4 r = acc[i][j];
+      if (res != nullptr) {
+        const u16x4 rv = *reinterpret_cast<const u16x4*>(res + o);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r[q] += bf16_bits_to_f32(rv[q]);
+      }
+      u16x4 ob;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) ob[q] = f32_to_bf16_bits(r[q]);
+      *reinterpret_cast<u16x4*>(out + o) = ob;
+    }
   }
 }
 
@@ -336,13 +418,15 @@ struct AttnArgs {
 // transposed values in LDS.  The window is cut further while the launch has fewer than
 // 2048 wavefronts (eight per compute unit), as long as a part keeps 64 positions (what a
 // wavefront requests at once anyway); then the tiles are spread over more workgroups until every compute unit has one (each
-// stages the values again, from L2).
+// stages the values again, from L2).  A window whose scores fit a wavefront's registers is not
+// cut: its maximum is then known before the weights are formed.
+constexpr int kWholeWindow = 256;  // positions whose scores a wavefront keeps in registers
 struct AttnPlan { int splits, tiles, groups; };
 static AttnPlan attn_plan(const AttnArgs& a) {
   const int rows = a.H / a.Hkv * a.N, tiles = (rows + 15) / 16, steps = (a.P + a.N + 31) / 32;
   const int heads = a.B * a.Hkv;
   AttnPlan p{1, 8, 1};
-  while (p.splits < 8 && 4 * p.splits <= steps && heads * tiles * p.splits < 2048) p.splits *= 2;
+  while (a.P + a.N > kWholeWindow && p.splits < 8 && 4 * p.splits <= steps && heads * tiles * p.splits < 2048) p.splits *= 2;
   p.tiles = 8 / p.splits;
   while (p.tiles > 1 && heads * ((tiles + p.tiles - 1) / p.tiles) < 256) p.tiles /= 2;
   if (p.tiles > tiles) p.tiles = tiles;
@@ -358,8 +442,10 @@ static AttnPlan attn_plan(const AttnArgs& a) {
 //                  contraction only needs A and B to agree on which key a slot means),
 //                  A = values transposed in LDS, read with that same key order
 //                  -> lane l holds query l % 16, coordinates 4 (l / 16) .. + 3 of the tile
-// One pass over the keys, 64 at a time with the next 128 requested ahead, under a running
-// maximum (the accumulators are rescaled when it grows); the parts of a split window are
+// One pass over the keys, 64 at a time with the next 128 requested ahead.  WHOLE: up to 256
+// positions, all scores stay in registers and the weights are formed once their maximum is
+// known.  Longer windows run under a running
+// maximum (the accumulators are rescaled when it grows), and the parts of a split window are
 // added through LDS in window order.  Weights are rounded to bf16 for the second
 // contraction, their sum is kept in fp32; all sums run in a fixed order.
 // What bounds it is latency - the loads behind one another, then the staging of the
@@ -369,7 +455,7 @@ static AttnPlan attn_plan(const AttnArgs& a) {
 // (6.9).  Of the 20 us the key loads cost 6 (an MFMA operand takes 64 bytes of 16 rows) and the
 // staging of the values 4.
 // NKS = 32-element steps of the head width.
-template <int NKS>
+template <int NKS, bool WHOLE>
 __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
   constexpr int NDT = 2 * NKS;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -470,9 +556,9 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
   f32x4 oacc[NDT];
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt) oacc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto consume = [&](int st, auto set) {
+  // scores of the four key tiles of a set; their largest
+  auto scores = [&](int st, auto set, f32x4* sc) {
     constexpr int z = decltype(set)::value;
-    f32x4 sc[4];
     float bm = neg_inf;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -487,16 +573,15 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int r = 0; r < 4; ++r) bm = 16 * i + r < lim ? fmaxf(bm, sc[i][r]) : bm;
-    bm = fmaxf(bm, __shfl_xor(bm, 16));
-    bm = fmaxf(bm, __shfl_xor(bm, 32));
-    const float m_new = fmaxf(mx, bm);  // finite: the first position of a step is in the window
-    const float corr = mx == neg_inf ? 0.f : expf((mx - m_new) * a.scale);
-    mx = m_new;
-    lsum *= corr;
-#pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) oacc[dt][r] *= corr;
+    return bm;
+  };
+  auto query_max = [&](float m) {  // over the lanes that hold a query's scores
+    m = fmaxf(m, __shfl_xor(m, 16));
+    return fmaxf(m, __shfl_xor(m, 32));
+  };
+  // weights of two steps under the maximum mx, their sum, the weighted values
+  auto weigh = [&](int st, const f32x4* sc) {
+    const int lim = min(nk, 32 * s1) - (32 * st + 4 * grp);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       if (st + c < s1) {
@@ -506,7 +591,7 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int i = 2 * c + half;
-            const float pr = 16 * i + r < lim ? expf((sc[i][r] - m_new) * a.scale) : 0.f;
+            const float pr = 16 * i + r < lim ? expf((sc[i][r] - mx) * a.scale) : 0.f;
             lsum += pr;
             pw[half][r] = f32_to_bf16_bits(pr);
           }
@@ -525,11 +610,40 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
       }
     }
   };
-  for (int st = s0; st < s1; st += 4) {
-    consume(st, S0{});
-    if (st + 4 < s1) load_keys(st + 4, S0{});
-    if (st + 2 < s1) consume(st + 2, S1{});
-    if (st + 6 < s1) load_keys(st + 6, S1{});
+  if constexpr (WHOLE) {
+    constexpr int kSets = kWholeWindow / 64;
+    f32x4 sc[kSets][4];
+    static_for(std::make_integer_sequence<int, kSets>{}, [&](auto i) {
+      constexpr int I = decltype(i)::value;
+      typedef std::integral_constant<int, I & 1> Set;
+      if (2 * I < s1) mx = fmaxf(mx, scores(2 * I, Set{}, sc[I]));
+      if (2 * I + 4 < s1) load_keys(2 * I + 4, Set{});
+    });
+    mx = query_max(mx);
+    static_for(std::make_integer_sequence<int, kSets>{}, [&](auto i) {
+      constexpr int I = decltype(i)::value;
+      if (2 * I < s1) weigh(2 * I, sc[I]);
+    });
+  } else {
+    auto consume = [&](int st, auto set) {
+      f32x4 sc[4];
+      const float bm = query_max(scores(st, set, sc));
+      const float m_new = fmaxf(mx, bm);  // finite: the first position of a step is in the window
+      const float corr = mx == neg_inf ? 0.f : expf((mx - m_new) * a.scale);
+      mx = m_new;
+      lsum *= corr;
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) oacc[dt][r] *= corr;
+      weigh(st, sc);
+    };
+    for (int st = s0; st < s1; st += 4) {
+      consume(st, S0{});
+      if (st + 4 < s1) load_keys(st + 4, S0{});
+      if (st + 2 < s1) consume(st + 2, S1{});
+      if (st + 6 < s1) load_keys(st + 6, S1{});
+    }
   }
   lsum += __shfl_xor(lsum, 16);
   lsum += __shfl_xor(lsum, 32);
@@ -589,27 +703,44 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
   }
 }
 
-// Long blocks (more than 32 token rows), LW = 2: workgroups of the projection and over how
-// many of them the reduction dimension is split.  Few workgroups (the output projection of
-// a 2048-wide layer has 32 per 128 token rows) leave most compute units without a stream.
-struct LdsLinearPlan { int blocks, rows, passes, ksplit; };
-static LdsLinearPlan lds_linear_plan(int T, const int* fout, int n_mats, int Din) {
-  constexpr int LW = 2;
-  LdsLinearPlan p{0, 128, 1, 1};
-  for (int m = 0; m < n_mats; ++m) p.blocks += (fout[m] / 32 + LW - 1) / LW;
-  // few workgroups: passes of 64 token rows (chunks of 128 reduction elements, half the
-  // steps of a pass of 128 rows, and twice the workgroups)
-  if (p.blocks * ((T + 127) / 128) < 100) p.rows = 64;
-  p.passes = (T + p.rows - 1) / p.rows;
-  // still few: the reduction dimension over two workgroups as well.  Measured on the
-  // output projection of the 2048-wide layer at 256 token rows: 41.3 us as one pass of 128
-  // rows per workgroup, 30.4 us with passes of 64, 25.8 us with the split on top (four-way:
-  // no better); the q/k/v launch, 160 workgroups, is best left alone (21.7 us; split 38.7 us,
-  // passes of 64 29.2 us).
-  if (p.blocks * p.passes < 150 && Din % 512 == 0) p.ksplit = 2;
+// Blocks of more than 32 token rows: the tile, the workgroups, whether the reduction is cut
+// in two.
+struct TileLinearPlan { int mt, blocks, kw; };
+static TileLinearPlan tile_linear_plan(int T, const int* fout, int n_mats, int Din) {
+  auto blocks = [&](int mt) {
+    int b = 0;
+    for (int m = 0; m < n_mats; ++m) b += (fout[m] + 32 * mt - 1) / (32 * mt);
+    return (b + 7) / 8 * 8 * ((T + 32 * mt - 1) / (32 * mt));
+  };
+  TileLinearPlan p{2, blocks(2), 1};
+  // The reduction is cut where a launch of one workgroup per 64 weight rows and 128 (64 if
+  // that makes fewer than 100) token rows has fewer than 150: half of the compute units
+  // would have four wavefronts or none (2048 x 4096 weights on 256 token rows: 20.5 us whole,
+  // 17.0 us cut).  The cut decides the order of the sums, so it depends on sizes alone.
+  int b64 = 0;
+  for (int m = 0; m < n_mats; ++m) b64 += (fout[m] / 32 + 1) / 2;
+  const int rows = b64 * ((T + 127) / 128) < 100 ? 64 : 128;
+  if (b64 * ((T + rows - 1) / rows) < 150 && Din % 512 == 0) p.kw = 2;
+  // Tiles of 128 x 128 need half the LDS and L2 traffic per multiply; two workgroups per
+  // compute unit have to be there for it to pay (4608 x 2560 weights on 432 rows, 144 such
+  // tiles: 33.5 us against 21.2 us in tiles of 64; at 512 and more they win).
+  else if (blocks(4) >= 512) p = TileLinearPlan{4, blocks(4), 1};
   return p;
 }
-constexpr size_t kLdsPartialBytes = 2 * 2 * 8 * 256 * 4;  // of one workgroup: LW x 2 tiles x 8 token tiles x 1 KB
+
+// Where the streaming form is still level with the tiles: 49 to 64 token rows (three or four
+// token tiles in one pass) on one matrix of 8192 x 8192 and more, where 128 and more
+// workgroups each stream a megabyte and the tiles' trip through LDS buys nothing (8192 x 8192,
+// 64 rows: 45.3 us streamed, 46.0 us in tiles; 48 rows 43.2 both; 2048 x 16384, 64 rows: 78.5
+// and 70.6).
+inline bool stream_linear(int T, const int* fout, int n_mats, int Din) {
+  return n_mats == 1 && T > 48 && T <= 64 && fout[0] >= 8192 && Din >= 8192;
+}
+constexpr int kStreamWaves = 2;
+inline int stream_ksplit(const int* fout, int Din) {  // the same rule as the tiles'
+  return (fout[0] / 32 + 1) / 2 < 150 && Din % 512 == 0 ? 2 : 1;
+}
+constexpr size_t kStreamPartialBytes = kStreamWaves * 2 * 8 * 256 * 4;  // of one workgroup
 
 // Scratch of one attention sub-layer (bytes from a 256-byte aligned base): q, k, v and the
 // per-head outputs of the block's tokens, bf16.
@@ -628,16 +759,14 @@ AttnLayout attn_layout(const des_shape_t& s, const des_attn_shape_t& t) {
   const size_t tiles_out = static_cast<size_t>(s.hidden) / 16;
   const size_t tiles = tiles_qkv > tiles_out ? tiles_qkv : tiles_out;
   size_t part_bytes = tiles * 4096, n_flags = tiles;
-  if (T > 32) {  // long blocks: one 32 KB partial per workgroup, one counter per output tile
-    const int f_qkv[3] = {t.n_heads * t.head_dim, t.n_kv_heads * t.head_dim, t.n_kv_heads * t.head_dim};
+  if (T > 32) {
+    part_bytes = n_flags = 0;
     const int f_out[1] = {s.hidden};
-    const LdsLinearPlan a = lds_linear_plan(static_cast<int>(T), f_qkv, 3, s.hidden);
-    const LdsLinearPlan b = lds_linear_plan(static_cast<int>(T), f_out, 1, t.n_heads * t.head_dim);
-    const size_t wa = static_cast<size_t>(a.blocks) * a.passes, wb = static_cast<size_t>(b.blocks) * b.passes;
-    const size_t pa = a.ksplit > 1 ? wa * a.ksplit * kLdsPartialBytes : 0;
-    const size_t pb = b.ksplit > 1 ? wb * b.ksplit * kLdsPartialBytes : 0;
-    part_bytes = pa > pb ? pa : pb;
-    n_flags = wa > wb ? wa : wb;
+    const int Din = t.n_heads * t.head_dim;
+    if (stream_linear(static_cast<int>(T), f_out, 1, Din)) {
+      n_flags = static_cast<size_t>(s.hidden / 32 + kStreamWaves - 1) / kStreamWaves;
+      part_bytes = n_flags * stream_ksplit(f_out, Din) * kStreamPartialBytes;
+    }
   }
   l.partial = p; p = align256(p + part_bytes);
   l.flags = p; p = align256(p + n_flags * 8);
@@ -652,7 +781,6 @@ size_t attn_core_lds(const des_shape_t& s, const des_attn_shape_t& t) {
   return static_cast<size_t>((t.head_dim + 15) / 16 * 16) * (nkp + 4) * 2;
 }
 
-template <int LW>
 static void launch_linear(const LinearArgs& a, int kernel_id, hipStream_t st) {
   if (a.T <= 32) {
     // Row tiles per workgroup: two halve the token-row traffic from L2, which costs as much
@@ -684,21 +812,19 @@ static void launch_linear(const LinearArgs& a, int kernel_id, hipStream_t st) {
     }
     return;
   }
-  static_assert(LW == 2, "lds_linear_plan and the partial tiles assume two wavefronts");
-  const LdsLinearPlan pl = lds_linear_plan(a.T, a.fout, a.n_mats, a.Din);
-  LinearArgs c = a;
-  c.ksplit = c.partial != nullptr ? pl.ksplit : 1;
-  const dim3 g(pl.blocks, pl.passes, c.ksplit), b(LW * kWave);
-  const int kd = a.Din / c.ksplit;
-#define DES_LAUNCH_LIN(KDV)                                                                   \
-  do {                                                                                        \
-    if (pl.rows == 64) launch(kernel_id, linear_lds_kernel<LW, KDV, 64>, g, b, 0, st, c);     \
-    else launch(kernel_id, linear_lds_kernel<LW, KDV, 128>, g, b, 0, st, c);                  \
-  } while (0)
-  if (kd == 2048) DES_LAUNCH_LIN(2048);
-  else if (kd == 4096) DES_LAUNCH_LIN(4096);
-  else DES_LAUNCH_LIN(0);
-#undef DES_LAUNCH_LIN
+  if (stream_linear(a.T, a.fout, a.n_mats, a.Din)) {
+    LinearArgs c = a;
+    c.ksplit = stream_ksplit(a.fout, a.Din);
+    const dim3 g((a.fout[0] / 32 + kStreamWaves - 1) / kStreamWaves, 1, c.ksplit), b(kStreamWaves * kWave);
+    if (a.Din / c.ksplit == 4096) launch(kernel_id, linear_lds_kernel<kStreamWaves, 4096, 64>, g, b, 0, st, c);
+    else launch(kernel_id, linear_lds_kernel<kStreamWaves, 0, 64>, g, b, 0, st, c);
+    return;
+  }
+  const TileLinearPlan pl = tile_linear_plan(a.T, a.fout, a.n_mats, a.Din);
+  const dim3 g(pl.blocks), b(256 * pl.kw);
+  if (pl.mt == 4) launch(kernel_id, linear_tile_kernel<4, 4, 1>, g, b, 0, st, a);
+  else if (pl.kw == 2) launch(kernel_id, linear_tile_kernel<2, 2, 2>, g, b, 0, st, a);
+  else launch(kernel_id, linear_tile_kernel<2, 2, 1>, g, b, 0, st, a);
 }
 
 int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void* x, const void* wq,
@@ -721,7 +847,7 @@ int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void
   p.partial = reinterpret_cast<float*>(ws + l.partial);
   p.flags = reinterpret_cast<unsigned long long*>(ws + l.flags);
   p.epoch = epoch;
-  launch_linear<2>(p, kKAttnProj, st);
+  launch_linear(p, kKAttnProj, st);
 
   AttnArgs c{};
   c.q = p.out[0]; c.k = p.out[1]; c.v = p.out[2];
@@ -750,8 +876,12 @@ int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void
     launch(kKAttnCore, kernel, grid, block, lds, st, c);
     return DES_OK;
   };
-  const int rc = nks == 1 ? core(attention_core_kernel<1>) : nks == 2 ? core(attention_core_kernel<2>)
-               : nks == 3 ? core(attention_core_kernel<3>) : core(attention_core_kernel<4>);
+  auto pick = [&](auto whole) -> int {
+    constexpr bool W = decltype(whole)::value;
+    return nks == 1 ? core(attention_core_kernel<1, W>) : nks == 2 ? core(attention_core_kernel<2, W>)
+         : nks == 3 ? core(attention_core_kernel<3, W>) : core(attention_core_kernel<4, W>);
+  };
+  const int rc = c.P + c.N <= kWholeWindow ? pick(std::true_type{}) : pick(std::false_type{});
   if (rc != DES_OK) return rc;
 
   LinearArgs o{};
@@ -765,7 +895,7 @@ int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void
   o.flags = p.flags;
   o.epoch = epoch;
   o.res = s.residual ? static_cast<const uint16_t*>(x) : nullptr;
-  launch_linear<2>(o, kKAttnOut, st);
+  launch_linear(o, kKAttnOut, st);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? DES_OK : hip_fail(e, "attention launch");
 }

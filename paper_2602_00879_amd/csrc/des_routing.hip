@@ -768,9 +768,26 @@ __device__ void permute_all(const RoutingArgs& a, char* smem, bool idx_dev, int 
     for_pairs(0, TK, mark);
   }
   __syncthreads();
-  // counts and the popcounts before each word: eight lanes per expert, each a run of
-  // consecutive words, an exclusive scan over the eight
-  {
+  // counts and the popcounts before each word: a thread per expert while that is a short
+  // loop, else eight lanes per expert, each a run of consecutive words, scanned over the eight
+  auto count_expert = [&](int e, int c) {
+    s_cnt[e] = c;
+    s_slot[e] = 0;
+    s_uoff[e] = 0;
+    if (e < M && part == 0) a.expert_counts[e] = c;
+  };
+  if (words <= 8) {
+    for (int e = tid; e < MP; e += kRtThreads) {
+      int c = 0;
+      if (e < M)
+        for (int w = 0; w < words; ++w) {
+          const size_t i = static_cast<size_t>(e) * words + w;
+          s_pre[i] = static_cast<uint16_t>(c);
+          c += __popc(member[i]);
+        }
+      count_expert(e, c);
+    }
+  } else {
     constexpr int GL = 8;
     const int run = (words + GL - 1) / GL, gl = tid % GL;
     for (int e = tid / GL; e < MP; e += kRtThreads / GL) {
@@ -792,12 +809,7 @@ __device__ void permute_all(const RoutingArgs& a, char* smem, bool idx_dev, int 
           pre += __popc(mrow[w]);
         }
       }
-      if (gl == GL - 1) {
-        s_cnt[e] = inc;
-        s_slot[e] = 0;
-        s_uoff[e] = 0;
-        if (e < M && part == 0) a.expert_counts[e] = inc;
-      }
+      if (gl == GL - 1) count_expert(e, inc);
     }
   }
   __syncthreads();

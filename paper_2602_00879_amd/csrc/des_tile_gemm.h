@@ -1,0 +1,126 @@
+// Tiled GEMM building block for the cases where many token rows meet one weight matrix (the
+// attention projections of longer blocks, experts with many pairs): weight rows and token
+// rows are both staged through LDS and shared by the four wavefronts of a workgroup.
+// gfx950 only.
+//
+// Where a matrix has at most a few dozen token rows the weights are a pure stream and go
+// from HBM straight into MFMA operands (des_stream_gemm.h).  With more, that form leaves a
+// wavefront with one long chain - read the token fragments from LDS, wait, multiply - and,
+// for one dense matrix, the chip with too few wavefronts.  Here a tile's reduction runs in
+// chunks of 64: two LDS buffers, the next chunks in registers on their way.  Loads are ordinary loads, the
+// compiler places their waits.
+#pragma once
+
+#include "des_common.h"
+#include "des_stream_gemm.h"
+
+namespace des {
+
+constexpr int kTileK = 64;  // reduction elements per chunk
+
+// LDS of one workgroup: two buffers of one chunk of (32 MT weight + 32 NT token) rows x 128
+// bytes, for each of the KW parts of the reduction.
+template <int MT, int NT, int KW>
+constexpr int tile_lds_bytes() { return KW * 2 * 32 * (MT + NT) * kTileK * 2; }
+
+// acc[m][n] += weight tile m x token tile n of this wavefront, over a reduction of `kd`
+// elements (a multiple of 32).  A group of four wavefronts works on a tile of 32 MT weight
+// rows x 32 NT token rows; wavefront (wm, wn) of the 2 x 2 has weight rows 16 MT wm .. and
+// token rows 16 NT wn ..  With KW = 2 the workgroup has two such groups, each with its half
+// of the reduction (`kd` and the pointers are the group's own, the lengths are equal).
+// Row pointers of this thread (t = thread of the group): aptr[i] = row i * 32 + t / 8 of the
+// weight tile, element 8 * (t % 8); bptr[i] likewise for the token tile (a row past the end
+// repeats another, the caller drops its results).  The whole workgroup calls it together.
+// Every sum runs over the reduction in ascending steps of 32 whatever the tile, so the
+// results do not depend on MT or NT.
+//
+// With few workgroups per compute unit a step is a chain (store, barrier, operand reads,
+// multiplies); requesting 4 or 6 chunks ahead or passing two chunks per barrier changes
+// nothing measurable, more wavefronts per compute unit (KW = 2) do: 2048 x 4096 weights on
+// 256 token rows 20.5 -> 17.0 us.
+//
+// Rows lie 128 bytes apart in LDS, the 16-byte piece p of row r at p ^ (r / 2 % 8): a
+// wavefront's writes (8 rows) and its operand reads (16 rows, one piece) both fall into
+// different banks.
+template <int MT, int NT, int KW>
+__device__ __forceinline__ void tile_gemm(const uint16_t* const (&aptr)[MT], const uint16_t* const (&bptr)[NT],
+                                          int kd, char* lds, f32x4 (&acc)[MT][NT]) {
+  constexpr int P = 2;  // chunks on their way in registers
+  constexpr int kBuf = 32 * (MT + NT) * kTileK * 2;
+  const int grp = KW > 1 ? threadIdx.x >> 8 : 0;
+  const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int steps = (kd + kTileK - 1) / kTileK;
+  const int piece = tid & 7, srow = tid >> 3;
+  lds += grp * 2 * kBuf;
+  const int sdst = srow * 128 + ((piece ^ ((srow >> 1) & 7)) << 4);  // + 32 rows: the same swizzle
+  uint4 ra[P][MT], rb[P][NT];
+  auto load = [&](int st, auto set) {
+    constexpr int z = decltype(set)::value;
+    // pieces past the end of the reduction fetch its last elements; store() replaces them
+    // with zeros
+    const int k = min(st * kTileK + piece * 8, kd - 8) - piece * 8;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) ra[z][i] = *reinterpret_cast<const uint4*>(aptr[i] + k);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) rb[z][i] = *reinterpret_cast<const uint4*>(bptr[i] + k);
+  };
+  auto store = [&](int st, auto set) {
+    constexpr int z = decltype(set)::value;
+    if ((st + 1) * kTileK > kd && st * kTileK + piece * 8 >= kd) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) ra[z][i] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+      for (int i = 0; i < NT; ++i) rb[z][i] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    char* buf = lds + (st & 1) * kBuf + sdst;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) *reinterpret_cast<uint4*>(buf + i * 4096) = ra[z][i];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) *reinterpret_cast<uint4*>(buf + (MT + i) * 4096) = rb[z][i];
+  };
+  const int r = lane & 15, g = lane >> 4, sw = (r >> 1) & 7;
+  auto compute = [&](int st) {
+    const char* a = lds + (st & 1) * kBuf + (wm * MT * 16 + r) * 128;
+    const char* b = lds + (st & 1) * kBuf + 32 * MT * 128 + (wn * NT * 16 + r) * 128;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int off = ((u * 4 + g) ^ sw) << 4;
+      bf16x8 fa[MT], fb[NT];
+#pragma unroll
+      for (int i = 0; i < MT; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(a + i * 2048 + off);
+#pragma unroll
+      for (int i = 0; i < NT; ++i) fb[i] = *reinterpret_cast<const bf16x8*>(b + i * 2048 + off);
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+    }
+  };
+  auto step = [&](int st, auto i, auto more) {  // chunk st is in LDS; i = st % P
+    typedef std::integral_constant<int, (decltype(i)::value + 1) % P> Next;
+    if (more || st + 1 < steps) store(st + 1, Next{});
+    if (more || st + 1 + P < steps) load(st + 1 + P, Next{});
+    compute(st);
+    __syncthreads();
+  };
+  auto unrolled = std::make_integer_sequence<int, P>{};
+  static_for(unrolled, [&](auto i) {
+    if (i < steps) load(i, i);
+  });
+  store(0, S0{});
+  if (P < steps) load(P, S0{});
+  __syncthreads();
+  // step st: the next chunk goes from registers to the buffer that the one before was read
+  // from (everybody is past the barrier that ended it), the one after P more is requested
+  int st = 0;
+  for (; st + 2 * P < steps; st += P)
+    static_for(unrolled, [&](auto i) { step(st + i, i, std::true_type{}); });
+  for (; st < steps; st += P)
+    static_for(unrolled, [&](auto i) {
+      if (st + i < steps) step(st + i, i, std::false_type{});
+    });
+}
+
+}  // namespace des
