@@ -199,8 +199,9 @@ __global__ __launch_bounds__(256 * KW, 2) void linear_tile_kernel(LinearArgs a) 
   const uint16_t* aptr[MT];
   const uint16_t* bptr[NT];
 #pragma unroll
-  for (int i = 0; i < MT; ++i)
-    aptr[i] = a.w[m] + static_cast<size_t>(min(f0 + i * 32 + (tid >> 3), fout - 1)) * Din + k0 + (tid & 7) * 8;
+  for (int i = 0; i < MT; ++i)  // (fout is a multiple of 16)
+    aptr[i] = tile_weight_ptr<false>(
+        a.w[m] + static_cast<size_t>(min(f0 / 16 + 2 * i + (tid >> 7), fout / 16 - 1)) * 16 * Din + k0, Din, tid);
 #pragma unroll
   for (int i = 0; i < NT; ++i)
     bptr[i] = a.in + static_cast<size_t>(min(g0 + i * 32 + (tid >> 3), a.T - 1)) * Din + k0 + (tid & 7) * 8;
@@ -209,7 +210,7 @@ __global__ __launch_bounds__(256 * KW, 2) void linear_tile_kernel(LinearArgs a) 
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  tile_gemm<MT, NT, KW>(aptr, bptr, kd, lds, acc);
+  tile_gemm<MT, NT, KW, 2, false>(aptr, bptr, kd, lds, acc);
   if constexpr (KW > 1) {  // (everybody is done with the buffers)
     float* other = reinterpret_cast<float*>(lds);  // [wave][MT x NT][64 lanes][4]
     if (part == 1) {

@@ -94,7 +94,6 @@ inline int max_live_experts(const des_shape_t& s) {
 // unit, and never more than this.
 constexpr int kMaxFusedRoutingBlocks = 256;
 
-constexpr int kSlotToks = 32;  // tokens per slot kept in the slot-major token table
 int device_compute_units();          // of the current device (cached)
 
 // Blocks of more than 32 tokens: an expert's pairs are handed to the FFN
@@ -160,7 +159,6 @@ struct WsLayout {
   size_t flags;     // u64   [router tiles + 2 * max(B, kMaxSelGroups)]  epoch flags of the routing launch
   size_t sel_part;  // u32   [kMaxSelGroups][3][kSelPartStride]  selectors' election partials
   size_t slot_of;   // int32 [M]       slot of each live expert
-  size_t slot_tok;  // u16   [n_slots][kSlotToks]  tokens of each slot's first pairs
   size_t offsets;   // int32 [M + 1]   exclusive scan of expert_counts
   size_t slots;     // int4  [n_slots] {expert, first sorted pair, pairs, token bitmap if T <= 32};
                     //       expert -1 = unused
@@ -191,7 +189,6 @@ inline WsLayout ws_layout(const des_shape_t& s) {
   w.flags = p;    p = align256(p + 8 * (tiles + 2 * nsel));
   w.sel_part = p; p = align256(p + 4 * static_cast<size_t>(kMaxSelGroups) * 3 * kSelPartStride);
   w.slot_of = p;  p = align256(p + 4 * static_cast<size_t>(s.n_experts));
-  w.slot_tok = p; p = align256(p + 2 * static_cast<size_t>(max_live_experts(s)) * kSlotToks);
   w.offsets = p;  p = align256(p + 4 * (static_cast<size_t>(s.n_experts) + 1));
   w.slots = p;    p = align256(p + 16 * static_cast<size_t>(max_live_experts(s)));
   w.meta = p;     p = align256(p + 4 * 64);

@@ -23,6 +23,7 @@
 #include "des_common.h"
 #include "des_select.h"
 #include "des_stream_gemm.h"
+#include "des_tile_gemm.h"
 
 namespace des {
 
@@ -35,7 +36,6 @@ struct FfnArgs {
   const float* topk_w;          // [T][K]
   const int4* slots;            // [n_slots] {expert, first sorted pair, pairs, 0}
   const int32_t *meta, *pair_tok, *pos;
-  const uint16_t* slot_tok;     // [n_slots][kSlotToks] tokens of each slot's first pairs
   void* h;                      // [(TK) x F] then [T x Fs]
   float* o;                     // [(TK + T) x D]
   void* y;                      // [T][D]
@@ -60,7 +60,7 @@ __device__ long long g_ffn_stamps[8192 * 4];
 struct Task {
   const uint16_t *w0, *w1;  // weight matrices of the expert (gate, up) or (down, -)
   int slot;                 // slot of the expert (-1 for the shared expert)
-  int pre_tok[2];           // this lane's token in the slot's first two token tiles
+  int pre_tok[2];           // blocks of <= 32 tokens: this lane's token in the slot's token tiles
   int count;                // pairs of this expert
   int pair0;                // first sorted position (routed) or 0 (shared)
   bool shared;
@@ -165,11 +165,11 @@ __device__ __forceinline__ size_t load_off(int i, int kd) {
   return PACKED ? static_cast<size_t>(i) * 512 : static_cast<size_t>(i & 1) * 8 * kd + (i >> 1) * 64;
 }
 
-// gate/up for pairs [g0, g0 + 16*NT) of the task, intermediate rows
+// gate/up for the task's pairs (at most 16*NT), intermediate rows
 // (ft0 .. ft0+FT-1)*16..+15.  The FT row tiles share every token fragment.
 template <int FT, int NT, int U, bool PACKED>
-__device__ __forceinline__ void gateup_group(const FfnArgs& a, const Task& t, int ft0, int g0,
-                                             int lane, char* turn) {
+__device__ __forceinline__ void gateup_group(const FfnArgs& a, const Task& t, int ft0, int lane,
+                                             char* turn) {
   static_assert(PACKED || U % 2 == 0, "row-major stages are whole 64-element blocks");
   const int D = a.D;
   const int nks = D / 32;
@@ -184,11 +184,8 @@ __device__ __forceinline__ void gateup_group(const FfnArgs& a, const Task& t, in
   const uint16_t* xp[NT];
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
-    int pi = min(g0 + i * 16 + (lane & 15), t.count - 1);  // clamped rows are dropped at the store
-    // the first two token tiles come from the slot-major table, fetched together
-    // with the slot record (entries past the slot's count name token 0)
-    const int tok = t.shared ? pi
-                    : ((g0 == 0 && i < 2) ? t.pre_tok[i < 2 ? i : 0] : a.pair_tok[t.pair0 + pi]);
+    int pi = min(i * 16 + (lane & 15), t.count - 1);  // clamped rows are dropped at the store
+    const int tok = t.shared ? pi : t.pre_tok[i];
     xp[i] = x + static_cast<size_t>(tok) * D + (lane >> 4) * 8;
   }
   f32x4 accg[FT][NT], accu[FT][NT];
@@ -263,7 +260,7 @@ __device__ __forceinline__ void gateup_group(const FfnArgs& a, const Task& t, in
   uint16_t* h = static_cast<uint16_t*>(a.h);
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
-    const int pi = g0 + i * 16 + (lane & 15);
+    const int pi = i * 16 + (lane & 15);
     if (pi < t.count) {
 #pragma unroll
       for (int f = 0; f < FT; ++f) {
@@ -282,14 +279,7 @@ __device__ __forceinline__ bool make_task(const FfnArgs& a, int slot_or_shared, 
   const size_t TK = static_cast<size_t>(a.T) * a.K;
   t.dmask = 0u;  // (every path: the down projection tests it)
   if (!shared) {
-    // the slot record and (for gate/up) this lane's tokens are fetched together:
-    // both addresses depend on the slot number only
     const int4 sl = a.slots[slot_or_shared];
-    if (!down && a.T > 32) {
-      const uint16_t* st = a.slot_tok + slot_or_shared * kSlotToks + (lane & 15);
-      t.pre_tok[0] = st[0];
-      t.pre_tok[1] = st[16];
-    }
     // an unused slot; also refuses a record that does not fit the problem (the
     // workspace is the caller's memory: never index weights or pairs with it blindly)
     if (sl.x < 0 || sl.x >= a.M || sl.y < 0 || sl.z < 1 ||
@@ -390,35 +380,8 @@ __device__ __forceinline__ bool gateup_task(const FfnArgs& a, int task, int lane
     v = shared_view(a, t, 2);
     ft = (task - routed) * GT;
   }
-  const int nt = (t.count + 15) / 16;
-  bool done = false;
-  if (MAXNT == 1 || nt <= 1) {
-    gateup_group<GT, 1, U1, PACKED>(v, t, ft, 0, lane, turn);
-    done = true;
-  }
-  if constexpr (MAXNT >= 2) {
-    if (!done && (MAXNT == 2 || nt <= 2)) {
-      gateup_group<GT, 2, U2, PACKED>(v, t, ft, 0, lane, turn);
-      done = true;
-    }
-  }
-  if constexpr (MAXNT >= 4) {
-    if (!done && (MAXNT == 4 || nt <= 4)) {
-      gateup_group<GT, 4, 2, PACKED>(v, t, ft, 0, lane, turn);
-      done = true;
-    }
-  }
-  if constexpr (MAXNT >= 8) {
-    if (!done && (MAXNT == 8 || nt <= 8)) {
-      gateup_group<GT, 8, PACKED ? 1 : 2, PACKED>(v, t, ft, 0, lane, turn);
-      done = true;
-    }
-  }
-  if constexpr (MAXNT >= 16) {
-    if (!done)
-      for (int g0 = 0; g0 < t.count; g0 += 256)
-        for (int f = 0; f < GT; ++f) gateup_group<1, 16, PACKED ? 1 : 2, PACKED>(v, t, ft + f, g0, lane, turn);
-  }
+  if (MAXNT == 1 || t.count <= 16) gateup_group<GT, 1, U1, PACKED>(v, t, ft, lane, turn);
+  else gateup_group<GT, MAXNT, U2, PACKED>(v, t, ft, lane, turn);
   DES_FSTAMP(task, 2);
 #ifdef DES_FFN_STAMPS
   if ((threadIdx.x & 63) == 0 && task < 8192)
@@ -437,7 +400,7 @@ template <int MAXNT, bool PACKED, int U1 = 2, int U2 = 2, int GT = kGuTiles>
 __global__ __launch_bounds__(kFfnWaves* kWave) void gateup_bf16_kernel(FfnArgs a) {
   const int lane = threadIdx.x & 63;
   int task = blockIdx.x * kFfnWaves + (threadIdx.x >> 6);
-  if constexpr (MAXNT <= 2) {
+  {
     if (a.dn.on) {
       // dense short block: the first wavefronts of the grid re-route the block's tokens
       // (Alg. 1 stage 2) while the others stream the coreset's weights
@@ -467,10 +430,10 @@ __global__ __launch_bounds__(kFfnWaves* kWave) void gateup_bf16_kernel(FfnArgs a
   if (task < tasks) gateup_task<MAXNT, PACKED, U1, U2, GT>(a, task, lane, s_turn + (threadIdx.x >> 6) * kTurn);
 }
 
-// down for pairs [g0, g0+16*NT), output rows (dt0 .. dt0+RT-1)*16
+// down for the task's pairs (at most 16*NT), output rows (dt0 .. dt0+RT-1)*16
 template <int RT, int NT, int U, bool PACKED>
-__device__ __forceinline__ void down_group(const FfnArgs& a, const Task& t, int dt0, int g0,
-                                           int lane, char* turn) {
+__device__ __forceinline__ void down_group(const FfnArgs& a, const Task& t, int dt0, int lane,
+                                           char* turn) {
   static_assert(PACKED || U % 2 == 0, "row-major stages are whole 64-element blocks");
   const int F = t.fdim;
   const int nks = F / 32;
@@ -481,10 +444,10 @@ __device__ __forceinline__ void down_group(const FfnArgs& a, const Task& t, int 
   const uint16_t* hp[NT];
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
-    const int pi = min(g0 + i * 16 + (lane & 15), t.count - 1);
+    const int pi = min(i * 16 + (lane & 15), t.count - 1);
     // (dense short block: H holds every token of the block for this slot; the routed
     // ones, in order, are this expert's pairs)
-    const int hrow = t.dmask ? t.pre_tok[i < 2 ? i : 0] : pi;
+    const int hrow = t.dmask ? t.pre_tok[i] : pi;
     hp[i] = h + (t.row_base + hrow) * F + (lane >> 4) * 8;
   }
   f32x4 acc[RT][NT];
@@ -545,13 +508,13 @@ __device__ __forceinline__ void down_group(const FfnArgs& a, const Task& t, int 
   const size_t orow0 = t.shared ? static_cast<size_t>(a.T) * a.K : static_cast<size_t>(t.pair0);
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
-    const int pi = g0 + i * 16 + (lane & 15);
+    const int pi = i * 16 + (lane & 15);
     if (pi < t.count) {
       size_t orow = orow0 + pi;
       if (t.dmask) {
         // dense short block: the pair's row is token * K + (which of the token's
         // choices this expert is)
-        const int tok = t.pre_tok[i < 2 ? i : 0];
+        const int tok = t.pre_tok[i];
         orow = static_cast<size_t>(tok) * a.K + a.dn.choice[t.slot * 32 + tok];
       }
 #pragma unroll
@@ -583,42 +546,12 @@ __device__ __forceinline__ bool down_task(const FfnArgs& a, int task, int lane, 
   }
   const int dt_begin = dg * RTG;
   const int dt_end = min(dt_begin + RTG, dtiles);
-  const int nt = (t.count + 15) / 16;
-  bool done = false;
-  if (dt_end - dt_begin == RTG) {
-    if (MAXNT == 1 || nt <= 1) {
-      down_group<RTG, 1, U1, PACKED>(v, t, dt_begin, 0, lane, turn);
-      done = true;
-    }
-    if constexpr (MAXNT >= 2) {
-      if (!done && (MAXNT == 2 || nt <= 2)) {
-        down_group<RTG, 2, U2, PACKED>(v, t, dt_begin, 0, lane, turn);
-        done = true;
-      }
-    }
-    if constexpr (MAXNT >= 4) {
-      if (!done && (MAXNT == 4 || nt <= 4)) {
-        down_group<RTG, 4, PACKED ? 1 : 2, PACKED>(v, t, dt_begin, 0, lane, turn);
-        done = true;
-      }
-    }
-    if constexpr (MAXNT >= 8) {
-      if (!done && (MAXNT == 8 || nt <= 8)) {
-        for (int r2 = 0; r2 < RTG; r2 += 2)
-          down_group<2, 8, PACKED ? 1 : 2, PACKED>(v, t, dt_begin + r2, 0, lane, turn);
-        done = true;
-      }
-    }
-  }
-  if (!done) {  // ragged row group, or more than 128 pairs: one row tile at a time
-    for (int dt = dt_begin; dt < dt_end; ++dt) {
-      if constexpr (MAXNT <= 4) {
-        down_group<1, MAXNT, 2, PACKED>(v, t, dt, 0, lane, turn);
-      } else {
-        for (int g0 = 0; g0 < t.count; g0 += 16 * MAXNT)
-          down_group<1, MAXNT, PACKED ? 1 : 2, PACKED>(v, t, dt, g0, lane, turn);
-      }
-    }
+  if (dt_end - dt_begin < RTG) {  // ragged row group: one row tile at a time
+    for (int dt = dt_begin; dt < dt_end; ++dt) down_group<1, MAXNT, 2, PACKED>(v, t, dt, lane, turn);
+  } else if (MAXNT == 1 || t.count <= 16) {
+    down_group<RTG, 1, U1, PACKED>(v, t, dt_begin, lane, turn);
+  } else {
+    down_group<RTG, MAXNT, U2, PACKED>(v, t, dt_begin, lane, turn);
   }
   return true;
 }
@@ -676,7 +609,7 @@ __device__ __forceinline__ bool lds_task(const FfnArgs& a, int per_expert, int p
 // it to be one of the unrolled cases, else 0.  A split takes every splits-th group of
 // 16*MAXNT pairs of the expert: an expert with more pairs than one pass holds
 // is spread over several workgroups (its weights are then read once per pass).
-template <bool PACKED, int MAXNT, int LW, int KD>
+template <int MAXNT, int LW, int KD>
 __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void gateup_lds_kernel(FfnArgs a) {
   constexpr int kRows = 16 * MAXNT;
   __shared__ __align__(16) uint16_t lds[lds_elems(KD)];
@@ -692,9 +625,9 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void g
   const int tile = group * LW + wave;
   const bool active = tile < t.fdim / 16;
   const uint16_t* w0 = uniform_ptr(t.w0);
-  const uint16_t* gp = tile_base<PACKED>(w0, active ? tile : 0, a.D);
-  const uint16_t* up = tile_base<PACKED>(uniform_ptr(t.w1), active ? tile : 0, a.D);
-  const uint32_t wlo = tile_lane_off<PACKED>(a.D, lane);
+  const uint16_t* gp = tile_base<true>(w0, active ? tile : 0, a.D);
+  const uint16_t* up = tile_base<true>(uniform_ptr(t.w1), active ? tile : 0, a.D);
+  const uint32_t wlo = tile_lane_off<true>(a.D, lane);
   const uint16_t* x = uniform_ptr(static_cast<const uint16_t*>(a.x));
   uint16_t* h = static_cast<uint16_t*>(v.h);
   for (int g0 = split * kRows; g0 < t.count; g0 += splits * kRows) {
@@ -713,7 +646,7 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void g
         accu[i] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
       constexpr int KC = NT <= 4 ? 128 : 64;  // rows * KC = one 16 KB buffer
-      dma_stream_gemm<NT, kLdsBufElems / KC, PACKED, LW, KC, KD>(gp, up, wlo, wave, a.D, rows, x,
+      dma_stream_gemm<NT, kLdsBufElems / KC, true, LW, KC, KD>(gp, up, wlo, wave, a.D, rows, x,
                                                                  row_off, lds, accg, accu);
       if (!active) return;
 #pragma unroll
@@ -744,7 +677,7 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void g
 #endif
 }
 
-template <bool PACKED, int MAXNT, int LW, int KD>
+template <int MAXNT, int LW, int KD>
 __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void down_lds_kernel(FfnArgs a) {
   constexpr int kRows = 16 * MAXNT;
   __shared__ __align__(16) uint16_t lds[lds_elems(KD)];
@@ -760,9 +693,9 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void d
   const bool active = dt0 < dtiles;
   const int F = t.fdim;
   const uint16_t* w0 = uniform_ptr(t.w0);
-  const uint16_t* p0 = tile_base<PACKED>(w0, active ? dt0 : 0, F);
-  const uint16_t* p1 = tile_base<PACKED>(w0, active ? dt0 + 1 : 0, F);
-  const uint32_t wlo = tile_lane_off<PACKED>(F, lane);
+  const uint16_t* p0 = tile_base<true>(w0, active ? dt0 : 0, F);
+  const uint16_t* p1 = tile_base<true>(w0, active ? dt0 + 1 : 0, F);
+  const uint32_t wlo = tile_lane_off<true>(F, lane);
   const uint16_t* h = uniform_ptr(static_cast<const uint16_t*>(v.h));
   const size_t orow0 = t.shared ? static_cast<size_t>(a.T) * a.K : static_cast<size_t>(t.pair0);
   for (int g0 = split * kRows; g0 < t.count; g0 += splits * kRows) {
@@ -779,7 +712,7 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void d
         acc1[i] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
       constexpr int KC = NT <= 4 ? 128 : 64;
-      dma_stream_gemm<NT, kLdsBufElems / KC, PACKED, LW, KC, KD>(p0, p1, wlo, wave, F, rows, h,
+      dma_stream_gemm<NT, kLdsBufElems / KC, true, LW, KC, KD>(p0, p1, wlo, wave, F, rows, h,
                                                                  row_off, lds, acc0, acc1);
       if (!active) return;
 #pragma unroll
@@ -797,6 +730,123 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void d
     else if (MAXNT <= 4 || nt <= 4) run(std::integral_constant<int, 4>{});
     else if (nt <= 6) run(std::integral_constant<int, MAXNT >= 8 ? 6 : 4>{});
     else run(std::integral_constant<int, MAXNT >= 8 ? 8 : 4>{});
+  }
+}
+
+// ------------------------------------------ many token rows: weights and tokens in LDS tiles
+// The same work list (a unit = up to 128 token rows of an expert), the tiles of
+// des_tile_gemm.h: a workgroup has 64 intermediate units (their gate and up rows), or 128
+// output rows, of one unit.  Every sum runs over the reduction in the same order as in the
+// other kernels, so which of them ran cannot be told from the results.
+constexpr int kTileMt = 4;  // row tiles of a wavefront
+template <bool PACKED, int MAXNT>
+__global__ __launch_bounds__(kTileThreads, 2) void gateup_tile_kernel(FfnArgs a) {
+  constexpr int MT = kTileMt, HT = MT / 2, kRows = 32 * MAXNT;
+  __shared__ __align__(16) char lds[tile_lds_bytes<MT, MAXNT, 1>()];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  Task t;
+  FfnArgs v;
+  int group, split, splits;
+  if (!lds_task<false>(a, (a.F / 16 + MT - 1) / MT, (a.Fs / 16 + MT - 1) / MT, group, split, splits, t, v, lane))
+    return;
+  const int tiles = t.fdim / 16, f0 = group * MT;  // this workgroup's first 16 units
+  const uint16_t* x = static_cast<const uint16_t*>(a.x);
+  uint16_t* h = static_cast<uint16_t*>(v.h);
+  // row tile q of the workgroup: wavefronts wm have gate tiles, then the up tiles of the same units
+  const uint16_t* aptr[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    const int q = 2 * i + (tid >> 7), ft = min(f0 + q / MT * HT + q % HT, tiles - 1);
+    aptr[i] = tile_weight_ptr<PACKED>((q % MT < HT ? t.w0 : t.w1) + static_cast<size_t>(ft) * 16 * a.D, a.D, tid);
+  }
+  for (int g0 = split * kRows; g0 < t.count; g0 += splits * kRows) {
+    const int rows = min(kRows, t.count - g0);
+    auto run = [&](auto ntc) {
+      constexpr int NT = decltype(ntc)::value;
+      const uint16_t* bptr[NT];
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        const int r = g0 + min(i * 32 + (tid >> 3), rows - 1);
+        bptr[i] = x + static_cast<size_t>(t.shared ? r : a.pair_tok[t.pair0 + r]) * a.D + (tid & 7) * 8;
+      }
+      f32x4 acc[MT][NT];
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      tile_gemm<MT, NT, 1, 1, PACKED>(aptr, bptr, a.D, lds, acc);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        const int r = (wn * NT + j) * 16 + (lane & 15);
+        if (r >= rows) continue;
+#pragma unroll
+        for (int i = 0; i < HT; ++i) {
+          const int ft = f0 + wm * HT + i;
+          if (ft >= tiles) continue;
+          u16x4 o;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) o[q] = f32_to_bf16_bits(silu_f(acc[i][j][q]) * acc[HT + i][j][q]);
+          *reinterpret_cast<u16x4*>(h + (t.row_base + g0 + r) * t.fdim + ft * 16 + 4 * (lane >> 4)) = o;
+        }
+      }
+    };
+    if (rows <= 32) run(std::integral_constant<int, 1>{});
+    else if (rows <= 64) run(std::integral_constant<int, 2>{});
+    else if (rows <= 96) run(std::integral_constant<int, MAXNT < 3 ? MAXNT : 3>{});
+    else run(std::integral_constant<int, MAXNT>{});
+  }
+}
+
+template <bool PACKED, int MAXNT>
+__global__ __launch_bounds__(kTileThreads, 2) void down_tile_kernel(FfnArgs a) {
+  constexpr int MT = kTileMt, kRows = 32 * MAXNT;
+  __shared__ __align__(16) char lds[tile_lds_bytes<MT, MAXNT, 1>()];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  Task t;
+  FfnArgs v;
+  int group, split, splits;
+  const int tiles = a.D / 16, per = (tiles + 2 * MT - 1) / (2 * MT);
+  if (!lds_task<true>(a, per, a.Fs > 0 ? per : 0, group, split, splits, t, v, lane)) return;
+  const int F = t.fdim, d0 = group * 2 * MT;
+  const uint16_t* h = static_cast<const uint16_t*>(v.h);
+  const size_t orow0 = t.shared ? static_cast<size_t>(a.T) * a.K : static_cast<size_t>(t.pair0);
+  const uint16_t* aptr[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+    aptr[i] = tile_weight_ptr<PACKED>(
+        t.w0 + static_cast<size_t>(min(d0 + 2 * i + (tid >> 7), tiles - 1)) * 16 * F, F, tid);
+  for (int g0 = split * kRows; g0 < t.count; g0 += splits * kRows) {
+    const int rows = min(kRows, t.count - g0);
+    auto run = [&](auto ntc) {
+      constexpr int NT = decltype(ntc)::value;
+      const uint16_t* bptr[NT];
+#pragma unroll
+      for (int i = 0; i < NT; ++i)
+        bptr[i] = h + (t.row_base + g0 + min(i * 32 + (tid >> 3), rows - 1)) * F + (tid & 7) * 8;
+      f32x4 acc[MT][NT];
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      tile_gemm<MT, NT, 1, 1, PACKED>(aptr, bptr, F, lds, acc);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        const int r = (wn * NT + j) * 16 + (lane & 15);
+        if (r >= rows) continue;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+          const int dt = d0 + wm * MT + i;
+          if (dt < tiles)
+            *reinterpret_cast<f32x4*>(a.o + (orow0 + g0 + r) * a.D + dt * 16 + 4 * (lane >> 4)) = acc[i][j];
+        }
+      }
+    };
+    if (rows <= 32) run(std::integral_constant<int, 1>{});
+    else if (rows <= 64) run(std::integral_constant<int, 2>{});
+    else if (rows <= 96) run(std::integral_constant<int, MAXNT < 3 ? MAXNT : 3>{});
+    else run(std::integral_constant<int, MAXNT>{});
   }
 }
 
@@ -1031,7 +1081,6 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
   a.slots = reinterpret_cast<const int4*>(ws + w.slots);
   a.meta = reinterpret_cast<const int32_t*>(ws + w.meta);
   a.pair_tok = reinterpret_cast<const int32_t*>(ws + w.pair_tok);
-  a.slot_tok = reinterpret_cast<const uint16_t*>(ws + w.slot_tok);
   a.units = reinterpret_cast<const int32_t*>(ws + w.units);
   a.pos = reinterpret_cast<const int32_t*>(ws + w.pos);
   a.h = ws + w.h;
@@ -1083,79 +1132,96 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
     const int dn_fine_tasks = a.n_slots * dn_fine_groups + (a.Fs > 0 ? dn_fine_groups : 0);
 #define DES_LAUNCH_FFN(NTV, PK)                                                             \
   do {                                                                                      \
-    if (gu_fine && NTV <= 2)                                                                \
+    if (gu_fine)                                                                \
       launch(kKGateUp, gateup_bf16_kernel<NTV, PK, 4, 4, 1>, dim3(gu_fine_tasks + n_s2), blk, 0, st, a); \
     else                                                                                    \
       launch(kKGateUp, gateup_bf16_kernel<NTV, PK>, dim3(gu_blocks), blk, 0, st, a);        \
-    if (dn_fine && NTV <= 2)                                                                \
+    if (dn_fine)                                                                \
       launch(kKDown, down_bf16_kernel<NTV, PK, 4, 4, 2>, dim3(dn_fine_tasks), blk, 0, st, a); \
     else                                                                                    \
       launch(kKDown, down_bf16_kernel<NTV, PK>, dim3(dn_blocks), blk, 0, st, a);            \
   } while (0)
-#define DES_LAUNCH_BY_NT(PK)                                                                \
-  do {                                                                                      \
-    if (maxnt <= 1) DES_LAUNCH_FFN(1, PK);                                                  \
-    else if (maxnt <= 2) DES_LAUNCH_FFN(2, PK);                                             \
-    else if (maxnt <= 4) DES_LAUNCH_FFN(4, PK);                                             \
-    else if (maxnt <= 8) DES_LAUNCH_FFN(8, PK);                                             \
-    else DES_LAUNCH_FFN(16, PK);                                                            \
-  } while (0)
-    const bool chunked = a.D % kKC == 0 && a.F % kKC == 0 && a.Fs % kKC == 0;
-    if (a.T > 32 && chunked) {
-      // Larger blocks: activations staged through LDS.  Token rows per workgroup
-      // pass: 64 while no expert can have more, else 128; an expert with more
-      // pairs is spread over up to kMaxSplits workgroups (the unit list).  Wavefronts per workgroup:
-      // two give the finest spread of the weight bytes over the compute units;
-      // four share the staged activations among more weight rows, which
-      // measured better once experts have many tokens (48-layer stack: 7.7 ms
-      // against 8.0 ms; down projection at T = 128: 23 us against 27 us).
+    if (a.T > 32) {
+      // Longer blocks: units of 64 token rows while no expert can have more, else 128; an
+      // expert with more pairs is spread over up to kMaxSplits of them (the unit list).
+      //
+      // Two forms of each kernel.  Streamed (weights straight into operands, token rows
+      // through LDS): packed weights whose reduction is one of the unrolled ones - or, with
+      // fewer than 32 pairs per possible expert, any whole number of its chunks.  Tiles (both
+      // through LDS): everything else.  128 experts of 2048 x 768 under 256 tokens, gate/up + down: packed 68.3 + 40.0
+      // us streamed, 77.6 + 43.6 in tiles; row-major (64 bytes of a row per operand load)
+      // 99.9 + 54.8 and 81.3 + 45.0.  64 experts of 1536 x 1408, packed, not unrolled:
+      // 16 pairs per expert 78.0 + 50.0 and 80.5 + 51.6, 32 pairs 111 + 64.9 and 98.5 + 56.5,
+      // 128 pairs 223 + 126 and 168 + 97; 512 x 896 with 8 pairs 27.5 + 13.9 and 25.9 + 17.5.  Sizes that are no multiple of the streamed chunk had one
+      // wavefront per 16 or 32 weight rows gather everything from L2 (256 experts of
+      // 1440 x 288, 189 tokens: 75.7 + 42.6, now 25 + 15).
       const int rows_pass = lds_rows_pass(a.T);
       const bool small = rows_pass == 64;
       int splits = (a.T + rows_pass - 1) / rows_pass;  // of the shared expert (all T rows)
       if (splits > kMaxSplits) splits = kMaxSplits;
-      const int n_units = max_units(s);
-      const int gu_lw = a.T <= 128 ? 2 : 4;
-      const int dn_lw = a.T <= 64 ? 2 : 4;
-      const int gu_lds = n_units * ((a.F / 16 + gu_lw - 1) / gu_lw) + splits * ((a.Fs / 16 + gu_lw - 1) / gu_lw);
-      const int per_dn = (a.D / 32 + dn_lw - 1) / dn_lw;
-      const int dn_lds = n_units * per_dn + (a.Fs > 0 ? splits * per_dn : 0);
-      const dim3 gg(gu_lds), dg(dn_lds);
       a.splits = splits;
+      const int n_units = max_units(s);
       // unrolled reduction lengths (the shared expert shares the down launch)
       const int gu_kd = a.D == 2048 ? 2048 : 0;
       const int dn_kd = (a.Fs != 0 && a.Fs != a.F) ? 0 : (a.F == 768 || a.F == 512) ? a.F : 0;
-#define DES_LAUNCH_GU(PK, MNT, LWV)                                                         \
+      const bool few = TK < 32 * a.n_slots;
+      const bool gu_stream = packed && a.D % kKC == 0 && (gu_kd > 0 || few);
+      const bool dn_stream = packed && a.F % kKC == 0 && a.Fs % kKC == 0 && (dn_kd > 0 || few);
+#define DES_LAUNCH_GU(MNT, LWV)                                                             \
   do {                                                                                      \
-    const dim3 lb(LWV* kWave);                                                              \
-    if (gu_kd == 2048) launch(kKGateUp, gateup_lds_kernel<PK, MNT, LWV, 2048>, gg, lb, 0, st, a); \
-    else launch(kKGateUp, gateup_lds_kernel<PK, MNT, LWV, 0>, gg, lb, 0, st, a);            \
+    if (gu_kd == 2048) launch(kKGateUp, gateup_lds_kernel<MNT, LWV, 2048>, gg, dim3(LWV* kWave), 0, st, a); \
+    else launch(kKGateUp, gateup_lds_kernel<MNT, LWV, 0>, gg, dim3(LWV* kWave), 0, st, a);  \
   } while (0)
-#define DES_LAUNCH_DN(PK, MNT, LWV)                                                         \
+#define DES_LAUNCH_DN(MNT, LWV)                                                             \
   do {                                                                                      \
-    const dim3 lb(LWV* kWave);                                                              \
-    if (dn_kd == 768) launch(kKDown, down_lds_kernel<PK, MNT, LWV, 768>, dg, lb, 0, st, a); \
-    else if (dn_kd == 512) launch(kKDown, down_lds_kernel<PK, MNT, LWV, 512>, dg, lb, 0, st, a); \
-    else launch(kKDown, down_lds_kernel<PK, MNT, LWV, 0>, dg, lb, 0, st, a);                \
+    if (dn_kd == 768) launch(kKDown, down_lds_kernel<MNT, LWV, 768>, dg, dim3(LWV* kWave), 0, st, a); \
+    else if (dn_kd == 512) launch(kKDown, down_lds_kernel<MNT, LWV, 512>, dg, dim3(LWV* kWave), 0, st, a); \
+    else launch(kKDown, down_lds_kernel<MNT, LWV, 0>, dg, dim3(LWV* kWave), 0, st, a);      \
   } while (0)
-#define DES_LAUNCH_LDS(PK)                                                        \
-  do {                                                                            \
-    if (small) DES_LAUNCH_GU(PK, 4, 2);                                           \
-    else if (gu_lw == 2) DES_LAUNCH_GU(PK, 8, 2);                                 \
-    else DES_LAUNCH_GU(PK, 8, 4);                                                 \
-    if (small) DES_LAUNCH_DN(PK, 4, 2);                                           \
-    else DES_LAUNCH_DN(PK, 8, 4);                                                 \
+#define DES_LAUNCH_TILE(id, kernel, g)                                                      \
+  do {                                                                                      \
+    const dim3 tb(kTileThreads);                                                            \
+    if (packed && small) launch(id, kernel<true, 2>, g, tb, 0, st, a);                      \
+    else if (packed) launch(id, kernel<true, 4>, g, tb, 0, st, a);                          \
+    else if (small) launch(id, kernel<false, 2>, g, tb, 0, st, a);                          \
+    else launch(id, kernel<false, 4>, g, tb, 0, st, a);                                     \
   } while (0)
-      if (packed) DES_LAUNCH_LDS(true);
-      else DES_LAUNCH_LDS(false);
+      if (gu_stream) {
+        // Wavefronts per workgroup: two give the finest spread of the weight bytes over the
+        // compute units; four share the staged activations among more weight rows, which
+        // measured better once experts have many tokens (48-layer stack: 7.7 ms against
+        // 8.0 ms; down projection at T = 128: 23 us against 27 us).
+        const int lw = a.T <= 128 ? 2 : 4;
+        const dim3 gg(n_units * ((a.F / 16 + lw - 1) / lw) + splits * ((a.Fs / 16 + lw - 1) / lw));
+        if (small) DES_LAUNCH_GU(4, 2);
+        else if (lw == 2) DES_LAUNCH_GU(8, 2);
+        else DES_LAUNCH_GU(8, 4);
+      } else {
+        const int per = (a.F / 16 + kTileMt - 1) / kTileMt, per_s = (a.Fs / 16 + kTileMt - 1) / kTileMt;
+        const dim3 gg(n_units * per + splits * per_s);
+        DES_LAUNCH_TILE(kKGateUp, gateup_tile_kernel, gg);
+      }
+      if (dn_stream) {
+        const int lw = a.T <= 64 ? 2 : 4;
+        const int per = (a.D / 32 + lw - 1) / lw;
+        const dim3 dg(n_units * per + (a.Fs > 0 ? splits * per : 0));
+        if (small) DES_LAUNCH_DN(4, 2);
+        else DES_LAUNCH_DN(8, 4);
+      } else {
+        const int per = (a.D / 16 + 2 * kTileMt - 1) / (2 * kTileMt);
+        const dim3 dg(n_units * per + (a.Fs > 0 ? splits * per : 0));
+        DES_LAUNCH_TILE(kKDown, down_tile_kernel, dg);
+      }
 #undef DES_LAUNCH_GU
 #undef DES_LAUNCH_DN
-#undef DES_LAUNCH_LDS
+#undef DES_LAUNCH_TILE
     } else if (packed) {
-      DES_LAUNCH_BY_NT(true);
+      if (maxnt <= 1) DES_LAUNCH_FFN(1, true);
+      else DES_LAUNCH_FFN(2, true);
     } else {
-      DES_LAUNCH_BY_NT(false);
+      if (maxnt <= 1) DES_LAUNCH_FFN(1, false);
+      else DES_LAUNCH_FFN(2, false);
     }
-#undef DES_LAUNCH_BY_NT
 #undef DES_LAUNCH_FFN
     dim3 cg(a.T, (a.D / 4 + 255) / 256);
     launch(kKCombine, combine_kernel<true>, cg, dim3(256), 0, st, a);

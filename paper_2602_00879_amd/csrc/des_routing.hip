@@ -72,7 +72,6 @@ struct RoutingArgs {
   uint32_t* sel_part;         // [B*groups][3][kSelPartStride] per-group election partials
   unsigned long long epoch;
   int32_t* slot_of;       // [M] slot of each live expert, -1 otherwise
-  uint16_t* slot_tok;     // [n_slots][kSlotToks] tokens of each slot's first pairs
   int B, N, M, K, C, k_seq, mode, cap, D, n_slots;
   int groups;             // selector workgroups per sequence (each takes every groups-th pass)
   int k_route;            // experts per token in stage 2 (<= K)
@@ -890,29 +889,17 @@ __device__ void permute_all(const RoutingArgs& a, char* smem, bool idx_dev, int 
         const int nu = units_of(c);
         for (int k = 0; k < nu; ++k) a.units[s_uoff[e] + k] = sl | (k << 16) | (nu << 24);
         if (sl == n_live - 1) a.meta[2] = s_uoff[e] + nu;  // the last slot closes the list
-        // entries of the slot-major token table past a slot's count must still name a
-        // valid token (the others are filled with the pairs below; up to 32 tokens the
-        // FFN kernels take an expert's tokens from the bitmap in its record)
-        for (int k = c; k < kSlotToks; ++k) a.slot_tok[sl * kSlotToks + k] = 0;
       }
     }
-    for (int s = n_live + tid; s < a.n_slots; s += kRtThreads) {
-      a.slots[s] = make_int4(-1, 0, 0, 0);
-      if (by_count)
-        for (int k = 0; k < kSlotToks; ++k) a.slot_tok[s * kSlotToks + k] = 0;
-    }
+    for (int s = n_live + tid; s < a.n_slots; s += kRtThreads) a.slots[s] = make_int4(-1, 0, 0, 0);
   }
   auto place = [&](int p, int e) {
     if (e < 0) { a.pos[p] = -1; return; }
     const int t = p / K;
     const size_t w = static_cast<size_t>(e) * words + (t >> 5);
-    const int within = s_pre[w] + __popc(member[w] & ((1u << (t & 31)) - 1u));
-    const int r = s_off[e] + within;
+    const int r = s_off[e] + s_pre[w] + __popc(member[w] & ((1u << (t & 31)) - 1u));
     a.pair_tok[r] = t;
     a.pos[p] = r;
-    const int sl = by_count ? s_slot[e] : s_liv[e];
-    if (T > 32 && within < kSlotToks && sl < a.n_slots)
-      a.slot_tok[sl * kSlotToks + within] = static_cast<uint16_t>(t);
   };
   if (keep) {
 #pragma unroll
@@ -952,7 +939,7 @@ __device__ void publish_empty(const RoutingArgs& a, int n_flags) {
 // ran in this workgroup: stage 2 has left, per expert, the bitmap of the tokens routed
 // to it (s_mask), so counts are popcounts, an expert's pairs in token order are its set
 // bits in order, and a pair's sorted position is a popcount below its token's bit.  No
-// second pass over the indices to build bitmaps, no token table (the FFN kernels take
+// second pass over the indices to build bitmaps (the FFN kernels take
 // the bitmap from the slot record).
 template <int LPT>
 __device__ void permute_small(const RoutingArgs& a, char* smem) {
@@ -1236,7 +1223,6 @@ int launch_routing(const des_shape_t& s, const void* x, const void* w_router, co
   a.slot_of = reinterpret_cast<int32_t*>(ws + w.slot_of);
   a.units = reinterpret_cast<int32_t*>(ws + w.units);
   a.rows_shift = lds_rows_pass(s.n_seqs * s.n_tokens) == 64 ? 6 : 7;
-  a.slot_tok = reinterpret_cast<uint16_t*>(ws + w.slot_tok);
   a.sel_part = reinterpret_cast<uint32_t*>(ws + w.sel_part);
   const int n_tiles = a.tiles_m * a.tiles_t;
   int fused_limit = device_compute_units();

@@ -7,7 +7,7 @@
 // from HBM straight into MFMA operands (des_stream_gemm.h).  With more, that form leaves a
 // wavefront with one long chain - read the token fragments from LDS, wait, multiply - and,
 // for one dense matrix, the chip with too few wavefronts.  Here a tile's reduction runs in
-// chunks of 64: two LDS buffers, the next chunks in registers on their way.  Loads are ordinary loads, the
+// chunks of 64: two LDS buffers, the next P chunks in registers on their way.  Loads are ordinary loads, the
 // compiler places their waits.
 #pragma once
 
@@ -16,7 +16,8 @@
 
 namespace des {
 
-constexpr int kTileK = 64;  // reduction elements per chunk
+constexpr int kTileK = 64;          // reduction elements per chunk
+constexpr int kTileThreads = 256;   // four wavefronts, 2 x 2 over the tile
 
 // LDS of one workgroup: two buffers of one chunk of (32 MT weight + 32 NT token) rows x 128
 // bytes, for each of the KW parts of the reduction.
@@ -28,9 +29,11 @@ constexpr int tile_lds_bytes() { return KW * 2 * 32 * (MT + NT) * kTileK * 2; }
 // rows x 32 NT token rows; wavefront (wm, wn) of the 2 x 2 has weight rows 16 MT wm .. and
 // token rows 16 NT wn ..  With KW = 2 the workgroup has two such groups, each with its half
 // of the reduction (`kd` and the pointers are the group's own, the lengths are equal).
-// Row pointers of this thread (t = thread of the group): aptr[i] = row i * 32 + t / 8 of the
-// weight tile, element 8 * (t % 8); bptr[i] likewise for the token tile (a row past the end
-// repeats another, the caller drops its results).  The whole workgroup calls it together.
+// Pointers of this thread (t = thread of the group): aptr[i] = tile_weight_ptr() of row tile
+// 2 i + t / 128 of the weight tile (row tiles 0 .. MT - 1 are wavefronts wm = 0's, the others
+// wm = 1's); bptr[i] = element 8 * (t % 8) of token row i * 32 + t / 8 (a tile or row past the
+// end repeats another, the caller drops its results).  PACKED: the weights' layout, operand
+// tiles of 16 rows x 32 elements.  The whole workgroup calls it together.
 // Every sum runs over the reduction in ascending steps of 32 whatever the tile, so the
 // results do not depend on MT or NT.
 //
@@ -42,10 +45,13 @@ constexpr int tile_lds_bytes() { return KW * 2 * 32 * (MT + NT) * kTileK * 2; }
 // Rows lie 128 bytes apart in LDS, the 16-byte piece p of row r at p ^ (r / 2 % 8): a
 // wavefront's writes (8 rows) and its operand reads (16 rows, one piece) both fall into
 // different banks.
-template <int MT, int NT, int KW>
+template <bool PACKED>
+__device__ __forceinline__ const uint16_t* tile_weight_ptr(const uint16_t* row_tile, int kd, int t) {
+  return PACKED ? row_tile + (t & 63) * 8 : row_tile + static_cast<size_t>((t >> 3) & 15) * kd + (t & 7) * 8;
+}
+template <int MT, int NT, int KW, int P, bool PACKED>
 __device__ __forceinline__ void tile_gemm(const uint16_t* const (&aptr)[MT], const uint16_t* const (&bptr)[NT],
                                           int kd, char* lds, f32x4 (&acc)[MT][NT]) {
-  constexpr int P = 2;  // chunks on their way in registers
   constexpr int kBuf = 32 * (MT + NT) * kTileK * 2;
   const int grp = KW > 1 ? threadIdx.x >> 8 : 0;
   const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
@@ -54,30 +60,40 @@ __device__ __forceinline__ void tile_gemm(const uint16_t* const (&aptr)[MT], con
   const int piece = tid & 7, srow = tid >> 3;
   lds += grp * 2 * kBuf;
   const int sdst = srow * 128 + ((piece ^ ((srow >> 1) & 7)) << 4);  // + 32 rows: the same swizzle
+  // weights: the same place (row-major), or two operand tiles per chunk (packed): this wavefront
+  // loads the first or the second, lane l has piece l / 16 of row l % 16 of it
+  const int arow = PACKED ? (wave >> 1) * 16 + (lane & 15) : srow;
+  const int apiece = PACKED ? (wave & 1) * 4 + (lane >> 4) : piece;
+  const int adst = arow * 128 + ((apiece ^ ((arow >> 1) & 7)) << 4);
   uint4 ra[P][MT], rb[P][NT];
   auto load = [&](int st, auto set) {
     constexpr int z = decltype(set)::value;
     // pieces past the end of the reduction fetch its last elements; store() replaces them
     // with zeros
     const int k = min(st * kTileK + piece * 8, kd - 8) - piece * 8;
+    const size_t ka = PACKED ? static_cast<size_t>(min(2 * st + (wave & 1), kd / 32 - 1)) * 512 : k;
 #pragma unroll
-    for (int i = 0; i < MT; ++i) ra[z][i] = *reinterpret_cast<const uint4*>(aptr[i] + k);
+    for (int i = 0; i < MT; ++i) ra[z][i] = *reinterpret_cast<const uint4*>(aptr[i] + ka);
 #pragma unroll
     for (int i = 0; i < NT; ++i) rb[z][i] = *reinterpret_cast<const uint4*>(bptr[i] + k);
   };
   auto store = [&](int st, auto set) {
     constexpr int z = decltype(set)::value;
-    if ((st + 1) * kTileK > kd && st * kTileK + piece * 8 >= kd) {
+    if ((st + 1) * kTileK > kd) {
+      if (st * kTileK + apiece * 8 >= kd) {
 #pragma unroll
-      for (int i = 0; i < MT; ++i) ra[z][i] = make_uint4(0u, 0u, 0u, 0u);
+        for (int i = 0; i < MT; ++i) ra[z][i] = make_uint4(0u, 0u, 0u, 0u);
+      }
+      if (st * kTileK + piece * 8 >= kd) {
 #pragma unroll
-      for (int i = 0; i < NT; ++i) rb[z][i] = make_uint4(0u, 0u, 0u, 0u);
+        for (int i = 0; i < NT; ++i) rb[z][i] = make_uint4(0u, 0u, 0u, 0u);
+      }
     }
-    char* buf = lds + (st & 1) * kBuf + sdst;
+    char* buf = lds + (st & 1) * kBuf;
 #pragma unroll
-    for (int i = 0; i < MT; ++i) *reinterpret_cast<uint4*>(buf + i * 4096) = ra[z][i];
+    for (int i = 0; i < MT; ++i) *reinterpret_cast<uint4*>(buf + i * 4096 + adst) = ra[z][i];
 #pragma unroll
-    for (int i = 0; i < NT; ++i) *reinterpret_cast<uint4*>(buf + (MT + i) * 4096) = rb[z][i];
+    for (int i = 0; i < NT; ++i) *reinterpret_cast<uint4*>(buf + (MT + i) * 4096 + sdst) = rb[z][i];
   };
   const int r = lane & 15, g = lane >> 4, sw = (r >> 1) & 7;
   auto compute = [&](int st) {

@@ -22,6 +22,16 @@ BATCHES = {
     "aligned": (64, 32, 256, 128, 128, 0, 8, 32),
     "most_tokens": (32, 128, 128, 64, 128, 128, 4, 8),
     "few_experts": (20, 100, 128, 8, 256, 0, 2, 3),
+    # the tiles of the expert kernels: units of at most 64 rows, reductions of whole chunks of
+    # 64 and half a chunk more (one chunk at most, too), row tiles that do not fill a workgroup,
+    # a shared expert of another width, unrolled and other packed sizes on both
+    # sides of 32 pairs per expert
+    "tiles_small": (5, 10, 224, 16, 160, 160, 2, 4),
+    "tiles_33_tokens": (3, 11, 32, 16, 32, 0, 3, 5),
+    "tiles_96_rows": (1, 97, 288, 8, 224, 64, 4, 4),
+    "streamed_31_pairs": (5, 33, 256, 16, 384, 128, 3, 6),
+    "tiles_32_pairs": (5, 35, 256, 16, 384, 128, 3, 6),
+    "unrolled_256_tokens": (8, 32, 2048, 8, 512, 512, 2, 4),
 }
 
 
