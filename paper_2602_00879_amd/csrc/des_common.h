@@ -27,6 +27,9 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
   return static_cast<uint16_t>(u >> 16);
 }
 
+// A value that is the same in all lanes, in a scalar register.
+__device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // ------------------------------------------------------- wavefront reductions
 // DPP controls (GFX9): quad_perm [1,0,3,2] = 0xB1, [2,3,0,1] = 0x4E,
 // row_shr:n = 0x110+n, row_bcast:15 = 0x142, row_bcast:31 = 0x143.

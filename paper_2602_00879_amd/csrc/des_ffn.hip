@@ -100,59 +100,6 @@ __device__ __forceinline__ bf16x8 zero8() {
   return z;
 }
 
-// The weight stream of one wavefront: `steps` stages in two register sets.  load(st, set)
-// requests stage st, compute(set) multiplies it.  The trips carry no branch, so the
-// compiler waits for exactly the stage it needs and the next one stays in flight (with a
-// test for the end around each load it waited for everything outstanding); the scheduling
-// barriers keep a stage's loads together in front of the multiplies.  More sets do not
-// help: what bounds these kernels is the chip's read rate and its spread over the compute
-// units (128-expert layer, 32 tokens: 34.4 us with two, three or four sets of two k-steps;
-// where fewer wavefronts are in flight the branch-free form pays: 16 of 256 experts 22.3 ->
-// 20.0 us, 4 tokens 20.2 -> 18.6 us, the down projections 12.1 -> 11.1 and 12.0 -> 10.6).
-template <typename Load, typename Compute>
-__device__ __forceinline__ void stream_pipeline(int steps, Load&& load, Compute&& compute) {
-  if (steps > 0) load(0, S0{});
-  int st = 0;
-  for (; st + 3 <= steps; st += 2) {
-    load(st + 1, S1{});
-    __builtin_amdgcn_sched_barrier(0);
-    compute(S0{});
-    __builtin_amdgcn_sched_barrier(0);
-    load(st + 2, S0{});
-    __builtin_amdgcn_sched_barrier(0);
-    compute(S1{});
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  if (st < steps) {
-    if (st + 1 < steps) load(st + 1, S1{});
-    compute(S0{});
-    if (st + 1 < steps) compute(S1{});
-  }
-}
-
-// Row-major weights.  An MFMA A operand takes 16 rows x 32 elements, 64 bytes of each
-// row: a load in operand order touches 16 half lines, and the kernels then ran at 3.6 TB/s
-// where packed tiles reach 5.8 (33 experts of 2048 x 768: gate/up 58.4 us, down 31.8 us; as
-// below 44.4 and 23.2, packed 42.5 and 21.8).  So row-major tiles are loaded in whole 128-byte lines (a load = 8 rows x 64 elements, lane l has
-// piece l % 8 of row l / 8) and turned into operand order through a few KB of LDS that
-// belong to the wavefront alone: two loads (v[0], v[1]: rows 0-7 and 8-15) become the
-// operands of two k-steps.  16-byte piece p of row r is kept at piece p ^ (r / 2 % 8), so
-// writes and reads both spread over all banks.
-constexpr int kTurnBytes = 2048;  // of LDS per 16 x 64 tile
-__device__ __forceinline__ void turn_write(const bf16x8& v0, const bf16x8& v1, char* tile, int lane) {
-  const int r = lane >> 3, p = lane & 7;
-  *reinterpret_cast<bf16x8*>(tile + r * 128 + ((p ^ (r >> 1)) << 4)) = v0;
-  *reinterpret_cast<bf16x8*>(tile + (r + 8) * 128 + ((p ^ ((r >> 1) + 4)) << 4)) = v1;
-}
-__device__ __forceinline__ bf16x8 turn_read(const char* tile, int u, int lane) {
-  const int r = lane & 15, p = u * 4 + (lane >> 4);
-  return *reinterpret_cast<const bf16x8*>(tile + r * 128 + ((p ^ (r >> 1)) << 4));
-}
-// the wavefront's LDS accesses stay in program order (they execute in order)
-__device__ __forceinline__ void turn_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 // This lane's place in the loads of row tile rt: packed tiles are in operand order already.
 template <bool PACKED>
 __device__ __forceinline__ const uint16_t* load_ptr(const uint16_t* base, int rt, int kd, int lane) {
@@ -380,7 +327,7 @@ __device__ __forceinline__ bool gateup_task(const FfnArgs& a, int task, int lane
     v = shared_view(a, t, 2);
     ft = (task - routed) * GT;
   }
-  if (MAXNT == 1 || t.count <= 16) gateup_group<GT, 1, U1, PACKED>(v, t, ft, lane, turn);
+  if (MAXNT == 1 || uniform_int(t.count) <= 16) gateup_group<GT, 1, U1, PACKED>(v, t, ft, lane, turn);
   else gateup_group<GT, MAXNT, U2, PACKED>(v, t, ft, lane, turn);
   DES_FSTAMP(task, 2);
 #ifdef DES_FFN_STAMPS
@@ -408,7 +355,7 @@ __global__ __launch_bounds__(kFfnWaves* kWave) void gateup_bf16_kernel(FfnArgs a
       if (task < n_s2) {
         __shared__ uint32_t s_sorted[kFfnWaves * kEpl * 64];
         uint32_t* srt = s_sorted + (threadIdx.x >> 6) * (kEpl * 64);
-        const int n_core = a.meta[0];
+        const int n_core = uniform_int(a.meta[0]);
         if (n_core <= 0) return;  // the routing launch gave up: nothing was elected
         switch (a.dn.lpt) {
           case 4: stage2_wave<4>(a.dn, a.T, a.M, a.K, n_core, task, srt); break;
@@ -435,8 +382,11 @@ template <int RT, int NT, int U, bool PACKED>
 __device__ __forceinline__ void down_group(const FfnArgs& a, const Task& t, int dt0, int lane,
                                            char* turn) {
   static_assert(PACKED || U % 2 == 0, "row-major stages are whole 64-element blocks");
-  const int F = t.fdim;
-  const int nks = F / 32;
+  // the trip counts are uniform (see stream_pipeline); the addresses of row-major tiles are
+  // better derived in vector registers (33 experts of 2048 x 768: 23.2 us against 26.1 us, the
+  // compiler spends scalar instructions per load otherwise), packed ones in scalars (19.7, 20.1)
+  const int F = PACKED ? uniform_int(t.fdim) : t.fdim;
+  const int nks = uniform_int(F / 32);
   const uint16_t* h = static_cast<const uint16_t*>(a.h);
   const uint16_t* ap[RT];
 #pragma unroll
@@ -546,9 +496,9 @@ __device__ __forceinline__ bool down_task(const FfnArgs& a, int task, int lane, 
   }
   const int dt_begin = dg * RTG;
   const int dt_end = min(dt_begin + RTG, dtiles);
-  if (dt_end - dt_begin < RTG) {  // ragged row group: one row tile at a time
-    for (int dt = dt_begin; dt < dt_end; ++dt) down_group<1, MAXNT, 2, PACKED>(v, t, dt, lane, turn);
-  } else if (MAXNT == 1 || t.count <= 16) {
+  if (uniform_int(dt_end - dt_begin) < RTG) {  // ragged row group: one row tile at a time
+    for (int dt = uniform_int(dt_begin); dt < uniform_int(dt_end); ++dt) down_group<1, MAXNT, 2, PACKED>(v, t, dt, lane, turn);
+  } else if (MAXNT == 1 || uniform_int(t.count) <= 16) {
     down_group<RTG, 1, U1, PACKED>(v, t, dt_begin, lane, turn);
   } else {
     down_group<RTG, MAXNT, U2, PACKED>(v, t, dt_begin, lane, turn);
@@ -595,8 +545,8 @@ __device__ __forceinline__ bool lds_task(const FfnArgs& a, int per_expert, int p
   }
   bx -= per_shared * a.splits;
   const int u = bx / per_expert;
-  if (u >= a.meta[2]) return false;
-  const int rec = a.units[u];
+  if (u >= uniform_int(a.meta[2])) return false;
+  const int rec = uniform_int(a.units[u]);
   if ((rec & 0xffff) >= a.n_slots || (rec >> 24) < 1 || (rec >> 24) > kMaxSplits) return false;
   split = (rec >> 16) & 0xff;
   nsplit = rec >> 24;
@@ -760,8 +710,9 @@ __global__ __launch_bounds__(kTileThreads, 2) void gateup_tile_kernel(FfnArgs a)
     const int q = 2 * i + (tid >> 7), ft = min(f0 + q / MT * HT + q % HT, tiles - 1);
     aptr[i] = tile_weight_ptr<PACKED>((q % MT < HT ? t.w0 : t.w1) + static_cast<size_t>(ft) * 16 * a.D, a.D, tid);
   }
-  for (int g0 = split * kRows; g0 < t.count; g0 += splits * kRows) {
-    const int rows = min(kRows, t.count - g0);
+  const int count = uniform_int(t.count);
+  for (int g0 = split * kRows; g0 < count; g0 += splits * kRows) {
+    const int rows = min(kRows, count - g0);
     auto run = [&](auto ntc) {
       constexpr int NT = decltype(ntc)::value;
       const uint16_t* bptr[NT];
@@ -809,7 +760,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void down_tile_kernel(FfnArgs a) {
   int group, split, splits;
   const int tiles = a.D / 16, per = (tiles + 2 * MT - 1) / (2 * MT);
   if (!lds_task<true>(a, per, a.Fs > 0 ? per : 0, group, split, splits, t, v, lane)) return;
-  const int F = t.fdim, d0 = group * 2 * MT;
+  const int F = uniform_int(t.fdim), d0 = group * 2 * MT;  // (see stream_pipeline)
   const uint16_t* h = static_cast<const uint16_t*>(v.h);
   const size_t orow0 = t.shared ? static_cast<size_t>(a.T) * a.K : static_cast<size_t>(t.pair0);
   const uint16_t* aptr[MT];
@@ -817,8 +768,9 @@ __global__ __launch_bounds__(kTileThreads, 2) void down_tile_kernel(FfnArgs a) {
   for (int i = 0; i < MT; ++i)
     aptr[i] = tile_weight_ptr<PACKED>(
         t.w0 + static_cast<size_t>(min(d0 + 2 * i + (tid >> 7), tiles - 1)) * 16 * F, F, tid);
-  for (int g0 = split * kRows; g0 < t.count; g0 += splits * kRows) {
-    const int rows = min(kRows, t.count - g0);
+  const int count = uniform_int(t.count);
+  for (int g0 = split * kRows; g0 < count; g0 += splits * kRows) {
+    const int rows = min(kRows, count - g0);
     auto run = [&](auto ntc) {
       constexpr int NT = decltype(ntc)::value;
       const uint16_t* bptr[NT];

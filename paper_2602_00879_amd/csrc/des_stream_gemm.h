@@ -1,4 +1,5 @@
-// Streaming GEMM building block shared by the kernels that stage token rows through
+// Streaming GEMM building blocks: the pieces that the short-block kernels share, and the one
+// shared by the kernels that stage token rows through
 // LDS (the expert FFN for blocks of more than 32 tokens, the dense projections of the
 // attention sub-layer): weights from HBM straight into MFMA operands, token rows from
 // L2 into LDS by direct loads, explicit wait counts.  gfx950 only.
@@ -17,6 +18,65 @@ typedef std::integral_constant<int, 1> S1;
 // elements between consecutive k-steps of a 16-row weight tile
 template <bool PACKED>
 __device__ __forceinline__ constexpr int frag_step() { return PACKED ? 512 : 32; }
+
+// ------------------------------------------ short blocks: weights straight into operands
+// The weight stream of one wavefront: `steps` stages in two register sets.  load(st, set)
+// requests stage st, compute(set) multiplies it.  The trips carry no branch, so the
+// compiler waits for exactly the stage it needs and the next one stays in flight (with a
+// test for the end around each load it waited for everything outstanding); the scheduling
+// barriers keep a stage's loads together in front of the multiplies.  More sets do not
+// help: what bounds these kernels is the chip's read rate and its spread over the compute
+// units (128-expert layer, 32 tokens: 34.4 us with two, three or four sets of two k-steps;
+// where fewer wavefronts are in flight the branch-free form pays: 16 of 256 experts 22.3 ->
+// 20.0 us, 4 tokens 20.2 -> 18.6 us, the down projections 12.1 -> 11.1 and 12.0 -> 10.6).
+// Every condition around a matrix instruction must be uniform to the compiler as well as in
+// fact (`steps` from kernel arguments, or through uniform_int): matrix instructions ignore
+// the execution mask, and a short block under a mask that the compiler takes for divergent
+// may be entered with all lanes off.
+template <typename Load, typename Compute>
+__device__ __forceinline__ void stream_pipeline(int steps, Load&& load, Compute&& compute) {
+  if (steps > 0) load(0, S0{});
+  int st = 0;
+  for (; st + 3 <= steps; st += 2) {
+    load(st + 1, S1{});
+    __builtin_amdgcn_sched_barrier(0);
+    compute(S0{});
+    __builtin_amdgcn_sched_barrier(0);
+    load(st + 2, S0{});
+    __builtin_amdgcn_sched_barrier(0);
+    compute(S1{});
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (st < steps) {
+    if (st + 1 < steps) load(st + 1, S1{});
+    compute(S0{});
+    if (st + 1 < steps) compute(S1{});
+  }
+}
+
+// Row-major weights.  An MFMA A operand takes 16 rows x 32 elements, 64 bytes of each
+// row: a load in operand order touches 16 half lines, and the kernels then ran at 3.6 TB/s
+// where packed tiles reach 5.8 (33 experts of 2048 x 768: gate/up 58.4 us, down 31.8 us; as
+// below 44.4 and 23.2, packed 42.5 and 21.8).  So row-major tiles are loaded in whole
+// 128-byte lines (a load = 8 rows x 64 elements, lane l has piece l % 8 of row l / 8) and
+// turned into operand order through a few KB of LDS that belong to the wavefront alone: two loads (v[0], v[1]: rows 0-7 and 8-15) become the
+// operands of two k-steps.  16-byte piece p of row r is kept at piece p ^ (r / 2 % 8), so
+// writes and reads both spread over all banks.
+constexpr int kTurnBytes = 2048;  // of LDS per 16 x 64 tile
+__device__ __forceinline__ void turn_write(const bf16x8& v0, const bf16x8& v1, char* tile, int lane) {
+  const int r = lane >> 3, p = lane & 7;
+  *reinterpret_cast<bf16x8*>(tile + r * 128 + ((p ^ (r >> 1)) << 4)) = v0;
+  *reinterpret_cast<bf16x8*>(tile + (r + 8) * 128 + ((p ^ ((r >> 1) + 4)) << 4)) = v1;
+}
+__device__ __forceinline__ bf16x8 turn_read(const char* tile, int u, int lane) {
+  const int r = lane & 15, p = u * 4 + (lane >> 4);
+  return *reinterpret_cast<const bf16x8*>(tile + r * 128 + ((p ^ (r >> 1)) << 4));
+}
+// the wavefront's LDS accesses stay in program order (they execute in order)
+__device__ __forceinline__ void turn_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
 // ------------------------------------------ token rows via LDS, weights via registers
 // With more than two token tiles per expert the direct scheme above runs out

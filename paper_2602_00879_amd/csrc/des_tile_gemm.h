@@ -25,7 +25,8 @@ template <int MT, int NT, int KW>
 constexpr int tile_lds_bytes() { return KW * 2 * 32 * (MT + NT) * kTileK * 2; }
 
 // acc[m][n] += weight tile m x token tile n of this wavefront, over a reduction of `kd`
-// elements (a multiple of 32).  A group of four wavefronts works on a tile of 32 MT weight
+// elements (a multiple of 32; uniform to the compiler too, see stream_pipeline).  A group of
+// four wavefronts works on a tile of 32 MT weight
 // rows x 32 NT token rows; wavefront (wm, wn) of the 2 x 2 has weight rows 16 MT wm .. and
 // token rows 16 NT wn ..  With KW = 2 the workgroup has two such groups, each with its half
 // of the reduction (`kd` and the pointers are the group's own, the lengths are equal).
