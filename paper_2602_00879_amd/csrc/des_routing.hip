@@ -181,30 +181,46 @@ __device__ __forceinline__ void router_tile_bf16(const RoutingArgs& a, int tile_
   }
 }
 
-// fp32 inputs: each wavefront takes (expert, token) dot products of the tile in
-// turn, lanes stride the reduction dimension with 16-byte loads.
+// fp32 inputs: wavefront w has expert w of the tile, lanes stride the reduction dimension with
+// 16-byte loads, eight tokens at a time so that their loads are in flight together (one dot
+// product after the other: routing of 30 tokens, 8 experts of width 120, 23.6 us, now 17.7).
 __device__ __forceinline__ void router_tile_f32(const RoutingArgs& a, int tile_m, int tile_t) {
+  static_assert(kRtWaves == 16, "one wavefront per expert of the tile");
+  constexpr int kTok = 8;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int T = a.B * a.N, D = a.D, M = a.M;
-  const float* x = static_cast<const float*>(a.x);
-  const float* wr = static_cast<const float*>(a.w_router);
-  for (int p = wave; p < 256; p += kRtWaves) {
-    const int e = tile_m * 16 + (p & 15), t = tile_t * 16 + (p >> 4);
-    if (e >= M || t >= T) continue;  // uniform per wave
-    const float4* xp = reinterpret_cast<const float4*>(x + static_cast<size_t>(t) * D);
-    const float4* wp = reinterpret_cast<const float4*>(wr + static_cast<size_t>(e) * D);
-    float s = 0.f;
-    for (int v = lane; v < D / 4; v += 64) {
-      const float4 p4 = xp[v], q4 = wp[v];
-      s = fmaf(p4.x, q4.x, s);
-      s = fmaf(p4.y, q4.y, s);
-      s = fmaf(p4.z, q4.z, s);
-      s = fmaf(p4.w, q4.w, s);
+  const int e = tile_m * 16 + wave;
+  if (e >= M) return;  // uniform per wave; no barrier below
+  const float4* wp = reinterpret_cast<const float4*>(static_cast<const float*>(a.w_router) + static_cast<size_t>(e) * D);
+  const float bias = a.bias ? a.bias[e] : 0.f;
+  for (int t0 = tile_t * 16; t0 < min(tile_t * 16 + 16, T); t0 += kTok) {
+    const float4* xp[kTok];
+    float s[kTok];
+#pragma unroll
+    for (int i = 0; i < kTok; ++i) {
+      xp[i] = reinterpret_cast<const float4*>(static_cast<const float*>(a.x) + static_cast<size_t>(min(t0 + i, T - 1)) * D);
+      s[i] = 0.f;
     }
-    s = wave_sum_f32(s);
-    if (lane == 0)
-      __hip_atomic_store(a.logits + static_cast<size_t>(t) * M + e, s + (a.bias ? a.bias[e] : 0.f),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int v = lane; v < D / 4; v += 64) {
+      const float4 q4 = wp[v];
+      float4 p4[kTok];
+#pragma unroll
+      for (int i = 0; i < kTok; ++i) p4[i] = xp[i][v];
+#pragma unroll
+      for (int i = 0; i < kTok; ++i) {
+        s[i] = fmaf(p4[i].x, q4.x, s[i]);
+        s[i] = fmaf(p4[i].y, q4.y, s[i]);
+        s[i] = fmaf(p4[i].z, q4.z, s[i]);
+        s[i] = fmaf(p4[i].w, q4.w, s[i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kTok; ++i) {
+      const float sum = wave_sum_f32(s[i]);
+      if (lane == 0 && t0 + i < T)
+        __hip_atomic_store(a.logits + static_cast<size_t>(t0 + i) * M + e, sum + bias, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
 }
 
