@@ -150,15 +150,18 @@ def make_shape(n_seqs: int, n_tokens: int, hidden: int, n_experts: int, ffn: int
                     GROUP_SCORES[group_score] if isinstance(group_score, str) else group_score, vote_atomic)
 
 
-def _ptr(t: Optional[torch.Tensor]):
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    """Device address (the entry points' argument types make a pointer of it)."""
     if t is None:
         return None
     assert t.is_contiguous(), "tensors handed to the library must be contiguous"
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    # the current stream's handle, without the Stream object that current_stream() builds: the
+    # smallest calls are bound by this host path
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def des_coreset_capacity(shape: DesShape) -> int:
@@ -187,15 +190,17 @@ def des_route(shape: DesShape, x: torch.Tensor, w_router: torch.Tensor,
 def des_select_coreset(shape: DesShape, logits: torch.Tensor,
                        out: Optional[Dict[str, torch.Tensor]] = None) -> Dict[str, torch.Tensor]:
     """`out`: the dict of a previous call, to reuse its output tensors."""
-    B, M = shape.n_seqs, shape.n_experts
-    cap = des_coreset_capacity(shape)
-    dev = logits.device
-    out = out if out is not None else dict(
-        coreset_idx=torch.empty((B, cap), dtype=torch.int32, device=dev),
-        coreset_size=torch.empty((B,), dtype=torch.int32, device=dev),
-        votes=torch.zeros((B, M), dtype=torch.float32, device=dev),
-        k_seq_used=torch.empty((B,), dtype=torch.int32, device=dev),
-    )
+    if out is None:
+        B, M, dev = shape.n_seqs, shape.n_experts, logits.device
+        cap = des_coreset_capacity(shape)
+        # (under DES-Vote the call writes every vote; otherwise there are none: zeros)
+        fill = torch.empty if shape.mode == DES_VOTE else torch.zeros
+        out = dict(
+            coreset_idx=torch.empty((B, cap), dtype=torch.int32, device=dev),
+            coreset_size=torch.empty((B,), dtype=torch.int32, device=dev),
+            votes=fill((B, M), dtype=torch.float32, device=dev),
+            k_seq_used=torch.empty((B,), dtype=torch.int32, device=dev),
+        )
     _check(lib().des_select_coreset(ctypes.byref(shape), _ptr(logits), _ptr(out["coreset_idx"]),
                                     _ptr(out["coreset_size"]), _ptr(out["votes"]),
                                     _ptr(out["k_seq_used"]), _stream()))
@@ -252,7 +257,7 @@ def des_moe_forward(shape: DesShape, x, w_router, router_bias, w_gate, w_up, w_d
         ctypes.byref(shape), _ptr(x), _ptr(w_router), _ptr(router_bias), _ptr(w_gate), _ptr(w_up),
         _ptr(w_down), _ptr(sg), _ptr(su), _ptr(sd), _ptr(b.y), _ptr(b.logits), _ptr(b.topk_idx),
         _ptr(b.topk_w), _ptr(b.expert_counts), _ptr(b.n_unique), _ptr(b.coreset_idx),
-        _ptr(b.coreset_size), _ptr(b.workspace), ctypes.c_size_t(b.workspace.numel()), _stream()))
+        _ptr(b.coreset_size), _ptr(b.workspace), b.workspace.numel(), _stream()))
     return b
 
 
@@ -276,7 +281,7 @@ def des_moe_stack_forward(shape: DesShape, n_layers: int, x, w_router, router_bi
     _check(lib().des_moe_stack_forward(
         ctypes.byref(shape), n_layers, _ptr(x), _ptr(w_router), _ptr(router_bias), _ptr(w_gate),
         _ptr(w_up), _ptr(w_down), _ptr(sg), _ptr(su), _ptr(sd), _ptr(b.y), _ptr(b.expert_counts),
-        _ptr(b.n_unique), _ptr(b.workspace), ctypes.c_size_t(b.workspace.numel()), _stream()))
+        _ptr(b.n_unique), _ptr(b.workspace), b.workspace.numel(), _stream()))
     return b
 
 
@@ -309,7 +314,7 @@ def des_block_attention(shape: DesShape, attn: DesAttnShape, x, wq, wk, wv, wo, 
         workspace = _workspace(des_attention_workspace_bytes(shape, attn), x.device)
     _check(lib().des_block_attention(
         ctypes.byref(shape), ctypes.byref(attn), _ptr(x), _ptr(wq), _ptr(wk), _ptr(wv), _ptr(wo),
-        _ptr(k_cache), _ptr(v_cache), _ptr(y), _ptr(workspace), ctypes.c_size_t(workspace.numel()),
+        _ptr(k_cache), _ptr(v_cache), _ptr(y), _ptr(workspace), workspace.numel(),
         _stream()))
     return y
 
@@ -335,7 +340,7 @@ def des_decoder_stack_forward(shape: DesShape, attn: DesAttnShape, n_layers: int
         ctypes.byref(shape), ctypes.byref(attn), n_layers, _ptr(x), _ptr(wq), _ptr(wk), _ptr(wv),
         _ptr(wo), _ptr(k_cache), _ptr(v_cache), _ptr(w_router), _ptr(router_bias), _ptr(w_gate),
         _ptr(w_up), _ptr(w_down), _ptr(sg), _ptr(su), _ptr(sd), _ptr(b.y), _ptr(b.expert_counts),
-        _ptr(b.n_unique), _ptr(b.workspace), ctypes.c_size_t(b.workspace.numel()), _stream()))
+        _ptr(b.n_unique), _ptr(b.workspace), b.workspace.numel(), _stream()))
     return b
 
 
