@@ -737,8 +737,21 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
   }
 }
 
-// Blocks of more than 32 token rows: the tile, the workgroups, whether the reduction is cut
-// in two.
+// Blocks of more than 32 token rows: is the reduction cut in two?  Where a launch of one
+// workgroup per 64 weight rows and 128 (64 if that makes fewer than 100) token rows has fewer
+// than 150: half of the compute units would have four wavefronts or none (2048 x 4096 weights
+// on 256 token rows: 20.5 us whole, 17.0 us cut).  The cut decides the order of the sums, so it
+// depends on sizes alone.
+struct LongCut { int workgroups; bool cut; };
+static LongCut long_cut(int T, const int* fout, int n_mats, int Din) {
+  int b64 = 0;
+  for (int m = 0; m < n_mats; ++m) b64 += (fout[m] / 32 + 1) / 2;
+  const int rows = b64 * ((T + 127) / 128) < 100 ? 64 : 128;
+  const int workgroups = b64 * ((T + rows - 1) / rows);
+  return LongCut{workgroups, workgroups < 150 && Din % 512 == 0};
+}
+
+// The tile and the number of workgroups of such a block.
 struct TileLinearPlan { int mt, blocks, kw; };
 static TileLinearPlan tile_linear_plan(int T, const int* fout, int n_mats, int Din) {
   auto blocks = [&](int mt) {
@@ -747,14 +760,7 @@ static TileLinearPlan tile_linear_plan(int T, const int* fout, int n_mats, int D
     return (b + 7) / 8 * 8 * ((T + 32 * mt - 1) / (32 * mt));
   };
   TileLinearPlan p{2, blocks(2), 1};
-  // The reduction is cut where a launch of one workgroup per 64 weight rows and 128 (64 if
-  // that makes fewer than 100) token rows has fewer than 150: half of the compute units
-  // would have four wavefronts or none (2048 x 4096 weights on 256 token rows: 20.5 us whole,
-  // 17.0 us cut).  The cut decides the order of the sums, so it depends on sizes alone.
-  int b64 = 0;
-  for (int m = 0; m < n_mats; ++m) b64 += (fout[m] / 32 + 1) / 2;
-  const int rows = b64 * ((T + 127) / 128) < 100 ? 64 : 128;
-  if (b64 * ((T + rows - 1) / rows) < 150 && Din % 512 == 0) p.kw = 2;
+  if (long_cut(T, fout, n_mats, Din).cut) p.kw = 2;
   // Tiles of 128 x 128 need half the LDS and L2 traffic per multiply; two workgroups per
   // compute unit have to be there for it to pay (4608 x 2560 weights on 432 rows, 144 such
   // tiles: 33.5 us against 21.2 us in tiles of 64; at 512 and more they win).
@@ -774,7 +780,9 @@ constexpr int kStreamWaves = 2;
 inline int stream_ksplit(const int* fout, int Din) {  // the same rule as the tiles'
   return (fout[0] / 32 + 1) / 2 < 150 && Din % 512 == 0 ? 2 : 1;
 }
-constexpr size_t kStreamPartialBytes = kStreamWaves * 2 * 8 * 256 * 4;  // of one workgroup
+
+// of one workgroup's part of a cut reduction: 4 weight tiles x up to 8 token tiles x 1 KB
+constexpr size_t kLongPartialBytes = kStreamWaves * 2 * 8 * 256 * 4;
 
 // Scratch of one attention sub-layer (bytes from a 256-byte aligned base): q, k, v and the
 // per-head outputs of the block's tokens, bf16.
@@ -794,13 +802,19 @@ AttnLayout attn_layout(const des_shape_t& s, const des_attn_shape_t& t) {
   const size_t tiles = tiles_qkv > tiles_out ? tiles_qkv : tiles_out;
   size_t part_bytes = tiles * 4096, n_flags = tiles;
   if (T > 32) {
-    part_bytes = n_flags = 0;
+    // Longer blocks: 32 KB for each half of a workgroup's cut reduction and a flag per
+    // workgroup, whether the halves meet there (the streaming form) or in LDS (the tiles).
+    // The size is part of the interface: a caller keeps one buffer for its longest block and
+    // the remainders after it, and at 33 to 96 tokens that buffer is this large because of
+    // these partials (2048-wide layer, 32 heads: 5.85 MB at 33 tokens, 1.90 MB at 32).
+    const int f_qkv[3] = {t.n_heads * t.head_dim, t.n_kv_heads * t.head_dim, t.n_kv_heads * t.head_dim};
     const int f_out[1] = {s.hidden};
-    const int Din = t.n_heads * t.head_dim;
-    if (stream_linear(static_cast<int>(T), f_out, 1, Din)) {
-      n_flags = static_cast<size_t>(s.hidden / 32 + kStreamWaves - 1) / kStreamWaves;
-      part_bytes = n_flags * stream_ksplit(f_out, Din) * kStreamPartialBytes;
-    }
+    const LongCut a = long_cut(static_cast<int>(T), f_qkv, 3, s.hidden);
+    const LongCut b = long_cut(static_cast<int>(T), f_out, 1, t.n_heads * t.head_dim);
+    const size_t wa = a.workgroups, wb = b.workgroups;
+    const size_t pa = a.cut ? wa * 2 * kLongPartialBytes : 0, pb = b.cut ? wb * 2 * kLongPartialBytes : 0;
+    part_bytes = pa > pb ? pa : pb;
+    n_flags = wa > wb ? wa : wb;
   }
   l.partial = p; p = align256(p + part_bytes);
   l.flags = p; p = align256(p + n_flags * 8);

@@ -204,6 +204,10 @@ inline WsLayout ws_layout(const des_shape_t& s) {
   w.h_rows = dense_rows > TK ? dense_rows : TK;
   w.h = p;        p = align256(p + act * (w.h_rows + Ts) * Fm);
   w.o = p;        p = align256(p + 4 * (TK + Ts) * static_cast<size_t>(s.hidden));
+  // The size is part of the interface - callers keep one buffer for blocks of several lengths -
+  // so it stays what it has been: 64 bytes per possible expert that nothing writes any more
+  // (without them a buffer for 34 tokens of a 512-expert layer no longer does for 25 of them).
+  p = align256(p + 64 * static_cast<size_t>(max_live_experts(s)));
   w.total = p;
   return w;
 }

@@ -166,6 +166,48 @@ def test_attention_shapes_are_checked_on_the_host():
     assert L.des_decoder_stack_forward(ctypes.byref(s), ctypes.byref(ok), 2, *d, ctypes.c_size_t(1 << 40), None) == -1
 
 
+# (changes to the benchmark layer, (query heads, key/value heads, head width, prefix, suffix),
+# bytes of the layer, the residual stack, the attention sub-layer, the decoder stack)
+SCRATCH = [
+    (dict(), (32, 4, 128, 16, 16), (4072192, 4353280, 1903104, 6256384)),
+    (dict(n_tokens=4), (32, 4, 128, 16, 16), (859392, 895232, 1387008, 2282240)),
+    (dict(n_tokens=33), (32, 4, 128, 16, 16), (2970880, 3261184, 5851904, 9113088)),
+    (dict(n_tokens=48), (32, 4, 128, 16, 16), (4138752, 4560128, 6128384, 10688512)),
+    (dict(n_tokens=64), (32, 4, 128, 16, 16), (5384960, 5946624, 6423296, 12369920)),
+    (dict(n_tokens=96), (32, 4, 128, 16, 16), (7877632, 8719872, 5965056, 14684928)),
+    (dict(n_tokens=128), (32, 4, 128, 16, 16), (10370048, 11492864, 6554880, 18047744)),
+    (dict(n_tokens=256), (32, 4, 128, 16, 16), (20340224, 22585344, 13108480, 35693824)),
+    (dict(n_seqs=8), (32, 4, 128, 16, 16), (20351744, 22597632, 13108480, 35706112)),
+    (dict(n_tokens=60, hidden=1024, n_experts=512, ffn=32, top_k=1, coreset=512, mode='vanilla'),
+     (16, 16, 64, 3, 0), (657408, 1028864, 3637760, 4666624)),
+    (dict(n_tokens=64, hidden=8192, n_experts=8, ffn=128, top_k=2, coreset=4),
+     (64, 8, 128, 0, 0), (4624640, 6725376, 10749184, 17474560)),
+    (dict(n_tokens=50, hidden=256, ffn_shared=96, n_experts=24, ffn=64, top_k=2, coreset=6, mode='seq'),
+     (2, 1, 128, 5, 6), (580352, 637952, 77056, 715008)),
+]
+
+
+@pytest.mark.parametrize("kw,at,want", SCRATCH)
+def test_scratch_sizes_stay(kw, at, want):
+    """Callers plan with these sizes: one buffer for the longest block also serves the
+    remainders after it, and a buffer that was large enough once stays so."""
+    s, a = _shape(**kw), B.make_attn_shape(*at)
+    assert (B.des_workspace_bytes(s), B.des_stack_workspace_bytes(s), B.des_attention_workspace_bytes(s, a),
+            B.des_decoder_workspace_bytes(s, a)) == want
+
+
+def test_a_buffer_for_the_longest_block_serves_the_remainders():
+    at = B.make_attn_shape(32, 4, 128, 16, 16)
+    for longest in (33, 40, 48, 64, 65, 96, 128, 200):
+        for n in range(1, 33):
+            assert B.des_attention_workspace_bytes(_shape(n_tokens=longest), at) >= \
+                B.des_attention_workspace_bytes(_shape(n_tokens=n), at)
+            assert B.des_decoder_workspace_bytes(_shape(n_tokens=longest), at) >= \
+                B.des_decoder_workspace_bytes(_shape(n_tokens=n), at)
+    wide = dict(hidden=1024, n_experts=512, ffn=32, top_k=1, coreset=512)
+    assert B.des_workspace_bytes(_shape(n_tokens=34, **wide)) >= B.des_workspace_bytes(_shape(n_tokens=25, **wide))
+
+
 def test_coreset_from_beta_matches_table_1_rounding():
     """M_core = floor(beta * M): the sizes printed in Table 1 of the paper, and the
     oracle's exact-fraction version on a grid of decimal budgets."""
