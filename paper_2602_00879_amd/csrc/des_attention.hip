@@ -446,24 +446,54 @@ struct AttnArgs {
   float scale;                         // 1 / sqrt(dh)
 };
 
+// LDS that the parts of a cut window exchange, after the values: maxima [8 wavefronts][16 queries],
+// running sums of the weights [tiles][64 lanes], the weights of two parts [2][tiles][steps][64 lanes][8].
+__host__ __device__ constexpr size_t exchange_bytes(int tiles, int steps_of_part) {
+  return 512 + tiles * 256 + 2 * static_cast<size_t>(tiles) * steps_of_part * 1024;
+}
+
 // How the work of one (sequence, key/value head) is cut.  Its query rows - the block's
 // tokens under each query head that shares the keys - form tiles of 16; a wavefront takes
 // one tile and one part of the window, a workgroup up to eight wavefronts that share the
-// transposed values in LDS.  The window is cut further while the launch has fewer than
-// 2048 wavefronts (eight per compute unit), as long as a part keeps 64 positions (what a
-// wavefront requests at once anyway); then the tiles are spread over more workgroups until every compute unit has one (each
-// stages the values again, from L2).  A window whose scores fit a wavefront's registers is not
-// cut: its maximum is then known before the weights are formed.
+// transposed values in LDS.  A window whose scores fit a wavefront's registers is not cut.
+// A longer window is cut until the scores of a part fit, and further while
+// the launch has fewer than 2048 wavefronts (eight per compute unit), as long as a part keeps
+// 64 positions (what a wavefront requests at once anyway); then the tiles are spread over more
+// workgroups until every compute unit has one (each stages the values again, from L2).
+// Where workgroups full of tiles cover the compute units already, cutting only stages the values
+// more often (64 sequences of 32 tokens, 32 heads on 4 of width 128): up to 512 positions stay
+// whole, half the keys requested ahead (496: 102 us, cut 169 us); beyond that, if the values
+// leave a compute unit one workgroup anyway, the scores are computed twice (576: 157 us, cut 287
+// us).  So they are where no cut into at most eight parts fits (windows beyond 2048).
 constexpr int kWholeWindow = 256;  // positions whose scores a wavefront keeps in registers
-struct AttnPlan { int splits, tiles, groups; };
-static AttnPlan attn_plan(const AttnArgs& a) {
+constexpr int kWideWindow = 512;   // ... if it requests half as many keys ahead
+struct AttnPlan { int splits, tiles, groups; size_t lds; };
+static AttnPlan attn_plan(const AttnArgs& a, size_t value_bytes) {
   const int rows = a.H / a.Hkv * a.N, tiles = (rows + 15) / 16, steps = (a.P + a.N + 31) / 32;
   const int heads = a.B * a.Hkv;
-  AttnPlan p{1, 8, 1};
-  while (a.P + a.N > kWholeWindow && p.splits < 8 && 4 * p.splits <= steps && heads * tiles * p.splits < 2048) p.splits *= 2;
-  p.tiles = 8 / p.splits;
-  while (p.tiles > 1 && heads * ((tiles + p.tiles - 1) / p.tiles) < 256) p.tiles /= 2;
-  if (p.tiles > tiles) p.tiles = tiles;
+  AttnPlan p{1, 8, 1, value_bytes};
+  auto part = [&]() { return (steps + p.splits - 1) / p.splits; };  // steps of a part
+  auto spread = [&]() {
+    p.tiles = 8 / p.splits;
+    while (p.tiles > 1 && heads * ((tiles + p.tiles - 1) / p.tiles) < 256) p.tiles /= 2;
+    if (p.tiles > tiles) p.tiles = tiles;
+  };
+  auto fits = [&]() {
+    return part() * 32 <= kWholeWindow && value_bytes + exchange_bytes(p.tiles, part()) <= 160 * 1024;
+  };
+  const bool full = tiles >= 8 && heads * ((tiles + 7) / 8) >= 256;
+  const bool whole = a.P + a.N <= (full ? kWideWindow : kWholeWindow) || (full && value_bytes > 80 * 1024);
+  if (!whole) {
+    p.splits = 2;
+    spread();
+    while (p.splits < 8 && (!fits() || (4 * p.splits <= steps && heads * tiles * p.splits < 2048))) {
+      p.splits *= 2;
+      spread();
+    }
+    if (!fits()) p.splits = 1;
+  }
+  spread();
+  if (p.splits > 1) p.lds += exchange_bytes(p.tiles, part());
   p.groups = (tiles + p.tiles - 1) / p.tiles;
   return p;
 }
@@ -476,20 +506,25 @@ static AttnPlan attn_plan(const AttnArgs& a) {
 //                  contraction only needs A and B to agree on which key a slot means),
 //                  A = values transposed in LDS, read with that same key order
 //                  -> lane l holds query l % 16, coordinates 4 (l / 16) .. + 3 of the tile
-// One pass over the keys, 64 at a time with the next 128 requested ahead.  WHOLE: up to 256
-// positions, all scores stay in registers and the weights are formed once their maximum is
-// known.  Longer windows run under a running
-// maximum (the accumulators are rescaled when it grows), and the parts of a split window are
-// added through LDS in window order.  Weights are rounded to bf16 for the second
-// contraction, their sum is kept in fp32; all sums run in a fixed order.
+// The maximum of the whole window comes first, the weights after it; all sums run over the
+// window in order, whatever the cut, so a query's result does not depend on how many others
+// the launch has.  Keys are read 64 at a time with the next 128 requested ahead.  Forms:
+//   kWhole  up to 256 positions: one wavefront per tile, all scores stay in registers;
+//   kWide   the same up to 512 positions, half as many keys requested ahead;
+//   kParts  the wavefronts of a tile score their parts of the window, exchange their maxima and
+//           form their weights side by side.  The weights then pass through LDS part after part;
+//           each wavefront adds up its share of the coordinates over the whole window;
+//   kTwice  one wavefront per tile, the scores computed twice.
+// Weights are rounded to bf16 for the second contraction, their sum is kept in fp32.
 // What bounds it is latency - the loads behind one another, then the staging of the
-// values: eight sequences of 32 tokens over 496 positions, 32 heads on 4, take 20 us
+// values: eight sequences of 32 tokens over 496 positions, 32 heads on 4, take 21 us
 // (one workgroup per query head, half of its wavefronts idle, scores computed twice and
 // values transposed two bytes at a time: 49.6 us); one block over 64 positions 7.0 us
-// (6.9).  Of the 20 us the key loads cost 6 (an MFMA operand takes 64 bytes of 16 rows) and the
-// staging of the values 4.
+// (6.9).  A running maximum with the parts added up at the end takes 19.5 us, but then the
+// rounding of the weights depends on the cut, and a part whose scores are all -inf has none.
 // NKS = 32-element steps of the head width.
-template <int NKS, bool WHOLE>
+enum AttnForm { kWhole, kWide, kParts, kTwice };
+template <int NKS, int FORM>
 __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
   constexpr int NDT = 2 * NKS;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -530,18 +565,19 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
   // this wavefront's part of the window, in steps of 32 positions
   const int per = (steps + S - 1) / S;
   const int s0 = min(part * per, steps), s1 = wave < S * a.tiles ? min(s0 + per, steps) : s0;
-  bf16x8 kf[2][4][NKS];
-  auto load_keys = [&](int st, auto set) {  // four key tiles (two steps); tiles past the part are skipped
+  constexpr int KT = FORM == kWide ? 2 : 4, KS = KT / 2;  // key tiles requested together; steps of them
+  bf16x8 kf[2][KT][NKS];
+  auto load_keys = [&](int st, auto set) {  // KT key tiles (KS steps); tiles past the part are skipped
     constexpr int z = decltype(set)::value;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < KT; ++i) {
       const uint16_t* krow = row_of(kc, kb, min(32 * st + 16 * i + col, nk - 1));
 #pragma unroll
       for (int s = 0; s < NKS; ++s) kf[z][i][s] = st + i / 2 < s1 ? load8(krow, s) : bf16x8{};
     }
   };
   if (s0 < s1) load_keys(s0, S0{});
-  if (s0 + 2 < s1) load_keys(s0 + 2, S1{});
+  if (s0 + KS < s1) load_keys(s0 + KS, S1{});
 
   // values -> LDS, transposed: a thread takes 8 coordinates of 4 consecutive positions and
   // writes 8 bytes per coordinate.  Slots beyond the window hold zeros (their weights are
@@ -578,110 +614,72 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
   }
   __syncthreads();
 
-  const int n_waves = S * a.tiles;  // wavefronts past these only helped with the values
-  if (wave >= n_waves) {
-    if (S > 1) {  // the barriers of the exchange below
-      __syncthreads();
-      __syncthreads();
-    }
-    return;
-  }
+  if (FORM != kParts && wave >= a.tiles) return;  // it only helped with the values
   float mx = neg_inf, lsum = 0.f;
   f32x4 oacc[NDT];
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt) oacc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // scores of the four key tiles of a set; their largest
+  // positions of this lane from step st on that count: inside the window and inside the part
+  auto limit = [&](int st) { return min(nk, 32 * s1) - (32 * st + 4 * grp); };
+  // scores of the key tiles of a set; the maximum takes them in
   auto scores = [&](int st, auto set, f32x4* sc) {
     constexpr int z = decltype(set)::value;
-    float bm = neg_inf;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < KT; ++i) {
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < NKS; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[z][i][s], qf[s], acc, 0, 0, 0);
       sc[i] = acc;
     }
-    // positions of this lane that count: inside the window and inside the part
-    const int lim = min(nk, 32 * s1) - (32 * st + 4 * grp);
+    const int lim = limit(st);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < KT; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) bm = 16 * i + r < lim ? fmaxf(bm, sc[i][r]) : bm;
-    return bm;
+      for (int r = 0; r < 4; ++r) mx = 16 * i + r < lim ? fmaxf(mx, sc[i][r]) : mx;
   };
-  auto query_max = [&](float m) {  // over the lanes that hold a query's scores
-    m = fmaxf(m, __shfl_xor(m, 16));
-    return fmaxf(m, __shfl_xor(m, 32));
+  auto query_max = [&]() {  // over the lanes that hold a query's scores
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
   };
-  // weights of two steps under the maximum mx, their sum, the weighted values
-  auto weigh = [&](int st, const f32x4* sc) {
-    const int lim = min(nk, 32 * s1) - (32 * st + 4 * grp);
+  // the weights of step st from the scores of its two tiles
+  auto form = [&](int st, const f32x4* sc, f32x4 (&w)[2]) {
+    const int lim = limit(st);
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) w[i][r] = 16 * i + r < lim ? expf((sc[i][r] - mx) * a.scale) : 0.f;
+  };
+  // ... into their sum, and as an operand
+  auto add_weights = [&](const f32x4 (&w)[2]) -> bf16x8 {
+    u16x4 pw[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        lsum += w[i][r];
+        pw[i][r] = f32_to_bf16_bits(w[i][r]);
+      }
+    struct { u16x4 lo, hi; } pp = {pw[0], pw[1]};
+    return __builtin_bit_cast(bf16x8, pp);
+  };
+  auto add_values = [&](int st, int dt, const bf16x8& pb, f32x4& o) {  // coordinates 16 dt .. + 15 of step st
+    const uint16_t* vrow = vt + (16 * dt + col) * ldv + 32 * st + 4 * grp;
+    struct { u16x4 lo, hi; } vv = {*reinterpret_cast<const u16x4*>(vrow), *reinterpret_cast<const u16x4*>(vrow + 16)};
+    o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vv), pb, o, 0, 0, 0);
+  };
+  auto weigh = [&](int st, const f32x4* sc) __attribute__((always_inline)) {  // the steps of a set, all coordinates
+#pragma unroll
+    for (int c = 0; c < KS; ++c) {
       if (st + c < s1) {
-        u16x4 pw[2];
+        f32x4 w[2];
+        form(st + c, sc + 2 * c, w);
+        const bf16x8 pb = add_weights(w);
 #pragma unroll
-        for (int half = 0; half < 2; ++half)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int i = 2 * c + half;
-            const float pr = 16 * i + r < lim ? expf((sc[i][r] - mx) * a.scale) : 0.f;
-            lsum += pr;
-            pw[half][r] = f32_to_bf16_bits(pr);
-          }
-        struct { u16x4 lo, hi; } pp = {pw[0], pw[1]};
-        const bf16x8 pb = __builtin_bit_cast(bf16x8, pp);
-#pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) {
-          if (dt < ndt) {
-            const uint16_t* vrow = vt + (16 * dt + col) * ldv + 32 * (st + c) + 4 * grp;
-            struct { u16x4 lo, hi; } vv = {*reinterpret_cast<const u16x4*>(vrow),
-                                           *reinterpret_cast<const u16x4*>(vrow + 16)};
-            oacc[dt] =
-                __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vv), pb, oacc[dt], 0, 0, 0);
-          }
-        }
+        for (int dt = 0; dt < NDT; ++dt)
+          if (dt < ndt) add_values(st + c, dt, pb, oacc[dt]);
       }
     }
   };
-  if constexpr (WHOLE) {
-    constexpr int kSets = kWholeWindow / 64;
-    f32x4 sc[kSets][4];
-    static_for(std::make_integer_sequence<int, kSets>{}, [&](auto i) {
-      constexpr int I = decltype(i)::value;
-      typedef std::integral_constant<int, I & 1> Set;
-      if (2 * I < s1) mx = fmaxf(mx, scores(2 * I, Set{}, sc[I]));
-      if (2 * I + 4 < s1) load_keys(2 * I + 4, Set{});
-    });
-    mx = query_max(mx);
-    static_for(std::make_integer_sequence<int, kSets>{}, [&](auto i) {
-      constexpr int I = decltype(i)::value;
-      if (2 * I < s1) weigh(2 * I, sc[I]);
-    });
-  } else {
-    auto consume = [&](int st, auto set) {
-      f32x4 sc[4];
-      const float bm = query_max(scores(st, set, sc));
-      const float m_new = fmaxf(mx, bm);  // finite: the first position of a step is in the window
-      const float corr = mx == neg_inf ? 0.f : expf((mx - m_new) * a.scale);
-      mx = m_new;
-      lsum *= corr;
-#pragma unroll
-      for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) oacc[dt][r] *= corr;
-      weigh(st, sc);
-    };
-    for (int st = s0; st < s1; st += 4) {
-      consume(st, S0{});
-      if (st + 4 < s1) load_keys(st + 4, S0{});
-      if (st + 2 < s1) consume(st + 2, S1{});
-      if (st + 6 < s1) load_keys(st + 6, S1{});
-    }
-  }
-  lsum += __shfl_xor(lsum, 16);
-  lsum += __shfl_xor(lsum, 32);
-
   uint16_t* orow = a.o + qoff;
   auto store = [&](int dt, const f32x4& o, float inv) {
     const int d0 = 16 * dt + 4 * grp;
@@ -692,49 +690,91 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
       *reinterpret_cast<u16x4*>(orow + d0) = ob;
     }
   };
-  if (S == 1) {
-    const float inv = 1.0f / lsum;
-#pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) store(dt, oacc[dt], inv);
-    return;
-  }
-  // the parts of a tile meet in LDS (the values are done with): each wavefront of the tile
-  // finishes its share of the coordinates, adding the parts in window order
-  __syncthreads();
-  float* parts = reinterpret_cast<float*>(smem_raw);         // [wave][NDT][64 lanes][4]
-  float* ml = parts + static_cast<size_t>(n_waves) * NDT * 256;  // [wave][2][16]: maximum, sum
-#pragma unroll
-  for (int dt = 0; dt < NDT; ++dt) *reinterpret_cast<f32x4*>(parts + ((wave * NDT + dt) * 64 + lane) * 4) = oacc[dt];
-  if (grp == 0) {
-    ml[wave * 32 + col] = mx;
-    ml[wave * 32 + 16 + col] = lsum;
-  }
-  __syncthreads();
-  const int w0 = wave - part;
-  float top = neg_inf, sum = 0.f, f[8];
-  for (int p = 0; p < S; ++p) top = fmaxf(top, ml[(w0 + p) * 32 + col]);
-#pragma unroll
-  for (int p = 0; p < 8; ++p) {
-    f[p] = 0.f;
-    if (p < S) {
-      const float m = ml[(w0 + p) * 32 + col];
-      f[p] = m == neg_inf ? 0.f : expf((m - top) * a.scale);  // (a part without positions)
-      sum += f[p] * ml[(w0 + p) * 32 + 16 + col];
-    }
-  }
-  const float inv = 1.0f / sum;
-  for (int dt = part; dt < ndt; dt += S) {
-    f32x4 o = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      if (p < S) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(parts + (((w0 + p) * NDT + dt) * 64 + lane) * 4);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o[r] = fmaf(v[r], f[p], o[r]);
+  if constexpr (FORM == kTwice) {
+    auto walk = [&](auto&& f) {  // the keys, 64 at a time: f(first step, scores)
+      f32x4 sc[KT];
+      for (int st = 0; st < s1; st += 2 * KS) {
+        scores(st, S0{}, sc);
+        if (st + 2 * KS < s1) load_keys(st + 2 * KS, S0{});
+        f(st, sc);
+        if (st + KS < s1) {
+          scores(st + KS, S1{}, sc);
+          if (st + 3 * KS < s1) load_keys(st + 3 * KS, S1{});
+          f(st + KS, sc);
+        }
       }
+    };
+    walk([](int, const f32x4*) {});
+    query_max();
+    load_keys(0, S0{});
+    load_keys(KS, S1{});
+    walk(weigh);
+  } else {
+    constexpr int kSets = (FORM == kWide ? kWideWindow : kWholeWindow) / (16 * KT);
+    f32x4 sc[kSets][KT];
+    static_for(std::make_integer_sequence<int, kSets>{}, [&](auto i) {
+      constexpr int I = decltype(i)::value;
+      typedef std::integral_constant<int, I & 1> Set;
+      const int st = s0 + KS * I;
+      if (st < s1) scores(st, Set{}, sc[I]);
+      if (st + 2 * KS < s1) load_keys(st + 2 * KS, Set{});
+    });
+    query_max();
+    if constexpr (FORM != kParts) {
+      static_for(std::make_integer_sequence<int, kSets>{}, [&](auto i) {
+        constexpr int I = decltype(i)::value;
+        if (KS * I < s1) weigh(KS * I, sc[I]);
+      });
+    } else {
+      const int q = wave / S;  // this wavefront's tile, if below a.tiles
+      const bool busy = q < a.tiles;
+      char* after = reinterpret_cast<char*>(smem_raw) + static_cast<size_t>(ndt) * 16 * ldv * 2;
+      float* part_max = reinterpret_cast<float*>(after);        // (see exchange_bytes)
+      float* part_sum = reinterpret_cast<float*>(after + 512) + (busy ? q : 0) * 64 + lane;
+      uint16_t* ring = reinterpret_cast<uint16_t*>(after + 512 + a.tiles * 256) + lane * 8;
+      if (grp == 0) part_max[wave * 16 + col] = mx;
+      __syncthreads();
+      for (int p = 0; p < S; ++p) mx = fmaxf(mx, part_max[(wave - part + p) * 16 + col]);
+      constexpr int kSteps = kWholeWindow / 32;
+      f32x4 w[kSteps][2];
+      static_for(std::make_integer_sequence<int, kSteps>{}, [&](auto i) {
+        constexpr int I = decltype(i)::value;
+        if (s0 + I < s1) form(s0 + I, &sc[I / 2][I % 2 * 2], w[I]);
+      });
+      // Turn p: the weights of part p meet the values, those of part p + 1 are put in place and added
+      // to the sum (the ring holds two parts; a turn's barrier separates its uses).
+      constexpr int kShare = NDT / 2;  // coordinate tiles of a wavefront: part, part + S, ...
+      for (int p = -1; p < S; ++p) {
+        if (busy && part == p + 1) {
+          if (p >= 0) lsum = *part_sum;
+          uint16_t* dst = ring + ((part & 1) * a.tiles + q) * per * 512;
+          static_for(std::make_integer_sequence<int, kSteps>{}, [&](auto i) {
+            constexpr int I = decltype(i)::value;
+            if (s0 + I < s1) *reinterpret_cast<bf16x8*>(dst + I * 512) = add_weights(w[I]);
+          });
+          *part_sum = lsum;
+        }
+        if (busy && p >= 0) {
+          const uint16_t* src = ring + ((p & 1) * a.tiles + q) * per * 512;
+          const int first = p * per, last = min(first + per, steps);
+          for (int st = first; st < last; ++st) {
+            const bf16x8 pb = *reinterpret_cast<const bf16x8*>(src + (st - first) * 512);
+#pragma unroll
+            for (int i = 0; i < kShare; ++i)
+              if (part + i * S < ndt) add_values(st, part + i * S, pb, oacc[i]);
+          }
+        }
+        if (p < S - 1) __syncthreads();
+      }
+      if (!busy) return;
+      lsum = *part_sum;  // (complete since the turn before the last)
     }
-    store(dt, o, inv);
   }
+  lsum += __shfl_xor(lsum, 16);
+  lsum += __shfl_xor(lsum, 32);
+  const float inv = 1.0f / lsum;
+#pragma unroll
+  for (int dt = 0; dt < (FORM == kParts ? NDT / 2 : NDT); ++dt) store(FORM == kParts ? part + dt * S : dt, oacc[dt], inv);
 }
 
 // Blocks of more than 32 token rows: is the reduction cut in two?  Where a launch of one
@@ -905,15 +945,11 @@ int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void
   c.B = s.n_seqs; c.N = s.n_tokens; c.H = t.n_heads; c.Hkv = t.n_kv_heads; c.dh = t.head_dim;
   c.P = attn_cached(t);
   c.scale = 1.0f / sqrtf(static_cast<float>(t.head_dim));
-  const AttnPlan pl = attn_plan(c);
+  const AttnPlan pl = attn_plan(c, attn_core_lds(s, t));
   c.splits = pl.splits;
   c.tiles = pl.tiles;
   const int waves = pl.splits * pl.tiles, nks = (t.head_dim + 31) / 32;
-  size_t lds = attn_core_lds(s, t);
-  if (pl.splits > 1) {  // the parts of a split window, after the values
-    const size_t merge = static_cast<size_t>(waves) * (2 * nks * 1024 + 128);
-    if (merge > lds) lds = merge;
-  }
+  const size_t lds = pl.lds;
   const dim3 grid(s.n_seqs * t.n_kv_heads, pl.groups), block((waves < 4 ? 4 : waves) * kWave);  // (four stage faster than one)
   auto core = [&](auto kernel) -> int {
     if (lds > 48 * 1024) {  // (a property of the function on the current device; cheap to repeat)
@@ -924,12 +960,15 @@ int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void
     launch(kKAttnCore, kernel, grid, block, lds, st, c);
     return DES_OK;
   };
-  auto pick = [&](auto whole) -> int {
-    constexpr bool W = decltype(whole)::value;
+  auto pick = [&](auto form) -> int {
+    constexpr int W = decltype(form)::value;
     return nks == 1 ? core(attention_core_kernel<1, W>) : nks == 2 ? core(attention_core_kernel<2, W>)
          : nks == 3 ? core(attention_core_kernel<3, W>) : core(attention_core_kernel<4, W>);
   };
-  const int rc = c.P + c.N <= kWholeWindow ? pick(std::true_type{}) : pick(std::false_type{});
+  const int rc = pl.splits > 1 ? pick(std::integral_constant<int, kParts>{})
+               : c.P + c.N <= kWholeWindow ? pick(std::integral_constant<int, kWhole>{})
+               : c.P + c.N <= kWideWindow ? pick(std::integral_constant<int, kWide>{})
+                                           : pick(std::integral_constant<int, kTwice>{});
   if (rc != DES_OK) return rc;
 
   LinearArgs o{};
