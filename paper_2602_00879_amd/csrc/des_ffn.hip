@@ -685,13 +685,13 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void d
 
 // ------------------------------------------ many token rows: weights and tokens in LDS tiles
 // The same work list (a unit = up to 128 token rows of an expert), the tiles of
-// des_tile_gemm.h: a workgroup has 64 intermediate units (their gate and up rows), or 128
+// des_tile_gemm.h: a workgroup has 16 MT intermediate units (their gate and up rows), or 32 MT
 // output rows, of one unit.  Every sum runs over the reduction in the same order as in the
-// other kernels, so which of them ran cannot be told from the results.
-constexpr int kTileMt = 4;  // row tiles of a wavefront
-template <bool PACKED, int MAXNT>
+// other kernels, so which of them ran cannot be told from the results.  P = chunks of the
+// reduction in registers on their way, where at most 64 token rows leave the room.
+template <bool PACKED, int MAXNT, int MT, int P>
 __global__ __launch_bounds__(kTileThreads, 2) void gateup_tile_kernel(FfnArgs a) {
-  constexpr int MT = kTileMt, HT = MT / 2, kRows = 32 * MAXNT;
+  constexpr int HT = MT / 2, kRows = 32 * MAXNT;
   __shared__ __align__(16) char lds[tile_lds_bytes<MT, MAXNT, 1>()];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -726,7 +726,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void gateup_tile_kernel(FfnArgs a)
       for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-      tile_gemm<MT, NT, 1, 1, PACKED>(aptr, bptr, a.D, lds, acc);
+      tile_gemm<MT, NT, 1, (NT <= 2 ? P : 1), PACKED>(aptr, bptr, a.D, lds, acc);
 #pragma unroll
       for (int j = 0; j < NT; ++j) {
         const int r = (wn * NT + j) * 16 + (lane & 15);
@@ -749,9 +749,9 @@ __global__ __launch_bounds__(kTileThreads, 2) void gateup_tile_kernel(FfnArgs a)
   }
 }
 
-template <bool PACKED, int MAXNT>
+template <bool PACKED, int MAXNT, int MT, int P>
 __global__ __launch_bounds__(kTileThreads, 2) void down_tile_kernel(FfnArgs a) {
-  constexpr int MT = kTileMt, kRows = 32 * MAXNT;
+  constexpr int kRows = 32 * MAXNT;
   __shared__ __align__(16) char lds[tile_lds_bytes<MT, MAXNT, 1>()];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -782,7 +782,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void down_tile_kernel(FfnArgs a) {
       for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-      tile_gemm<MT, NT, 1, 1, PACKED>(aptr, bptr, F, lds, acc);
+      tile_gemm<MT, NT, 1, (NT <= 2 ? P : 1), PACKED>(aptr, bptr, F, lds, acc);
 #pragma unroll
       for (int j = 0; j < NT; ++j) {
         const int r = (wn * NT + j) * 16 + (lane & 15);
@@ -1100,13 +1100,13 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
       // Two forms of each kernel.  Streamed (weights straight into operands, token rows
       // through LDS): packed weights whose reduction is one of the unrolled ones - or, with
       // fewer than 32 pairs per possible expert, any whole number of its chunks.  Tiles (both
-      // through LDS): everything else.  128 experts of 2048 x 768 under 256 tokens, gate/up + down: packed 68.3 + 40.0
-      // us streamed, 77.6 + 43.6 in tiles; row-major (64 bytes of a row per operand load)
-      // 99.9 + 54.8 and 81.3 + 45.0.  64 experts of 1536 x 1408, packed, not unrolled:
-      // 16 pairs per expert 78.0 + 50.0 and 80.5 + 51.6, 32 pairs 111 + 64.9 and 98.5 + 56.5,
-      // 128 pairs 223 + 126 and 168 + 97; 512 x 896 with 8 pairs 27.5 + 13.9 and 25.9 + 17.5.  Sizes that are no multiple of the streamed chunk had one
-      // wavefront per 16 or 32 weight rows gather everything from L2 (256 experts of
-      // 1440 x 288, 189 tokens: 75.7 + 42.6, now 25 + 15).
+      // through LDS): everything else.  128 experts of 2048 x 768 under 256 tokens, gate/up +
+      // down: packed 68.3 + 40.0 us streamed, 77.6 + 43.6 in tiles; row-major (64 bytes of a row
+      // per operand load) 99.9 + 54.8 and 81.3 + 45.0.  64 experts of 1536 x 1408, packed, not
+      // unrolled: 16 pairs per expert 78.0 + 50.0 and 80.5 + 51.6, 32 pairs 111 + 64.9 and
+      // 98.5 + 56.5, 128 pairs 223 + 126 and 168 + 97.  Sizes that are no multiple of the streamed
+      // chunk had one wavefront per 16 or 32 weight rows gather everything from L2 (64 experts of
+      // 1440 x 288, packed, 200 tokens, 12 pairs per expert: gate/up 60.2, in tiles 22.8).
       const int rows_pass = lds_rows_pass(a.T);
       const bool small = rows_pass == 64;
       int splits = (a.T + rows_pass - 1) / rows_pass;  // of the shared expert (all T rows)
@@ -1130,14 +1130,31 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
     else if (dn_kd == 512) launch(kKDown, down_lds_kernel<MNT, LWV, 512>, dg, dim3(LWV* kWave), 0, st, a); \
     else launch(kKDown, down_lds_kernel<MNT, LWV, 0>, dg, dim3(LWV* kWave), 0, st, a);      \
   } while (0)
-#define DES_LAUNCH_TILE(id, kernel, g)                                                      \
+#define DES_LAUNCH_TILE(id, kernel, g, MT, P)                                               \
   do {                                                                                      \
     const dim3 tb(kTileThreads);                                                            \
-    if (packed && small) launch(id, kernel<true, 2>, g, tb, 0, st, a);                      \
-    else if (packed) launch(id, kernel<true, 4>, g, tb, 0, st, a);                          \
-    else if (small) launch(id, kernel<false, 2>, g, tb, 0, st, a);                          \
-    else launch(id, kernel<false, 4>, g, tb, 0, st, a);                                     \
+    if (packed && small) launch(id, kernel<true, 2, MT, P>, g, tb, 0, st, a);               \
+    else if (packed) launch(id, kernel<true, 4, MT, P>, g, tb, 0, st, a);                   \
+    else if (small) launch(id, kernel<false, 2, MT, P>, g, tb, 0, st, a);                   \
+    else launch(id, kernel<false, 4, MT, P>, g, tb, 0, st, a);                              \
   } while (0)
+      // Tiles: four row tiles per wavefront share a token fragment where there is enough to do,
+      // two make twice the workgroups where there is not, and with two chunks requested ahead
+      // they hide more of a chunk's way.  Counted in workgroups of the larger tile (for the most
+      // experts that can be live).  Gate/up: below one per compute unit, two and two (4 experts
+      // of 7168 x 2048, row-major, 64 tokens: 100 us -> 50, streamed 71; packed, 8 experts of
+      // 4096 x 1408, 128 tokens: 60 -> 53, streamed 54); up to 1.75 per unit, two tiles but one
+      // chunk (128 experts of 2048 x 768, coreset of 32, row-major, 72 tokens: 39.4 -> 36.7, with
+      // two chunks 44.9; above that 128 experts under 64 tokens, vanilla: 62.6 -> 69.8).  Experts
+      // with a few pairs each under units sized for 128 rows: two and two as well (128 experts of
+      // 2048 x 768, 80 tokens, 5 pairs each: 76 -> 58.5, streamed 64.7).  Down: two and two up to
+      // 1.5 workgroups per unit (512 x 896, 64 tokens: 10.8 -> 7.0, streamed 9.3; 592 workgroups:
+      // 21.4 -> 23.5).
+      auto units_of = [&](int width) { return (width + 63) / 64; };  // of 4 row tiles
+      const int gu_wgs = n_units * units_of(a.F) + splits * units_of(a.Fs);
+      const int dn_wgs = (n_units + (a.Fs > 0 ? splits : 0)) * ((a.D + 127) / 128);
+      const bool gu_two = gu_wgs < 256 || (!small && TK < 8 * a.n_slots);
+      const int gu_mt = gu_two || gu_wgs < 448 ? 2 : 4, dn_mt = dn_wgs < 384 ? 2 : 4;
       if (gu_stream) {
         // Wavefronts per workgroup: two give the finest spread of the weight bytes over the
         // compute units; four share the staged activations among more weight rows, which
@@ -1149,9 +1166,10 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
         else if (lw == 2) DES_LAUNCH_GU(8, 2);
         else DES_LAUNCH_GU(8, 4);
       } else {
-        const int per = (a.F / 16 + kTileMt - 1) / kTileMt, per_s = (a.Fs / 16 + kTileMt - 1) / kTileMt;
-        const dim3 gg(n_units * per + splits * per_s);
-        DES_LAUNCH_TILE(kKGateUp, gateup_tile_kernel, gg);
+        const dim3 gg(n_units * ((a.F / 16 + gu_mt - 1) / gu_mt) + splits * ((a.Fs / 16 + gu_mt - 1) / gu_mt));
+        if (gu_two) DES_LAUNCH_TILE(kKGateUp, gateup_tile_kernel, gg, 2, 2);
+        else if (gu_mt == 2) DES_LAUNCH_TILE(kKGateUp, gateup_tile_kernel, gg, 2, 1);
+        else DES_LAUNCH_TILE(kKGateUp, gateup_tile_kernel, gg, 4, 1);
       }
       if (dn_stream) {
         const int lw = a.T <= 64 ? 2 : 4;
@@ -1160,9 +1178,10 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
         if (small) DES_LAUNCH_DN(4, 2);
         else DES_LAUNCH_DN(8, 4);
       } else {
-        const int per = (a.D / 16 + 2 * kTileMt - 1) / (2 * kTileMt);
+        const int per = (a.D / 16 + 2 * dn_mt - 1) / (2 * dn_mt);
         const dim3 dg(n_units * per + (a.Fs > 0 ? splits * per : 0));
-        DES_LAUNCH_TILE(kKDown, down_tile_kernel, dg);
+        if (dn_mt == 2) DES_LAUNCH_TILE(kKDown, down_tile_kernel, dg, 2, 2);
+        else DES_LAUNCH_TILE(kKDown, down_tile_kernel, dg, 4, 1);
       }
 #undef DES_LAUNCH_GU
 #undef DES_LAUNCH_DN

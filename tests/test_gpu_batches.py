@@ -32,6 +32,12 @@ BATCHES = {
     "streamed_31_pairs": (5, 33, 256, 16, 384, 128, 3, 6),
     "tiles_32_pairs": (5, 35, 256, 16, 384, 128, 3, 6),
     "unrolled_256_tokens": (8, 32, 2048, 8, 512, 512, 2, 4),
+    # ... enough workgroups for four row tiles per wavefront, and fewer (two, one chunk ahead),
+    # in units of 64 and of 128 rows, row tiles that do not fill a workgroup
+    "tiles_four_60_tokens": (2, 30, 160, 256, 96, 32, 4, 256),
+    "tiles_four_150_tokens": (3, 50, 416, 128, 224, 96, 7, 128),
+    "tiles_two_60_tokens": (2, 30, 96, 128, 96, 0, 3, 128),
+    "tiles_two_150_tokens": (1, 150, 96, 64, 288, 0, 4, 64),
 }
 
 
