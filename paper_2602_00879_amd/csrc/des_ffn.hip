@@ -307,6 +307,10 @@ __device__ __forceinline__ FfnArgs shared_view(const FfnArgs& a, Task& t, size_t
 #define DES_FFN_WAVES 1
 #endif
 constexpr int kFfnWaves = DES_FFN_WAVES;  // wavefronts per workgroup; each is an independent task
+// The wavefront's task, a scalar: it guards matrix instructions (see stream_pipeline).
+__device__ __forceinline__ int ffn_task() {
+  return blockIdx.x * kFfnWaves + (kFfnWaves == 1 ? 0 : uniform_int(threadIdx.x >> 6));
+}
 constexpr int kGuTiles = 2;   // gate/up row tiles per task (F % 32 == 0, so F/16 is even)
 
 // One gate/up task (see the kernel comment): returns false if the slot is unused.
@@ -346,7 +350,7 @@ __device__ __forceinline__ bool gateup_task(const FfnArgs& a, int task, int lane
 template <int MAXNT, bool PACKED, int U1 = 2, int U2 = 2, int GT = kGuTiles>
 __global__ __launch_bounds__(kFfnWaves* kWave) void gateup_bf16_kernel(FfnArgs a) {
   const int lane = threadIdx.x & 63;
-  int task = blockIdx.x * kFfnWaves + (threadIdx.x >> 6);
+  int task = ffn_task();
   {
     if (a.dn.on) {
       // dense short block: the first wavefronts of the grid re-route the block's tokens
@@ -509,7 +513,7 @@ __device__ __forceinline__ bool down_task(const FfnArgs& a, int task, int lane, 
 template <int MAXNT, bool PACKED, int U1 = 2, int U2 = 2, int RTG = 4>
 __global__ __launch_bounds__(kFfnWaves* kWave) void down_bf16_kernel(FfnArgs a) {
   const int lane = threadIdx.x & 63;
-  const int task = blockIdx.x * kFfnWaves + (threadIdx.x >> 6);
+  const int task = ffn_task();
   const int groups = (a.D / 16 + RTG - 1) / RTG;
   const int tasks = a.n_slots * groups + (a.Fs > 0 ? groups : 0);
   constexpr int kUmax = (U1 > U2 ? U1 : U2) > 2 ? (U1 > U2 ? U1 : U2) : 2;
@@ -580,8 +584,9 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void g
   const uint32_t wlo = tile_lane_off<true>(a.D, lane);
   const uint16_t* x = uniform_ptr(static_cast<const uint16_t*>(a.x));
   uint16_t* h = static_cast<uint16_t*>(v.h);
-  for (int g0 = split * kRows; g0 < t.count; g0 += splits * kRows) {
-    const int rows = min(kRows, t.count - g0);
+  const int count = uniform_int(t.count);  // guards matrix instructions (see stream_pipeline)
+  for (int g0 = split * kRows; g0 < count; g0 += splits * kRows) {
+    const int rows = min(kRows, count - g0);
     const int nt = (rows + 15) / 16;
     auto row_off = [&](int r) {
       const int tok = t.shared ? g0 + r : a.pair_tok[t.pair0 + g0 + r];
@@ -602,7 +607,7 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void g
 #pragma unroll
       for (int i = 0; i < NT; ++i) {
         const int pi = g0 + i * 16 + (lane & 15);
-        if (pi < t.count) {
+        if (pi < count) {
           u16x4 o;
 #pragma unroll
           for (int q = 0; q < 4; ++q) o[q] = f32_to_bf16_bits(silu_f(accg[i][q]) * accu[i][q]);
@@ -641,15 +646,15 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void d
   if (!lds_task<true>(a, per, a.Fs > 0 ? per : 0, group, split, splits, t, v, lane)) return;
   const int dt0 = (group * LW + wave) * 2;
   const bool active = dt0 < dtiles;
-  const int F = t.fdim;
+  const int F = uniform_int(t.fdim), count = uniform_int(t.count);  // guard matrix instructions
   const uint16_t* w0 = uniform_ptr(t.w0);
   const uint16_t* p0 = tile_base<true>(w0, active ? dt0 : 0, F);
   const uint16_t* p1 = tile_base<true>(w0, active ? dt0 + 1 : 0, F);
   const uint32_t wlo = tile_lane_off<true>(F, lane);
   const uint16_t* h = uniform_ptr(static_cast<const uint16_t*>(v.h));
   const size_t orow0 = t.shared ? static_cast<size_t>(a.T) * a.K : static_cast<size_t>(t.pair0);
-  for (int g0 = split * kRows; g0 < t.count; g0 += splits * kRows) {
-    const int rows = min(kRows, t.count - g0);
+  for (int g0 = split * kRows; g0 < count; g0 += splits * kRows) {
+    const int rows = min(kRows, count - g0);
     const int nt = (rows + 15) / 16;
     const int hrow0 = static_cast<int>(t.row_base) + g0;
     auto row_off = [&](int r) { return (hrow0 + r) * F; };
@@ -668,7 +673,7 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void d
 #pragma unroll
       for (int i = 0; i < NT; ++i) {
         const int pi = g0 + i * 16 + (lane & 15);
-        if (pi < t.count) {
+        if (pi < count) {
           float* dst = a.o + (orow0 + pi) * a.D + dt0 * 16 + 4 * (lane >> 4);
           *reinterpret_cast<f32x4*>(dst) = acc0[i];
           *reinterpret_cast<f32x4*>(dst + 16) = acc1[i];

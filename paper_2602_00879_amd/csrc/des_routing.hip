@@ -137,7 +137,8 @@ __device__ __forceinline__ bool flags_wait(const unsigned long long* f, int n,
 // the accumulator of lane l holds column (l%16), rows 4*(l/16)..+3.
 __device__ __forceinline__ void router_tile_bf16(const RoutingArgs& a, int tile_m, int tile_t,
                                                  float* part /* [16][256] LDS */) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = uniform_int(threadIdx.x >> 6);  // (it guards matrix instructions, see stream_pipeline)
   const int T = a.B * a.N, D = a.D, M = a.M;
   const int i0 = tile_m * 16, t0 = tile_t * 16;
   const int r = lane & 15, kq = (lane >> 4) * 8;

@@ -1,5 +1,6 @@
-"""Checks on the generated gfx950 code of the FFN kernels and of the attention
-projections, which share the streaming building block (no GPU needed).
+"""Checks on the generated gfx950 code (no GPU needed): of the FFN kernels and of the attention
+projections, which share the streaming building block, and of every kernel with matrix
+instructions.
 
 The kernels for blocks of more than 32 tokens issue their loads from inline asm
 and wait for them with explicit counts.  The compiler neither inserts the wait
@@ -16,26 +17,37 @@ of the generated code are checked here:
   * no move, spill or LDS write reads the destination of such a load between the load
     and the explicit wait that covers it (the compiler believes the value is there as
     soon as the asm statement has been issued and could copy it, e.g. on a loop back edge).
+
+Matrix instructions ignore the execution mask.  A block of them under a mask that the compiler
+takes for divergent is skipped by a branch only if the compiler thinks the branch worth its
+while; without it the block runs with all lanes off and adds what it should not.  So no matrix
+instruction may follow a narrowing of the mask that has no branch for "no lane left".
 """
+import functools
 import os
 import re
+import tempfile
 
 import pytest
 
 from paper_2602_00879_amd import build as B
 
 
+@functools.lru_cache(maxsize=None)
+def _asm(source):
+    with tempfile.TemporaryDirectory() as d:
+        return open(B.device_asm(source, os.path.join(d, source + ".s"))).read()
+
+
 @pytest.fixture(scope="module", params=["des_ffn.hip", "des_attention.hip"])
-def ffn_asm(request, tmp_path_factory):
-    out = str(tmp_path_factory.mktemp("isa") / (request.param + ".s"))
-    B.device_asm(request.param, out)
-    return open(out).read()
+def ffn_asm(request):
+    return _asm(request.param)
 
 
 def _kernels(text):
     """{kernel name: list of instructions} of every kernel in the assembly."""
     out = {}
-    for m in re.finditer(r"\n(_ZN3des\w+):[^\n]*\n(.*?)\n\s*s_endpgm", text, re.S):
+    for m in re.finditer(r"\n(_ZN3des\w+):[^\n]*\n(.*?)\n\.Lfunc_end", text, re.S):
         ins = []
         for line in m.group(2).split("\n"):
             line = line.split(";")[0].strip()
@@ -151,7 +163,7 @@ def test_no_read_of_an_asynchronously_loaded_register_before_its_wait(ffn_asm):
     errors = []
     n = 0
     _TRACKED[0] = 0
-    for m in re.finditer(r"\n(_ZN3des\w*lds_kernel\w+):[^\n]*\n(.*?)\n\s*s_endpgm", ffn_asm, re.S):
+    for m in re.finditer(r"\n(_ZN3des\w*lds_kernel\w+):[^\n]*\n(.*?)\n\.Lfunc_end", ffn_asm, re.S):
         n += 1
         lines = [l.split(";")[0].strip() for l in m.group(2).split("\n")]
         lines = [l for l in lines if l and not l.startswith(".")]
@@ -170,3 +182,37 @@ def test_no_read_of_an_asynchronously_loaded_register_before_its_wait(ffn_asm):
     assert n > 0 and _TRACKED[0] > 40
     assert not errors, "\n".join(errors[:10])
 
+
+
+def _masked_matrix_instructions(text):
+    """(matrix instructions seen, those that run under a narrowed mask without a skip branch)"""
+    seen, bad = 0, []
+    for m in re.finditer(r"\n(_ZN3des\w+):[^\n]*\n(.*?)\n\.Lfunc_end", text, re.S):
+        narrowed = None
+        for line in m.group(2).split("\n"):
+            ins = line.split(";")[0].strip()
+            if re.match(r"s_(and|andn2)_(saveexec_b64|b64 exec, exec)", ins):
+                narrowed = ins
+            elif re.match(r"s_cbranch_exec|s_(or|mov)_b64 exec|s_or_saveexec", ins):
+                narrowed = None
+            elif ins.startswith("v_mfma"):
+                seen += 1
+                if narrowed:
+                    bad.append(f"{m.group(1)}: '{ins}' after '{narrowed}'")
+    return seen, bad
+
+
+@pytest.mark.parametrize("source", ["des_ffn.hip", "des_attention.hip", "des_routing.hip"])
+def test_no_matrix_instruction_under_a_mask_without_a_skip_branch(source):
+    seen, bad = _masked_matrix_instructions(_asm(source))
+    assert seen == len(re.findall(r"^\s*v_mfma", _asm(source), re.M)) > 0
+    assert not bad, "\n".join(bad[:10])
+
+
+def test_the_mask_scan_flags_the_pattern():
+    mfma = "\tv_mfma_f32_16x16x32_bf16 v[0:3], v[4:7], v[8:11], v[0:3]\n"
+    kernel = ("\n_ZN3des1kEv: ; @k\n\ts_and_saveexec_b64 s[0:1], vcc\n%s" + mfma +
+              "\ts_or_b64 exec, exec, s[0:1]\n" + mfma + "\ts_endpgm\n.Lfunc_end0:\n")
+    seen, bad = _masked_matrix_instructions(kernel % "")
+    assert seen == 2 and len(bad) == 1
+    assert _masked_matrix_instructions(kernel % "\ts_cbranch_execz .LBB0_2\n") == (2, [])
