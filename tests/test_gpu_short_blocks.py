@@ -37,3 +37,25 @@ def test_short_blocks(name, mode):
     packed = (*(B.des_pack_expert_weights(dev[k]) for k in ("w_gate", "w_up", "w_down")), sh)
     out_p = H.run_gpu(cfg, dev, mode, layout=B.DES_LAYOUT_PACKED, packed_weights=packed)
     assert torch.equal(out.y, out_p.y) and torch.equal(out.topk_idx, out_p.topk_idx)
+
+
+@pytest.mark.parametrize("D", [4, 68, 1024])
+def test_fp32_router_scores_do_not_depend_on_the_number_of_tokens(D):
+    """Tokens are scored in groups of eight, four, two and one: the same bits for a token in any
+    of them.  Against float64: a score is rounded D / 64 + 8 times on its way (a lane's products, six
+    steps over the lanes, the bias), each time by at most 2^-24 of a number below 6 sqrt(D)."""
+    M, T = 19, 35
+    g = torch.Generator().manual_seed(5)
+    x, w, b = (torch.randn(*s, generator=g) for s in ((1, T, D), (M, D), (M,)))
+    xd, wd, bd = x.cuda(), w.cuda(), b.cuda()
+    print(f"fp32 router, width {D}", flush=True)
+    ref = x.double()[0] @ w.double().T + b.double()
+    want = None
+    for n in range(T, 0, -1):
+        shape = B.make_shape(1, n, D, M, 4, 2, 4, "vote", "f32")
+        logits, _ = B.des_route(shape, xd[:, :n].contiguous(), wd, bd)
+        torch.cuda.synchronize()
+        if want is None:
+            want = logits[0]
+            assert (want.cpu().double() - ref).abs().max().item() <= (D / 64 + 8) * 2.0 ** -24 * 6 * D ** 0.5
+        assert torch.equal(logits[0], want[:n]), n
