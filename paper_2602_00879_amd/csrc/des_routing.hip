@@ -1058,6 +1058,8 @@ __global__ __launch_bounds__(kRtThreads) void routing_kernel(RoutingArgs a) {
   const int n_sel = a.do_select ? a.B * a.groups : 0;
   const int all_tiles = a.tiles_m * a.tiles_t;
   const int n_flags = all_tiles + 2 * a.B * a.groups;
+  int part = 0;         // of the permutation
+  bool idx_dev = false;
   if (blk < n_sel) {  // ---- role S
     DES_STAMP(a, 0);
     if (!select_sequence<LPT, EXT>(a, blk / a.groups, blk % a.groups, smem, false,
@@ -1067,44 +1069,43 @@ __global__ __launch_bounds__(kRtThreads) void routing_kernel(RoutingArgs a) {
     }
     DES_STAMP(a, 5);
     if (a.topk_idx == nullptr) return;
-    if (a.dense) {  // no stage 2, no permutation here; the flags of this call are consumed
-      if (a.use_flags)
-        for (int i = threadIdx.x; i < n_flags; i += kRtThreads) a.flags[i] = 0ull;
+    if (!a.dense && !(n_sel == 1 && a.do_permute)) {  // the permutation is another workgroup's
+      if (a.use_flags) {
+        stores_done();
+        __syncthreads();
+        if (threadIdx.x == 0) flag_publish(a.flags + all_tiles + n_sel + blk, a.epoch, false);
+      }
       return;
     }
-    if (n_sel == 1 && a.do_permute) {  // a single selector: permute right here
-      // same workgroup, same compute unit: the barrier orders the topk_idx
-      // stores before the loads below, no device-scope fence needed
-      __syncthreads();
-      DES_STAMP(a, 6);
-      if (a.small_perm) permute_small<LPT>(a, smem);
-      else permute_all<SelLds<LPT>::MP>(a, smem, false, 0, 1);
-      DES_STAMP(a, 7);
-      // every flag of this call has been consumed: clear them, so that a replay
-      // of a captured launch (same epoch) cannot be satisfied by stale flags
-      if (a.use_flags)
-        for (int i = threadIdx.x; i < n_flags; i += kRtThreads) a.flags[i] = 0ull;
-      return;
-    }
-    if (a.use_flags) {
-      stores_done();
-      __syncthreads();
-      if (threadIdx.x == 0) flag_publish(a.flags + all_tiles + n_sel + blk, a.epoch, false);
-    }
-    return;
-  }
-  blk -= n_sel;
-  if (blk < a.perm_parts && a.do_permute && a.B * a.groups > 1) {  // ---- role P
+    // a single selector permutes right here (a dense block has no permutation, and no stage 2
+    // here): same workgroup, same compute unit, so the barrier orders the topk_idx stores
+    // before the loads below, no device-scope fence needed
+    __syncthreads();
+    DES_STAMP(a, 6);
+  } else {  // ---- role P
+    part = blk - n_sel;
+    if (part >= a.perm_parts || !a.do_permute || a.B * a.groups == 1) return;
     if (a.use_flags && a.do_select &&
         !flags_wait(a.flags + all_tiles + a.B * a.groups, a.B * a.groups, a.epoch, false,
                     a.max_wait)) {
       publish_empty(a, n_flags);  // a bounded wait expired
       return;
     }
-    permute_all<SelLds<LPT>::MP>(a, smem, a.use_flags && a.do_select, blk, a.perm_parts);
-    if (a.use_flags)  // all selectors have consumed the other flags and published theirs
-      for (int i = threadIdx.x; i < n_flags; i += kRtThreads) a.flags[i] = 0ull;
+    idx_dev = a.use_flags && a.do_select;
   }
+  // (one place for both roles: a second copy of the permutation makes the kernel 8 KB longer,
+  // 46 against 38 KB, and its code is fetched anew by every launch: selection alone +0.2 us)
+  if (a.dense) {
+  } else if (a.small_perm) {
+    permute_small<LPT>(a, smem);
+  } else {
+    permute_all<SelLds<LPT>::MP>(a, smem, idx_dev, part, a.perm_parts);
+  }
+  DES_STAMP(a, 7);
+  // every flag of this call has been consumed: clear them, so that a replay
+  // of a captured launch (same epoch) cannot be satisfied by stale flags
+  if (a.use_flags)
+    for (int i = threadIdx.x; i < n_flags; i += kRtThreads) a.flags[i] = 0ull;
 }
 
 // probs[t][:] = router weights of token t (softmax of its logits, or their
