@@ -32,145 +32,6 @@ struct LinearArgs {
   unsigned long long epoch;   // of this call: never zero, never repeated (stale words cannot match)
 };
 
-// Arrival count of the workgroups that share an output tile (reduction dimension split
-// over several workgroups).  The word holds (call's epoch << 8 | arrivals); whatever it
-// held before this call - garbage, an earlier call's count - is not this epoch and reads
-// as zero arrivals, so nothing has to be cleared beforehand.  Returns this workgroup's
-// arrival number, 1-based.  Device-scope compare-and-swap; nobody ever waits for anybody.
-__device__ __forceinline__ int arrive(unsigned long long* word, unsigned long long epoch) {
-  const unsigned long long tag = (epoch & 0x00ffffffffffffffull) << 8;
-  unsigned long long cur = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  for (;;) {
-    const unsigned long long base = (cur & ~0xffull) == tag ? cur : tag;
-    const unsigned long long want = base + 1ull;
-    if (__hip_atomic_compare_exchange_strong(word, &cur, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT))
-      return static_cast<int>(want & 0xffull);
-  }
-}
-
-// Very large matrices under 33 to 64 token rows (see stream_linear()) are weight scans:
-// out[m][t][f] = sum_d in[t][d] * w[m][f][d].  A workgroup of LW wavefronts owns LW pairs
-// of 16-row weight tiles of one matrix and up to ROWS token rows (blockIdx.y
-// names which; the weights are streamed once per ROWS rows).  KD = the reduction length of a workgroup if
-// it is the unrolled one, else 0.  With ksplit > 1 the reduction
-// dimension is split over that many workgroups (blockIdx.z): each writes its fp32 partial
-// tiles with device-scope stores and counts itself in; the last to arrive adds all the
-// partials in order of their part of the reduction dimension, whoever finished when.
-template <int LW, int KD, int ROWS>
-__global__ __launch_bounds__(LW* kWave, 2) void linear_lds_kernel(LinearArgs a) {
-  constexpr int kRows = ROWS;
-  __shared__ __align__(16) uint16_t lds[lds_elems(KD)];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int part = blockIdx.z, kd = a.Din / a.ksplit, k0 = part * kd;
-  int bx = blockIdx.x, m = 0;
-  for (; m < a.n_mats; ++m) {  // which matrix this workgroup belongs to
-    const int per = (a.fout[m] / 32 + LW - 1) / LW;
-    if (bx < per) break;
-    bx -= per;
-  }
-  if (m >= a.n_mats) return;
-  const int fout = a.fout[m], Din = a.Din;
-  const int pair = bx * LW + wave;          // pair of row tiles this wavefront owns
-  const bool active = pair * 2 < fout / 16;
-  const uint16_t* w = uniform_ptr(a.w[m]);
-  const uint16_t* p0 = tile_base<false>(w, active ? pair * 2 : 0, Din) + k0;
-  const uint16_t* p1 = tile_base<false>(w, active ? pair * 2 + 1 : 0, Din) + k0;
-  const uint32_t wlo = tile_lane_off<false>(Din, lane);
-  const uint16_t* in = uniform_ptr(a.in) + k0;
-  // this output tile's place among the launch's (x, y) workgroups: its partials and counter
-  const size_t tile_id = static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x;
-  uint16_t* out = a.out[m];
-  const uint16_t* res = m == 0 ? a.res : nullptr;
-  {  // one pass of up to 128 token rows per workgroup (blockIdx.y)
-    const int g0 = blockIdx.y * kRows;
-    const int rows = min(kRows, a.T - g0);
-    const int nt = (rows + 15) / 16;
-    auto row_off = [&](int r) { return (g0 + r) * Din; };
-    auto run = [&](auto ntc) {
-      constexpr int NT = decltype(ntc)::value;
-      f32x4 acc0[NT], acc1[NT];
-#pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        acc0[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        acc1[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-      constexpr int KC = NT <= 4 ? 128 : 64;
-      dma_stream_gemm<NT, kLdsBufElems / KC, false, LW, KC, KD>(p0, p1, wlo, wave, kd, rows, in, row_off, lds,
-                                                                 acc0, acc1);
-      if (a.ksplit > 1) {
-        // partial tiles of this wavefront: [tile][part][wave][2][8 token tiles][64 lanes][4]
-        constexpr size_t kPerWave = 2 * 8 * 256;
-        float* base = a.partial + (tile_id * a.ksplit * LW) * kPerWave;
-        float* mine = base + (static_cast<size_t>(part) * LW + wave) * kPerWave;
-#pragma unroll
-        for (int i = 0; i < NT; ++i)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            __hip_atomic_store(mine + (i * 64 + lane) * 4 + q, acc0[i][q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(mine + ((8 + i) * 64 + lane) * 4 + q, acc1[i][q], __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-          }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's partials have left the compute unit
-        __shared__ int s_last;
-        __syncthreads();
-        if (tid == 0) {
-          s_last = arrive(a.flags + tile_id, a.epoch) == a.ksplit ? 1 : 0;
-          // everybody has arrived: clear the count, so that a replay of a captured launch
-          // (same epoch) counts from zero again
-          if (s_last) __hip_atomic_store(a.flags + tile_id, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-        if (!s_last) return;
-#pragma unroll
-        for (int i = 0; i < NT; ++i) {
-          acc0[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-          acc1[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        for (int h = 0; h < a.ksplit; ++h) {  // parts in order, not in order of arrival
-          const float* src = base + (static_cast<size_t>(h) * LW + wave) * kPerWave;
-#pragma unroll
-          for (int i = 0; i < NT; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              acc0[i][q] += __hip_atomic_load(src + (i * 64 + lane) * 4 + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              acc1[i][q] += __hip_atomic_load(src + ((8 + i) * 64 + lane) * 4 + q, __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-      }
-      if (!active) return;
-#pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        const int pi = g0 + i * 16 + (lane & 15);
-        if (pi < a.T) {
-#pragma unroll
-          for (int half = 0; half < 2; ++half) {
-            const f32x4 v = half ? acc1[i] : acc0[i];
-            const size_t o = static_cast<size_t>(pi) * fout + (pair * 2 + half) * 16 + 4 * (lane >> 4);
-            f32x4 r = v;
-            if (res != nullptr) {
-              const u16x4 rv = *reinterpret_cast<const u16x4*>(res + o);
-#pragma unroll
-              for (int q = 0; q < 4; ++q) r[q] += bf16_bits_to_f32(rv[q]);
-            }
-            u16x4 ob;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) ob[q] = f32_to_bf16_bits(r[q]);
-            *reinterpret_cast<u16x4*>(out + o) = ob;
-          }
-        }
-      }
-    };
-    if (nt <= 1) run(std::integral_constant<int, 1>{});
-    else if (nt <= 2) run(std::integral_constant<int, 2>{});
-    else if (kRows <= 64 || nt <= 4) run(std::integral_constant<int, 4>{});
-    else if (nt <= 6) run(std::integral_constant<int, kRows <= 64 ? 4 : 6>{});
-    else run(std::integral_constant<int, kRows <= 64 ? 4 : 8>{});
-  }
-}
-
 // out[m][t][f] = sum_d in[t][d] * w[m][f][d] for blocks of more than 32 token rows, in tiles
 // of 32 MT weight rows x 32 NT token rows (des_tile_gemm.h).  KW = 2: the two halves of the
 // reduction dimension go to the two halves of the workgroup and meet in LDS, first half +
@@ -808,21 +669,8 @@ static TileLinearPlan tile_linear_plan(int T, const int* fout, int n_mats, int D
   return p;
 }
 
-// Where the streaming form is still level with the tiles: 49 to 64 token rows (three or four
-// token tiles in one pass) on one matrix of 8192 x 8192 and more, where 128 and more
-// workgroups each stream a megabyte and the tiles' trip through LDS buys nothing (8192 x 8192,
-// 64 rows: 45.3 us streamed, 46.0 us in tiles; 48 rows 43.2 both; 2048 x 16384, 64 rows: 78.5
-// and 70.6).
-inline bool stream_linear(int T, const int* fout, int n_mats, int Din) {
-  return n_mats == 1 && T > 48 && T <= 64 && fout[0] >= 8192 && Din >= 8192;
-}
-constexpr int kStreamWaves = 2;
-inline int stream_ksplit(const int* fout, int Din) {  // the same rule as the tiles'
-  return (fout[0] / 32 + 1) / 2 < 150 && Din % 512 == 0 ? 2 : 1;
-}
-
-// of one workgroup's part of a cut reduction: 4 weight tiles x up to 8 token tiles x 1 KB
-constexpr size_t kLongPartialBytes = kStreamWaves * 2 * 8 * 256 * 4;
+// of one half of a cut reduction: 4 weight tiles x up to 8 token tiles x 1 KB
+constexpr size_t kLongPartialBytes = 4 * 8 * 1024;
 
 // Scratch of one attention sub-layer (bytes from a 256-byte aligned base): q, k, v and the
 // per-head outputs of the block's tokens, bf16.
@@ -842,11 +690,10 @@ AttnLayout attn_layout(const des_shape_t& s, const des_attn_shape_t& t) {
   const size_t tiles = tiles_qkv > tiles_out ? tiles_qkv : tiles_out;
   size_t part_bytes = tiles * 4096, n_flags = tiles;
   if (T > 32) {
-    // Longer blocks: 32 KB for each half of a workgroup's cut reduction and a flag per
-    // workgroup, whether the halves meet there (the streaming form) or in LDS (the tiles).
-    // The size is part of the interface: a caller keeps one buffer for its longest block and
-    // the remainders after it, and at 33 to 96 tokens that buffer is this large because of
-    // these partials (2048-wide layer, 32 heads: 5.85 MB at 33 tokens, 1.90 MB at 32).
+    // Longer blocks need none (the halves of a cut reduction meet in LDS), but the size is part
+    // of the interface: a caller keeps one buffer for its longest block and the remainders after
+    // it, which do.  So it stays at 32 KB for each half of a workgroup's cut reduction and a flag
+    // per workgroup (2048-wide layer, 32 heads: 5.85 MB at 33 tokens, 1.90 MB at 32).
     const int f_qkv[3] = {t.n_heads * t.head_dim, t.n_kv_heads * t.head_dim, t.n_kv_heads * t.head_dim};
     const int f_out[1] = {s.hidden};
     const LongCut a = long_cut(static_cast<int>(T), f_qkv, 3, s.hidden);
@@ -898,14 +745,6 @@ static void launch_linear(const LinearArgs& a, int kernel_id, hipStream_t st) {
       if (a.T <= 16) launch(kernel_id, linear_splitk_kernel<1, 1>, g, blk, 0, st, b);
       else launch(kernel_id, linear_splitk_kernel<1, 2>, g, blk, 0, st, b);
     }
-    return;
-  }
-  if (stream_linear(a.T, a.fout, a.n_mats, a.Din)) {
-    LinearArgs c = a;
-    c.ksplit = stream_ksplit(a.fout, a.Din);
-    const dim3 g((a.fout[0] / 32 + kStreamWaves - 1) / kStreamWaves, 1, c.ksplit), b(kStreamWaves * kWave);
-    if (a.Din / c.ksplit == 4096) launch(kernel_id, linear_lds_kernel<kStreamWaves, 4096, 64>, g, b, 0, st, c);
-    else launch(kernel_id, linear_lds_kernel<kStreamWaves, 0, 64>, g, b, 0, st, c);
     return;
   }
   const TileLinearPlan pl = tile_linear_plan(a.T, a.fout, a.n_mats, a.Din);

@@ -4,14 +4,15 @@
 // The layer is bound by the one-time read of the live experts' weights
 // (Eq. 2: the b * |union S_n| term), so the kernels are organised around the
 // weight stream, not around the tokens:
-//   * a wavefront owns 16 weight rows (gate and up rows of the same
-//     intermediate units, or 4 x 16 down rows) and walks the whole reduction
-//     dimension, loading each weight fragment straight into the matrix-core A
-//     operand with 16-byte loads - every weight byte is read by exactly one
-//     wavefront, exactly once;
-//   * the expert's tokens are the matrix-core B operand (16 tokens per tile,
-//     up to 16 tiles held in accumulators), so a partly empty token tile
+//   * at most 32 tokens: a wavefront owns 16 or 32 intermediate units (their gate and up
+//     rows), or 32 or 64 down rows, of one expert and walks the whole reduction dimension,
+//     loading each weight fragment straight into the matrix-core A operand with 16-byte
+//     loads - every weight byte is read by exactly one wavefront, exactly once; the expert's
+//     tokens are the B operand (one or two tiles of 16), so a partly empty token tile
 //     wastes matrix-core cycles, which are free here, and no bandwidth;
+//   * more: an expert's tokens form units of up to 128 rows that go through LDS and are
+//     shared by a workgroup's wavefronts, the weights straight into operands (streamed) or
+//     through LDS as well (tiles);
 //   * the grid is sized for the worst case and every wavefront looks its
 //     expert up in the device-resident live list, so the host never waits for
 //     the routing result.
@@ -93,13 +94,6 @@ __device__ __forceinline__ bf16x8 ld8(const uint16_t* p) {
 __device__ __forceinline__ bf16x8 ld8_stream(const uint16_t* p) {
   return __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(p));
 }
-__device__ __forceinline__ bf16x8 zero8() {
-  bf16x8 z;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) z[i] = static_cast<__bf16>(0.0f);
-  return z;
-}
-
 // This lane's place in the loads of row tile rt: packed tiles are in operand order already.
 template <bool PACKED>
 __device__ __forceinline__ const uint16_t* load_ptr(const uint16_t* base, int rt, int kd, int lane) {
@@ -579,9 +573,9 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void g
   const int tile = group * LW + wave;
   const bool active = tile < t.fdim / 16;
   const uint16_t* w0 = uniform_ptr(t.w0);
-  const uint16_t* gp = tile_base<true>(w0, active ? tile : 0, a.D);
-  const uint16_t* up = tile_base<true>(uniform_ptr(t.w1), active ? tile : 0, a.D);
-  const uint32_t wlo = tile_lane_off<true>(a.D, lane);
+  const uint16_t* gp = tile_base(w0, active ? tile : 0, a.D);
+  const uint16_t* up = tile_base(uniform_ptr(t.w1), active ? tile : 0, a.D);
+  const uint32_t wlo = tile_lane_off(lane);
   const uint16_t* x = uniform_ptr(static_cast<const uint16_t*>(a.x));
   uint16_t* h = static_cast<uint16_t*>(v.h);
   const int count = uniform_int(t.count);  // guards matrix instructions (see stream_pipeline)
@@ -601,7 +595,7 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void g
         accu[i] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
       constexpr int KC = NT <= 4 ? 128 : 64;  // rows * KC = one 16 KB buffer
-      dma_stream_gemm<NT, kLdsBufElems / KC, true, LW, KC, KD>(gp, up, wlo, wave, a.D, rows, x,
+      dma_stream_gemm<NT, kLdsBufElems / KC, LW, KC, KD>(gp, up, wlo, wave, a.D, rows, x,
                                                                  row_off, lds, accg, accu);
       if (!active) return;
 #pragma unroll
@@ -648,9 +642,9 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void d
   const bool active = dt0 < dtiles;
   const int F = uniform_int(t.fdim), count = uniform_int(t.count);  // guard matrix instructions
   const uint16_t* w0 = uniform_ptr(t.w0);
-  const uint16_t* p0 = tile_base<true>(w0, active ? dt0 : 0, F);
-  const uint16_t* p1 = tile_base<true>(w0, active ? dt0 + 1 : 0, F);
-  const uint32_t wlo = tile_lane_off<true>(F, lane);
+  const uint16_t* p0 = tile_base(w0, active ? dt0 : 0, F);
+  const uint16_t* p1 = tile_base(w0, active ? dt0 + 1 : 0, F);
+  const uint32_t wlo = tile_lane_off(lane);
   const uint16_t* h = uniform_ptr(static_cast<const uint16_t*>(v.h));
   const size_t orow0 = t.shared ? static_cast<size_t>(a.T) * a.K : static_cast<size_t>(t.pair0);
   for (int g0 = split * kRows; g0 < count; g0 += splits * kRows) {
@@ -667,7 +661,7 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void d
         acc1[i] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
       constexpr int KC = NT <= 4 ? 128 : 64;
-      dma_stream_gemm<NT, kLdsBufElems / KC, true, LW, KC, KD>(p0, p1, wlo, wave, F, rows, h,
+      dma_stream_gemm<NT, kLdsBufElems / KC, LW, KC, KD>(p0, p1, wlo, wave, F, rows, h,
                                                                  row_off, lds, acc0, acc1);
       if (!active) return;
 #pragma unroll

@@ -1,8 +1,7 @@
 // Streaming GEMM building blocks: the pieces that the short-block kernels share, and the one
-// shared by the kernels that stage token rows through
-// LDS (the expert FFN for blocks of more than 32 tokens, the dense projections of the
-// attention sub-layer): weights from HBM straight into MFMA operands, token rows from
-// L2 into LDS by direct loads, explicit wait counts.  gfx950 only.
+// of the expert FFN's kernels that stage token rows through LDS (packed weights, more than 32
+// tokens): weights from HBM straight into MFMA operands, token rows from L2 into LDS by direct
+// loads, explicit wait counts.  gfx950 only.
 #pragma once
 
 #include <type_traits>
@@ -125,15 +124,11 @@ __device__ __forceinline__ T* uniform_ptr(T* p) {
   const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
   return reinterpret_cast<T*>((static_cast<unsigned long long>(hi) << 32) | lo);
 }
-// Weight tile rt of a [rows][kd] matrix as uniform base + per-lane byte offset.
-template <bool PACKED>
+// Weight tile rt of a packed [rows][kd] matrix (uniform), and a lane's byte offset in a fragment.
 __device__ __forceinline__ const uint16_t* tile_base(const uint16_t* base, int rt, int kd) {
-  return base + static_cast<size_t>(rt) * 16 * kd;  // 16 rows of kd values in either layout
+  return base + static_cast<size_t>(rt) * 16 * kd;
 }
-template <bool PACKED>
-__device__ __forceinline__ uint32_t tile_lane_off(int kd, int lane) {
-  return PACKED ? lane * 16u : ((lane & 15) * static_cast<uint32_t>(kd) + (lane >> 4) * 8u) * 2u;
-}
+__device__ __forceinline__ uint32_t tile_lane_off(int lane) { return lane * 16u; }
 // Waits until at most N vector-memory operations are outstanding and makes the
 // fragments of a stage depend on that wait.
 template <int N>
@@ -170,7 +165,7 @@ __device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F&&
 //
 // A wavefront without a tile of its own (row tiles not a multiple of LW) runs
 // on tile 0 and drops its result.
-template <int NT, int ROWS, bool PACKED, int LW, int KC, int KD, typename RowOff>
+template <int NT, int ROWS, int LW, int KC, int KD, typename RowOff>
 __device__ __forceinline__ void dma_stream_gemm(const uint16_t* a0, const uint16_t* a1,
                                                 uint32_t w_lane_off, int wave, int kd,
                                                 int rows_valid, const uint16_t* base,
@@ -193,7 +188,7 @@ __device__ __forceinline__ void dma_stream_gemm(const uint16_t* a0, const uint16
   constexpr int NW = 2 * KS;         // weight loads per wavefront and chunk
   constexpr int kBufBytes = ROWS * RB;
   constexpr int kTile = 16 * RB;     // bytes of one token tile in a buffer
-  constexpr int kFragBytes = frag_step<PACKED>() * 2;  // between k-steps of a weight tile
+  constexpr int kFragBytes = frag_step<true>() * 2;  // between k-steps of a weight tile
   auto swz = [](int r) { return KC == 128 ? (r & 15) : ((r >> 1) & 7); };
   // All addresses are a uniform base, advanced per chunk in scalar registers,
   // plus a per-lane byte offset that never changes.
@@ -226,8 +221,8 @@ __device__ __forceinline__ void dma_stream_gemm(const uint16_t* a0, const uint16
   bf16x8 aw0[KD > 0 ? 3 : 2][KS], aw1[KD > 0 ? 3 : 2][KS];
   auto loadw = [&](int chunk, auto stage) {
     constexpr int s = decltype(stage)::value;
-    const uint16_t* q0 = a0 + static_cast<size_t>(chunk) * KS * frag_step<PACKED>();
-    const uint16_t* q1 = a1 + static_cast<size_t>(chunk) * KS * frag_step<PACKED>();
+    const uint16_t* q0 = a0 + static_cast<size_t>(chunk) * KS * frag_step<true>();
+    const uint16_t* q1 = a1 + static_cast<size_t>(chunk) * KS * frag_step<true>();
     ld8_async<0 * kFragBytes>(aw0[s][0], q0, w_lane_off);
     ld8_async<0 * kFragBytes>(aw1[s][0], q1, w_lane_off);
     ld8_async<1 * kFragBytes>(aw0[s][1], q0, w_lane_off);

@@ -45,13 +45,13 @@ CASES = {
     "long_block": (1, 300, 128, 4, 4, 32, 7),
     # the projections' forms: tiles with the reduction whole or cut, rows and columns that do
     # not fill a tile, a reduction of whole 64-element chunks and of one chunk more or less,
-    # the large tile, the streamed one
+    # the large tile, wide matrices
     "tile_33_rows": (1, 33, 128, 4, 2, 32, 3),
     "tile_cut_65_rows": (1, 65, 1024, 8, 2, 64, 3),
     "tile_whole_65_rows": (5, 13, 1152, 8, 2, 48, 0),
     "tile_large": (10, 103, 1152, 72, 8, 128, 0),
-    "streamed_50_rows": (1, 50, 8192, 64, 1, 128, 0),
-    "streamed_64_rows_odd_length": (2, 32, 8192, 65, 1, 128, 0),
+    "tile_50_rows_wide": (1, 50, 8192, 64, 1, 128, 0),
+    "tile_64_rows_odd_length": (2, 32, 8192, 65, 1, 128, 0),
 }
 
 

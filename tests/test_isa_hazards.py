@@ -1,6 +1,5 @@
-"""Checks on the generated gfx950 code (no GPU needed): of the FFN kernels and of the attention
-projections, which share the streaming building block, and of every kernel with matrix
-instructions.
+"""Checks on the generated gfx950 code (no GPU needed): of the FFN kernels for longer blocks, which
+use the streaming building block, and of every kernel with matrix instructions.
 
 The kernels for blocks of more than 32 tokens issue their loads from inline asm
 and wait for them with explicit counts.  The compiler neither inserts the wait
@@ -39,9 +38,9 @@ def _asm(source):
         return open(B.device_asm(source, os.path.join(d, source + ".s"))).read()
 
 
-@pytest.fixture(scope="module", params=["des_ffn.hip", "des_attention.hip"])
-def ffn_asm(request):
-    return _asm(request.param)
+@pytest.fixture(scope="module")
+def ffn_asm():
+    return _asm("des_ffn.hip")
 
 
 def _kernels(text):
