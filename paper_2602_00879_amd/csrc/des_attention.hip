@@ -662,10 +662,14 @@ static TileLinearPlan tile_linear_plan(int T, const int* fout, int n_mats, int D
   };
   TileLinearPlan p{2, blocks(2), 1};
   if (long_cut(T, fout, n_mats, Din).cut) p.kw = 2;
-  // Tiles of 128 x 128 need half the LDS and L2 traffic per multiply; two workgroups per
-  // compute unit have to be there for it to pay (4608 x 2560 weights on 432 rows, 144 such
-  // tiles: 33.5 us against 21.2 us in tiles of 64; at 512 and more they win).
-  else if (blocks(4) >= 512) p = TileLinearPlan{4, blocks(4), 1};
+  // Tiles of 128 x 128 need half the LDS and L2 traffic per multiply, but have to fill the
+  // compute units: from two per unit on, and, where a tile is long enough to pay for its start,
+  // from one per unit if the last round of units is at least two thirds full (4096 x 4096
+  // weights: 1376 rows, 352 tiles, 81.6 us in tiles of 64, 67.6; 2048 x 16384, 2048 rows, 256
+  // tiles, 306 and 167; but 3072 x 4096, 1024 rows, 320 tiles, 51.0 and 53.1; 1024 x 1024, 2976
+  // rows, 384 tiles, 20.5 and 22.6).
+  else if (const int b4 = blocks(4); b4 >= 512 || (Din >= 2048 && b4 >= 256 && 2 * ((b4 + 255) / 256 * 256) <= 3 * b4))
+    p = TileLinearPlan{4, b4, 1};
   return p;
 }
 
@@ -719,12 +723,15 @@ size_t attn_core_lds(const des_shape_t& s, const des_attn_shape_t& t) {
 static void launch_linear(const LinearArgs& a, int kernel_id, hipStream_t st) {
   if (a.T <= 32) {
     // Row tiles per workgroup: two halve the token-row traffic from L2, which costs as much
-    // as the weight stream here (measured on the 2048-wide layer: q/k/v 13.6 us against
-    // 17.2 us with one), but only while the workgroups still cover most compute units
-    // (output projection, 128 tiles: 16 us with one tile per workgroup, 21 us with two).
+    // as the weight stream here (q/k/v of the 2048-wide layer, 320 tiles, 32 rows: 8.4 us
+    // against 11.2 us with one), but only while the workgroups still cover most compute units
+    // (its output projection, 128 tiles: 8.1 us with one, 9.2 us with two; 256 tiles of 2048:
+    // 7.1 and 9.4 us).
     // Fewer than 150 workgroups: the reduction dimension is split over two workgroups as
-    // well (output projection 15.9 -> 13.3 us; with 160 workgroups, q/k/v, the exchange of
-    // partial tiles costs more than the better spread gains: 18.4 against 14.1 us).
+    // well (the output projection 9.1 -> 8.1 us; q/k/v with 160 workgroups would take 11.9 us
+    // instead of 8.4).  At 1024 x 1024 the exchange of partial tiles costs more than the spread
+    // gains (4.2 us whole, 5.2 us split): the split stays there because it decides the order of
+    // the sums.  (Times with the weights in the last-level cache.)
     // Wavefronts per workgroup (k-slices): a whole number of 32-element steps each, at
     // least 256 reduction elements per row, at most 8.
     int tiles = 0;

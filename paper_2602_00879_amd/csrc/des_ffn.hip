@@ -1072,10 +1072,12 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
     // an expert serves a token at most once, so no task has more than T pairs
     const int maxnt = (a.T + 15) / 16;
     const dim3 blk(kFfnWaves * kWave);
-    // Few experts (small coreset): halve the task size so that enough wavefronts
-    // keep bytes in flight.  Measured: gate/up gains below ~512 tasks (18.4 vs
-    // 20.5 us at 272) and loses above (36.4 vs 34.4 us at 768); the down projection
-    // gains up to 1024 tasks while a halved task still streams >= 48 KB (F >= 768).
+    // Few experts (small coreset): halve the task size so that enough wavefronts keep bytes in
+    // flight; a halved down task should still stream >= 48 KB (F >= 768).  2048 x 768, whole and
+    // halved tasks, in us: gate/up under 8 tokens 13.5 and 9.4 at 192 tasks, 16.8 and 17.2 at
+    // 384, 25.9 and 24.8 at 768; under 32 tokens 15.7 and 13.4, 20.1 and 20.1, 32.7 and 37.0.
+    // Down under 8 tokens 7.8 and 6.1 at 256 tasks, 9.4 and 9.3 at 512, 12.1 and 11.9 at 1024;
+    // under 32 tokens 9.8 and 9.4, 11.3 and 12.7, 20.4 and 19.7.
     const bool gu_fine = gu_tasks < 512;
     const bool dn_fine = dn_tasks <= 1024 && a.F >= 768;
     const int gu_fine_tasks = a.n_slots * (a.F / 16) + a.Fs / 16;
