@@ -158,10 +158,15 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+# the current stream's handle without the Stream object that current_stream() builds (the smallest
+# calls are bound by this host path); not a public name of torch, hence the other way beside it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    # the current stream's handle, without the Stream object that current_stream() builds: the
-    # smallest calls are bound by this host path
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def des_coreset_capacity(shape: DesShape) -> int:

@@ -208,6 +208,25 @@ def test_a_buffer_for_the_longest_block_serves_the_remainders():
     assert B.des_workspace_bytes(_shape(n_tokens=34, **wide)) >= B.des_workspace_bytes(_shape(n_tokens=25, **wide))
 
 
+def test_stream_handle_without_the_short_way(monkeypatch):
+    """A torch without the private call still hands over the current stream."""
+    class Stream:
+        cuda_stream = 4711
+    monkeypatch.setattr(B, "_raw_stream", None)
+    monkeypatch.setattr(B.torch.cuda, "current_stream", lambda *a: Stream)
+    assert B._stream() == 4711
+
+
+@pytest.mark.gpu
+def test_stream_handle_is_the_current_streams():
+    torch = B.torch
+    side = torch.cuda.Stream()
+    assert B._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert B._stream() == side.cuda_stream != 0
+    assert B._stream() == torch.cuda.current_stream().cuda_stream
+
+
 def test_coreset_from_beta_matches_table_1_rounding():
     """M_core = floor(beta * M): the sizes printed in Table 1 of the paper, and the
     oracle's exact-fraction version on a grid of decimal budgets."""
