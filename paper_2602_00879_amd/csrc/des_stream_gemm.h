@@ -95,8 +95,9 @@ __device__ __forceinline__ void turn_fence() {
 // them nor for the weights, explicit vmcnt counts do.  The token fragments are volatile LDS
 // reads, which keeps them in program order with the asm statements and the barriers; the
 // compiler counts them itself, so the next fragments are on their way while one group is
-// multiplied (128-expert layer, 128 tokens: gate/up 41.2 us with a wait after every group,
-// 40.0 us so; 8 x 32 tokens 139.6 -> 137.9 us per layer).  None of the asm statements claims
+// multiplied (128-expert layer, 128 tokens: gate/up 41.9 us with a wait after every group,
+// 39.9 us so; experts of 512 x 896, 112 tokens: 11.3 and 10.3 us; 8 x 32 and 64 x 32 tokens of
+// the former: no difference).  None of the asm statements claims
 // to touch memory (a "memory" clobber makes the compiler wait for every pending load first);
 // they are volatile, which keeps them in program order with each other and the barriers.
 constexpr int kKC = 128;            // reduction lengths must be multiples of this
