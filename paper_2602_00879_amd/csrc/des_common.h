@@ -100,13 +100,12 @@ constexpr int kMaxFusedRoutingBlocks = 256;
 int device_compute_units();          // of the current device (cached)
 
 // Blocks of more than 32 tokens: an expert's pairs are handed to the FFN
-// workgroups in units of this many token rows (what one workgroup pass holds),
-// at most kMaxSplits units per expert (an expert with more rows has each unit
-// take several passes).  The permutation lists the live units, longest expert
-// first; the FFN launches index that list, so no workgroup is spent on units
+// workgroups in units of at most this many token rows (what one workgroup holds); an expert
+// with more has as many units as it takes.  The permutation lists the live units, longest
+// expert first; the FFN launches index that list, so no workgroup is spent on units
 // that do not exist and neighbouring workgroups have neighbouring units.
 inline int lds_rows_pass(int T) { return T <= 64 ? 64 : 128; }
-constexpr int kMaxSplits = 8;
+constexpr int kMaxSplits = 32;  // 4096 tokens, the most an expert can have, in units of 128
 inline int max_units(const des_shape_t& s) {
   const long long TK = static_cast<long long>(s.n_seqs) * s.n_tokens * s.top_k;
   const int rows = lds_rows_pass(s.n_seqs * s.n_tokens);

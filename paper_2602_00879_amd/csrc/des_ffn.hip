@@ -518,107 +518,147 @@ __global__ __launch_bounds__(kFfnWaves* kWave) void down_bf16_kernel(FfnArgs a) 
 
 // ------------------------------------------ larger blocks: activations via LDS
 // (the streaming building block dma_stream_gemm lives in des_stream_gemm.h)
-// Which expert, which of its row groups and which pairs a workgroup works on,
-// shared by the two kernels.  The grid is one-dimensional and read in hand-out
-// order: the shared expert first (every token: the longest workgroups), then
-// the live units of the routed experts as the permutation lists them - longest
-// expert first, an expert's units next to each other (they read the same
-// weights).  So when the workgroups do not all fit on the chip at once the long
-// ones start first, consecutive workgroups (which the hardware deals out to the
-// XCDs in turn) carry similar work, and the grid's tail beyond the live units
-// exits on one scalar load.  `split` of `nsplit`: this workgroup takes every
-// nsplit-th group of rows of the expert, starting with group `split`.
-template <bool DOWN>
-__device__ __forceinline__ bool lds_task(const FfnArgs& a, int per_expert, int per_shared, int& group,
-                                         int& split, int& nsplit, Task& t, FfnArgs& v, int lane) {
-  int bx = blockIdx.x;
+// Which expert, which of its weight-row groups and which pairs a workgroup works on.  The grid is
+// one-dimensional and read in hand-out order: the shared expert first (every token: the longest
+// workgroups), then the live units of the routed experts as the permutation lists them - longest
+// expert first, an expert's units next to each other.  So when the workgroups do not all fit on
+// the chip at once the long ones start first, consecutive workgroups carry similar work, and the
+// grid's tail beyond the live units exits on one scalar load.
+//
+// The units of an expert read the same weights.  The hardware deals workgroups out to the eight
+// XCDs in turn, each with an L2 of its own: an expert's workgroups are numbered so that an XCD gets
+// a run of its row groups with all their units, which then stream those weights side by side, one
+// from memory and the others from that L2 (2048 tokens, 1024 on each of 16 experts of 2048 x 768:
+// gate/up 161 -> 122 us, the next form's 146 -> 105; with every unit's groups on one XCD instead,
+// which saves fetches of token rows, 162).  The weights of an expert with one unit are read once
+// on the chip and loaded non-temporally: kept in L2 and the last-level cache they displace the
+// token rows (128 tokens: 40.0 -> 44.2 us).
+struct LdsTask {
+  int group;        // weight-row group of the expert
+  int g0, rows;     // its pairs [g0, g0 + rows)
+  bool alone;       // no other workgroup reads these weights
+};
+__device__ __forceinline__ void unit_share(int i, int per, int nsplit, int& group, int& split) {
+  if (nsplit == 1) {  // (a run of row groups per XCD is no help here: 80 tokens, experts of 2048 x 512, down 13.4 -> 14.9 us)
+    group = i;
+    split = 0;
+    return;
+  }
+  // blocks of eight units: with all of an expert's side by side their token rows would not stay in an L2
+  const int block = i / (8 * per), m = min(8, nsplit - 8 * block);
+  i -= block * 8 * per;
+  const int n = m * per, j = i & 7;  // workgroup i of the block's n; those with the same j share an XCD
+  const int p = j * (n >> 3) + min(j, n & 7) + (i >> 3);
+  group = p / m;
+  split = 8 * block + p % m;
+}
+// EVEN: an expert's units have the same number of rows, so that they keep the same pace (else all but
+// the last have as many as a unit can: fewer tiles of 32 rows in all, which is what the tile kernels pay for).
+template <bool DOWN, bool EVEN>
+__device__ __forceinline__ bool lds_task(const FfnArgs& a, int per_expert, int per_shared, int max_rows, LdsTask& k,
+                                         Task& t, FfnArgs& v, int lane) {
+  int bx = blockIdx.x, split, nsplit;
   v = a;
   if (bx < per_shared * a.splits) {
     make_task(a, 0, true, DOWN, t, lane);
     v = shared_view(a, t, 2);
-    split = bx / per_shared;
     nsplit = a.splits;
-    group = bx % per_shared;
-    return true;
+    unit_share(bx, per_shared, nsplit, k.group, split);
+  } else {
+    bx -= per_shared * a.splits;
+    const int u = bx / per_expert;
+    if (u >= uniform_int(a.meta[2])) return false;
+    const int rec = uniform_int(a.units[u]);
+    nsplit = rec >> 24;
+    if ((rec & 0xffff) >= a.n_slots || nsplit < 1 || nsplit > kMaxSplits || ((rec >> 16) & 0xff) >= nsplit) return false;
+    unit_share(bx - (u - ((rec >> 16) & 0xff)) * per_expert, per_expert, nsplit, k.group, split);
+    if (!make_task(a, rec & 0xffff, false, DOWN, t, lane)) return false;
   }
-  bx -= per_shared * a.splits;
-  const int u = bx / per_expert;
-  if (u >= uniform_int(a.meta[2])) return false;
-  const int rec = uniform_int(a.units[u]);
-  if ((rec & 0xffff) >= a.n_slots || (rec >> 24) < 1 || (rec >> 24) > kMaxSplits) return false;
-  split = (rec >> 16) & 0xff;
-  nsplit = rec >> 24;
-  group = bx % per_expert;
-  return make_task(a, rec & 0xffff, false, DOWN, t, lane);
+  const int count = uniform_int(t.count);  // (scalars: they guard matrix instructions, see stream_pipeline)
+  const int share = EVEN ? min(max_rows, (count + nsplit - 1) / nsplit) : max_rows;
+  k.g0 = split * share;
+  k.rows = min(share, count - k.g0);
+  k.alone = nsplit == 1;
+  return k.rows > 0;
 }
 
-// MAXNT = token tiles per workgroup pass (the LDS buffer holds 16*MAXNT rows);
-// LW = wavefronts per workgroup; KD = the reduction length when the host knows
-// it to be one of the unrolled cases, else 0.  A split takes every splits-th group of
-// 16*MAXNT pairs of the expert: an expert with more pairs than one pass holds
-// is spread over several workgroups (its weights are then read once per pass).
-template <int MAXNT, int LW, int KD>
-__global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void gateup_lds_kernel(FfnArgs a) {
-  constexpr int kRows = 16 * MAXNT;
-  __shared__ __align__(16) uint16_t lds[lds_elems(KD)];
+// Calls f(token tiles, alone) with the number of 16-row token tiles that the code is built for
+// (even units of an expert with several have more than half of the rows they can have).
+template <int MAXNT, typename F>
+__device__ __forceinline__ void by_token_tiles(int rows, bool alone, F&& f) {
+  const int nt = (rows + 15) / 16;
+  if (MAXNT < 8 || alone) {
+    if (nt <= 1) f(std::integral_constant<int, 1>{}, std::true_type{});
+    else if (nt <= 2) f(std::integral_constant<int, 2>{}, std::true_type{});
+    else if (MAXNT < 8 || nt <= 4) f(std::integral_constant<int, 4>{}, std::true_type{});
+    else if constexpr (MAXNT >= 8) {
+      if (nt <= 6) f(std::integral_constant<int, 6>{}, std::true_type{});
+      else f(std::integral_constant<int, 8>{}, std::true_type{});
+    }
+  } else if constexpr (MAXNT >= 8) {
+    if (nt <= 6) f(std::integral_constant<int, 6>{}, std::false_type{});
+    else f(std::integral_constant<int, 8>{}, std::false_type{});
+  }
+}
+
+// MAXNT = token tiles of a unit at most (the LDS buffer holds 16*MAXNT rows); LW = wavefronts
+// per workgroup; KD = the reduction length when the host knows it to be one of the unrolled
+// cases, else 0; RT = weight tiles of a wavefront, for gate/up half of them gate and half up.
+template <int MAXNT, int LW, int KD, int RT>
+__global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4 || RT == 4) ? 2 : 1)) void gateup_lds_kernel(FfnArgs a) {
+  constexpr int HT = RT / 2;
+  __shared__ __align__(16) uint16_t lds[lds_elems(RT, KD)];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   Task t;
+  LdsTask k;
   FfnArgs v;
-  int group, split, splits;
-  const int per_r = (a.F / 16 + LW - 1) / LW;
-  const int per_s = (a.Fs / 16 + LW - 1) / LW;
+  const int per_r = (a.F / 16 + LW * HT - 1) / (LW * HT);
+  const int per_s = (a.Fs / 16 + LW * HT - 1) / (LW * HT);
   DES_FSTAMP(blockIdx.x, 0);
-  if (!lds_task<false>(a, per_r, per_s, group, split, splits, t, v, lane)) return;  // uniform per workgroup
-  const int tile = group * LW + wave;
-  const bool active = tile < t.fdim / 16;
-  const uint16_t* w0 = uniform_ptr(t.w0);
-  const uint16_t* gp = tile_base(w0, active ? tile : 0, a.D);
-  const uint16_t* up = tile_base(uniform_ptr(t.w1), active ? tile : 0, a.D);
+  if (!lds_task<false, true>(a, per_r, per_s, 16 * MAXNT, k, t, v, lane)) return;  // uniform per workgroup
+  const int tiles = t.fdim / 16, tile = (k.group * LW + wave) * HT;
+  const uint16_t* wp[RT];
+#pragma unroll
+  for (int i = 0; i < HT; ++i) {  // a tile past the matrix repeats the last one, dropped at the store
+    wp[i] = tile_base(uniform_ptr(t.w0), min(tile + i, tiles - 1), a.D);
+    wp[HT + i] = tile_base(uniform_ptr(t.w1), min(tile + i, tiles - 1), a.D);
+  }
   const uint32_t wlo = tile_lane_off(lane);
   const uint16_t* x = uniform_ptr(static_cast<const uint16_t*>(a.x));
-  uint16_t* h = static_cast<uint16_t*>(v.h);
-  const int count = uniform_int(t.count);  // guards matrix instructions (see stream_pipeline)
-  for (int g0 = split * kRows; g0 < count; g0 += splits * kRows) {
-    const int rows = min(kRows, count - g0);
-    const int nt = (rows + 15) / 16;
-    auto row_off = [&](int r) {
-      const int tok = t.shared ? g0 + r : a.pair_tok[t.pair0 + g0 + r];
-      return tok * a.D;
-    };
-    auto run = [&](auto ntc) {
-      constexpr int NT = decltype(ntc)::value;
-      f32x4 accg[NT], accu[NT];
+  auto row_off = [&](int r) {
+    const int tok = t.shared ? k.g0 + r : a.pair_tok[t.pair0 + k.g0 + r];
+    return tok * a.D;
+  };
+  by_token_tiles<MAXNT>(k.rows, k.alone, [&](auto ntc, auto alone) {
+    constexpr int NT = decltype(ntc)::value;
+    f32x4 acc[RT][NT];
 #pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        accg[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        accu[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int i = 0; i < NT; ++i) acc[r][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int KC = NT <= 4 && RT == 2 ? 128 : 64;  // rows * KC: at most one 16 KB buffer
+    dma_stream_gemm<RT, NT, (MAXNT < 8 || KC == 128 ? 64 : 128), LW, KC, KD, decltype(alone)::value>(
+        wp, wlo, wave, a.D, k.rows, x, row_off, lds, acc);
+    uint16_t* h = static_cast<uint16_t*>(v.h) + (t.row_base + k.g0) * t.fdim + 4 * (lane >> 4);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int r = i * 16 + (lane & 15);
+      if (r >= k.rows) continue;
+#pragma unroll
+      for (int f = 0; f < HT; ++f) {
+        if (tile + f >= tiles) continue;
+        u16x4 o;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = f32_to_bf16_bits(silu_f(acc[f][i][q]) * acc[HT + f][i][q]);
+        *reinterpret_cast<u16x4*>(h + static_cast<size_t>(r) * t.fdim + (tile + f) * 16) = o;
       }
-      constexpr int KC = NT <= 4 ? 128 : 64;  // rows * KC = one 16 KB buffer
-      dma_stream_gemm<NT, kLdsBufElems / KC, LW, KC, KD>(gp, up, wlo, wave, a.D, rows, x,
-                                                                 row_off, lds, accg, accu);
-      if (!active) return;
-#pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        const int pi = g0 + i * 16 + (lane & 15);
-        if (pi < count) {
-          u16x4 o;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) o[q] = f32_to_bf16_bits(silu_f(accg[i][q]) * accu[i][q]);
-          *reinterpret_cast<u16x4*>(h + (t.row_base + pi) * t.fdim + tile * 16 + 4 * (lane >> 4)) = o;
-        }
-      }
-    };
-    if (nt <= 1) run(std::integral_constant<int, 1>{});
-    else if (nt <= 2) run(std::integral_constant<int, 2>{});
-    else if (MAXNT <= 4 || nt <= 4) run(std::integral_constant<int, 4>{});
-    else if (nt <= 6) run(std::integral_constant<int, MAXNT >= 8 ? 6 : 4>{});
-    else run(std::integral_constant<int, MAXNT >= 8 ? 8 : 4>{});
-  }
+    }
+  });
 #ifdef DES_FFN_STAMPS
   DES_FSTAMP(blockIdx.x, 2);
   if (threadIdx.x == 0 && blockIdx.x < 8192) {  // pairs this workgroup worked on, where it ran
-    g_ffn_stamps[blockIdx.x * 4 + 3] = max(0, min(static_cast<int>(t.count) - split * kRows, kRows));
+    g_ffn_stamps[blockIdx.x * 4 + 3] = k.rows;
     g_ffn_stamps[blockIdx.x * 4 + 1] =
         (static_cast<long long>(__builtin_amdgcn_s_getreg(20 | (31 << 11))) << 32) |
         static_cast<unsigned>(__builtin_amdgcn_s_getreg(4 | (31 << 11)));
@@ -626,60 +666,45 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void g
 #endif
 }
 
-template <int MAXNT, int LW, int KD>
-__global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4) ? 2 : 1)) void down_lds_kernel(FfnArgs a) {
-  constexpr int kRows = 16 * MAXNT;
-  __shared__ __align__(16) uint16_t lds[lds_elems(KD)];
+template <int MAXNT, int LW, int KD, int RT>
+__global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4 || RT == 4) ? 2 : 1)) void down_lds_kernel(FfnArgs a) {
+  __shared__ __align__(16) uint16_t lds[lds_elems(RT, KD)];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   Task t;
+  LdsTask k;
   FfnArgs v;
-  int group, split, splits;
-  const int dtiles = a.D / 16;                       // even: D is a multiple of 32
-  const int per = (dtiles / 2 + LW - 1) / LW;        // a wavefront owns two row tiles
-  if (!lds_task<true>(a, per, a.Fs > 0 ? per : 0, group, split, splits, t, v, lane)) return;
-  const int dt0 = (group * LW + wave) * 2;
-  const bool active = dt0 < dtiles;
-  const int F = uniform_int(t.fdim), count = uniform_int(t.count);  // guard matrix instructions
-  const uint16_t* w0 = uniform_ptr(t.w0);
-  const uint16_t* p0 = tile_base(w0, active ? dt0 : 0, F);
-  const uint16_t* p1 = tile_base(w0, active ? dt0 + 1 : 0, F);
+  const int dtiles = a.D / 16, per = (dtiles + RT * LW - 1) / (RT * LW);
+  if (!lds_task<true, true>(a, per, a.Fs > 0 ? per : 0, 16 * MAXNT, k, t, v, lane)) return;
+  const int dt0 = (k.group * LW + wave) * RT;
+  const int F = uniform_int(t.fdim);  // guards matrix instructions
+  const uint16_t* wp[RT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) wp[r] = tile_base(uniform_ptr(t.w0), min(dt0 + r, dtiles - 1), F);
   const uint32_t wlo = tile_lane_off(lane);
-  const uint16_t* h = uniform_ptr(static_cast<const uint16_t*>(v.h));
-  const size_t orow0 = t.shared ? static_cast<size_t>(a.T) * a.K : static_cast<size_t>(t.pair0);
-  for (int g0 = split * kRows; g0 < count; g0 += splits * kRows) {
-    const int rows = min(kRows, count - g0);
-    const int nt = (rows + 15) / 16;
-    const int hrow0 = static_cast<int>(t.row_base) + g0;
-    auto row_off = [&](int r) { return (hrow0 + r) * F; };
-    auto run = [&](auto ntc) {
-      constexpr int NT = decltype(ntc)::value;
-      f32x4 acc0[NT], acc1[NT];
+  const uint16_t* h = uniform_ptr(static_cast<const uint16_t*>(v.h) + (t.row_base + k.g0) * F);
+  const size_t orow0 = (t.shared ? static_cast<size_t>(a.T) * a.K : static_cast<size_t>(t.pair0)) + k.g0;
+  auto row_off = [&](int r) { return r * F; };
+  by_token_tiles<MAXNT>(k.rows, k.alone, [&](auto ntc, auto alone) {
+    constexpr int NT = decltype(ntc)::value;
+    f32x4 acc[RT][NT];
 #pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        acc0[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        acc1[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-      constexpr int KC = NT <= 4 ? 128 : 64;
-      dma_stream_gemm<NT, kLdsBufElems / KC, LW, KC, KD>(p0, p1, wlo, wave, F, rows, h,
-                                                                 row_off, lds, acc0, acc1);
-      if (!active) return;
+    for (int r = 0; r < RT; ++r)
 #pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        const int pi = g0 + i * 16 + (lane & 15);
-        if (pi < count) {
-          float* dst = a.o + (orow0 + pi) * a.D + dt0 * 16 + 4 * (lane >> 4);
-          *reinterpret_cast<f32x4*>(dst) = acc0[i];
-          *reinterpret_cast<f32x4*>(dst + 16) = acc1[i];
-        }
-      }
-    };
-    if (nt <= 1) run(std::integral_constant<int, 1>{});
-    else if (nt <= 2) run(std::integral_constant<int, 2>{});
-    else if (MAXNT <= 4 || nt <= 4) run(std::integral_constant<int, 4>{});
-    else if (nt <= 6) run(std::integral_constant<int, MAXNT >= 8 ? 6 : 4>{});
-    else run(std::integral_constant<int, MAXNT >= 8 ? 8 : 4>{});
-  }
+      for (int i = 0; i < NT; ++i) acc[r][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int KC = NT <= 4 && RT == 2 ? 128 : 64;
+    dma_stream_gemm<RT, NT, (MAXNT < 8 || KC == 128 ? 64 : 128), LW, KC, KD, decltype(alone)::value>(
+        wp, wlo, wave, F, k.rows, h, row_off, lds, acc);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int r = i * 16 + (lane & 15);
+      if (r >= k.rows) continue;
+      float* dst = a.o + (orow0 + r) * a.D + dt0 * 16 + 4 * (lane >> 4);
+#pragma unroll
+      for (int q = 0; q < RT; ++q)
+        if (dt0 + q < dtiles) *reinterpret_cast<f32x4*>(dst + 16 * q) = acc[q][i];
+    }
+  });
 }
 
 // ------------------------------------------ many token rows: weights and tokens in LDS tiles
@@ -695,11 +720,10 @@ __global__ __launch_bounds__(kTileThreads, 2) void gateup_tile_kernel(FfnArgs a)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   Task t;
+  LdsTask k;
   FfnArgs v;
-  int group, split, splits;
-  if (!lds_task<false>(a, (a.F / 16 + MT - 1) / MT, (a.Fs / 16 + MT - 1) / MT, group, split, splits, t, v, lane))
-    return;
-  const int tiles = t.fdim / 16, f0 = group * MT;  // this workgroup's first 16 units
+  if (!lds_task<false, false>(a, (a.F / 16 + MT - 1) / MT, (a.Fs / 16 + MT - 1) / MT, kRows, k, t, v, lane)) return;
+  const int tiles = t.fdim / 16, f0 = k.group * MT;  // this workgroup's first 16 units
   const uint16_t* x = static_cast<const uint16_t*>(a.x);
   uint16_t* h = static_cast<uint16_t*>(v.h);
   // row tile q of the workgroup: wavefronts wm have gate tiles, then the up tiles of the same units
@@ -709,9 +733,8 @@ __global__ __launch_bounds__(kTileThreads, 2) void gateup_tile_kernel(FfnArgs a)
     const int q = 2 * i + (tid >> 7), ft = min(f0 + q / MT * HT + q % HT, tiles - 1);
     aptr[i] = tile_weight_ptr<PACKED>((q % MT < HT ? t.w0 : t.w1) + static_cast<size_t>(ft) * 16 * a.D, a.D, tid);
   }
-  const int count = uniform_int(t.count);
-  for (int g0 = split * kRows; g0 < count; g0 += splits * kRows) {
-    const int rows = min(kRows, count - g0);
+  const int g0 = k.g0, rows = k.rows;
+  {
     auto run = [&](auto ntc) {
       constexpr int NT = decltype(ntc)::value;
       const uint16_t* bptr[NT];
@@ -755,11 +778,11 @@ __global__ __launch_bounds__(kTileThreads, 2) void down_tile_kernel(FfnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   Task t;
+  LdsTask k;
   FfnArgs v;
-  int group, split, splits;
   const int tiles = a.D / 16, per = (tiles + 2 * MT - 1) / (2 * MT);
-  if (!lds_task<true>(a, per, a.Fs > 0 ? per : 0, group, split, splits, t, v, lane)) return;
-  const int F = uniform_int(t.fdim), d0 = group * 2 * MT;  // (see stream_pipeline)
+  if (!lds_task<true, false>(a, per, a.Fs > 0 ? per : 0, kRows, k, t, v, lane)) return;
+  const int F = uniform_int(t.fdim), d0 = k.group * 2 * MT;  // (see stream_pipeline)
   const uint16_t* h = static_cast<const uint16_t*>(v.h);
   const size_t orow0 = t.shared ? static_cast<size_t>(a.T) * a.K : static_cast<size_t>(t.pair0);
   const uint16_t* aptr[MT];
@@ -767,9 +790,8 @@ __global__ __launch_bounds__(kTileThreads, 2) void down_tile_kernel(FfnArgs a) {
   for (int i = 0; i < MT; ++i)
     aptr[i] = tile_weight_ptr<PACKED>(
         t.w0 + static_cast<size_t>(min(d0 + 2 * i + (tid >> 7), tiles - 1)) * 16 * F, F, tid);
-  const int count = uniform_int(t.count);
-  for (int g0 = split * kRows; g0 < count; g0 += splits * kRows) {
-    const int rows = min(kRows, count - g0);
+  const int g0 = k.g0, rows = k.rows;
+  {
     auto run = [&](auto ntc) {
       constexpr int NT = decltype(ntc)::value;
       const uint16_t* bptr[NT];
@@ -1096,12 +1118,12 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
   } while (0)
     if (a.T > 32) {
       // Longer blocks: units of 64 token rows while no expert can have more, else 128; an
-      // expert with more pairs is spread over up to kMaxSplits of them (the unit list).
+      // expert with more pairs has several of them (the unit list).
       //
-      // Two forms of each kernel.  Streamed (weights straight into operands, token rows
+      // Three forms of each kernel: with four weight tiles per wavefront (below), streamed, tiles.  Streamed (weights straight into operands, token rows
       // through LDS): packed weights whose reduction is one of the unrolled ones - or, with
       // fewer than 32 pairs per possible expert, any whole number of its chunks.  Tiles (both
-      // through LDS): everything else.  128 experts of 2048 x 768 under 256 tokens, gate/up +
+      // through LDS): everything else that is left.  128 experts of 2048 x 768 under 256 tokens, gate/up +
       // down: packed 68.3 + 40.0 us streamed, 77.6 + 43.6 in tiles; row-major (64 bytes of a row
       // per operand load) 99.9 + 54.8 and 81.3 + 45.0.  64 experts of 1536 x 1408, packed, not
       // unrolled: 16 pairs per expert 78.0 + 50.0 and 80.5 + 51.6, 32 pairs 111 + 64.9 and
@@ -1122,14 +1144,14 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
       const bool dn_stream = packed && a.F % kKC == 0 && a.Fs % kKC == 0 && (dn_kd > 0 || few);
 #define DES_LAUNCH_GU(MNT, LWV)                                                             \
   do {                                                                                      \
-    if (gu_kd == 2048) launch(kKGateUp, gateup_lds_kernel<MNT, LWV, 2048>, gg, dim3(LWV* kWave), 0, st, a); \
-    else launch(kKGateUp, gateup_lds_kernel<MNT, LWV, 0>, gg, dim3(LWV* kWave), 0, st, a);  \
+    if (gu_kd == 2048) launch(kKGateUp, gateup_lds_kernel<MNT, LWV, 2048, 2>, gg, dim3(LWV* kWave), 0, st, a); \
+    else launch(kKGateUp, gateup_lds_kernel<MNT, LWV, 0, 2>, gg, dim3(LWV* kWave), 0, st, a);  \
   } while (0)
 #define DES_LAUNCH_DN(MNT, LWV)                                                             \
   do {                                                                                      \
-    if (dn_kd == 768) launch(kKDown, down_lds_kernel<MNT, LWV, 768>, dg, dim3(LWV* kWave), 0, st, a); \
-    else if (dn_kd == 512) launch(kKDown, down_lds_kernel<MNT, LWV, 512>, dg, dim3(LWV* kWave), 0, st, a); \
-    else launch(kKDown, down_lds_kernel<MNT, LWV, 0>, dg, dim3(LWV* kWave), 0, st, a);      \
+    if (dn_kd == 768) launch(kKDown, down_lds_kernel<MNT, LWV, 768, 2>, dg, dim3(LWV* kWave), 0, st, a); \
+    else if (dn_kd == 512) launch(kKDown, down_lds_kernel<MNT, LWV, 512, 2>, dg, dim3(LWV* kWave), 0, st, a); \
+    else launch(kKDown, down_lds_kernel<MNT, LWV, 0, 2>, dg, dim3(LWV* kWave), 0, st, a);      \
   } while (0)
 #define DES_LAUNCH_TILE(id, kernel, g, MT, P)                                               \
   do {                                                                                      \
@@ -1156,7 +1178,24 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
       const int dn_wgs = (n_units + (a.Fs > 0 ? splits : 0)) * ((a.D + 127) / 128);
       const bool gu_two = gu_wgs < 256 || (!small && TK < 8 * a.n_slots);
       const int gu_mt = gu_two || gu_wgs < 448 ? 2 : 4, dn_mt = dn_wgs < 384 ? 2 : 4;
-      if (gu_stream) {
+      // Streamed with four weight tiles per wavefront instead of two, for packed weights and many
+      // pairs per expert: a token fragment from LDS meets twice the weights and the launch can
+      // reach the matrix cores' rate (16 experts of 2048 x 768, 1024 pairs each: gate/up 160 us in
+      // two tiles, 105; 16 of 4096 x 1408, 2048 tokens, k = 2: 176 in LDS tiles, 121; 64 sequences
+      // of 32 tokens on 128 experts: 204 and 168).  It has half as many wavefronts, each with
+      // half of the room for requested weights: from 120 pairs per possible expert on, where the
+      // reduction is not one of the unrolled ones and not short from 40 on (24 experts of 640 x 1152,
+      // 43 pairs: 15.3 against 17.8), and with fewer than 224 workgroups (for the most experts that
+      // can be live) never (32 experts of 1280 x 384, 64 pairs, 144 workgroups: 18.6 against 26.0).
+      auto four = [&](int kd, bool unrolled, int wgs) {
+        return packed && !small && kd % kKC == 0 && wgs >= 224 &&
+               (TK >= 120 * a.n_slots || (kd >= 1152 && !unrolled && TK >= 40 * a.n_slots));
+      };
+      const int gu_four_wgs = n_units * ((a.F + 127) / 128) + splits * ((a.Fs + 127) / 128);
+      const int dn_four_wgs = (n_units + (a.Fs > 0 ? splits : 0)) * ((a.D + 255) / 256);
+      if (four(a.D, gu_kd > 0, gu_four_wgs)) {
+        launch(kKGateUp, gateup_lds_kernel<8, 4, 0, 4>, dim3(gu_four_wgs), dim3(4 * kWave), 0, st, a);
+      } else if (gu_stream) {
         // Wavefronts per workgroup: two give the finest spread of the weight bytes over the
         // compute units; four share the staged activations among more weight rows, which
         // measured better once experts have many tokens (48-layer stack: 7.7 ms against
@@ -1172,7 +1211,9 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
         else if (gu_mt == 2) DES_LAUNCH_TILE(kKGateUp, gateup_tile_kernel, gg, 2, 1);
         else DES_LAUNCH_TILE(kKGateUp, gateup_tile_kernel, gg, 4, 1);
       }
-      if (dn_stream) {
+      if (a.Fs % kKC == 0 && four(a.F, dn_kd > 0, dn_four_wgs)) {
+        launch(kKDown, down_lds_kernel<8, 4, 0, 4>, dim3(dn_four_wgs), dim3(4 * kWave), 0, st, a);
+      } else if (dn_stream) {
         const int lw = a.T <= 64 ? 2 : 4;
         const int per = (a.D / 32 + lw - 1) / lw;
         const dim3 dg(n_units * per + (a.Fs > 0 ? splits * per : 0));

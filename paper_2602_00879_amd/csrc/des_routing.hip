@@ -844,7 +844,7 @@ __device__ void permute_all(const RoutingArgs& a, char* smem, bool idx_dev, int 
   // once, the long ones must not be the ones that start last.  Rank by counting,
   // the comparison range split over the threads that share an expert; the
   // partial ranks meet in an integer LDS add.  The same pass counts the units
-  // (groups of 2^rows_shift pairs, at most kMaxSplits per expert) of the experts
+  // (groups of up to 2^rows_shift pairs) of the experts
   // ahead: the expert's place in the unit list.
   const bool by_count = T > 32;
   const int rsh = a.rows_shift;

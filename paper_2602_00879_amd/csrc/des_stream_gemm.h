@@ -82,9 +82,8 @@ __device__ __forceinline__ void turn_fence() {
 // of registers for its prefetch (every token fragment is double-buffered in
 // registers).  For T > 32 the expert's activation rows go through LDS instead:
 //   * a workgroup of LW wavefronts works on LW weight-row groups of one expert;
-//     each wavefront streams its own two weight tiles from HBM straight into
-//     MFMA operands, three chunks of 128 reduction elements deep, so that two
-//     chunks (16 KB per wavefront) stay in flight across every barrier;
+//     each wavefront streams its own two or four weight tiles straight into
+//     MFMA operands, two chunks ahead, so that they stay in flight across every barrier;
 //   * the expert's token rows of the next chunk are gathered from L2 into LDS
 //     by direct global-to-LDS loads (no staging registers), double-buffered;
 //   * LDS rows are 256 B with the 16-byte pieces of row r stored at piece
@@ -108,14 +107,20 @@ constexpr int kKC = 128;            // reduction lengths must be multiples of th
 // up across the rotating stages and early exits of the chunk loop and waits for
 // everything at every use, which would drain the prefetch; so these loads and
 // their waits are explicit.)
-template <int OFF>
+// NT_HINT: a non-temporal load, for weights that one workgroup alone reads.
+template <int OFF, bool NT_HINT>
 __device__ __forceinline__ void ld8_async(bf16x8& v, const uint16_t* ubase, uint32_t lane_off) {
   // s_nop 4: the base may have just been written by a vector instruction (a
   // scalar register restored from a spill lane); a vector-memory instruction
   // needs five wait states after that, and the compiler adds none inside asm.
-  asm volatile("s_nop 4\n\tglobal_load_dwordx4 %0, %1, %2 offset:%3 nt"
-               : "=v"(v)
-               : "v"(lane_off), "s"(ubase), "n"(OFF));
+  if constexpr (NT_HINT)
+    asm volatile("s_nop 4\n\tglobal_load_dwordx4 %0, %1, %2 offset:%3 nt"
+                 : "=v"(v)
+                 : "v"(lane_off), "s"(ubase), "n"(OFF));
+  else
+    asm volatile("s_nop 4\n\tglobal_load_dwordx4 %0, %1, %2 offset:%3"
+                 : "=v"(v)
+                 : "v"(lane_off), "s"(ubase), "n"(OFF));
 }
 // A pointer the compiler may keep in scalar registers (the value is the same in all lanes).
 template <typename T>
@@ -132,16 +137,16 @@ __device__ __forceinline__ const uint16_t* tile_base(const uint16_t* base, int r
 __device__ __forceinline__ uint32_t tile_lane_off(int lane) { return lane * 16u; }
 // Waits until at most N vector-memory operations are outstanding and makes the
 // fragments of a stage depend on that wait.
-template <int N>
-__device__ __forceinline__ void wait_weights(bf16x8 (&a)[4], bf16x8 (&b)[4]) {
-  asm volatile("s_waitcnt vmcnt(%8)"
-               : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]),
-                 "+v"(b[3])
-               : "n"(N));
-}
-template <int N>
-__device__ __forceinline__ void wait_weights(bf16x8 (&a)[2], bf16x8 (&b)[2]) {
-  asm volatile("s_waitcnt vmcnt(%4)" : "+v"(a[0]), "+v"(a[1]), "+v"(b[0]), "+v"(b[1]) : "n"(N));
+template <int N, int KS, int RT>
+__device__ __forceinline__ void wait_weights(bf16x8 (&a)[KS][RT]) {
+  static_assert(RT * KS == 4 || RT * KS == 8, "fragments of a stage");
+  bf16x8* p = &a[0][0];
+  if constexpr (RT * KS == 8)
+    asm volatile("s_waitcnt vmcnt(%8)"
+                 : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]), "+v"(p[4]), "+v"(p[5]), "+v"(p[6]), "+v"(p[7])
+                 : "n"(N));
+  else
+    asm volatile("s_waitcnt vmcnt(%4)" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]) : "n"(N));
 }
 
 template <int... I, typename F>
@@ -149,14 +154,13 @@ __device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F&&
   (f(std::integral_constant<int, I>{}), ...);
 }
 
-// acc0/acc1 += A0/A1 (this wavefront's two 16-row weight tiles, reduction
-// length kd) x token rows.  KC = reduction elements per chunk (128 or 64), KD =
-// the reduction length if known at compile time (then kd == KD), else 0; kd is a
-// multiple of KC.  Row r of the pass (r < 16*NT) is `base + row_off(min(r,
-// rows_valid-1))`.  `lds` is the workgroup's buffer of NB * ROWS * 2*KC bytes
-// (ROWS >= 16*NT), NB = 3 if KD > 0, else 2.  All LW wavefronts of the workgroup call it together;
-// a0, a1, base and `wave` are wavefront-uniform; w_lane_off is the lane's byte
-// offset inside a weight fragment.
+// acc[r] += A[r] (this wavefront's RT 16-row weight tiles, reduction length kd) x token rows.
+// KC = reduction elements per chunk (128 or 64), KD = the reduction length if known at compile
+// time (then kd == KD), else 0; kd is a multiple of KC, of 2 KC with RT = 4.  Row r of the pass
+// (r < 16*NT) is `base + row_off(min(r, rows_valid-1))`.  `lds` is the workgroup's buffer of
+// NB * ROWS * 2*KC bytes (ROWS >= 16*NT), NB = 2 if RT = 2 and KD = 0, else 3.  All LW wavefronts
+// of the workgroup call it together; a[], base and `wave` are wavefront-uniform; w_lane_off is
+// the lane's byte offset inside a weight fragment.  NT_HINT: see ld8_async.
 //
 // LDS rows hold one chunk of a token row (2*KC bytes) with the 16-byte piece p
 // of row r stored at piece index p ^ swz(r), swz(r) = r & 15 for 256-byte rows,
@@ -164,16 +168,14 @@ __device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F&&
 // into 16 different bank groups.  A direct load writes lane l at base + 16*l,
 // so the swizzle is applied on the global side (which piece a lane fetches).
 //
-// A wavefront without a tile of its own (row tiles not a multiple of LW) runs
-// on tile 0 and drops its result.
-template <int NT, int ROWS, int LW, int KC, int KD, typename RowOff>
-__device__ __forceinline__ void dma_stream_gemm(const uint16_t* a0, const uint16_t* a1,
-                                                uint32_t w_lane_off, int wave, int kd,
-                                                int rows_valid, const uint16_t* base,
-                                                RowOff row_off, uint16_t* lds,
-                                                f32x4 (&acc0)[NT], f32x4 (&acc1)[NT]) {
+// A tile past the matrix repeats another (the caller drops its result).
+template <int RT, int NT, int ROWS, int LW, int KC, int KD, bool NT_HINT, typename RowOff>
+__device__ __forceinline__ void dma_stream_gemm(const uint16_t* const (&a)[RT], uint32_t w_lane_off, int wave,
+                                                int kd, int rows_valid, const uint16_t* base, RowOff row_off,
+                                                uint16_t* lds, f32x4 (&acc)[RT][NT]) {
   static_assert(KC == 128 || KC == 64, "chunk of 4 or 2 k-steps");
   static_assert(KD % KC == 0, "reduction length must be whole chunks");
+  static_assert(RT == 2 || (RT == 4 && KC == 64 && KD == 0), "forms below");
   const int lane = threadIdx.x & 63;
   const int nchunks = kd / KC;
   constexpr int NCH = KD / KC;
@@ -186,7 +188,7 @@ __device__ __forceinline__ void dma_stream_gemm(const uint16_t* a0, const uint16
                                      // so that the wait counts below hold for all of them; one
                                      // without a group of its own repeats the last group
                                      // (same bytes to the same place)
-  constexpr int NW = 2 * KS;         // weight loads per wavefront and chunk
+  constexpr int NW = RT * KS;        // weight loads per wavefront and chunk
   constexpr int kBufBytes = ROWS * RB;
   constexpr int kTile = 16 * RB;     // bytes of one token tile in a buffer
   constexpr int kFragBytes = frag_step<true>() * 2;  // between k-steps of a weight tile
@@ -203,12 +205,11 @@ __device__ __forceinline__ void dma_stream_gemm(const uint16_t* a0, const uint16
   // (asm, not the builtin: after the builtin the compiler waits for all
   // outstanding loads as soon as an address register is reused)
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<size_t>(DES_LDS_PTR(lds)));
-  auto dma = [&](int chunk, auto bufc) {
-    constexpr int bs = decltype(bufc)::value;
+  auto dma = [&](int chunk, uint32_t buf) {  // buf: byte offset of the buffer, uniform
     const uint16_t* g = base + chunk * KC;  // uniform
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
-      const uint32_t dst = lds0 + bs * kBufBytes + min(i * LW + wave, NG - 1) * 1024;  // uniform
+      const uint32_t dst = lds0 + buf + min(i * LW + wave, NG - 1) * 1024;  // uniform
       const uint32_t o = off[i];
       // Wait states the compiler would insert for its own instructions but does
       // not for asm: one between the write of M0 and the load, five between a
@@ -219,21 +220,16 @@ __device__ __forceinline__ void dma_stream_gemm(const uint16_t* a0, const uint16
                    : "m0");
     }
   };
-  bf16x8 aw0[KD > 0 ? 3 : 2][KS], aw1[KD > 0 ? 3 : 2][KS];
+  bf16x8 aw[KD > 0 ? 3 : 2][KS][RT];
+  auto loadw1 = [&](int chunk, auto stage, auto uc) {  // the fragments of k-step u of a chunk
+    constexpr int s = decltype(stage)::value, u = decltype(uc)::value;
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+      ld8_async<u * kFragBytes, NT_HINT>(aw[s][u][r], a[r] + static_cast<size_t>(chunk) * KS * frag_step<true>(),
+                                         w_lane_off);
+  };
   auto loadw = [&](int chunk, auto stage) {
-    constexpr int s = decltype(stage)::value;
-    const uint16_t* q0 = a0 + static_cast<size_t>(chunk) * KS * frag_step<true>();
-    const uint16_t* q1 = a1 + static_cast<size_t>(chunk) * KS * frag_step<true>();
-    ld8_async<0 * kFragBytes>(aw0[s][0], q0, w_lane_off);
-    ld8_async<0 * kFragBytes>(aw1[s][0], q1, w_lane_off);
-    ld8_async<1 * kFragBytes>(aw0[s][1], q0, w_lane_off);
-    ld8_async<1 * kFragBytes>(aw1[s][1], q1, w_lane_off);
-    if constexpr (KS == 4) {
-      ld8_async<2 * kFragBytes>(aw0[s][2], q0, w_lane_off);
-      ld8_async<2 * kFragBytes>(aw1[s][2], q1, w_lane_off);
-      ld8_async<3 * kFragBytes>(aw0[s][3], q0, w_lane_off);
-      ld8_async<3 * kFragBytes>(aw1[s][3], q1, w_lane_off);
-    }
+    static_for(std::make_integer_sequence<int, KS>{}, [&](auto uc) { loadw1(chunk, stage, uc); });
   };
   // byte offset in a buffer of this lane's fragment of token tile 0, k-step u of a chunk
   uint32_t fa[KS];
@@ -241,17 +237,17 @@ __device__ __forceinline__ void dma_stream_gemm(const uint16_t* a0, const uint16
   for (int u = 0; u < KS; ++u) fa[u] = (lane & 15) * RB + (((u * 4 + (lane >> 4)) ^ swz(lane & 15)) << 4);
   typedef __attribute__((address_space(3))) const volatile bf16x8 LdsFrag;
   const auto lds_base = reinterpret_cast<__attribute__((address_space(3))) const volatile char*>(DES_LDS_PTR(lds));
-  auto compute = [&](auto bufc, auto stage) {
-    constexpr int bs = decltype(bufc)::value;
+  // multiplies the chunk in buffer `buf` with the weights of a stage; done(u): k-step u's weights are free
+  auto compute = [&](uint32_t buf, auto stage, auto&& done) {
     constexpr int s = decltype(stage)::value;
-    constexpr int G = NT > 4 ? NT / 2 : NT;  // token tiles fetched from LDS at a time
+    constexpr int G = NT <= 4 ? NT : RT == 4 ? 2 : NT / 2;  // token tiles fetched from LDS at a time
     constexpr int NGR = NT / G, STEPS = KS * NGR;
     bf16x8 b[2][G];
     auto fetch = [&](auto stepc) {
       constexpr int st = decltype(stepc)::value, u = st / NGR, g = st % NGR * G;
 #pragma unroll
       for (int i = 0; i < G; ++i)
-        b[st & 1][i] = *reinterpret_cast<LdsFrag*>(lds_base + fa[u] + bs * kBufBytes + (g + i) * kTile);
+        b[st & 1][i] = *reinterpret_cast<LdsFrag*>(lds_base + (fa[u] + buf) + (g + i) * kTile);
     };
     fetch(S0{});
     static_for(std::make_integer_sequence<int, STEPS>{}, [&](auto stepc) {
@@ -259,14 +255,17 @@ __device__ __forceinline__ void dma_stream_gemm(const uint16_t* a0, const uint16
       if constexpr (st + 1 < STEPS) fetch(std::integral_constant<int, st + 1>{});
       __builtin_amdgcn_sched_barrier(0);  // (the next fragments are requested before these multiplies)
 #pragma unroll
-      for (int i = 0; i < G; ++i) {
-        acc0[g + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw0[s][u], b[st & 1][i], acc0[g + i], 0, 0, 0);
-        acc1[g + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw1[s][u], b[st & 1][i], acc1[g + i], 0, 0, 0);
-      }
+      for (int i = 0; i < G; ++i)
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+          acc[r][g + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[s][u][r], b[st & 1][i], acc[r][g + i], 0, 0, 0);
+      if constexpr (g + G == NT) done(std::integral_constant<int, u>{});
     });
     // every read of this buffer has come back before the next barrier lets it be overwritten
     asm volatile("s_waitcnt lgkmcnt(0)");
   };
+  const auto nothing = [](auto) {};
+  static_assert(ND + NW <= 63, "wait count must fit the counter");
   if constexpr (KD > 0) {
     // Reduction length known at compile time, three LDS buffers: straight-line
     // code, activations and weights both two chunks ahead.  Issue order of
@@ -277,26 +276,53 @@ __device__ __forceinline__ void dma_stream_gemm(const uint16_t* a0, const uint16
     // step c means A(c) and W(c) have landed while chunk c+1 is still in flight.
     // A(c+2) overwrites the buffer chunk c-1 was read from; the barrier of step
     // c comes after everybody's reads of it.
-    static_assert(ND + NW <= 63, "wait count must fit the counter");
-    dma(0, S0{});
+    dma(0, 0);
     loadw(0, S0{});
     if constexpr (NCH > 1) {
-      dma(1, S1{});
+      dma(1, kBufBytes);
       loadw(1, S1{});
     }
     static_for(std::make_integer_sequence<int, NCH>{}, [&](auto cc) {
       constexpr int c = decltype(cc)::value;
       typedef std::integral_constant<int, c % 3> Cur;
       typedef std::integral_constant<int, (c + 2) % 3> Nxt;
-      if constexpr (c + 1 < NCH) wait_weights<ND + NW>(aw0[c % 3], aw1[c % 3]);
-      else wait_weights<0>(aw0[c % 3], aw1[c % 3]);
+      wait_weights<(c + 1 < NCH) ? ND + NW : 0>(aw[c % 3]);
       __builtin_amdgcn_s_barrier();
       if constexpr (c + 2 < NCH) {
-        dma(c + 2, Nxt{});
+        dma(c + 2, Nxt::value * kBufBytes);
         loadw(c + 2, Nxt{});
       }
-      compute(Cur{}, Cur{});
+      compute(Cur::value * kBufBytes, Cur{}, nothing);
     });
+  } else if constexpr (RT == 4) {
+    // Any even number of chunks, in the order above, but the weights have two stages only (the
+    // accumulators take half of the registers): a k-step's fragments are requested for two
+    // chunks later as soon as they have been multiplied.
+    uint32_t cur = 0;  // the current chunk's buffer
+    auto step = [&](int c, auto stage, auto more, auto last) {  // more: chunk c + 2 exists
+      constexpr int s = decltype(stage)::value;
+      wait_weights<last ? 0 : ND + NW>(aw[s]);
+      __builtin_amdgcn_s_barrier();
+      if constexpr (more) dma(c + 2, cur >= kBufBytes ? cur - kBufBytes : 2 * kBufBytes);
+      compute(cur, stage, [&](auto uc) {
+        if constexpr (more) {
+          __builtin_amdgcn_sched_barrier(0);
+          loadw1(c + 2, stage, uc);
+        }
+      });
+      cur = cur == 2 * kBufBytes ? 0 : cur + kBufBytes;
+    };
+    dma(0, 0);
+    loadw(0, S0{});
+    dma(1, kBufBytes);
+    loadw(1, S1{});
+    int c = 0;
+    for (; c + 2 < nchunks; c += 2) {
+      step(c, S0{}, std::true_type{}, std::false_type{});
+      step(c + 1, S1{}, std::true_type{}, std::false_type{});
+    }
+    step(c, S0{}, std::false_type{}, std::false_type{});
+    step(c + 1, S1{}, std::false_type{}, std::true_type{});
   } else {
     // Any reduction length: two stages.  Step c: everything this wavefront asked
     // for (its share of the activations of chunk c, its weights of chunk c) has
@@ -305,30 +331,29 @@ __device__ __forceinline__ void dma_stream_gemm(const uint16_t* a0, const uint16
     // c+1 overwrite while chunk c is multiplied.
     auto step = [&](int c, auto bufc, auto nextbuf) {
       constexpr int s = decltype(bufc)::value;
-      wait_weights<0>(aw0[s], aw1[s]);
+      wait_weights<0>(aw[s]);
       __builtin_amdgcn_s_barrier();
       if (c + 1 < nchunks) {
-        dma(c + 1, nextbuf);
+        dma(c + 1, decltype(nextbuf)::value * kBufBytes);
         loadw(c + 1, nextbuf);
       }
-      compute(bufc, bufc);
+      compute(s * kBufBytes, bufc, nothing);
     };
-    dma(0, S0{});
+    dma(0, 0);
     loadw(0, S0{});
     for (int c = 0; c < nchunks; c += 2) {
       step(c, S0{}, S1{});
       if (c + 1 >= nchunks) break;
       step(c + 1, S1{}, S0{});
     }
+    asm volatile("s_waitcnt vmcnt(0)");  // (nothing is outstanding: the last step waited for everything)
   }
-  __builtin_amdgcn_s_barrier();  // nobody still reads a buffer the next pass refills
 }
 
 // Every pass works in buffers of 16 KB: up to 64 token rows with chunks of 128
-// reduction elements, or up to 128 rows with chunks of 64.  Three buffers when
-// the reduction length is a compile-time constant (48 KB: three workgroups per
-// compute unit), else two.
+// reduction elements, or up to 128 rows with chunks of 64.  Three buffers (48 KB) where
+// chunks are requested two ahead, else two.
 constexpr int kLdsBufElems = 8192;
-__host__ __device__ constexpr int lds_elems(int kd) { return (kd > 0 ? 3 : 2) * kLdsBufElems; }
+__host__ __device__ constexpr int lds_elems(int rt, int kd) { return (rt > 2 || kd > 0 ? 3 : 2) * kLdsBufElems; }
 
 }  // namespace des

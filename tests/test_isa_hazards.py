@@ -215,3 +215,12 @@ def test_the_mask_scan_flags_the_pattern():
     seen, bad = _masked_matrix_instructions(kernel % "")
     assert seen == 2 and len(bad) == 1
     assert _masked_matrix_instructions(kernel % "\ts_cbranch_execz .LBB0_2\n") == (2, [])
+
+
+def test_loads_without_the_non_temporal_hint_are_waited_for_as_well(ffn_asm):
+    """The same scan over the hand-written loads of weights that several workgroups read: it knows
+    such loads by their hint, so they get one here."""
+    hinted, n = re.subn(r"(\ts_nop 4\n\tglobal_load_dwordx4 v\[\d+:\d+\], v\d+, s\[\d+:\d+\](?: offset:\d+)?)[ \t]*(?=\n)",
+                        r"\1 nt", ffn_asm)
+    assert n > 40
+    test_no_read_of_an_asynchronously_loaded_register_before_its_wait(hinted)
