@@ -716,7 +716,7 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4 || RT == 4) ? 2 :
 template <bool PACKED, int MAXNT, int MT, int P>
 __global__ __launch_bounds__(kTileThreads, 2) void gateup_tile_kernel(FfnArgs a) {
   constexpr int HT = MT / 2, kRows = 32 * MAXNT;
-  __shared__ __align__(16) char lds[tile_lds_bytes<MT, MAXNT, 1>()];
+  __shared__ __align__(16) char lds[tile_lds_bytes<MT, MAXNT>()];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   Task t;
@@ -748,7 +748,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void gateup_tile_kernel(FfnArgs a)
       for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-      tile_gemm<MT, NT, 1, (NT <= 2 ? P : 1), PACKED>(aptr, bptr, a.D, lds, acc);
+      tile_gemm<MT, NT, (NT <= 2 ? P : 1), PACKED>(aptr, bptr, a.D, lds, acc);
 #pragma unroll
       for (int j = 0; j < NT; ++j) {
         const int r = (wn * NT + j) * 16 + (lane & 15);
@@ -774,7 +774,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void gateup_tile_kernel(FfnArgs a)
 template <bool PACKED, int MAXNT, int MT, int P>
 __global__ __launch_bounds__(kTileThreads, 2) void down_tile_kernel(FfnArgs a) {
   constexpr int kRows = 32 * MAXNT;
-  __shared__ __align__(16) char lds[tile_lds_bytes<MT, MAXNT, 1>()];
+  __shared__ __align__(16) char lds[tile_lds_bytes<MT, MAXNT>()];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   Task t;
@@ -803,7 +803,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void down_tile_kernel(FfnArgs a) {
       for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-      tile_gemm<MT, NT, 1, (NT <= 2 ? P : 1), PACKED>(aptr, bptr, F, lds, acc);
+      tile_gemm<MT, NT, (NT <= 2 ? P : 1), PACKED>(aptr, bptr, F, lds, acc);
 #pragma unroll
       for (int j = 0; j < NT; ++j) {
         const int r = (wn * NT + j) * 16 + (lane & 15);

@@ -224,3 +224,10 @@ def test_loads_without_the_non_temporal_hint_are_waited_for_as_well(ffn_asm):
                         r"\1 nt", ffn_asm)
     assert n > 40
     test_no_read_of_an_asynchronously_loaded_register_before_its_wait(hinted)
+
+
+def test_direct_lds_loads_of_the_attention_projections():
+    """The two wait-state rules of the direct loads, for the file whose tiles load both operands so."""
+    asm = _asm("des_attention.hip")
+    test_no_vector_written_scalar_base_too_close_to_a_load(asm.replace("linear_tile_kernel", "linear_lds_kernel"))
+    test_m0_write_is_one_wait_state_before_direct_lds_load(asm)
