@@ -1108,6 +1108,69 @@ __global__ __launch_bounds__(kRtThreads) void routing_kernel(RoutingArgs a) {
     for (int i = threadIdx.x; i < n_flags; i += kRtThreads) a.flags[i] = 0ull;
 }
 
+// The router as a launch of its own (des_route, and batches whose routing does not fit one launch):
+// a workgroup has ET x TT of the 16 x 16 tiles of router_tile_bf16, each summed up in the same order.
+template <int ET, int TT>
+__global__ __launch_bounds__(kRtThreads, 8) void router_kernel(RoutingArgs a) {
+  constexpr int U = ET * TT == 1 ? 4 : 2;  // k-steps per trip; two workgroups share a compute unit
+  __shared__ __align__(16) float part[kRtWaves * ET * TT * 256];
+  const int lane = threadIdx.x & 63;
+  const int wave = uniform_int(threadIdx.x >> 6);  // (it guards matrix instructions, see stream_pipeline)
+  const int T = a.B * a.N, D = a.D, M = a.M, nks = D / 32;
+  const int groups = (a.tiles_m + ET - 1) / ET;
+  const int i0 = blockIdx.x % groups * 16 * ET, t0 = blockIdx.x / groups * 16 * TT;
+  const int r = lane & 15, kq = (lane >> 4) * 8;
+  const uint16_t *ap[ET], *bp[TT];  // clamped rows are computed and dropped
+#pragma unroll
+  for (int e = 0; e < ET; ++e)
+    ap[e] = static_cast<const uint16_t*>(a.w_router) + static_cast<size_t>(min(i0 + 16 * e + r, M - 1)) * D + kq;
+#pragma unroll
+  for (int t = 0; t < TT; ++t)
+    bp[t] = static_cast<const uint16_t*>(a.x) + static_cast<size_t>(min(t0 + 16 * t + r, T - 1)) * D + kq;
+  // the element that this thread will finish
+  const int tile = threadIdx.x >> 8, er = threadIdx.x & 15, tc = (threadIdx.x >> 4) & 15;
+  const int ef = i0 + 16 * (tile / TT) + er, tf = t0 + 16 * (tile % TT) + tc;
+  const bool mine = tile < ET * TT && ef < M && tf < T;
+  const float bias = mine && a.bias ? a.bias[ef] : 0.f;
+  f32x4 acc[ET][TT];
+#pragma unroll
+  for (int e = 0; e < ET; ++e)
+#pragma unroll
+    for (int t = 0; t < TT; ++t) acc[e][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int ks = wave; ks < nks; ks += U * kRtWaves) {
+    bf16x8 av[U][ET], bv[U][TT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = min(ks + u * kRtWaves, nks - 1) * 32;  // clamped steps are skipped below
+#pragma unroll
+      for (int e = 0; e < ET; ++e) av[u][e] = *reinterpret_cast<const bf16x8*>(ap[e] + k);
+#pragma unroll
+      for (int t = 0; t < TT; ++t) bv[u][t] = *reinterpret_cast<const bf16x8*>(bp[t] + k);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (ks + u * kRtWaves < nks)
+#pragma unroll
+        for (int e = 0; e < ET; ++e)
+#pragma unroll
+          for (int t = 0; t < TT; ++t)
+            acc[e][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u][e], bv[u][t], acc[e][t], 0, 0, 0);
+  }
+#pragma unroll
+  for (int e = 0; e < ET; ++e)
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        part[(wave * ET * TT + e * TT + t) * 256 + (4 * (lane >> 4) + q) * 16 + r] = acc[e][t][q];
+  __syncthreads();
+  if (!mine) return;
+  float s = 0.f;
+#pragma unroll
+  for (int w = 0; w < kRtWaves; ++w) s += part[(w * ET * TT + tile) * 256 + er * 16 + tc];  // fixed order
+  a.logits[static_cast<size_t>(tf) * M + ef] = s + bias;
+}
+
 // probs[t][:] = router weights of token t (softmax of its logits, or their
 // sigmoids); one wavefront per token (des_route only).
 __global__ __launch_bounds__(64) void softmax_kernel(const float* __restrict__ logits,
@@ -1198,13 +1261,31 @@ bool dense_block(const des_shape_t& s) {
   return s.n_tokens <= selector_tokens_per_pass(s.n_experts) && n_tiles + 1 <= fused_limit;
 }
 
+static int launch_router_tiles(const RoutingArgs& a, hipStream_t st) {
+  const int tiles = a.tiles_m * a.tiles_t;
+  if (!a.bf16) return launch_routing_grid(a, tiles, kKRouter, st);
+  const dim3 b(kRtThreads);
+  // Four tiles per workgroup read half as much per tile, where one tile each makes more than one
+  // round of the chip.  128 experts of width 2048: 384 tiles 9.5 us in ones, 11.5 in fours (which
+  // take a second trip through the reduction there), 544 13.2 and 11.4, 1024 17.3 and 11.4; 96 of
+  // width 768: 192 tiles 5.9 and 7.1, 288 8.8 and 6.8; 64 of width 3072: 256 10.6 and 14.3, 384 16.6
+  // and 14.3.  (As a role of the routing kernel, with its registers, 1024 tiles took 20.4.)
+  const bool wide = tiles > 512 || (tiles > 256 && (a.D <= 1024 || a.D > 2048));
+  if (wide)
+    launch(kKRouter, router_kernel<2, 2>, dim3((a.tiles_m + 1) / 2 * ((a.tiles_t + 1) / 2)), b, 0, st, a);
+  else
+    launch(kKRouter, router_kernel<1, 1>, dim3(tiles), b, 0, st, a);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? DES_OK : hip_fail(e, "router launch");
+}
+
 int launch_router(const des_shape_t& s, const void* x, const void* w_router, const float* bias,
                   float* logits, hipStream_t st) {
   RoutingArgs a;
   fill_common(a, s);
   a.x = x; a.w_router = w_router; a.bias = bias; a.logits = logits;
   a.do_router = 1;
-  return launch_routing_grid(a, a.tiles_m * a.tiles_t, kKRouter, st);
+  return launch_router_tiles(a, st);
 }
 
 int launch_softmax(const des_shape_t& s, const float* logits, float* probs, hipStream_t st) {
@@ -1281,7 +1362,7 @@ int launch_routing(const des_shape_t& s, const void* x, const void* w_router, co
   // too large to wait inside one launch: the same roles as three launches
   RoutingArgs r = a;
   r.do_router = 1;
-  int rc = launch_routing_grid(r, n_tiles, kKRouter, st);
+  int rc = launch_router_tiles(r, st);
   if (rc != DES_OK) return rc;
   RoutingArgs sel = a;
   sel.do_select = 1;

@@ -1,0 +1,32 @@
+"""The router as a launch of its own: four tiles per workgroup (large batches) against one, on the same
+tokens in smaller calls, bit for bit, and against float64.  Expert and token tiles that do not fill a
+workgroup, reductions shorter than a workgroup's wavefronts and with a remainder."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_00879_amd import binding as B
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,D,T,part", [(136, 96, 1073, 100), (256, 2048, 530, 131), (24, 3104, 2200, 550), (16, 32, 4096, 4000)])
+def test_router_tiles(M, D, T, part):
+    print(f"router {M} {D} {T}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    x = torch.randn((1, T, D), generator=g, device="cuda").bfloat16()
+    w = (torch.randn((M, D), generator=g, device="cuda") * 0.02).bfloat16()
+    bias = torch.randn(M, generator=g, device="cuda")
+
+    def route(rows):
+        shape = B.make_shape(1, rows.shape[1], D, M, 32, 1, M, "vanilla", "bf16")
+        return B.des_route(shape, rows.contiguous(), w, bias)
+
+    logits, probs = route(x)
+    for t in range(0, T, part):
+        l, p = route(x[:, t:t + part])
+        assert torch.equal(l, logits[:, t:t + part]) and torch.equal(p, probs[:, t:t + part])
+    ref = x[0].double().cpu().numpy() @ w.double().cpu().numpy().T + bias.double().cpu().numpy()
+    assert np.abs(logits[0].cpu().numpy() - ref).max() <= H.LOGIT_ATOL
