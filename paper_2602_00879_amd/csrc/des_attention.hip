@@ -33,15 +33,15 @@ struct LinearArgs {
 };
 
 // out[m][t][f] = sum_d in[t][d] * w[m][f][d] for blocks of more than 32 token rows, in tiles
-// of 32 MT weight rows x 32 NT token rows (tile_gemm_dma).  KW = 2: the two halves of the
+// of 32 MT weight rows x 32 NT token rows (tile_gemm_dma, with NB buffers; NB = 0: tile_gemm).  KW = 2: the two halves of the
 // reduction dimension go to the two halves of the workgroup and meet in LDS, first half +
 // second half.
 // Consecutive workgroups go to the eight XCDs in turn: the grid is walked so that one XCD
 // has all the token tiles of a weight tile (its L2 then reads those weights once).
 template <int MT, int NT, int KW, int NB>
-__global__ __launch_bounds__(256 * KW, 1) void linear_tile_kernel(LinearArgs a) {
+__global__ __launch_bounds__(256 * KW, NB == 0 ? 2 : 1) void linear_tile_kernel(LinearArgs a) {
   constexpr int BM = 32 * MT, BN = 32 * NT;
-  __shared__ __align__(16) char lds[tile_dma_lds_bytes<MT, NT, KW, NB>()];
+  __shared__ __align__(16) char lds[NB == 0 ? tile_lds_bytes<MT, NT>() : tile_dma_lds_bytes<MT, NT, KW, NB>()];
   const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
   const int part = KW > 1 ? threadIdx.x >> 8 : 0;
   const int wm = wave >> 1, wn = wave & 1;
@@ -57,21 +57,34 @@ __global__ __launch_bounds__(256 * KW, 1) void linear_tile_kernel(LinearArgs a) 
   }
   if (m >= a.n_mats) return;  // (the grid is rounded up to whole rounds of the XCDs)
   const int fout = a.fout[m], Din = a.Din, f0 = mb * BM;
-  uint32_t aoff[MT], boff[NT];
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-    aoff[i] = static_cast<uint32_t>(min(i * 32 + (tid >> 3), fout - 1 - f0)) * Din * 2u + tile_piece(tid) * 16u;
-#pragma unroll
-  for (int i = 0; i < NT; ++i)
-    boff[i] = static_cast<uint32_t>(min(i * 32 + (tid >> 3), a.T - 1 - g0)) * Din * 2u + tile_piece(tid) * 16u;
-  const uint16_t* abase = uniform_ptr(a.w[m] + static_cast<size_t>(f0) * Din + k0);
-  const uint16_t* bbase = uniform_ptr(a.in + static_cast<size_t>(g0) * Din + k0);
   f32x4 acc[MT][NT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  tile_gemm_dma<MT, NT, KW, NB>(abase, bbase, aoff, boff, kd, lds, acc);
+  if constexpr (NB == 0) {  // chunks through registers (tile_gemm)
+    static_assert(KW == 1, "one group");
+    const uint16_t* aptr[MT];
+    const uint16_t* bptr[NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+      aptr[i] = a.w[m] + static_cast<size_t>(min(f0 + i * 32 + (tid >> 3), fout - 1)) * Din + (tid & 7) * 8;
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+      bptr[i] = a.in + static_cast<size_t>(min(g0 + i * 32 + (tid >> 3), a.T - 1)) * Din + (tid & 7) * 8;
+    tile_gemm<MT, NT, 2, false>(aptr, bptr, kd, lds, acc);
+  } else {
+    uint32_t aoff[MT], boff[NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+      aoff[i] = static_cast<uint32_t>(min(i * 32 + (tid >> 3), fout - 1 - f0)) * Din * 2u + tile_piece(tid) * 16u;
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+      boff[i] = static_cast<uint32_t>(min(i * 32 + (tid >> 3), a.T - 1 - g0)) * Din * 2u + tile_piece(tid) * 16u;
+    const uint16_t* abase = uniform_ptr(a.w[m] + static_cast<size_t>(f0) * Din + k0);
+    const uint16_t* bbase = uniform_ptr(a.in + static_cast<size_t>(g0) * Din + k0);
+    tile_gemm_dma<MT, NT, KW, NB>(abase, bbase, aoff, boff, kd, lds, acc);
+  }
   if constexpr (KW > 1) {  // (everybody is done with the buffers)
     float* other = reinterpret_cast<float*>(lds);  // [wave][MT x NT][64 lanes][4]
     if (part == 1) {
@@ -662,18 +675,28 @@ static LongCut long_cut(int T, const int* fout, int n_mats, int Din) {
 // longer than the best of the five, 21 % less than the two tiles there were, whose chunks passed
 // through registers (us, 2048 x 4096 weights on 64 / 256 / 1024 rows: 15.5 / 15.5 / 30.7, now
 // 9.2 / 12.3 / 25.2; 5120 x 2048: 9.7 / 17.0 / 35.7, now 7.3 / 13.1 / 28.3).
-struct TileLinearPlan { int mt, nt, blocks, kw; };
+struct TileLinearPlan { int mt, nt, blocks, kw; bool regs; };
 static TileLinearPlan tile_linear_plan(int T, const int* fout, int n_mats, int Din) {
   const int kw = long_cut(T, fout, n_mats, Din).cut ? 2 : 1;
   constexpr int kTiles[][2] = {{4, 4}, {4, 2}, {2, 2}, {2, 1}, {1, 1}};
-  TileLinearPlan best{0, 0, 0, kw};
+  auto blocks = [&](int mt, int nt) {
+    int b = 0;
+    for (int m = 0; m < n_mats; ++m) b += (fout[m] + 32 * mt - 1) / (32 * mt);
+    return (b + 7) / 8 * 8 * ((T + 32 * nt - 1) / (32 * nt));
+  };
+  // The most rows: tiles of 128 x 128 that pass through registers, two chunks ahead, where they fill the
+  // compute units.  With both operands in the last-level cache they are the slower ones (2048 rows, 5120
+  // x 2048 weights: 58.5 us, straight into LDS 53.1), but less so than the others where a long context
+  // has streamed through it in between (62.5 against 72.7; output 48.5 against 56.2).
+  if (const int b4 = blocks(4, 4); kw == 1 && T >= 1792 &&
+      (b4 >= 512 || (Din >= 2048 && b4 >= 256 && 2 * ((b4 + 255) / 256 * 256) <= 3 * b4)))
+    return TileLinearPlan{4, 4, b4, 1, true};
+  TileLinearPlan best{0, 0, 0, kw, false};
   long best_cost = 0;
   for (const auto& t : kTiles) {
     const int mt = t[0], nt = t[1];
     if (mt * nt == 16 && kw == 2) continue;  // (two groups of such tiles exceed the LDS)
-    int b = 0;
-    for (int m = 0; m < n_mats; ++m) b += (fout[m] + 32 * mt - 1) / (32 * mt);
-    b = (b + 7) / 8 * 8 * ((T + 32 * nt - 1) / (32 * nt));
+    const int b = blocks(mt, nt);
     const long k = (b + 255) / 256;  // tiles of the fullest compute unit
     const long unit = kw == 2         ? 270 * k + 10
                       : mt * nt == 16 ? (k == 1 ? 250 : k == 2 ? 330 : 205 * k)
@@ -681,7 +704,7 @@ static TileLinearPlan tile_linear_plan(int T, const int* fout, int n_mats, int D
                                       : (k == 1 ? 190 : k == 2 ? (mt > nt ? 256 : 247) : 140 * k + 20);
     const long cost = unit * (mt + nt);
     if (best.mt == 0 || cost < best_cost) {
-      best = TileLinearPlan{mt, nt, b, kw};
+      best = TileLinearPlan{mt, nt, b, kw, false};
       best_cost = cost;
     }
   }
@@ -773,7 +796,8 @@ static void launch_linear(const LinearArgs& a, int kernel_id, hipStream_t st) {
   const dim3 g(pl.blocks), b(256 * pl.kw);
   // (buffers of a chunk: three, two for the largest tile so that two workgroups share a compute unit)
   auto pick = [&](auto kernel1, auto kernel2) { launch(kernel_id, pl.kw == 2 ? kernel2 : kernel1, g, b, 0, st, a); };
-  if (pl.nt == 4) launch(kernel_id, linear_tile_kernel<4, 4, 1, 2>, g, b, 0, st, a);
+  if (pl.regs) launch(kernel_id, linear_tile_kernel<4, 4, 1, 0>, g, b, 0, st, a);
+  else if (pl.nt == 4) launch(kernel_id, linear_tile_kernel<4, 4, 1, 2>, g, b, 0, st, a);
   else if (pl.mt == 4) pick(linear_tile_kernel<4, 2, 1, 3>, linear_tile_kernel<4, 2, 2, 3>);
   else if (pl.nt == 2) pick(linear_tile_kernel<2, 2, 1, 3>, linear_tile_kernel<2, 2, 2, 3>);
   else if (pl.mt == 2) pick(linear_tile_kernel<2, 1, 1, 3>, linear_tile_kernel<2, 1, 2, 3>);
