@@ -391,18 +391,19 @@ static AttnPlan attn_plan(const AttnArgs& a, size_t value_bytes) {
 //   kTwice  one wavefront per tile, the scores computed twice.
 // Weights are rounded to bf16 for the second contraction, their sum is kept in fp32.
 // What bounds it is latency - the loads behind one another, then the staging of the
-// values: eight sequences of 32 tokens over 496 positions, 32 heads on 4, take 21 us
+// values: eight sequences of 32 tokens over 496 positions, 32 heads on 4, take 19.6 us
 // (one workgroup per query head, half of its wavefronts idle, scores computed twice and
-// values transposed two bytes at a time: 49.6 us); one block over 64 positions 7.0 us
-// (6.9).  A running maximum with the parts added up at the end takes 19.5 us, but then the
+// values transposed two bytes at a time: 49.6 us); one block over 64 positions 5.3 us.
+// A running maximum with the parts added up at the end was 1.6 us faster, but then the
 // rounding of the weights depends on the cut, and a part whose scores are all -inf has none.
 // NKS = 32-element steps of the head width.
+typedef short i16x4 __attribute__((ext_vector_type(4)));
 enum AttnForm { kWhole, kWide, kParts, kTwice };
-template <int NKS, int FORM>
+template <int NKS, int FORM, bool ROWS>
 __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
   constexpr int NDT = 2 * NKS;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  uint16_t* vt = reinterpret_cast<uint16_t*>(smem_raw);  // [ndt * 16][ldv]: values, transposed
+  uint16_t* vt = reinterpret_cast<uint16_t*>(smem_raw);  // [ndt * 16][ldv]: values, transposed (unless ROWS)
   const int N = a.N, dh = a.dh, P = a.P, nk = a.P + a.N;
   const int nkp = (nk + 31) & ~31, ldv = nkp + 4, steps = nkp / 32;
   const int ndt = (dh + 15) / 16;
@@ -453,9 +454,32 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
   if (s0 < s1) load_keys(s0, S0{});
   if (s0 + KS < s1) load_keys(s0 + KS, S1{});
 
+  // ROWS (heads of 64 or 128): the values lie in LDS as rows, brought there by direct loads while the
+  // scores are computed, and the transposing LDS read turns four positions x 16 coordinates into the
+  // operand.  Rows of kRow bytes, the 32-byte segment g of row r at g ^ value_swizzle(r): the 16 rows
+  // of an operand read spread over all banks.  (Through registers, transposed 8 bytes at a time, the
+  // staging was a phase of its own with conflicts in its LDS writes: 8 sequences over 496 positions,
+  // 22.1 us; so, and with the operands of the weights formed outside the turns below, 19.6.)
+  constexpr int kRow = ROWS ? NKS * 64 : 256, kPieces = kRow / 16;
+  auto value_swizzle = [](int r) { return kRow == 256 ? (r & 7) : ((r >> 1) & 3); };
+  if constexpr (ROWS) {
+    constexpr int kRows = 1024 / kRow;  // of one direct load
+    const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<size_t>(DES_LDS_PTR(smem_raw)));
+    const int sub = lane / kPieces, p = lane % kPieces, n_waves = n_threads >> 6;
+    for (int i = wave; i < nkp / kRows; i += n_waves) {
+      const int j = i * kRows + sub;
+      if (j < nk) {
+        const uint16_t* src = row_of(vc, vb, j) + (p ^ (value_swizzle(j) << 1)) * 8;
+        // (the wait state between the write of M0 and the load, see dma_stream_gemm)
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds0 + i * 1024)
+                     : "m0");
+      } else {  // slots beyond the window hold zeros (their weights are zero too, but 0 x garbage could be NaN)
+        *reinterpret_cast<uint4*>(smem_raw + i * 1024 + lane * 16) = make_uint4(0u, 0u, 0u, 0u);
+      }
+    }
+  } else
   // values -> LDS, transposed: a thread takes 8 coordinates of 4 consecutive positions and
-  // writes 8 bytes per coordinate.  Slots beyond the window hold zeros (their weights are
-  // zero too, but 0 x garbage could be NaN).
+  // writes 8 bytes per coordinate.  Slots beyond the window hold zeros.
   {
     const int vec = dh / 8, n_piece = nkp / 4 * vec;
     auto fetch = [&](int i, uint4 (&raw)[4]) {
@@ -486,9 +510,17 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
       put(i + n_threads, r1);
     }
   }
-  __syncthreads();
+  // the values are there (direct loads: the compiler does not know of them)
+  auto values_ready = [&]() {
+    if (ROWS) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  };
+  if (!ROWS) values_ready();
 
-  if (FORM != kParts && wave >= a.tiles) return;  // it only helped with the values
+  if (FORM != kParts && wave >= a.tiles) {  // it only helped with the values
+    if (ROWS) values_ready();
+    return;
+  }
   float mx = neg_inf, lsum = 0.f;
   f32x4 oacc[NDT];
 #pragma unroll
@@ -523,22 +555,31 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) w[i][r] = 16 * i + r < lim ? expf((sc[i][r] - mx) * a.scale) : 0.f;
   };
-  // ... into their sum, and as an operand
-  auto add_weights = [&](const f32x4 (&w)[2]) -> bf16x8 {
-    u16x4 pw[2];
+  // ... into their sum, and as an operand (the pack rounds to nearest even, like f32_to_bf16_bits)
+  auto add_to_sum = [&](const f32x4 (&w)[2]) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        lsum += w[i][r];
-        pw[i][r] = f32_to_bf16_bits(w[i][r]);
-      }
-    struct { u16x4 lo, hi; } pp = {pw[0], pw[1]};
-    return __builtin_bit_cast(bf16x8, pp);
+      for (int r = 0; r < 4; ++r) lsum += w[i][r];
+  };
+  auto operand = [&](const f32x4 (&w)[2]) -> bf16x8 {
+    typedef float f32x8 __attribute__((ext_vector_type(8)));
+    return __builtin_convertvector(__builtin_shufflevector(w[0], w[1], 0, 1, 2, 3, 4, 5, 6, 7), bf16x8);
   };
   auto add_values = [&](int st, int dt, const bf16x8& pb, f32x4& o) {  // coordinates 16 dt .. + 15 of step st
-    const uint16_t* vrow = vt + (16 * dt + col) * ldv + 32 * st + 4 * grp;
-    struct { u16x4 lo, hi; } vv = {*reinterpret_cast<const u16x4*>(vrow), *reinterpret_cast<const u16x4*>(vrow + 16)};
+    struct { u16x4 lo, hi; } vv;
+    if constexpr (ROWS) {
+      typedef __attribute__((address_space(3))) i16x4 LdsI16x4;
+      // lanes 4 i .. 4 i + 3 of 16 address position i's 16 coordinates; a lane gets four positions of its own
+      const int j = 32 * st + 4 * grp + (col >> 2);  // (16 rows on: the same swizzle)
+      unsigned char* at = smem_raw + j * kRow + ((dt ^ value_swizzle(j)) << 5) + (col & 3) * 8;
+      vv.lo = __builtin_bit_cast(u16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsI16x4*)DES_LDS_PTR(at)));
+      vv.hi = __builtin_bit_cast(u16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsI16x4*)DES_LDS_PTR(at + 16 * kRow)));
+    } else {
+      const uint16_t* vrow = vt + (16 * dt + col) * ldv + 32 * st + 4 * grp;
+      vv.lo = *reinterpret_cast<const u16x4*>(vrow);
+      vv.hi = *reinterpret_cast<const u16x4*>(vrow + 16);
+    }
     o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vv), pb, o, 0, 0, 0);
   };
   auto weigh = [&](int st, const f32x4* sc) __attribute__((always_inline)) {  // the steps of a set, all coordinates
@@ -547,7 +588,8 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
       if (st + c < s1) {
         f32x4 w[2];
         form(st + c, sc + 2 * c, w);
-        const bf16x8 pb = add_weights(w);
+        add_to_sum(w);
+        const bf16x8 pb = operand(w);
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt)
           if (dt < ndt) add_values(st + c, dt, pb, oacc[dt]);
@@ -579,6 +621,7 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
       }
     };
     walk([](int, const f32x4*) {});
+    if (ROWS) values_ready();
     query_max();
     load_keys(0, S0{});
     load_keys(KS, S1{});
@@ -594,6 +637,7 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
       if (st + 2 * KS < s1) load_keys(st + 2 * KS, Set{});
     });
     query_max();
+    if (ROWS && FORM != kParts) values_ready();
     if constexpr (FORM != kParts) {
       static_for(std::make_integer_sequence<int, kSets>{}, [&](auto i) {
         constexpr int I = decltype(i)::value;
@@ -607,13 +651,17 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
       float* part_sum = reinterpret_cast<float*>(after + 512) + (busy ? q : 0) * 64 + lane;
       uint16_t* ring = reinterpret_cast<uint16_t*>(after + 512 + a.tiles * 256) + lane * 8;
       if (grp == 0) part_max[wave * 16 + col] = mx;
-      __syncthreads();
+      values_ready();
       for (int p = 0; p < S; ++p) mx = fmaxf(mx, part_max[(wave - part + p) * 16 + col]);
       constexpr int kSteps = kWholeWindow / 32;
       f32x4 w[kSteps][2];
+      bf16x8 wp[kSteps];  // (all parts form theirs side by side, a turn below only adds them up)
       static_for(std::make_integer_sequence<int, kSteps>{}, [&](auto i) {
         constexpr int I = decltype(i)::value;
-        if (s0 + I < s1) form(s0 + I, &sc[I / 2][I % 2 * 2], w[I]);
+        if (s0 + I < s1) {
+          form(s0 + I, &sc[I / 2][I % 2 * 2], w[I]);
+          wp[I] = operand(w[I]);
+        }
       });
       // Turn p: the weights of part p meet the values, those of part p + 1 are put in place and added
       // to the sum (the ring holds two parts; a turn's barrier separates its uses).
@@ -624,7 +672,10 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
           uint16_t* dst = ring + ((part & 1) * a.tiles + q) * per * 512;
           static_for(std::make_integer_sequence<int, kSteps>{}, [&](auto i) {
             constexpr int I = decltype(i)::value;
-            if (s0 + I < s1) *reinterpret_cast<bf16x8*>(dst + I * 512) = add_weights(w[I]);
+            if (s0 + I < s1) {
+              *reinterpret_cast<bf16x8*>(dst + I * 512) = wp[I];
+              add_to_sum(w[I]);
+            }
           });
           *part_sum = lsum;
         }
@@ -849,10 +900,17 @@ int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void
     launch(kKAttnCore, kernel, grid, block, lds, st, c);
     return DES_OK;
   };
+  // Values as rows (64 or 128 coordinates: whole numbers of the swizzled 32-byte segments), except
+  // under short windows in workgroups full of tiles, where the staging is little and shared by eight
+  // tiles (64 positions, 64 sequences of 32 tokens: 21.5 us transposed, 22.9 as rows; 132 positions:
+  // 39.1 and 37.6; 16 sequences over 64 positions, four tiles: 8.4 and 8.1).
+  const bool rows = c.P + c.N > 96 || pl.tiles < 8;
   auto pick = [&](auto form) -> int {
     constexpr int W = decltype(form)::value;
-    return nks == 1 ? core(attention_core_kernel<1, W>) : nks == 2 ? core(attention_core_kernel<2, W>)
-         : nks == 3 ? core(attention_core_kernel<3, W>) : core(attention_core_kernel<4, W>);
+    if (rows && t.head_dim == 64) return core(attention_core_kernel<2, W, true>);
+    if (rows && t.head_dim == 128) return core(attention_core_kernel<4, W, true>);
+    return nks == 1 ? core(attention_core_kernel<1, W, false>) : nks == 2 ? core(attention_core_kernel<2, W, false>)
+         : nks == 3 ? core(attention_core_kernel<3, W, false>) : core(attention_core_kernel<4, W, false>);
   };
   const int rc = pl.splits > 1 ? pick(std::integral_constant<int, kParts>{})
                : c.P + c.N <= kWholeWindow ? pick(std::integral_constant<int, kWhole>{})
