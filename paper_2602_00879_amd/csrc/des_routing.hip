@@ -90,6 +90,7 @@ struct RoutingArgs {
   const int32_t* prev_n_unique;  // the previous layer's n_unique (a stack), or null: a negative
                                  // value there is carried into this layer's n_unique
   int do_router, do_select, do_permute, use_flags, bf16;
+  int solo;               // one router tile and one selector workgroup: it computes the tile itself
   int skip_router_tiles;  // test hook: the fused launch runs without its router tiles
   int small_perm;         // one selector workgroup, at most 32 tokens, no skipping: the permutation
                           // is built from per-expert token bitmaps recorded during stage 2
@@ -1039,9 +1040,9 @@ template <int LPT, bool EXT>
 __global__ __launch_bounds__(kRtThreads) void routing_kernel(RoutingArgs a) {
   constexpr int kLds = SelLds<LPT>::total > kMinRoutingLds ? SelLds<LPT>::total : kMinRoutingLds;
   __shared__ __align__(16) char smem[kLds];
-  const int n_tiles = (a.do_router && !a.skip_router_tiles) ? a.tiles_m * a.tiles_t : 0;
+  const int n_tiles = (a.do_router && !a.skip_router_tiles && !a.solo) ? a.tiles_m * a.tiles_t : 0;
   int blk = blockIdx.x;
-  if (blk < n_tiles) {  // ---- role R
+  if (blk < n_tiles || a.solo) {  // ---- role R
     if (blk == 0) DES_STAMP(a, 8);
     if (a.bf16) router_tile_bf16(a, blk % a.tiles_m, blk / a.tiles_m, reinterpret_cast<float*>(smem));
     else router_tile_f32(a, blk % a.tiles_m, blk / a.tiles_m);
@@ -1049,10 +1050,10 @@ __global__ __launch_bounds__(kRtThreads) void routing_kernel(RoutingArgs a) {
     if (a.use_flags) {
       stores_done();  // this thread's logits have reached the level all compute units share
       __syncthreads();
-      if (threadIdx.x == 0) flag_publish(a.flags + blk, a.epoch, false);
+      if (threadIdx.x == 0 && !a.solo) flag_publish(a.flags + blk, a.epoch, false);
     }
     if (blk == 0) DES_STAMP(a, 10);
-    return;
+    if (!a.solo) return;
   }
   blk -= n_tiles;
   const int n_sel = a.do_select ? a.B * a.groups : 0;
@@ -1063,7 +1064,7 @@ __global__ __launch_bounds__(kRtThreads) void routing_kernel(RoutingArgs a) {
   if (blk < n_sel) {  // ---- role S
     DES_STAMP(a, 0);
     if (!select_sequence<LPT, EXT>(a, blk / a.groups, blk % a.groups, smem, false,
-                              a.use_flags && a.do_router)) {
+                              a.use_flags && a.do_router && !a.solo)) {
       publish_empty(a, n_flags);  // a bounded wait expired
       return;
     }
@@ -1357,7 +1358,10 @@ int launch_routing(const des_shape_t& s, const void* x, const void* w_router, co
       if (g_test_skip_router == 2) g_test_skip_router = g_test_max_wait = 0;  // one launch only
       return launch_routing_grid(a, roles - n_tiles, kKRouting, st);
     }
-    return launch_routing_grid(a, roles, kKRouting, st);
+    // A single tile: handing it to another workgroup would cost more than it saves (8 tokens, 16
+    // experts of width 256, fp32: routing 14.4 -> 13.4 us).
+    a.solo = n_tiles == 1 && roles == 2;
+    return launch_routing_grid(a, a.solo ? 1 : roles, kKRouting, st);
   }
   // too large to wait inside one launch: the same roles as three launches
   RoutingArgs r = a;

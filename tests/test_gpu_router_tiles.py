@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from paper_2602_00879_amd import binding as B
+from paper_2602_00879_amd import workloads as W
 from tests import helpers as H
 
 pytestmark = pytest.mark.gpu
@@ -30,3 +31,14 @@ def test_router_tiles(M, D, T, part):
         assert torch.equal(l, logits[:, t:t + part]) and torch.equal(p, probs[:, t:t + part])
     ref = x[0].double().cpu().numpy() @ w.double().cpu().numpy().T + bias.double().cpu().numpy()
     assert np.abs(logits[0].cpu().numpy() - ref).max() <= H.LOGIT_ATOL
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,N", [(3, 1), (16, 16), (16, 17), (17, 16)])
+@pytest.mark.parametrize("mode", ["vote", "seq", "vanilla"])
+def test_one_tile_and_its_neighbours(dtype, M, N, mode):
+    """A single router tile is computed by the selector's workgroup, two by workgroups of their own."""
+    cfg = W.LayerConfig("one_tile", dtype, 1, N, 64, M, 32, 0, 2, 3, 1.1, 41)
+    layer = W.make_layer(cfg)
+    out = H.run_gpu(cfg, H.layer_to_device(layer), mode)
+    H.check_against_oracle(cfg, layer, out, mode, label=f"{dtype} {M} {N} {mode}")
