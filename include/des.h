@@ -379,6 +379,16 @@ int des_kernel_timing_read(int kernel_id, double* total_ms, int64_t* launches);
  */
 int des_test_hooks(int skip_router, int max_wait_iters);
 
+/*
+ * Test aid, host only: the form that a call's launch would have, so that a test can hold the
+ * shapes it picks to the forms it is there for.  launch 0 / 1: the attention sub-layer's q/k/v /
+ * output projection; plan = {weight rows / 32, token rows / 32 of a tile, groups that share its
+ * reduction, chunks pass through registers}, all zero for at most 32 token rows.  launch 2: the
+ * router as a launch of its own (attn unused); plan = {expert tiles, token tiles of a workgroup,
+ * 0, 0}, all zero in fp32.
+ */
+int des_test_plan(const des_shape_t* s, const des_attn_shape_t* attn, int32_t launch, int32_t plan[4]);
+
 const char* des_strerror(int code);
 /* Text of the last HIP error seen by this thread's DES_ERR_HIP ("" if none). */
 const char* des_last_hip_error(void);

@@ -27,7 +27,7 @@ EXPORTS = (
     "des_kernel_timing_enable", "des_kernel_timing_count", "des_kernel_timing_name",
     "des_kernel_timing_read", "des_hbm_read_probe", "des_coreset_from_beta", "des_test_hooks",
     "des_attention_workspace_bytes", "des_block_attention", "des_decoder_workspace_bytes",
-    "des_decoder_stack_forward",
+    "des_decoder_stack_forward", "des_test_plan",
 )
 
 
@@ -103,6 +103,8 @@ def lib() -> ctypes.CDLL:
         L.des_coreset_from_beta.argtypes = [ctypes.c_double, i32]
         L.des_test_hooks.restype = ctypes.c_int
         L.des_test_hooks.argtypes = [ctypes.c_int, ctypes.c_int]
+        L.des_test_plan.restype = ctypes.c_int
+        L.des_test_plan.argtypes = [sp, ap, i32, ctypes.POINTER(i32)]
         L.des_strerror.restype = ctypes.c_char_p
         L.des_strerror.argtypes = [ctypes.c_int]
         L.des_last_hip_error.restype = ctypes.c_char_p
@@ -374,6 +376,13 @@ def des_test_hooks(skip_router, max_wait_iters: int) -> None:
     """Test aid: forces the give-up path of the bounded waits ((0, 0) = normal;
     skip_router = 2: for the next fused routing launch only)."""
     _check(lib().des_test_hooks(int(skip_router), int(max_wait_iters)))
+
+
+def des_test_plan(shape: DesShape, attn: Optional[DesAttnShape], launch: int) -> Tuple[int, ...]:
+    """Test aid, host only: the form of a launch (0 q/k/v, 1 output projection, 2 router; see des.h)."""
+    plan = (ctypes.c_int32 * 4)()
+    _check(lib().des_test_plan(ctypes.byref(shape), None if attn is None else ctypes.byref(attn), launch, plan))
+    return tuple(plan)
 
 
 def des_kernel_timing_enable(enable: bool) -> None:

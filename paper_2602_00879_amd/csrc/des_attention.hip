@@ -720,12 +720,26 @@ static LongCut long_cut(int T, const int* fout, int n_mats, int Din) {
 //
 // A launch is bound by what a compute unit can pull into its LDS: (mt + nt) x 32 rows of the reduction
 // per tile, for as many tiles as the fullest unit has.  Small tiles spread over all units, large ones
-// reload less.  The relative times below, per row and tile on one unit, are measured (112 projections,
-// 33 to 2048 rows, every tile): tiles side by side on a unit overlap, so a second one costs a third,
-// a third one and more about their own time.  Of 112 x 2 launches the tile that they name takes 1 %
-// longer than the best of the five, 21 % less than the two tiles there were, whose chunks passed
-// through registers (us, 2048 x 4096 weights on 64 / 256 / 1024 rows: 15.5 / 15.5 / 30.7, now
-// 9.2 / 12.3 / 25.2; 5120 x 2048: 9.7 / 17.0 / 35.7, now 7.3 / 13.1 / 28.3).
+// reload less.  Measured in two states, because a layer's weights come from memory in a model (the
+// experts of the layer before have streamed through the last-level cache) and from that cache when one
+// layer is called again: 13 pairs of widths x 29 batches of 33 to 4096 rows, both projections, every
+// tile; the second of two figures is with the cache flushed.  Chunks that pass through registers (64 x
+// 64 or 128 x 128) were the only form once; against them the launches take 17 % and 12 % less, at most
+// 6 % and 16 % longer, and 1.7 % longer than in the best of the tiles (2048 x 4096 weights, 256 rows:
+// 17.0 / 21.0 us, now 13.5 / 17.3; 1024 rows 32.5 / 35.2, now 26.8 / 37.2).
+//
+// Where 128 x 128 tiles fill the units they are the best, in one of two forms.  Straight into LDS, one
+// chunk ahead: two tiles share a unit and hide each other's waits, so an even number of tiles per unit
+// takes 19 % and 9 % less than in registers (2048 x 4096 weights, 4096 rows: 67.7 / 80.5 us against 84.0
+// / 85.3).  With an odd number the last tile waits alone for every chunk, which costs more the further
+// away the weights are (6144 x 2048, 1760 rows, three tiles: 53.8 / 69.4 against 60.9 / 63.4; 4096 x
+// 4096, 1024 rows, one: 47.3 / 61.2 against 49.4 / 51.0): through registers, two chunks ahead.  So do
+// launches of more than eight tiles per unit (level, and 17 % longer where 18 fill their rounds) and
+// reductions beyond 8192 (16384: 466 against 324).
+//
+// Else the cheapest by the relative times below, per row and tile on one unit: tiles side by side on a
+// unit overlap, so a second one costs a third, a third one and more about their own time; two groups of
+// 64 x 64 or more take a unit's LDS for themselves, a second such tile comes after the first.
 struct TileLinearPlan { int mt, nt, blocks, kw; bool regs; };
 static TileLinearPlan tile_linear_plan(int T, const int* fout, int n_mats, int Din) {
   const int kw = long_cut(T, fout, n_mats, Din).cut ? 2 : 1;
@@ -735,21 +749,19 @@ static TileLinearPlan tile_linear_plan(int T, const int* fout, int n_mats, int D
     for (int m = 0; m < n_mats; ++m) b += (fout[m] + 32 * mt - 1) / (32 * mt);
     return (b + 7) / 8 * 8 * ((T + 32 * nt - 1) / (32 * nt));
   };
-  // The most rows: tiles of 128 x 128 that pass through registers, two chunks ahead, where they fill the
-  // compute units.  With both operands in the last-level cache they are the slower ones (2048 rows, 5120
-  // x 2048 weights: 58.5 us, straight into LDS 53.1), but less so than the others where a long context
-  // has streamed through it in between (62.5 against 72.7; output 48.5 against 56.2).
-  if (const int b4 = blocks(4, 4); kw == 1 && T >= 1792 &&
-      (b4 >= 512 || (Din >= 2048 && b4 >= 256 && 2 * ((b4 + 255) / 256 * 256) <= 3 * b4)))
-    return TileLinearPlan{4, 4, b4, 1, true};
+  // (filled: two tiles per unit, or, where a tile is long enough to pay for its start, one, if the last
+  // round of units is at least two thirds full)
+  if (const int b4 = blocks(4, 4), k = (b4 + 255) / 256;
+      kw == 1 && (b4 >= 512 || (Din >= 2048 && b4 >= 256 && 2 * 256 * k <= 3 * b4)))
+    return TileLinearPlan{4, 4, b4, 1, k % 2 != 0 || k > 8 || Din > 8192};
   TileLinearPlan best{0, 0, 0, kw, false};
   long best_cost = 0;
   for (const auto& t : kTiles) {
     const int mt = t[0], nt = t[1];
-    if (mt * nt == 16 && kw == 2) continue;  // (two groups of such tiles exceed the LDS)
+    if (mt * nt == 16 && kw == 2) continue;  // (15 % longer at best)
     const int b = blocks(mt, nt);
     const long k = (b + 255) / 256;  // tiles of the fullest compute unit
-    const long unit = kw == 2         ? 270 * k + 10
+    const long unit = kw == 2         ? (mt * nt >= 4 && k > 1 ? 400 * k : 270 * k + 10)
                       : mt * nt == 16 ? (k == 1 ? 250 : k == 2 ? 330 : 205 * k)
                       : mt * nt == 8  ? (k == 1 ? 210 : k == 2 ? 280 : 155 * k)
                                       : (k == 1 ? 190 : k == 2 ? (mt > nt ? 256 : 247) : 140 * k + 20);
@@ -800,6 +812,15 @@ AttnLayout attn_layout(const des_shape_t& s, const des_attn_shape_t& t) {
   l.flags = p; p = align256(p + n_flags * 8);
   l.total = p;
   return l;
+}
+
+void projection_plan(const des_shape_t& s, const des_attn_shape_t& t, bool output, int32_t* plan) {
+  const int T = s.n_seqs * s.n_tokens, HD = t.n_heads * t.head_dim, KD = t.n_kv_heads * t.head_dim;
+  const int f_qkv[3] = {HD, KD, KD}, f_out[1] = {s.hidden};
+  plan[0] = plan[1] = plan[2] = plan[3] = 0;
+  if (T <= 32) return;
+  const TileLinearPlan p = output ? tile_linear_plan(T, f_out, 1, HD) : tile_linear_plan(T, f_qkv, 3, s.hidden);
+  plan[0] = p.mt; plan[1] = p.nt; plan[2] = p.kw; plan[3] = p.regs;
 }
 
 size_t attn_core_lds(const des_shape_t& s, const des_attn_shape_t& t) {

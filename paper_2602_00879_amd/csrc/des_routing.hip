@@ -1262,22 +1262,33 @@ bool dense_block(const des_shape_t& s) {
   return s.n_tokens <= selector_tokens_per_pass(s.n_experts) && n_tiles + 1 <= fused_limit;
 }
 
+// Four tiles per workgroup read half as much per tile, where one tile each makes more than one
+// round of the chip.  128 experts of width 2048: 384 tiles 9.5 us in ones, 11.5 in fours (which
+// take a second trip through the reduction there), 544 13.2 and 11.4, 1024 17.3 and 11.4; 96 of
+// width 768: 192 tiles 5.9 and 7.1, 288 8.8 and 6.8; 64 of width 3072: 256 10.6 and 14.3, 384 16.6
+// and 14.3.  (As a role of the routing kernel, with its registers, 1024 tiles took 20.4.)
+static bool wide_router(const RoutingArgs& a) {
+  const int tiles = a.tiles_m * a.tiles_t;
+  return tiles > 512 || (tiles > 256 && (a.D <= 1024 || a.D > 2048));
+}
+
 static int launch_router_tiles(const RoutingArgs& a, hipStream_t st) {
   const int tiles = a.tiles_m * a.tiles_t;
   if (!a.bf16) return launch_routing_grid(a, tiles, kKRouter, st);
   const dim3 b(kRtThreads);
-  // Four tiles per workgroup read half as much per tile, where one tile each makes more than one
-  // round of the chip.  128 experts of width 2048: 384 tiles 9.5 us in ones, 11.5 in fours (which
-  // take a second trip through the reduction there), 544 13.2 and 11.4, 1024 17.3 and 11.4; 96 of
-  // width 768: 192 tiles 5.9 and 7.1, 288 8.8 and 6.8; 64 of width 3072: 256 10.6 and 14.3, 384 16.6
-  // and 14.3.  (As a role of the routing kernel, with its registers, 1024 tiles took 20.4.)
-  const bool wide = tiles > 512 || (tiles > 256 && (a.D <= 1024 || a.D > 2048));
-  if (wide)
+  if (wide_router(a))
     launch(kKRouter, router_kernel<2, 2>, dim3((a.tiles_m + 1) / 2 * ((a.tiles_t + 1) / 2)), b, 0, st, a);
   else
     launch(kKRouter, router_kernel<1, 1>, dim3(tiles), b, 0, st, a);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? DES_OK : hip_fail(e, "router launch");
+}
+
+void router_plan(const des_shape_t& s, int32_t* plan) {
+  RoutingArgs a;
+  fill_common(a, s);
+  plan[0] = plan[1] = !a.bf16 ? 0 : wide_router(a) ? 2 : 1;
+  plan[2] = plan[3] = 0;
 }
 
 int launch_router(const des_shape_t& s, const void* x, const void* w_router, const float* bias,

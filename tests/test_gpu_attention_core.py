@@ -45,7 +45,7 @@ CASES = {
     "long_block": (1, 300, 128, 4, 4, 32, 7),
     # the projections' forms: tiles with the reduction whole or cut, rows and columns that do
     # not fill a tile, a reduction of whole 64-element chunks and of one chunk more or less,
-    # the large tile, wide matrices
+    # large and wide matrices (test_gpu_projection_tiles.py has an entry per tile)
     "tile_33_rows": (1, 33, 128, 4, 2, 32, 3),
     "tile_cut_65_rows": (1, 65, 1024, 8, 2, 64, 3),
     "tile_whole_65_rows": (5, 13, 1152, 8, 2, 48, 0),

@@ -1,0 +1,62 @@
+"""The rules that choose a launch's form, asked on the host (no GPU): the tile of the attention projections
+at the sizes where its rule changes, and that the shapes of the GPU tests reach the forms they are there for."""
+import pytest
+
+from paper_2602_00879_amd import binding as B
+from tests import test_gpu_projection_tiles as tiles
+
+
+def _plans(case, residual=0):
+    Bn, N, D, Hq, G, dh, P = case
+    shape = B.make_shape(Bn, N, D, 16, 128, 2, 4, "vanilla", "bf16", residual=residual)
+    attn = B.make_attn_shape(Hq, G, dh, P, 0)
+    return B.des_test_plan(shape, attn, 0), B.des_test_plan(shape, attn, 1)
+
+
+@pytest.mark.parametrize("name", list(tiles.TILES))
+def test_projection_tests_reach_their_tiles(name):
+    case, qkv, out = tiles.TILES[name]
+    assert _plans(case) == (qkv, out)
+
+
+def test_residual_test_reaches_the_register_tile():
+    case, qkv, out = tiles.REGISTERS_OUT
+    assert _plans(case, 1) == (qkv, out)
+
+
+def test_every_tile_has_a_test():
+    """All that launch_linear can choose: five tiles, whole or cut (not the largest), and the register tile."""
+    reached = {p for case, qkv, out in tiles.TILES.values() for p in (qkv, out)}
+    sizes = [(4, 4), (4, 2), (2, 2), (2, 1), (1, 1)]
+    assert reached == {(m, n, kw, 0) for m, n in sizes for kw in (1, 2) if (m, n, kw) != (4, 4, 2)} | {(4, 4, 1, 1)}
+
+
+# (rows, hidden, query heads, key/value heads, head width, launch): tile.  Compute units filled by 128 x 128
+# tiles: one, two, three, four and nine per unit, one whose last round is not full, and the longest reduction.
+RULE = [
+    ((1024, 4096, 32, 8, 128, 1), (4, 4, 1, 1)),     # one per unit
+    ((2048, 2048, 32, 8, 128, 1), (4, 4, 1, 1)),
+    ((3072, 2048, 32, 4, 128, 1), (4, 4, 1, 0)),     # two
+    ((1760, 2048, 16, 16, 128, 0), (4, 4, 1, 1)),    # three
+    ((2048, 5120, 40, 8, 128, 0), (4, 4, 1, 0)),     # four
+    ((2048, 2048, 128, 8, 128, 0), (4, 4, 1, 1)),    # nine
+    ((1280, 5120, 40, 8, 128, 0), (4, 4, 1, 1)),     # three again
+    ((4096, 2048, 128, 8, 128, 1), (4, 4, 1, 1)),    # two, reduction of 16384
+    ((2304, 512, 8, 1, 64, 1), (2, 1, 2, 0)),        # two groups of 64 x 64 would take turns on a unit
+    ((32, 2048, 32, 4, 128, 0), (0, 0, 0, 0)),       # a kernel of its own
+]
+
+
+@pytest.mark.parametrize("case,tile", RULE)
+def test_rule_of_the_projection_tile(case, tile):
+    T, D, Hq, G, dh, launch = case
+    n = next(n for n in (32, 1) if T % n == 0)
+    assert _plans((T // n, n, D, Hq, G, dh, 0))[launch] == tile
+
+
+def test_plan_is_refused_where_the_call_is():
+    shape = B.make_shape(1, 33, 100, 16, 128, 2, 4, "vanilla", "bf16")
+    with pytest.raises(B.DesError):
+        B.des_test_plan(shape, B.make_attn_shape(4, 2, 32, 0, 0), 0)
+    with pytest.raises(B.DesError):
+        B.des_test_plan(B.make_shape(1, 33, 128, 16, 128, 2, 4, "vanilla", "bf16"), None, 0)
