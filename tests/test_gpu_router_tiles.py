@@ -1,6 +1,7 @@
 """The router as a launch of its own: four tiles per workgroup (large batches) against one, on the same
 tokens in smaller calls, bit for bit, and against float64.  Expert and token tiles that do not fill a
-workgroup, reductions shorter than a workgroup's wavefronts and with a remainder."""
+workgroup, reductions shorter than a workgroup's wavefronts and with a remainder.  (test_launch_plans.py
+holds the sizes to those two forms.)"""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +13,11 @@ from tests import helpers as H
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,D,T,part", [(136, 96, 1073, 100), (256, 2048, 530, 131), (24, 3104, 2200, 550), (16, 32, 4096, 4000)])
+# (experts, width, tokens, tokens of a smaller call)
+ROUTER = [(136, 96, 1073, 100), (256, 2048, 530, 131), (24, 3104, 2200, 550), (24, 32, 4096, 1000)]
+
+
+@pytest.mark.parametrize("M,D,T,part", ROUTER)
 def test_router_tiles(M, D, T, part):
     print(f"router {M} {D} {T}", flush=True)
     g = torch.Generator(device="cuda")

@@ -4,6 +4,7 @@ import pytest
 
 from paper_2602_00879_amd import binding as B
 from tests import test_gpu_projection_tiles as tiles
+from tests import test_gpu_router_tiles as router
 
 
 def _plans(case, residual=0):
@@ -60,3 +61,11 @@ def test_plan_is_refused_where_the_call_is():
         B.des_test_plan(shape, B.make_attn_shape(4, 2, 32, 0, 0), 0)
     with pytest.raises(B.DesError):
         B.des_test_plan(B.make_shape(1, 33, 128, 16, 128, 2, 4, "vanilla", "bf16"), None, 0)
+
+
+@pytest.mark.parametrize("M,D,T,part", router.ROUTER)
+def test_router_test_compares_four_tiles_with_one(M, D, T, part):
+    def form(n):
+        return B.des_test_plan(B.make_shape(1, n, D, M, 32, 1, M, "vanilla", "bf16"), None, 2)
+    assert form(T) == (2, 2, 0, 0)
+    assert {form(min(part, T - t)) for t in range(0, T, part)} == {(1, 1, 0, 0)}
