@@ -716,7 +716,13 @@ __global__ __launch_bounds__(LW* kWave, ((KD > 0 || MAXNT <= 4 || RT == 4) ? 2 :
 template <bool PACKED, int MAXNT, int MT, int P>
 __global__ __launch_bounds__(kTileThreads, 2) void gateup_tile_kernel(FfnArgs a) {
   constexpr int HT = MT / 2, kRows = 32 * MAXNT;
-  __shared__ __align__(16) char lds[tile_lds_bytes<MT, MAXNT>()];
+  // Packed weights, two chunks ahead, units sized for 128 rows (many experts with a few pairs each): two
+  // workgroups per compute unit are faster than the three whose tiles fit (96 experts of 2016 x 288 and a
+  // shared one, 80 tokens: 36.1 us against 39.9, with the last-level cache flushed 40.3 against 44.1).  Not
+  // so for row-major weights (128 experts of 2048 x 768, 65 tokens: 63.2 against 57.6) and in the down
+  // projection (32 experts of 1024 x 352, 2048 tokens: 16.7 against 14.8).
+  constexpr int kLds = PACKED && P == 2 && MAXNT == 4 ? 56 * 1024 : tile_lds_bytes<MT, MAXNT>();
+  __shared__ __align__(16) char lds[kLds];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   Task t;

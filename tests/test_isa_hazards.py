@@ -231,3 +231,10 @@ def test_direct_lds_loads_of_the_attention_projections():
     asm = _asm("des_attention.hip")
     test_no_vector_written_scalar_base_too_close_to_a_load(asm.replace("linear_tile_kernel", "linear_lds_kernel"))
     test_m0_write_is_one_wait_state_before_direct_lds_load(asm)
+
+
+def test_packed_gateup_tile_two_chunks_ahead_runs_two_workgroups_per_unit(ffn_asm):
+    """Its tiles would fit three times into the 160 KB of a compute unit, which is slower."""
+    m = re.search(r"\.amdhsa_kernel (\S*gateup_tile_kernelILb1ELi4ELi2ELi2E\S*)\n(.*?)\.end_amdhsa_kernel", ffn_asm, re.S)
+    lds = int(re.search(r"\.amdhsa_group_segment_fixed_size (\d+)", m.group(2)).group(1))
+    assert 2 * lds <= 160 * 1024 < 3 * lds
