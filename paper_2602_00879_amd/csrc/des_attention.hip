@@ -33,9 +33,9 @@ struct LinearArgs {
 };
 
 // out[m][t][f] = sum_d in[t][d] * w[m][f][d] for blocks of more than 32 token rows, in tiles
-// of 32 MT weight rows x 32 NT token rows (tile_gemm_dma, with NB buffers; NB = 0: tile_gemm).  KW = 2: the two halves of the
-// reduction dimension go to the two halves of the workgroup and meet in LDS, first half +
-// second half.
+// of 32 MT weight rows x 32 NT token rows (tile_gemm_dma, with NB buffers; NB = 0: tile_gemm).
+// KW = 2: the two halves of the reduction dimension go to the two halves of the workgroup and
+// meet in LDS, first half + second half.
 // Consecutive workgroups go to the eight XCDs in turn: the grid is walked so that one XCD
 // has all the token tiles of a weight tile (its L2 then reads those weights once).
 template <int MT, int NT, int KW, int NB>
@@ -563,7 +563,6 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
       for (int r = 0; r < 4; ++r) lsum += w[i][r];
   };
   auto operand = [&](const f32x4 (&w)[2]) -> bf16x8 {
-    typedef float f32x8 __attribute__((ext_vector_type(8)));
     return __builtin_convertvector(__builtin_shufflevector(w[0], w[1], 0, 1, 2, 3, 4, 5, 6, 7), bf16x8);
   };
   auto add_values = [&](int st, int dt, const bf16x8& pb, f32x4& o) {  // coordinates 16 dt .. + 15 of step st
@@ -911,7 +910,8 @@ int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void
   c.tiles = pl.tiles;
   const int waves = pl.splits * pl.tiles, nks = (t.head_dim + 31) / 32;
   const size_t lds = pl.lds;
-  const dim3 grid(s.n_seqs * t.n_kv_heads, pl.groups), block((waves < 4 ? 4 : waves) * kWave);  // (four stage faster than one)
+  // (four wavefronts stage faster than one)
+  const dim3 grid(s.n_seqs * t.n_kv_heads, pl.groups), block((waves < 4 ? 4 : waves) * kWave);
   auto core = [&](auto kernel) -> int {
     if (lds > 48 * 1024) {  // (a property of the function on the current device; cheap to repeat)
       const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),

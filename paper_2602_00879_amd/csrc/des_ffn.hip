@@ -539,7 +539,7 @@ struct LdsTask {
   bool alone;       // no other workgroup reads these weights
 };
 __device__ __forceinline__ void unit_share(int i, int per, int nsplit, int& group, int& split) {
-  if (nsplit == 1) {  // (a run of row groups per XCD is no help here: 80 tokens, experts of 2048 x 512, down 13.4 -> 14.9 us)
+  if (nsplit == 1) {  // (a run of row groups per XCD is no help: 80 tokens, 2048 x 512, down 13.4 -> 14.9 us)
     group = i;
     split = 0;
     return;
@@ -740,41 +740,39 @@ __global__ __launch_bounds__(kTileThreads, 2) void gateup_tile_kernel(FfnArgs a)
     aptr[i] = tile_weight_ptr<PACKED>((q % MT < HT ? t.w0 : t.w1) + static_cast<size_t>(ft) * 16 * a.D, a.D, tid);
   }
   const int g0 = k.g0, rows = k.rows;
-  {
-    auto run = [&](auto ntc) {
-      constexpr int NT = decltype(ntc)::value;
-      const uint16_t* bptr[NT];
+  auto run = [&](auto ntc) {
+    constexpr int NT = decltype(ntc)::value;
+    const uint16_t* bptr[NT];
 #pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        const int r = g0 + min(i * 32 + (tid >> 3), rows - 1);
-        bptr[i] = x + static_cast<size_t>(t.shared ? r : a.pair_tok[t.pair0 + r]) * a.D + (tid & 7) * 8;
+    for (int i = 0; i < NT; ++i) {
+      const int r = g0 + min(i * 32 + (tid >> 3), rows - 1);
+      bptr[i] = x + static_cast<size_t>(t.shared ? r : a.pair_tok[t.pair0 + r]) * a.D + (tid & 7) * 8;
+    }
+    f32x4 acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    tile_gemm<MT, NT, (NT <= 2 ? P : 1), PACKED>(aptr, bptr, a.D, lds, acc);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int r = (wn * NT + j) * 16 + (lane & 15);
+      if (r >= rows) continue;
+#pragma unroll
+      for (int i = 0; i < HT; ++i) {
+        const int ft = f0 + wm * HT + i;
+        if (ft >= tiles) continue;
+        u16x4 o;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = f32_to_bf16_bits(silu_f(acc[i][j][q]) * acc[HT + i][j][q]);
+        *reinterpret_cast<u16x4*>(h + (t.row_base + g0 + r) * t.fdim + ft * 16 + 4 * (lane >> 4)) = o;
       }
-      f32x4 acc[MT][NT];
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-      tile_gemm<MT, NT, (NT <= 2 ? P : 1), PACKED>(aptr, bptr, a.D, lds, acc);
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const int r = (wn * NT + j) * 16 + (lane & 15);
-        if (r >= rows) continue;
-#pragma unroll
-        for (int i = 0; i < HT; ++i) {
-          const int ft = f0 + wm * HT + i;
-          if (ft >= tiles) continue;
-          u16x4 o;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) o[q] = f32_to_bf16_bits(silu_f(acc[i][j][q]) * acc[HT + i][j][q]);
-          *reinterpret_cast<u16x4*>(h + (t.row_base + g0 + r) * t.fdim + ft * 16 + 4 * (lane >> 4)) = o;
-        }
-      }
-    };
-    if (rows <= 32) run(std::integral_constant<int, 1>{});
-    else if (rows <= 64) run(std::integral_constant<int, 2>{});
-    else if (rows <= 96) run(std::integral_constant<int, MAXNT < 3 ? MAXNT : 3>{});
-    else run(std::integral_constant<int, MAXNT>{});
-  }
+    }
+  };
+  if (rows <= 32) run(std::integral_constant<int, 1>{});
+  else if (rows <= 64) run(std::integral_constant<int, 2>{});
+  else if (rows <= 96) run(std::integral_constant<int, MAXNT < 3 ? MAXNT : 3>{});
+  else run(std::integral_constant<int, MAXNT>{});
 }
 
 template <bool PACKED, int MAXNT, int MT, int P>
@@ -797,36 +795,34 @@ __global__ __launch_bounds__(kTileThreads, 2) void down_tile_kernel(FfnArgs a) {
     aptr[i] = tile_weight_ptr<PACKED>(
         t.w0 + static_cast<size_t>(min(d0 + 2 * i + (tid >> 7), tiles - 1)) * 16 * F, F, tid);
   const int g0 = k.g0, rows = k.rows;
-  {
-    auto run = [&](auto ntc) {
-      constexpr int NT = decltype(ntc)::value;
-      const uint16_t* bptr[NT];
+  auto run = [&](auto ntc) {
+    constexpr int NT = decltype(ntc)::value;
+    const uint16_t* bptr[NT];
 #pragma unroll
-      for (int i = 0; i < NT; ++i)
-        bptr[i] = h + (t.row_base + g0 + min(i * 32 + (tid >> 3), rows - 1)) * F + (tid & 7) * 8;
-      f32x4 acc[MT][NT];
+    for (int i = 0; i < NT; ++i)
+      bptr[i] = h + (t.row_base + g0 + min(i * 32 + (tid >> 3), rows - 1)) * F + (tid & 7) * 8;
+    f32x4 acc[MT][NT];
 #pragma unroll
-      for (int i = 0; i < MT; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-      tile_gemm<MT, NT, (NT <= 2 ? P : 1), PACKED>(aptr, bptr, F, lds, acc);
+      for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    tile_gemm<MT, NT, (NT <= 2 ? P : 1), PACKED>(aptr, bptr, F, lds, acc);
 #pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const int r = (wn * NT + j) * 16 + (lane & 15);
-        if (r >= rows) continue;
+    for (int j = 0; j < NT; ++j) {
+      const int r = (wn * NT + j) * 16 + (lane & 15);
+      if (r >= rows) continue;
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-          const int dt = d0 + wm * MT + i;
-          if (dt < tiles)
-            *reinterpret_cast<f32x4*>(a.o + (orow0 + g0 + r) * a.D + dt * 16 + 4 * (lane >> 4)) = acc[i][j];
-        }
+      for (int i = 0; i < MT; ++i) {
+        const int dt = d0 + wm * MT + i;
+        if (dt < tiles)
+          *reinterpret_cast<f32x4*>(a.o + (orow0 + g0 + r) * a.D + dt * 16 + 4 * (lane >> 4)) = acc[i][j];
       }
-    };
-    if (rows <= 32) run(std::integral_constant<int, 1>{});
-    else if (rows <= 64) run(std::integral_constant<int, 2>{});
-    else if (rows <= 96) run(std::integral_constant<int, MAXNT < 3 ? MAXNT : 3>{});
-    else run(std::integral_constant<int, MAXNT>{});
-  }
+    }
+  };
+  if (rows <= 32) run(std::integral_constant<int, 1>{});
+  else if (rows <= 64) run(std::integral_constant<int, 2>{});
+  else if (rows <= 96) run(std::integral_constant<int, MAXNT < 3 ? MAXNT : 3>{});
+  else run(std::integral_constant<int, MAXNT>{});
 }
 
 // ------------------------------------------------------------------ fp32 path
@@ -1126,16 +1122,17 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
       // Longer blocks: units of 64 token rows while no expert can have more, else 128; an
       // expert with more pairs has several of them (the unit list).
       //
-      // Three forms of each kernel: with four weight tiles per wavefront (below), streamed, tiles.  Streamed (weights straight into operands, token rows
-      // through LDS): packed weights whose reduction is one of the unrolled ones - or, with
-      // fewer than 32 pairs per possible expert, any whole number of its chunks.  Tiles (both
-      // through LDS): everything else that is left.  128 experts of 2048 x 768 under 256 tokens, gate/up +
-      // down: packed 68.3 + 40.0 us streamed, 77.6 + 43.6 in tiles; row-major (64 bytes of a row
-      // per operand load) 99.9 + 54.8 and 81.3 + 45.0.  64 experts of 1536 x 1408, packed, not
-      // unrolled: 16 pairs per expert 78.0 + 50.0 and 80.5 + 51.6, 32 pairs 111 + 64.9 and
-      // 98.5 + 56.5, 128 pairs 223 + 126 and 168 + 97.  Sizes that are no multiple of the streamed
-      // chunk had one wavefront per 16 or 32 weight rows gather everything from L2 (64 experts of
-      // 1440 x 288, packed, 200 tokens, 12 pairs per expert: gate/up 60.2, in tiles 22.8).
+      // Three forms of each kernel: streamed with four weight tiles per wavefront (below), streamed
+      // with two, tiles.  Streamed (weights straight into operands, token rows through LDS): packed
+      // weights whose reduction is one of the unrolled ones - or, with fewer than 32 pairs per
+      // possible expert, any whole number of its chunks.  Tiles (both through LDS): everything else.
+      // 128 experts of 2048 x 768 under 256 tokens, gate/up + down: packed 68.3 + 40.0 us streamed,
+      // 77.6 + 43.6 in tiles; row-major (64 bytes of a row per operand load) 99.9 + 54.8 and 81.3 +
+      // 45.0.  64 experts of 1536 x 1408, packed, not unrolled: 16 pairs per expert 78.0 + 50.0 and
+      // 80.5 + 51.6, 32 pairs 111 + 64.9 and 98.5 + 56.5, 128 pairs 223 + 126 and 168 + 97.  Sizes
+      // that are no multiple of the streamed chunk had one wavefront per 16 or 32 weight rows gather
+      // everything from L2 (64 experts of 1440 x 288, packed, 200 tokens, 12 pairs per expert:
+      // gate/up 60.2, in tiles 22.8).
       const int rows_pass = lds_rows_pass(a.T);
       const bool small = rows_pass == 64;
       int splits = (a.T + rows_pass - 1) / rows_pass;  // of the shared expert (all T rows)

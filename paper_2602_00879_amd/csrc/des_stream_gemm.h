@@ -58,8 +58,8 @@ __device__ __forceinline__ void stream_pipeline(int steps, Load&& load, Compute&
 // where packed tiles reach 5.8 (33 experts of 2048 x 768: gate/up 58.4 us, down 31.8 us; as
 // below 44.4 and 23.2, packed 42.5 and 21.8).  So row-major tiles are loaded in whole
 // 128-byte lines (a load = 8 rows x 64 elements, lane l has piece l % 8 of row l / 8) and
-// turned into operand order through a few KB of LDS that belong to the wavefront alone: two loads (v[0], v[1]: rows 0-7 and 8-15) become the
-// operands of two k-steps.  16-byte piece p of row r is kept at piece p ^ (r / 2 % 8), so
+// turned into operand order through a few KB of LDS that belong to the wavefront alone: two loads
+// (v[0], v[1]: rows 0-7 and 8-15) become the operands of two k-steps.  16-byte piece p of row r is kept at piece p ^ (r / 2 % 8), so
 // writes and reads both spread over all banks.
 constexpr int kTurnBytes = 2048;  // of LDS per 16 x 64 tile
 __device__ __forceinline__ void turn_write(const bf16x8& v0, const bf16x8& v1, char* tile, int lane) {
@@ -82,14 +82,13 @@ __device__ __forceinline__ void turn_fence() {
 // of registers for its prefetch (every token fragment is double-buffered in
 // registers).  For T > 32 the expert's activation rows go through LDS instead:
 //   * a workgroup of LW wavefronts works on LW weight-row groups of one expert;
-//     each wavefront streams its own two or four weight tiles straight into
-//     MFMA operands, two chunks ahead, so that they stay in flight across every barrier;
-//   * the expert's token rows of the next chunk are gathered from L2 into LDS
-//     by direct global-to-LDS loads (no staging registers), double-buffered;
-//   * LDS rows are 256 B with the 16-byte pieces of row r stored at piece
-//     index p ^ (r & 15): a direct load writes lane l at base + 16*l, so the
-//     swizzle is applied on the global side (which piece a lane fetches), and
-//     the 16 token rows an MFMA operand reads fall into 16 different banks.
+//     each wavefront streams its own weight tiles straight into MFMA operands;
+//   * the expert's token rows are gathered from L2 into LDS by direct
+//     global-to-LDS loads (no staging registers).
+// Three forms: two weight tiles and a reduction known at compile time, or four tiles and any
+// even number of chunks, have both requested two chunks ahead (three buffers of token rows),
+// so that they stay in flight across every barrier; two tiles and any number of chunks, one
+// chunk ahead (two buffers).
 // The compiler does not know about the direct loads (they are asm): it neither waits for
 // them nor for the weights, explicit vmcnt counts do.  The token fragments are volatile LDS
 // reads, which keeps them in program order with the asm statements and the barriers; the
@@ -346,7 +345,9 @@ __device__ __forceinline__ void dma_stream_gemm(const uint16_t* const (&a)[RT], 
       if (c + 1 >= nchunks) break;
       step(c + 1, S1{}, S0{});
     }
-    asm volatile("s_waitcnt vmcnt(0)");  // (nothing is outstanding: the last step waited for everything)
+    // Nothing is outstanding (the last step requests nothing and has waited for the rest).  The check of
+    // the generated code for reads of a register whose load is under way cannot know that: this tells it.
+    asm volatile("s_waitcnt vmcnt(0)");
   }
 }
 

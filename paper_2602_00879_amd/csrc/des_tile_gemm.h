@@ -193,7 +193,7 @@ __device__ __forceinline__ void tile_gemm_dma(const uint16_t* abase, const uint1
         for (int j = 0; j < NT; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[u][i], fb[u][j], acc[i][j], 0, 0, 0);
   };
-  static_assert(NB >= 2 && NB <= 4, "chunks ahead");
+  static_assert(NB == 2 || NB == 3, "chunks ahead");
   static_assert((NB - 1) * ND <= 63, "wait counts must fit the counter");
 #pragma unroll
   for (int i = 0; i < NB - 1; ++i)
@@ -202,7 +202,6 @@ __device__ __forceinline__ void tile_gemm_dma(const uint16_t* abase, const uint1
   for (int st = 0; st < steps; ++st) {
     // chunk st has landed (loads complete in order; the chunks after it stay in flight) ...
     if (st + NB - 2 < steps) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NB - 2) * ND));
-    else if (NB == 4 && st + 1 < steps) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ND));
     else asm volatile("s_waitcnt vmcnt(0)");
     // ... everybody's share of it, and everybody has read the buffer that is filled next
     asm volatile("s_waitcnt lgkmcnt(0)");
