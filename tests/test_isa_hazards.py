@@ -61,14 +61,16 @@ def _wait_states(instr):
     return int(m.group(1)) + 1 if m else 1
 
 
-def test_no_vector_written_scalar_base_too_close_to_a_load(ffn_asm):
-    kernels = _kernels(ffn_asm)
-    assert any("lds_kernel" in k for k in kernels)
-    for name, ins in kernels.items():
+def _scalar_bases(text):
+    """{kernel: loads with a scalar base}; none comes less than five wait states after a vector
+    instruction that wrote the base."""
+    seen = {}
+    for name, ins in _kernels(text).items():
         for i, instr in enumerate(ins):
             m = re.match(r"global_load_(?:lds_)?dwordx4 .*s\[(\d+):(\d+)\]", instr)
             if not m:
                 continue
+            seen[name] = seen.get(name, 0) + 1
             base = {int(m.group(1)), int(m.group(2))}
             ws = 0
             for j in range(i - 1, max(-1, i - 8), -1):
@@ -76,15 +78,17 @@ def test_no_vector_written_scalar_base_too_close_to_a_load(ffn_asm):
                 assert not (w and int(w.group(1)) in base and ws < 5), (
                     f"{name}: '{ins[j]}' only {ws} wait states before '{instr}'")
                 ws += _wait_states(ins[j])
+    return seen
 
 
-def test_m0_write_is_one_wait_state_before_direct_lds_load(ffn_asm):
-    n = 0
-    for name, ins in _kernels(ffn_asm).items():
+def _direct_loads(text):
+    """{kernel: direct-to-LDS loads}; each comes at least one wait state after the write of M0."""
+    seen = {}
+    for name, ins in _kernels(text).items():
         for i, instr in enumerate(ins):
             if not instr.startswith("global_load_lds_dwordx4"):
                 continue
-            n += 1
+            seen[name] = seen.get(name, 0) + 1
             j = i - 1
             ws = 0
             while j >= 0 and not ins[j].startswith("s_mov_b32 m0"):
@@ -92,7 +96,17 @@ def test_m0_write_is_one_wait_state_before_direct_lds_load(ffn_asm):
                 j -= 1
                 assert i - j < 6, f"{name}: no M0 write just before '{instr}'"
             assert ws >= 1, f"{name}: M0 written immediately before '{instr}'"
-    assert n > 0
+    return seen
+
+
+def test_no_vector_written_scalar_base_too_close_to_a_load(ffn_asm):
+    seen = _scalar_bases(ffn_asm)
+    assert all(seen.get(k, 0) > 0 for k in _kernels(ffn_asm) if "lds_kernel" in k)
+
+
+def test_m0_write_is_one_wait_state_before_direct_lds_load(ffn_asm):
+    seen = _direct_loads(ffn_asm)
+    assert all(seen.get(k, 0) > 0 for k in _kernels(ffn_asm) if "lds_kernel" in k)
 
 
 def test_asm_load_kernels_do_not_spill(ffn_asm):
@@ -226,11 +240,19 @@ def test_loads_without_the_non_temporal_hint_are_waited_for_as_well(ffn_asm):
     test_no_read_of_an_asynchronously_loaded_register_before_its_wait(hinted)
 
 
-def test_direct_lds_loads_of_the_attention_projections():
-    """The two wait-state rules of the direct loads, for the file whose tiles load both operands so."""
+def test_direct_lds_loads_of_the_attention_kernels():
+    """The two wait-state rules in the file whose projections load both operands straight into LDS, from
+    a scalar base, and whose core brings in values so: every such kernel has loads that were looked at."""
     asm = _asm("des_attention.hip")
-    test_no_vector_written_scalar_base_too_close_to_a_load(asm.replace("linear_tile_kernel", "linear_lds_kernel"))
-    test_m0_write_is_one_wait_state_before_direct_lds_load(asm)
+    bases, direct = _scalar_bases(asm), _direct_loads(asm)
+    tiles = [k for k in _kernels(asm) if "linear_tile_kernel" in k]
+    straight = [k for k in tiles if not k.split("linear_tile_kernel")[1].startswith("ILi4ELi4ELi1ELi0E")]
+    assert len(straight) == len(tiles) - 1 == 9
+    for k in straight:
+        assert direct.get(k, 0) == bases.get(k, 0) >= 6, k
+    rows = [k for k in _kernels(asm) if re.search(r"attention_core_kernelI\w+Lb1E", k)]
+    assert len(rows) == 8 and all(direct.get(k, 0) > 0 for k in rows)
+    assert set(direct) == set(straight) | set(rows)
 
 
 def test_packed_gateup_tile_two_chunks_ahead_runs_two_workgroups_per_unit(ffn_asm):
