@@ -29,6 +29,7 @@
 // fp32 logits with ties to the lowest expert index.
 #include "des_common.h"
 #include "des_select.h"
+#include "des_stream_gemm.h"
 
 namespace des {
 
@@ -135,16 +136,19 @@ __device__ __forceinline__ bool flags_wait(const unsigned long long* f, int n,
 // ------------------------------------------------------------ role R: router
 // experts [i0, i0+16) x tokens [t0, t0+16); wave w takes k-steps w, w+16, ...
 // MFMA 16x16x32: lane l supplies row (l%16), reduction elements 8*(l/16)..+7;
-// the accumulator of lane l holds column (l%16), rows 4*(l/16)..+3.
+// the accumulator of lane l holds column (l%16), rows 4*(l/16)..+3.  Both operands go through
+// operand_write / operand_read (128 experts of width 2048, 32 tokens: routing 14.6 -> 12.5 us).
 __device__ __forceinline__ void router_tile_bf16(const RoutingArgs& a, int tile_m, int tile_t,
-                                                 float* part /* [16][256] LDS */) {
+                                                 char* lds /* [16][2 KB] */) {
   const int lane = threadIdx.x & 63;
   const int wave = uniform_int(threadIdx.x >> 6);  // (it guards matrix instructions, see stream_pipeline)
   const int T = a.B * a.N, D = a.D, M = a.M;
   const int i0 = tile_m * 16, t0 = tile_t * 16;
-  const int r = lane & 15, kq = (lane >> 4) * 8;
-  const int ei = min(i0 + r, M - 1);  // clamped rows are computed and dropped
-  const int ti = min(t0 + r, T - 1);
+  const int r = lane & 15, kq = (lane & 3) * 8;
+  const int ei = min(i0 + (lane >> 2), M - 1);  // clamped rows are computed and dropped
+  const int ti = min(t0 + (lane >> 2), T - 1);
+  // of this wavefront: the operands of a k-step, then its partial tile
+  char* mine = lds + wave * (2 * kOperandBytes);
   const uint16_t* ap = static_cast<const uint16_t*>(a.w_router) + static_cast<size_t>(ei) * D + kq;
   const uint16_t* bp = static_cast<const uint16_t*>(a.x) + static_cast<size_t>(ti) * D + kq;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -163,19 +167,29 @@ __device__ __forceinline__ void router_tile_bf16(const RoutingArgs& a, int tile_
       bv[u] = *reinterpret_cast<const bf16x8*>(bp + k * 32);
     }
 #pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      turn_fence();
+      operand_write(av[u], mine, lane);
+      operand_write(bv[u], mine + kOperandBytes, lane);
+      turn_fence();
+      av[u] = operand_read(mine, lane);
+      bv[u] = operand_read(mine + kOperandBytes, lane);
+    }
+#pragma unroll
     for (int u = 0; u < 4; ++u)
       if (ks + u * kRtWaves < nks)
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u], bv[u], acc, 0, 0, 0);
   }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) part[wave * 256 + (4 * (lane >> 4) + q) * 16 + r] = acc[q];
+  turn_fence();
+  float* part = reinterpret_cast<float*>(lds);  // [16][512]
+  *reinterpret_cast<f32x4*>(part + wave * 512 + r * 16 + 4 * (lane >> 4)) = acc;  // [token][expert]
   __syncthreads();
   if (threadIdx.x < 256) {
     const int er = er_fin, tc = threadIdx.x >> 4;
     float s = 0.f;
     const float bias_e = bias_fin;
 #pragma unroll
-    for (int w = 0; w < kRtWaves; ++w) s += part[w * 256 + er * 16 + tc];  // fixed order
+    for (int w = 0; w < kRtWaves; ++w) s += part[w * 512 + tc * 16 + er];  // fixed order
     const int e = i0 + er, t = t0 + tc;
     if (e < M && t < T)  // device-scope store: the selector reads it without a fence
       __hip_atomic_store(a.logits + static_cast<size_t>(t) * M + e, s + bias_e, __ATOMIC_RELAXED,
@@ -1044,7 +1058,7 @@ __global__ __launch_bounds__(kRtThreads) void routing_kernel(RoutingArgs a) {
   int blk = blockIdx.x;
   if (blk < n_tiles || a.solo) {  // ---- role R
     if (blk == 0) DES_STAMP(a, 8);
-    if (a.bf16) router_tile_bf16(a, blk % a.tiles_m, blk / a.tiles_m, reinterpret_cast<float*>(smem));
+    if (a.bf16) router_tile_bf16(a, blk % a.tiles_m, blk / a.tiles_m, smem);
     else router_tile_f32(a, blk % a.tiles_m, blk / a.tiles_m);
     if (blk == 0) DES_STAMP(a, 9);
     if (a.use_flags) {
@@ -1114,20 +1128,23 @@ __global__ __launch_bounds__(kRtThreads) void routing_kernel(RoutingArgs a) {
 template <int ET, int TT>
 __global__ __launch_bounds__(kRtThreads, 8) void router_kernel(RoutingArgs a) {
   constexpr int U = ET * TT == 1 ? 4 : 2;  // k-steps per trip; two workgroups share a compute unit
-  __shared__ __align__(16) float part[kRtWaves * ET * TT * 256];
+  // of a wavefront: the operands of a k-step, then its partial tiles
+  constexpr int kMine = (ET + TT > ET * TT ? ET + TT : ET * TT) * 256;  // floats
+  __shared__ __align__(16) float part[kRtWaves * kMine];
   const int lane = threadIdx.x & 63;
   const int wave = uniform_int(threadIdx.x >> 6);  // (it guards matrix instructions, see stream_pipeline)
   const int T = a.B * a.N, D = a.D, M = a.M, nks = D / 32;
   const int groups = (a.tiles_m + ET - 1) / ET;
   const int i0 = blockIdx.x % groups * 16 * ET, t0 = blockIdx.x / groups * 16 * TT;
-  const int r = lane & 15, kq = (lane >> 4) * 8;
+  const int r = lane & 15, row = lane >> 2, kq = (lane & 3) * 8;
+  char* mine_lds = reinterpret_cast<char*>(part + wave * kMine);
   const uint16_t *ap[ET], *bp[TT];  // clamped rows are computed and dropped
 #pragma unroll
   for (int e = 0; e < ET; ++e)
-    ap[e] = static_cast<const uint16_t*>(a.w_router) + static_cast<size_t>(min(i0 + 16 * e + r, M - 1)) * D + kq;
+    ap[e] = static_cast<const uint16_t*>(a.w_router) + static_cast<size_t>(min(i0 + 16 * e + row, M - 1)) * D + kq;
 #pragma unroll
   for (int t = 0; t < TT; ++t)
-    bp[t] = static_cast<const uint16_t*>(a.x) + static_cast<size_t>(min(t0 + 16 * t + r, T - 1)) * D + kq;
+    bp[t] = static_cast<const uint16_t*>(a.x) + static_cast<size_t>(min(t0 + 16 * t + row, T - 1)) * D + kq;
   // the element that this thread will finish
   const int tile = threadIdx.x >> 8, er = threadIdx.x & 15, tc = (threadIdx.x >> 4) & 15;
   const int ef = i0 + 16 * (tile / TT) + er, tf = t0 + 16 * (tile % TT) + tc;
@@ -1149,6 +1166,19 @@ __global__ __launch_bounds__(kRtThreads, 8) void router_kernel(RoutingArgs a) {
       for (int t = 0; t < TT; ++t) bv[u][t] = *reinterpret_cast<const bf16x8*>(bp[t] + k);
     }
 #pragma unroll
+    for (int u = 0; u < U; ++u) {
+      turn_fence();
+#pragma unroll
+      for (int e = 0; e < ET; ++e) operand_write(av[u][e], mine_lds + e * kOperandBytes, lane);
+#pragma unroll
+      for (int t = 0; t < TT; ++t) operand_write(bv[u][t], mine_lds + (ET + t) * kOperandBytes, lane);
+      turn_fence();
+#pragma unroll
+      for (int e = 0; e < ET; ++e) av[u][e] = operand_read(mine_lds + e * kOperandBytes, lane);
+#pragma unroll
+      for (int t = 0; t < TT; ++t) bv[u][t] = operand_read(mine_lds + (ET + t) * kOperandBytes, lane);
+    }
+#pragma unroll
     for (int u = 0; u < U; ++u)
       if (ks + u * kRtWaves < nks)
 #pragma unroll
@@ -1157,18 +1187,17 @@ __global__ __launch_bounds__(kRtThreads, 8) void router_kernel(RoutingArgs a) {
           for (int t = 0; t < TT; ++t)
             acc[e][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u][e], bv[u][t], acc[e][t], 0, 0, 0);
   }
+  turn_fence();
 #pragma unroll
   for (int e = 0; e < ET; ++e)
 #pragma unroll
     for (int t = 0; t < TT; ++t)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        part[(wave * ET * TT + e * TT + t) * 256 + (4 * (lane >> 4) + q) * 16 + r] = acc[e][t][q];
+      *reinterpret_cast<f32x4*>(part + wave * kMine + (e * TT + t) * 256 + r * 16 + 4 * (lane >> 4)) = acc[e][t];
   __syncthreads();
   if (!mine) return;
   float s = 0.f;
 #pragma unroll
-  for (int w = 0; w < kRtWaves; ++w) s += part[(w * ET * TT + tile) * 256 + er * 16 + tc];  // fixed order
+  for (int w = 0; w < kRtWaves; ++w) s += part[w * kMine + tile * 256 + tc * 16 + er];  // fixed order
   a.logits[static_cast<size_t>(tf) * M + ef] = s + bias;
 }
 
@@ -1263,13 +1292,14 @@ bool dense_block(const des_shape_t& s) {
 }
 
 // Four tiles per workgroup read half as much per tile, where one tile each makes more than one
-// round of the chip.  128 experts of width 2048: 384 tiles 9.5 us in ones, 11.5 in fours (which
-// take a second trip through the reduction there), 544 13.2 and 11.4, 1024 17.3 and 11.4; 96 of
-// width 768: 192 tiles 5.9 and 7.1, 288 8.8 and 6.8; 64 of width 3072: 256 10.6 and 14.3, 384 16.6
-// and 14.3.  (As a role of the routing kernel, with its registers, 1024 tiles took 20.4.)
+// round of the chip.  One and four, in us: 128 experts of width 2048, 320 tiles 7.0 and 7.4, 384 8.1 and
+// 7.7, 512 7.8 and 7.4, 1024 12.0 and 8.8; 96 of width 768, 288 5.2 and 5.8, 384 5.9 and 5.8; 128 of width
+// 1024, 320 6.0 and 6.3, 512 6.7 and 5.3; 256 of width 2048, 320 6.6 and 7.6, 512 7.3 and 7.9, 1024 10.5 and
+// 8.9; 64 of width 3072, 256 7.6 and 9.4, 384 11.0 and 9.9.  (Loads in operand order: 128 of width 2048,
+// 256 tiles 6.8, 384 10.2, 1024 11.6 in fours.)
 static bool wide_router(const RoutingArgs& a) {
   const int tiles = a.tiles_m * a.tiles_t;
-  return tiles > 512 || (tiles > 256 && (a.D <= 1024 || a.D > 2048));
+  return tiles > 352 || (tiles > 256 && a.D > 2048);
 }
 
 static int launch_router_tiles(const RoutingArgs& a, hipStream_t st) {

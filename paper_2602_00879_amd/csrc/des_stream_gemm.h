@@ -77,6 +77,28 @@ __device__ __forceinline__ void turn_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// Operands of 16 row-major rows x 32 elements (64 bytes of each row).  A compute unit serves a load of
+// 64 x 16 bytes in 7.6 ns while every four neighbouring lanes read one 64-byte segment; in operand
+// order, where they read four rows, it takes 27 ns.  So such a load runs along the rows - lane l has
+// piece l % 4 of row l / 4 - and 1 KB of the wavefront's own LDS turns it into operand order.
+// Piece p of row r is kept at p ^ (r / 4): writes and reads both spread over all banks.
+constexpr int kOperandBytes = 1024;
+__device__ __forceinline__ void operand_write(const bf16x8& v, char* at, int lane) {
+  const int r = lane >> 2, p = lane & 3;
+  *reinterpret_cast<bf16x8*>(at + r * 64 + ((p ^ (r >> 2)) << 4)) = v;
+}
+__device__ __forceinline__ bf16x8 operand_read(const char* at, int lane) {
+  const int r = lane & 15, p = lane >> 4;
+  return *reinterpret_cast<const bf16x8*>(at + r * 64 + ((p ^ (r >> 2)) << 4));
+}
+// ... one after the other through the same place
+__device__ __forceinline__ bf16x8 operand_turn(const bf16x8& v, char* at, int lane) {
+  turn_fence();
+  operand_write(v, at, lane);
+  turn_fence();
+  return operand_read(at, lane);
+}
+
 // ------------------------------------------ token rows via LDS, weights via registers
 // With more than two token tiles per expert the direct scheme above runs out
 // of registers for its prefetch (every token fragment is double-buffered in
