@@ -317,13 +317,17 @@ struct AttnArgs {
   uint16_t* o;                         // [T][H*dh] per-head outputs
   int B, N, H, Hkv, dh, P;
   int splits, tiles;                   // of a workgroup: parts of the window x query tiles (wavefronts)
+  int turn;                            // cut window: queries and keys go through LDS into operand order
   float scale;                         // 1 / sqrt(dh)
 };
 
 // LDS that the parts of a cut window exchange, after the values: maxima [8 wavefronts][16 queries],
-// running sums of the weights [tiles][64 lanes], the weights of two parts [2][tiles][steps][64 lanes][8].
+// running sums of the weights [tiles][64 lanes], the weights of two parts [2][tiles][steps][64 lanes][8];
+// before the weights, the same place turns the wavefronts' keys into operand order.
+constexpr size_t kKeyTurnBytes = 8 * kOperandBytes;  // of a workgroup
 __host__ __device__ constexpr size_t exchange_bytes(int tiles, int steps_of_part) {
-  return 512 + tiles * 256 + 2 * static_cast<size_t>(tiles) * steps_of_part * 1024;
+  const size_t ring = 2 * static_cast<size_t>(tiles) * steps_of_part * 1024;
+  return 512 + tiles * 256 + (ring > kKeyTurnBytes ? ring : kKeyTurnBytes);
 }
 
 // How the work of one (sequence, key/value head) is cut.  Its query rows - the block's
@@ -391,7 +395,7 @@ static AttnPlan attn_plan(const AttnArgs& a, size_t value_bytes) {
 //   kTwice  one wavefront per tile, the scores computed twice.
 // Weights are rounded to bf16 for the second contraction, their sum is kept in fp32.
 // What bounds it is latency - the loads behind one another, then the staging of the
-// values: eight sequences of 32 tokens over 496 positions, 32 heads on 4, take 19.6 us
+// values: eight sequences of 32 tokens over 496 positions, 32 heads on 4, take 16.3 us
 // (one workgroup per query head, half of its wavefronts idle, scores computed twice and
 // values transposed two bytes at a time: 49.6 us); one block over 64 positions 5.3 us.
 // A running maximum with the parts added up at the end was 1.6 us faster, but then the
@@ -402,6 +406,8 @@ enum AttnForm { kWhole, kWide, kParts, kTwice };
 template <int NKS, int FORM, bool ROWS>
 __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
   constexpr int NDT = 2 * NKS;
+  // Queries and keys of wide heads under a cut window may be loaded along their rows (a.turn)
+  const bool along = FORM == kParts && NKS == 4 && a.turn;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   uint16_t* vt = reinterpret_cast<uint16_t*>(smem_raw);  // [ndt * 16][ldv]: values, transposed (unless ROWS)
   const int N = a.N, dh = a.dh, P = a.P, nk = a.P + a.N;
@@ -424,19 +430,27 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
   auto row_of = [&](const uint16_t* cache, const uint16_t* block, int j) -> const uint16_t* {
     return j < P ? cache + static_cast<size_t>(j) * dh : block + static_cast<size_t>(j - P) * bstride;
   };
-  auto load8 = [&](const uint16_t* row, int s) -> bf16x8 {  // elements 32 s + 8 grp .. + 7, zeros past dh
-    const int e = 32 * s + 8 * grp;
+  const int lrow = along ? lane >> 2 : col, lpiece = along ? lane & 3 : grp;  // of a 16 x 32 operand, loading
+  char* turn = reinterpret_cast<char*>(smem_raw) + static_cast<size_t>(ndt) * 16 * ldv * 2 +
+               512 + a.tiles * 256 + wave * kOperandBytes;  // (in the place of the ring)
+  auto load8 = [&](const uint16_t* row, int s) -> bf16x8 {  // elements 32 s + 8 lpiece .. + 7, zeros past dh
+    const int e = 32 * s + 8 * lpiece;
     uint4 raw = make_uint4(0u, 0u, 0u, 0u);
     if (e < dh) raw = *reinterpret_cast<const uint4*>(row + e);
     return __builtin_bit_cast(bf16x8, raw);
   };
   // this lane's query row (rows past the last repeat it and are not stored)
-  const int row = (blockIdx.y * a.tiles + wave / S) * 16 + col, qrow = min(row, rows - 1);
-  const size_t qoff = (static_cast<size_t>(b) * N + qrow % N) * (a.H * dh) +
-                      static_cast<size_t>(g * rep + qrow / N) * dh;
+  const int row0 = (blockIdx.y * a.tiles + wave / S) * 16, row = row0 + col;
+  auto query_off = [&](int r) {
+    r = min(r, rows - 1);
+    return (static_cast<size_t>(b) * N + r % N) * (a.H * dh) + static_cast<size_t>(g * rep + r / N) * dh;
+  };
   bf16x8 qf[NKS];
+  {
+    const uint16_t* q = a.q + query_off(row0 + lrow);
 #pragma unroll
-  for (int s = 0; s < NKS; ++s) qf[s] = load8(a.q + qoff, s);
+    for (int s = 0; s < NKS; ++s) qf[s] = load8(q, s);
+  }
   // this wavefront's part of the window, in steps of 32 positions
   const int per = (steps + S - 1) / S;
   const int s0 = min(part * per, steps), s1 = wave < S * a.tiles ? min(s0 + per, steps) : s0;
@@ -446,7 +460,7 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
     constexpr int z = decltype(set)::value;
 #pragma unroll
     for (int i = 0; i < KT; ++i) {
-      const uint16_t* krow = row_of(kc, kb, min(32 * st + 16 * i + col, nk - 1));
+      const uint16_t* krow = row_of(kc, kb, min(32 * st + 16 * i + lrow, nk - 1));
 #pragma unroll
       for (int s = 0; s < NKS; ++s) kf[z][i][s] = st + i / 2 < s1 ? load8(krow, s) : bf16x8{};
     }
@@ -525,11 +539,21 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
   f32x4 oacc[NDT];
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt) oacc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (along) {
+#pragma unroll
+    for (int s = 0; s < NKS; ++s) qf[s] = operand_turn(qf[s], turn, lane);
+  }
   // positions of this lane from step st on that count: inside the window and inside the part
   auto limit = [&](int st) { return min(nk, 32 * s1) - (32 * st + 4 * grp); };
   // scores of the key tiles of a set; the maximum takes them in
   auto scores = [&](int st, auto set, f32x4* sc) {
     constexpr int z = decltype(set)::value;
+    if (along) {
+#pragma unroll
+      for (int i = 0; i < KT; ++i)
+#pragma unroll
+        for (int s = 0; s < NKS; ++s) kf[z][i][s] = operand_turn(kf[z][i][s], turn, lane);
+    }
 #pragma unroll
     for (int i = 0; i < KT; ++i) {
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -595,7 +619,7 @@ __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
       }
     }
   };
-  uint16_t* orow = a.o + qoff;
+  uint16_t* orow = a.o + query_off(row);
   auto store = [&](int dt, const f32x4& o, float inv) {
     const int d0 = 16 * dt + 4 * grp;
     if (row < rows && d0 < dh) {
@@ -908,6 +932,15 @@ int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void
   const AttnPlan pl = attn_plan(c, attn_core_lds(s, t));
   c.splits = pl.splits;
   c.tiles = pl.tiles;
+  // Where four wavefronts or more share a compute unit their key loads in operand order queue up (see
+  // operand_write): heads of 128, eight sequences over 496 positions 19.3 -> 16.3 us, 128 tokens over 568
+  // 16.0 -> 14.2, 30 x 17 over 457 49.4 -> 42.4.  With fewer the way through LDS is what counts (one block
+  // over 272 positions, 256 wavefronts: 11.4 and 11.9; whole windows: 64 positions 6.0 and 6.4, 16 x 128 over
+  // 528 level), and so it is for heads up to 96 (30 x 17: 26.6 and 27.9; of 64 16.6 and 20.0) and for one or
+  // two query tiles per key/value head, where the keys come from memory (16 heads on 16, 16 x 16 over 416:
+  // 15.2 and 16.1; 30 x 17 over 457: 39.6 and 40.5).
+  const int query_tiles = pl.groups * pl.tiles;
+  c.turn = query_tiles >= 4 && s.n_seqs * t.n_kv_heads * query_tiles * pl.splits >= 1024;
   const int waves = pl.splits * pl.tiles, nks = (t.head_dim + 31) / 32;
   const size_t lds = pl.lds;
   // (four wavefronts stage faster than one)
