@@ -140,6 +140,9 @@ inline bool dense_shape(const des_shape_t& s) {
          !(s.n_group > 1 && s.topk_group < s.n_group);
 }
 bool dense_block(const des_shape_t& s);  // dense_shape and the routing fits one launch
+// At most 32 tokens, bf16: spare workgroups of the routing launch leave x in the order of the gate/up
+// projection's operand loads, in the place of O (which the down projection writes, after that).
+bool x_in_operand_order(const des_shape_t& s);
 
 struct DenseArgs {
   int on;                  // 0: general path

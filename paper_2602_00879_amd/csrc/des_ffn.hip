@@ -45,6 +45,7 @@ struct FfnArgs {
   const int32_t* units;         // live units of the routed experts, longest expert first:
                                 // slot | split << 16 | splits of that slot << 24; meta[2] of them
   size_t h_rows;                // routed rows of H (the shared expert's rows follow them)
+  const uint16_t* xo;           // at most 32 tokens: x in operand order (see operand_off), or null
   DenseArgs dn;                 // dense short block: stage 2 beside gate/up, see des_common.h
 };
 
@@ -106,6 +107,14 @@ __device__ __forceinline__ size_t load_off(int i, int kd) {
   return PACKED ? static_cast<size_t>(i) * 512 : static_cast<size_t>(i & 1) * 8 * kd + (i >> 1) * 64;
 }
 
+// x of at most 32 tokens in operand order, eight elements of a token next to the same eight of the
+// following ones: element offset of piece `oct` (elements 8 * oct ..) of token t.  The lanes of an
+// operand load then read runs of 256 bytes; in rows they read four rows per four lanes, at a quarter of
+// the rate (see operand_write), which bounds the kernel where a wavefront has few weight rows per token
+// fragment (17 experts of 2048 x 512, 32 tokens, 16 units per wavefront: 20.0 -> 18.4 us; 32 of
+// 2048 x 768 in 32 units, where the weights do: 34.5 -> 34.0).
+__device__ __forceinline__ int operand_off(int oct, int t, int T) { return (oct * T + t) * 8; }
+
 // gate/up for the task's pairs (at most 16*NT), intermediate rows
 // (ft0 .. ft0+FT-1)*16..+15.  The FT row tiles share every token fragment.
 template <int FT, int NT, int U, bool PACKED>
@@ -123,11 +132,12 @@ __device__ __forceinline__ void gateup_group(const FfnArgs& a, const Task& t, in
     up[f] = load_ptr<PACKED>(t.w1, ft0 + f, D, lane);
   }
   const uint16_t* xp[NT];
+  const int xstep = a.xo ? 32 * a.T : 32;  // elements to the next k-step
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
     int pi = min(i * 16 + (lane & 15), t.count - 1);  // clamped rows are dropped at the store
     const int tok = t.shared ? pi : t.pre_tok[i];
-    xp[i] = x + static_cast<size_t>(tok) * D + (lane >> 4) * 8;
+    xp[i] = a.xo ? a.xo + operand_off(lane >> 4, tok, a.T) : x + static_cast<size_t>(tok) * D + (lane >> 4) * 8;
   }
   f32x4 accg[FT][NT], accu[FT][NT];
 #pragma unroll
@@ -149,7 +159,7 @@ __device__ __forceinline__ void gateup_group(const FfnArgs& a, const Task& t, in
         au[s][u][f] = ld8_stream(up[f] + load_off<PACKED>(ks, D));
       }
 #pragma unroll
-      for (int i = 0; i < NT; ++i) bx[s][u][i] = ld8(xp[i] + ks * 32);
+      for (int i = 0; i < NT; ++i) bx[s][u][i] = ld8(xp[i] + ks * xstep);
     }
   };
   auto compute = [&](auto stage) {
@@ -186,7 +196,7 @@ __device__ __forceinline__ void gateup_group(const FfnArgs& a, const Task& t, in
   for (int ks = nks / U * U; ks < nks; ++ks) {  // k-steps left over by the stages
     bf16x8 x1[NT];
 #pragma unroll
-    for (int i = 0; i < NT; ++i) x1[i] = ld8(xp[i] + ks * 32);
+    for (int i = 0; i < NT; ++i) x1[i] = ld8(xp[i] + ks * xstep);
 #pragma unroll
     for (int f = 0; f < FT; ++f) {
       const bf16x8 g1 = ld8_stream(frag_ptr<PACKED>(t.w0, ft0 + f, D, lane) + static_cast<size_t>(ks) * frag_step<PACKED>());
@@ -1086,6 +1096,7 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
   a.residual = s.residual;
   a.splits = 1;
   a.h_rows = w.h_rows;
+  a.xo = x_in_operand_order(s) ? reinterpret_cast<const uint16_t*>(ws + w.o) : nullptr;
   a.dn = DenseArgs{};
   int n_s2 = 0;  // wavefronts of the gate/up launch that run stage 2 (dense short block)
   if (dense_block(s)) {

@@ -99,6 +99,8 @@ struct RoutingArgs {
                           // and the slot table of the coreset; stage 2 runs beside the gate/up
                           // projection, there is no permutation
   uint32_t* tokmask;      // [n_slots] cleared here for that stage 2
+  uint16_t* xo;           // [D / 8][T][8] x in operand order, by the workgroups from x_first on, or null
+  int x_first;
 };
 
 // ------------------------------------------------------------------ flags
@@ -1056,6 +1058,15 @@ __global__ __launch_bounds__(kRtThreads) void routing_kernel(RoutingArgs a) {
   __shared__ __align__(16) char smem[kLds];
   const int n_tiles = (a.do_router && !a.skip_router_tiles && !a.solo) ? a.tiles_m * a.tiles_t : 0;
   int blk = blockIdx.x;
+  if (a.xo != nullptr && blk >= a.x_first) {  // x for the gate/up launch; nobody in this launch waits for it
+    const int T = a.B * a.N, pieces = T * (a.D / 8), step = (gridDim.x - a.x_first) * kRtThreads;
+    for (int p = (blk - a.x_first) * kRtThreads + threadIdx.x; p < pieces; p += step) {
+      const int oct = p / (4 * T) * 4 + p % 4, t = p / 4 % T;  // (four neighbouring lanes along a row)
+      *reinterpret_cast<uint4*>(a.xo + (static_cast<size_t>(oct) * T + t) * 8) =
+          *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.x) + static_cast<size_t>(t) * a.D + oct * 8);
+    }
+    return;
+  }
   if (blk < n_tiles || a.solo) {  // ---- role R
     if (blk == 0) DES_STAMP(a, 8);
     if (a.bf16) router_tile_bf16(a, blk % a.tiles_m, blk / a.tiles_m, smem);
@@ -1281,6 +1292,27 @@ static void fill_common(RoutingArgs& a, const des_shape_t& s) {
   }
 }
 
+// Selector workgroups per sequence and workgroups in all (without those that only copy x) of
+// launch_routing's single launch, and whether all can be resident at once.
+struct RoutingRoles { int groups, roles; bool fit; };
+static RoutingRoles routing_roles(const des_shape_t& s) {
+  const int n_tiles = ((s.n_experts + 15) / 16) * ((s.n_seqs * s.n_tokens + 15) / 16);
+  int fused_limit = device_compute_units();
+  if (fused_limit > kMaxFusedRoutingBlocks) fused_limit = kMaxFusedRoutingBlocks;
+  // A selector workgroup handles selector_tokens_per_pass() tokens at once; a
+  // longer sequence is spread over several selector workgroups when they all fit.
+  const int tpp = selector_tokens_per_pass(s.n_experts);
+  int groups = (s.n_tokens + tpp - 1) / tpp;
+  if (groups > kMaxSelGroups / s.n_seqs) groups = kMaxSelGroups / s.n_seqs > 0 ? kMaxSelGroups / s.n_seqs : 1;
+  if (n_tiles + s.n_seqs * groups + 1 > fused_limit) groups = 1;
+  const int roles = n_tiles + s.n_seqs * groups + (s.n_seqs * groups > 1 ? 1 : 0);
+  return RoutingRoles{groups, roles, roles <= fused_limit};
+}
+
+bool x_in_operand_order(const des_shape_t& s) {
+  return s.dtype == DES_BF16 && s.n_seqs * s.n_tokens <= 32 && routing_roles(s).fit;
+}
+
 // The conditions of launch_routing's single launch with one selector workgroup, for a
 // shape that qualifies (dense_shape): the FFN launches must take the same decision.
 bool dense_block(const des_shape_t& s) {
@@ -1374,35 +1406,35 @@ int launch_routing(const des_shape_t& s, const void* x, const void* w_router, co
   a.rows_shift = lds_rows_pass(s.n_seqs * s.n_tokens) == 64 ? 6 : 7;
   a.sel_part = reinterpret_cast<uint32_t*>(ws + w.sel_part);
   const int n_tiles = a.tiles_m * a.tiles_t;
-  int fused_limit = device_compute_units();
-  if (fused_limit > kMaxFusedRoutingBlocks) fused_limit = kMaxFusedRoutingBlocks;
-  // A selector workgroup handles selector_tokens_per_pass() tokens at once; a
-  // longer sequence is spread over several selector workgroups when they all fit.
-  const int tpp = selector_tokens_per_pass(s.n_experts);
-  int groups = (s.n_tokens + tpp - 1) / tpp;
-  if (groups > kMaxSelGroups / a.B) groups = kMaxSelGroups / a.B > 0 ? kMaxSelGroups / a.B : 1;
-  if (n_tiles + a.B * groups + 1 > fused_limit) groups = 1;
-  const int roles = n_tiles + a.B * groups + (a.B * groups > 1 ? 1 : 0);
+  const auto [groups, roles, fit] = routing_roles(s);
   // One selector workgroup and at most 32 tokens: the short permutation.  (Skipping
   // drops a token's experts after they were drawn, so the bitmaps of stage 2 would name
   // pairs that no longer exist: it keeps the general permutation.)
   const bool small = a.B == 1 && groups == 1 && s.n_tokens <= 32 && !(s.skip_beta > 0.0f);
-  if (roles <= fused_limit) {  // all workgroups resident at once: one launch
+  if (fit) {  // all workgroups resident at once: one launch
     a.groups = groups;
     a.small_perm = small;
     a.dense = dense_block(s) ? 1 : 0;
     a.tokmask = reinterpret_cast<uint32_t*>(ws + w.tokmask);
     a.do_router = a.do_select = a.do_permute = 1;
     a.use_flags = 1;
+    int n_x = 0;
+    if (x_in_operand_order(s)) {
+      a.xo = reinterpret_cast<uint16_t*>(ws + w.o);
+      const int pieces = s.n_seqs * s.n_tokens * (s.hidden / 8);
+      n_x = pieces > 16 * kRtThreads ? 16 : (pieces + kRtThreads - 1) / kRtThreads;
+    }
     if (g_test_skip_router) {  // test hook: nobody computes the logits, the selectors' wait expires
       a.skip_router_tiles = 1;
       if (g_test_skip_router == 2) g_test_skip_router = g_test_max_wait = 0;  // one launch only
-      return launch_routing_grid(a, roles - n_tiles, kKRouting, st);
+      a.x_first = roles - n_tiles;
+      return launch_routing_grid(a, a.x_first + n_x, kKRouting, st);
     }
     // A single tile: handing it to another workgroup would cost more than it saves (8 tokens, 16
     // experts of width 256, fp32: routing 14.4 -> 13.4 us).
     a.solo = n_tiles == 1 && roles == 2;
-    return launch_routing_grid(a, a.solo ? 1 : roles, kKRouting, st);
+    a.x_first = a.solo ? 1 : roles;
+    return launch_routing_grid(a, a.x_first + n_x, kKRouting, st);
   }
   // too large to wait inside one launch: the same roles as three launches
   RoutingArgs r = a;
