@@ -171,6 +171,11 @@ def _stream() -> int:
     return _raw_stream(torch.cuda.current_device())
 
 
+# outputs of the smallest calls, which are bound by this host path: torch.empty takes 1.7 us for a
+# tensor, this and empty_like 1.3 (route and select of 32 tokens, six outputs: 22.4 us in all)
+_empty_strided = torch.empty_strided
+
+
 def des_coreset_capacity(shape: DesShape) -> int:
     return int(lib().des_coreset_capacity(ctypes.byref(shape)))
 
@@ -187,7 +192,7 @@ def des_route(shape: DesShape, x: torch.Tensor, w_router: torch.Tensor,
               router_bias: Optional[torch.Tensor], want_probs: bool = True
               ) -> Tuple[torch.Tensor, Optional[torch.Tensor]]:
     B, N, M = shape.n_seqs, shape.n_tokens, shape.n_experts
-    logits = torch.empty((B, N, M), dtype=torch.float32, device=x.device)
+    logits = _empty_strided((B, N, M), (N * M, M, 1), dtype=torch.float32, device=x.device)
     probs = torch.empty_like(logits) if want_probs else None
     _check(lib().des_route(ctypes.byref(shape), _ptr(x), _ptr(w_router), _ptr(router_bias),
                            _ptr(logits), _ptr(probs), _stream()))
@@ -200,13 +205,14 @@ def des_select_coreset(shape: DesShape, logits: torch.Tensor,
     if out is None:
         B, M, dev = shape.n_seqs, shape.n_experts, logits.device
         cap = des_coreset_capacity(shape)
-        # (under DES-Vote the call writes every vote; otherwise there are none: zeros)
-        fill = torch.empty if shape.mode == DES_VOTE else torch.zeros
+        size = _empty_strided((B,), (1,), dtype=torch.int32, device=dev)
         out = dict(
-            coreset_idx=torch.empty((B, cap), dtype=torch.int32, device=dev),
-            coreset_size=torch.empty((B,), dtype=torch.int32, device=dev),
-            votes=fill((B, M), dtype=torch.float32, device=dev),
-            k_seq_used=torch.empty((B,), dtype=torch.int32, device=dev),
+            coreset_idx=_empty_strided((B, cap), (cap, 1), dtype=torch.int32, device=dev),
+            coreset_size=size,
+            # (under DES-Vote the call writes every vote; otherwise there are none: zeros)
+            votes=(_empty_strided((B, M), (M, 1), dtype=torch.float32, device=dev) if shape.mode == DES_VOTE
+                   else torch.zeros((B, M), dtype=torch.float32, device=dev)),
+            k_seq_used=torch.empty_like(size),
         )
     _check(lib().des_select_coreset(ctypes.byref(shape), _ptr(logits), _ptr(out["coreset_idx"]),
                                     _ptr(out["coreset_size"]), _ptr(out["votes"]),
