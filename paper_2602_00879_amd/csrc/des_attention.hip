@@ -322,12 +322,10 @@ struct AttnArgs {
 };
 
 // LDS that the parts of a cut window exchange, after the values: maxima [8 wavefronts][16 queries],
-// running sums of the weights [tiles][64 lanes], the weights of two parts [2][tiles][steps][64 lanes][8];
-// before the weights, the same place turns the wavefronts' keys into operand order.
-constexpr size_t kKeyTurnBytes = 8 * kOperandBytes;  // of a workgroup
+// running sums of the weights [tiles][64 lanes], the weights of two parts [2][tiles][steps][64 lanes][8]
+// (before the weights, the same place may turn the wavefronts' keys into operand order).
 __host__ __device__ constexpr size_t exchange_bytes(int tiles, int steps_of_part) {
-  const size_t ring = 2 * static_cast<size_t>(tiles) * steps_of_part * 1024;
-  return 512 + tiles * 256 + (ring > kKeyTurnBytes ? ring : kKeyTurnBytes);
+  return 512 + tiles * 256 + 2 * static_cast<size_t>(tiles) * steps_of_part * 1024;
 }
 
 // How the work of one (sequence, key/value head) is cut.  Its query rows - the block's
@@ -940,9 +938,11 @@ int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void
   // two query tiles per key/value head, where the keys come from memory (16 heads on 16, 16 x 16 over 416:
   // 15.2 and 16.1; 30 x 17 over 457: 39.6 and 40.5).
   const int query_tiles = pl.groups * pl.tiles;
-  c.turn = query_tiles >= 4 && s.n_seqs * t.n_kv_heads * query_tiles * pl.splits >= 1024;
   const int waves = pl.splits * pl.tiles, nks = (t.head_dim + 31) / 32;
-  const size_t lds = pl.lds;
+  const size_t with_turn = attn_core_lds(s, t) + 512 + pl.tiles * 256 + (waves < 4 ? 4 : waves) * kOperandBytes;
+  c.turn = pl.splits > 1 && query_tiles >= 4 && s.n_seqs * t.n_kv_heads * query_tiles * pl.splits >= 1024 &&
+           with_turn <= 160 * 1024;
+  const size_t lds = c.turn && with_turn > pl.lds ? with_turn : pl.lds;
   // (four wavefronts stage faster than one)
   const dim3 grid(s.n_seqs * t.n_kv_heads, pl.groups), block((waves < 4 ? 4 : waves) * kWave);
   auto core = [&](auto kernel) -> int {
