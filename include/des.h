@@ -380,6 +380,13 @@ int des_kernel_timing_read(int kernel_id, double* total_ms, int64_t* launches);
 int des_test_hooks(int skip_router, int max_wait_iters);
 
 /*
+ * Test aid: the next call that asks for the number of the device's compute units is told `units`
+ * (0: as if the question had failed), once; after that the device is asked again.  A layer's routing
+ * is one launch where its workgroups fit that number, else three.  Process-wide, not thread-safe.
+ */
+int des_test_compute_units(int units);
+
+/*
  * Test aid, host only: the form that a call's launch would have, so that a test can hold the
  * shapes it picks to the forms it is there for.  launch 0 / 1: the attention sub-layer's q/k/v /
  * output projection; plan = {weight rows / 32, token rows / 32 of a tile, groups that share its

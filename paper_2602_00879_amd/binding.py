@@ -27,7 +27,7 @@ EXPORTS = (
     "des_kernel_timing_enable", "des_kernel_timing_count", "des_kernel_timing_name",
     "des_kernel_timing_read", "des_hbm_read_probe", "des_coreset_from_beta", "des_test_hooks",
     "des_attention_workspace_bytes", "des_block_attention", "des_decoder_workspace_bytes",
-    "des_decoder_stack_forward", "des_test_plan",
+    "des_decoder_stack_forward", "des_test_plan", "des_test_compute_units",
 )
 
 
@@ -103,6 +103,8 @@ def lib() -> ctypes.CDLL:
         L.des_coreset_from_beta.argtypes = [ctypes.c_double, i32]
         L.des_test_hooks.restype = ctypes.c_int
         L.des_test_hooks.argtypes = [ctypes.c_int, ctypes.c_int]
+        L.des_test_compute_units.restype = ctypes.c_int
+        L.des_test_compute_units.argtypes = [ctypes.c_int]
         L.des_test_plan.restype = ctypes.c_int
         L.des_test_plan.argtypes = [sp, ap, i32, ctypes.POINTER(i32)]
         L.des_strerror.restype = ctypes.c_char_p
@@ -382,6 +384,11 @@ def des_test_hooks(skip_router, max_wait_iters: int) -> None:
     """Test aid: forces the give-up path of the bounded waits ((0, 0) = normal;
     skip_router = 2: for the next fused routing launch only)."""
     _check(lib().des_test_hooks(int(skip_router), int(max_wait_iters)))
+
+
+def des_test_compute_units(units: int) -> None:
+    """Test aid: the answer to the next question for the device's compute units (see des.h)."""
+    _check(lib().des_test_compute_units(int(units)))
 
 
 def des_test_plan(shape: DesShape, attn: Optional[DesAttnShape], launch: int) -> Tuple[int, ...]:

@@ -195,10 +195,11 @@ int des_moe_forward(const des_shape_t* s, const void* x, const void* w_router,
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   char* ws = static_cast<char*>(workspace);
   const unsigned long long epoch = next_epoch();
-  rc = launch_routing(*s, x, w_router, router_bias, logits, coreset_idx, coreset_size, topk_idx,
+  const LayerForm form = layer_form(*s);
+  rc = launch_routing(*s, form, x, w_router, router_bias, logits, coreset_idx, coreset_size, topk_idx,
                       topk_w, expert_counts, n_unique, nullptr, ws, epoch, st);
   if (rc != DES_OK) return rc;
-  return launch_ffn(*s, x, w_gate, w_up, w_down, ws_gate, ws_up, ws_down, logits, topk_idx, topk_w,
+  return launch_ffn(*s, form, x, w_gate, w_up, w_down, ws_gate, ws_up, ws_down, logits, topk_idx, topk_w,
                     expert_counts, n_unique, y, ws, epoch, st);
 }
 
@@ -269,6 +270,7 @@ int des_moe_stack_forward(const des_shape_t* s_in, int32_t n_layers, const void*
   char* ws = static_cast<char*>(workspace);
   const size_t el = s.dtype == DES_BF16 ? 2 : 4;
   const size_t M = s.n_experts, D = s.hidden, F = s.ffn, Fs = s.ffn_shared;
+  const LayerForm form = layer_form(s);  // (of every layer)
   const char* cur = static_cast<const char*>(x);
   for (int layer = 0; layer < n_layers; ++layer) {
     // the last layer writes y; the others alternate between the two buffers
@@ -288,12 +290,12 @@ int des_moe_stack_forward(const des_shape_t* s_in, int32_t n_layers, const void*
     float* tw = reinterpret_cast<float*>(ws + l.topk_w);
     char* lws = ws + l.layer_ws;
     const unsigned long long epoch = next_epoch();
-    rc = launch_routing(s, cur, wr, rb, logits, reinterpret_cast<int32_t*>(ws + l.core_idx),
+    rc = launch_routing(s, form, cur, wr, rb, logits, reinterpret_cast<int32_t*>(ws + l.core_idx),
                         reinterpret_cast<int32_t*>(ws + l.core_size), tidx, tw,
                         expert_counts + li * M, n_unique + li,
                         layer > 0 ? n_unique + li - 1 : nullptr, lws, epoch, st);
     if (rc != DES_OK) return rc;
-    rc = launch_ffn(s, cur, wg, wu, wd, sg, su, sd, logits, tidx, tw, expert_counts + li * M,
+    rc = launch_ffn(s, form, cur, wg, wu, wd, sg, su, sd, logits, tidx, tw, expert_counts + li * M,
                     n_unique + li, out, lws, epoch, st);
     if (rc != DES_OK) return rc;
     cur = out;
@@ -376,6 +378,7 @@ int des_decoder_stack_forward(const des_shape_t* s_in, const des_attn_shape_t* t
   const size_t HD = static_cast<size_t>(t->n_heads) * t->head_dim;
   const size_t KD = static_cast<size_t>(t->n_kv_heads) * t->head_dim;
   const size_t cache = static_cast<size_t>(s.n_seqs) * t->n_kv_heads * attn_cached(*t) * t->head_dim;
+  const LayerForm form = layer_form(s);  // (of every layer)
   const char* cur = static_cast<const char*>(x);
   for (int layer = 0; layer < n_layers; ++layer) {
     const size_t li = static_cast<size_t>(layer);
@@ -403,11 +406,11 @@ int des_decoder_stack_forward(const des_shape_t* s_in, const des_attn_shape_t* t
     float* tw = reinterpret_cast<float*>(ws + l.topk_w);
     char* lws = ws + l.layer_ws;
     const unsigned long long epoch = next_epoch();
-    rc = launch_routing(s, a, wr, rb, logits, reinterpret_cast<int32_t*>(ws + l.core_idx),
+    rc = launch_routing(s, form, a, wr, rb, logits, reinterpret_cast<int32_t*>(ws + l.core_idx),
                         reinterpret_cast<int32_t*>(ws + l.core_size), tidx, tw, expert_counts + li * M,
                         n_unique + li, layer > 0 ? n_unique + li - 1 : nullptr, lws, epoch, st);
     if (rc != DES_OK) return rc;
-    rc = launch_ffn(s, a, wg, wu, wd, sg, su, sd, logits, tidx, tw, expert_counts + li * M,
+    rc = launch_ffn(s, form, a, wg, wu, wd, sg, su, sd, logits, tidx, tw, expert_counts + li * M,
                     n_unique + li, out, lws, epoch, st);
     if (rc != DES_OK) return rc;
     cur = out;
@@ -443,6 +446,12 @@ int des_test_hooks(int skip_router, int max_wait_iters) {
   if (max_wait_iters < 0) return DES_ERR_SHAPE;
   g_test_skip_router = skip_router < 0 ? 0 : (skip_router > 2 ? 1 : skip_router);
   g_test_max_wait = max_wait_iters;
+  return DES_OK;
+}
+
+int des_test_compute_units(int units) {
+  if (units < 0) return DES_ERR_SHAPE;
+  g_test_compute_units = units;
   return DES_OK;
 }
 

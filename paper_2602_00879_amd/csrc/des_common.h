@@ -97,8 +97,6 @@ inline int max_live_experts(const des_shape_t& s) {
 // unit, and never more than this.
 constexpr int kMaxFusedRoutingBlocks = 256;
 
-int device_compute_units();          // of the current device (cached)
-
 // Blocks of more than 32 tokens: an expert's pairs are handed to the FFN
 // workgroups in units of at most this many token rows (what one workgroup holds); an expert
 // with more has as many units as it takes.  The permutation lists the live units, longest
@@ -139,10 +137,19 @@ inline bool dense_shape(const des_shape_t& s) {
          (s.k_route == 0 || s.k_route == s.top_k) && !(s.skip_beta > 0.0f) &&
          !(s.n_group > 1 && s.topk_group < s.n_group);
 }
-bool dense_block(const des_shape_t& s);  // dense_shape and the routing fits one launch
-// At most 32 tokens, bf16: spare workgroups of the routing launch leave x in the order of the gate/up
-// projection's operand loads, in the place of O (which the down projection writes, after that).
-bool x_in_operand_order(const des_shape_t& s);
+
+// How a layer's routing is launched.  The FFN launches read what it leaves, so one layer call decides
+// once and hands the decision to both: asked twice, two answers about the device could differ.
+struct LayerForm {
+  int groups;   // selector workgroups per sequence
+  int roles;    // workgroups of the single launch, without those that only copy x
+  bool fused;   // all of them can be resident at once: one launch
+  bool dense;   // dense_shape, one launch and one selector workgroup
+  bool x_copy;  // at most 32 tokens, bf16, one launch: spare workgroups of it leave x in the order of the
+                // gate/up projection's operand loads, in the place of O (the down projection writes
+                // that, after gate/up)
+};
+LayerForm layer_form(const des_shape_t& s);  // of a launch on the current device
 
 struct DenseArgs {
   int on;                  // 0: general path
@@ -221,16 +228,16 @@ int launch_softmax(const des_shape_t& s, const float* logits, float* probs, hipS
 int launch_select(const des_shape_t& s, const float* logits, int32_t* coreset_idx,
                   int32_t* coreset_size, float* votes, int32_t* k_seq_used, hipStream_t st);
 // router + election + re-routing + permutation (one launch when it fits)
-int launch_routing(const des_shape_t& s, const void* x, const void* w_router, const float* bias,
-                   float* logits, int32_t* coreset_idx, int32_t* coreset_size, int32_t* topk_idx,
-                   float* topk_w, int32_t* expert_counts, int32_t* n_unique,
+int launch_routing(const des_shape_t& s, const LayerForm& form, const void* x, const void* w_router,
+                   const float* bias, float* logits, int32_t* coreset_idx, int32_t* coreset_size,
+                   int32_t* topk_idx, float* topk_w, int32_t* expert_counts, int32_t* n_unique,
                    const int32_t* prev_n_unique, char* ws, unsigned long long epoch,
                    hipStream_t st);
 // Test hooks of the routing launch (des_test_hooks).
-extern int g_test_max_wait, g_test_skip_router;
-int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const void* w_up,
-               const void* w_down, const void* ws_gate, const void* ws_up, const void* ws_down,
-               const float* logits, int32_t* topk_idx, float* topk_w, int32_t* expert_counts,
+extern int g_test_max_wait, g_test_skip_router, g_test_compute_units;
+int launch_ffn(const des_shape_t& s, const LayerForm& form, const void* x, const void* w_gate,
+               const void* w_up, const void* w_down, const void* ws_gate, const void* ws_up,
+               const void* ws_down, const float* logits, int32_t* topk_idx, float* topk_w, int32_t* expert_counts,
                int32_t* n_unique, void* y, char* ws, unsigned long long epoch, hipStream_t st);
 // Attention sub-layer (des_attention.hip): scratch layout, LDS need of the per-head
 // kernel, and the three launches.

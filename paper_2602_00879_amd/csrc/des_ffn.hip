@@ -1071,9 +1071,9 @@ int launch_read_probe(const void* src, size_t bytes, void* sink, hipStream_t st)
 }
 
 // ------------------------------------------------------------------ launcher
-int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const void* w_up,
-               const void* w_down, const void* ws_gate, const void* ws_up, const void* ws_down,
-               const float* logits, int32_t* topk_idx, float* topk_w, int32_t* expert_counts,
+int launch_ffn(const des_shape_t& s, const LayerForm& form, const void* x, const void* w_gate,
+               const void* w_up, const void* w_down, const void* ws_gate, const void* ws_up,
+               const void* ws_down, const float* logits, int32_t* topk_idx, float* topk_w, int32_t* expert_counts,
                int32_t* n_unique, void* y, char* ws, unsigned long long epoch, hipStream_t st) {
   const WsLayout w = ws_layout(s);
   FfnArgs a;
@@ -1096,10 +1096,10 @@ int launch_ffn(const des_shape_t& s, const void* x, const void* w_gate, const vo
   a.residual = s.residual;
   a.splits = 1;
   a.h_rows = w.h_rows;
-  a.xo = x_in_operand_order(s) ? reinterpret_cast<const uint16_t*>(ws + w.o) : nullptr;
+  a.xo = form.x_copy ? reinterpret_cast<const uint16_t*>(ws + w.o) : nullptr;
   a.dn = DenseArgs{};
   int n_s2 = 0;  // wavefronts of the gate/up launch that run stage 2 (dense short block)
-  if (dense_block(s)) {
+  if (form.dense) {
     a.dn.on = 1;
     a.dn.lpt = 1024 / selector_tokens_per_pass(s.n_experts);
     a.dn.sigmoid = s.router_act == DES_ROUTER_SIGMOID;

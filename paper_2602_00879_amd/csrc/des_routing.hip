@@ -27,6 +27,8 @@
 // votes stay in the owning lane's registers, and rows / waves are combined in a
 // fixed order.  Every ranking compares order-preserving integer keys of the
 // fp32 logits with ties to the lowest expert index.
+#include <atomic>
+
 #include "des_common.h"
 #include "des_select.h"
 #include "des_stream_gemm.h"
@@ -38,6 +40,7 @@ constexpr int kRtThreads = kRtWaves * kWave;  // 1024
 constexpr int kMaxWaitIters = 1 << 22;        // bounded waits (~ seconds), then give up
 int g_test_max_wait = 0;     // test hooks (des_test_hooks): a tiny wait bound, and a fused
 int g_test_skip_router = 0;  // routing launch without its router tiles, so that a wait expires
+int g_test_compute_units = -1;  // (des_test_compute_units) answer to the next question for their number
 
 #ifdef DES_ROUTING_TIMESTAMPS  // development aid: 100 MHz timestamps into meta[16..]
 #define DES_STAMP(a, i) do { if (threadIdx.x == 0 && (a).meta != nullptr) reinterpret_cast<long long*>((a).meta + 16)[i] = wall_clock64(); } while (0)
@@ -95,7 +98,7 @@ struct RoutingArgs {
   int skip_router_tiles;  // test hook: the fused launch runs without its router tiles
   int small_perm;         // one selector workgroup, at most 32 tokens, no skipping: the permutation
                           // is built from per-expert token bitmaps recorded during stage 2
-  int dense;              // dense short block (dense_block()): the launch ends with the election
+  int dense;              // dense short block (LayerForm): the launch ends with the election
                           // and the slot table of the coreset; stage 2 runs beside the gate/up
                           // projection, there is no permutation
   uint32_t* tokmask;      // [n_slots] cleared here for that stage 2
@@ -1276,20 +1279,25 @@ static int launch_routing_grid(const RoutingArgs& a, int grid, int kernel_id, hi
   return e == hipSuccess ? DES_OK : hip_fail(e, "routing launch");
 }
 
-// Compute units of the current device (cached).  A routing workgroup fills a
-// whole compute unit (16 wavefronts at up to 128 registers), so the fused
-// launch may use at most this many workgroups if all are to be resident.
-int device_compute_units() {
-  static int cached_dev = -1, cached_cus = 0;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  if (dev != cached_dev) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 0;
-    cached_dev = dev;
-    cached_cus = n;
+// Compute units of the current device (kept per device, 0 = not known yet; threads may ask at the
+// same time).  A routing workgroup fills a whole compute unit (16 wavefronts at up to 128
+// registers), so the fused launch may use at most this many workgroups if all are to be resident.
+static int device_compute_units() {
+  constexpr int kDevices = 64;
+  static std::atomic<int> known[kDevices];
+  if (g_test_compute_units >= 0) {
+    const int n = g_test_compute_units;
+    g_test_compute_units = -1;
+    return n;
   }
-  return cached_cus;
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  const bool keep = dev >= 0 && dev < kDevices;
+  if (keep) n = known[dev].load(std::memory_order_relaxed);
+  if (n > 0) return n;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+  if (keep) known[dev].store(n, std::memory_order_relaxed);
+  return n;
 }
 
 static void fill_common(RoutingArgs& a, const des_shape_t& s) {
@@ -1316,10 +1324,7 @@ static void fill_common(RoutingArgs& a, const des_shape_t& s) {
   }
 }
 
-// Selector workgroups per sequence and workgroups in all (without those that only copy x) of
-// launch_routing's single launch, and whether all can be resident at once.
-struct RoutingRoles { int groups, roles; bool fit; };
-static RoutingRoles routing_roles(const des_shape_t& s) {
+LayerForm layer_form(const des_shape_t& s) {
   const int n_tiles = ((s.n_experts + 15) / 16) * ((s.n_seqs * s.n_tokens + 15) / 16);
   int fused_limit = device_compute_units();
   if (fused_limit > kMaxFusedRoutingBlocks) fused_limit = kMaxFusedRoutingBlocks;
@@ -1330,21 +1335,9 @@ static RoutingRoles routing_roles(const des_shape_t& s) {
   if (groups > kMaxSelGroups / s.n_seqs) groups = kMaxSelGroups / s.n_seqs > 0 ? kMaxSelGroups / s.n_seqs : 1;
   if (n_tiles + s.n_seqs * groups + 1 > fused_limit) groups = 1;
   const int roles = n_tiles + s.n_seqs * groups + (s.n_seqs * groups > 1 ? 1 : 0);
-  return RoutingRoles{groups, roles, roles <= fused_limit};
-}
-
-bool x_in_operand_order(const des_shape_t& s) {
-  return s.dtype == DES_BF16 && s.n_seqs * s.n_tokens <= 32 && routing_roles(s).fit;
-}
-
-// The conditions of launch_routing's single launch with one selector workgroup, for a
-// shape that qualifies (dense_shape): the FFN launches must take the same decision.
-bool dense_block(const des_shape_t& s) {
-  if (!dense_shape(s)) return false;
-  int fused_limit = device_compute_units();
-  if (fused_limit > kMaxFusedRoutingBlocks) fused_limit = kMaxFusedRoutingBlocks;
-  const int n_tiles = ((s.n_experts + 15) / 16) * ((s.n_tokens + 15) / 16);
-  return s.n_tokens <= selector_tokens_per_pass(s.n_experts) && n_tiles + 1 <= fused_limit;
+  const bool fused = roles <= fused_limit;
+  return LayerForm{groups, roles, fused, fused && dense_shape(s) && s.n_tokens <= tpp,
+                   fused && s.dtype == DES_BF16 && s.n_seqs * s.n_tokens <= 32};
 }
 
 // Four tiles per workgroup read half as much per tile, where one tile each makes more than one
@@ -1405,9 +1398,9 @@ int launch_select(const des_shape_t& s, const float* logits, int32_t* coreset_id
   return launch_routing_grid(a, a.B, kKSelect, st);
 }
 
-int launch_routing(const des_shape_t& s, const void* x, const void* w_router, const float* bias,
-                   float* logits, int32_t* coreset_idx, int32_t* coreset_size, int32_t* topk_idx,
-                   float* topk_w, int32_t* expert_counts, int32_t* n_unique,
+int launch_routing(const des_shape_t& s, const LayerForm& form, const void* x, const void* w_router,
+                   const float* bias, float* logits, int32_t* coreset_idx, int32_t* coreset_size,
+                   int32_t* topk_idx, float* topk_w, int32_t* expert_counts, int32_t* n_unique,
                    const int32_t* prev_n_unique, char* ws, unsigned long long epoch,
                    hipStream_t st) {
   const WsLayout w = ws_layout(s);
@@ -1430,20 +1423,19 @@ int launch_routing(const des_shape_t& s, const void* x, const void* w_router, co
   a.rows_shift = lds_rows_pass(s.n_seqs * s.n_tokens) == 64 ? 6 : 7;
   a.sel_part = reinterpret_cast<uint32_t*>(ws + w.sel_part);
   const int n_tiles = a.tiles_m * a.tiles_t;
-  const auto [groups, roles, fit] = routing_roles(s);
   // One selector workgroup and at most 32 tokens: the short permutation.  (Skipping
   // drops a token's experts after they were drawn, so the bitmaps of stage 2 would name
   // pairs that no longer exist: it keeps the general permutation.)
-  const bool small = a.B == 1 && groups == 1 && s.n_tokens <= 32 && !(s.skip_beta > 0.0f);
-  if (fit) {  // all workgroups resident at once: one launch
-    a.groups = groups;
+  const bool small = a.B == 1 && form.groups == 1 && s.n_tokens <= 32 && !(s.skip_beta > 0.0f);
+  if (form.fused) {  // all workgroups resident at once: one launch
+    a.groups = form.groups;
     a.small_perm = small;
-    a.dense = dense_block(s) ? 1 : 0;
+    a.dense = form.dense ? 1 : 0;
     a.tokmask = reinterpret_cast<uint32_t*>(ws + w.tokmask);
     a.do_router = a.do_select = a.do_permute = 1;
     a.use_flags = 1;
     int n_x = 0;
-    if (x_in_operand_order(s)) {
+    if (form.x_copy) {
       a.xo = reinterpret_cast<uint16_t*>(ws + w.o);
       const int pieces = s.n_seqs * s.n_tokens * (s.hidden / 8);
       n_x = pieces > 16 * kRtThreads ? 16 : (pieces + kRtThreads - 1) / kRtThreads;
@@ -1451,13 +1443,13 @@ int launch_routing(const des_shape_t& s, const void* x, const void* w_router, co
     if (g_test_skip_router) {  // test hook: nobody computes the logits, the selectors' wait expires
       a.skip_router_tiles = 1;
       if (g_test_skip_router == 2) g_test_skip_router = g_test_max_wait = 0;  // one launch only
-      a.x_first = roles - n_tiles;
+      a.x_first = form.roles - n_tiles;
       return launch_routing_grid(a, a.x_first + n_x, kKRouting, st);
     }
     // A single tile: handing it to another workgroup would cost more than it saves (8 tokens, 16
     // experts of width 256, fp32: routing 14.4 -> 13.4 us).
-    a.solo = n_tiles == 1 && roles == 2;
-    a.x_first = a.solo ? 1 : roles;
+    a.solo = n_tiles == 1 && form.roles == 2;
+    a.x_first = a.solo ? 1 : form.roles;
     return launch_routing_grid(a, a.x_first + n_x, kKRouting, st);
   }
   // too large to wait inside one launch: the same roles as three launches
