@@ -392,7 +392,9 @@ int des_test_compute_units(int units);
  * output projection; plan = {weight rows / 32, token rows / 32 of a tile, groups that share its
  * reduction, chunks pass through registers}, all zero for at most 32 token rows.  launch 2: the
  * router as a launch of its own (attn unused); plan = {expert tiles, token tiles of a workgroup,
- * 0, 0}, all zero in fp32.
+ * 0, 0}, all zero in fp32.  launch 3: the attention core; plan = {parts of the window, query tiles of
+ * a workgroup, workgroups per key/value head, queries and keys are loaded along their rows}.  launch
+ * 4: its LDS; plan = {bytes of a workgroup, bytes of the values among them, 0, 0}.
  */
 int des_test_plan(const des_shape_t* s, const des_attn_shape_t* attn, int32_t launch, int32_t plan[4]);
 

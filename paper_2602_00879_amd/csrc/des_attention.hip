@@ -343,11 +343,22 @@ __host__ __device__ constexpr size_t exchange_bytes(int tiles, int steps_of_part
 // us).  So they are where no cut into at most eight parts fits (windows beyond 2048).
 constexpr int kWholeWindow = 256;  // positions whose scores a wavefront keeps in registers
 constexpr int kWideWindow = 512;   // ... if it requests half as many keys ahead
-struct AttnPlan { int splits, tiles, groups; size_t lds; };
+//
+// Queries and keys of 128-wide heads under a cut window are loaded along their rows and turned into operand
+// order (`turn`) where four wavefronts or more share a compute unit: there their loads in operand order
+// queue up (see operand_write).  Eight sequences over 496 positions 19.3 -> 16.3 us, 128 tokens over 568 16.0
+// -> 14.2, 30 x 17 over 457 49.4 -> 42.4.  With fewer the way through LDS is what counts (one block over 272
+// positions, 256 wavefronts: 11.4 and 11.9; whole windows: 64 positions 6.0 and 6.4, 16 x 128 over 528 level),
+// and so it is for other widths (104: 30 launches over 272 to 640 positions take 3 to 12 % longer; 96, 30 x 17:
+// 26.6 and 27.9; 64: 16.6 and 20.0) and for few query tiles per key/value head, where the keys come from memory:
+// one or two (16 heads on 16, 16 x 16 over 416: 15.2 and 16.1; 30 x 17 over 457: 39.6 and 40.5), and four to
+// seven above 48 MB of keys and values (32 heads on 8: 32 x 16 over 400, 52 MB, 33.0 and 34.4; 24 x 16 over 480,
+// 47 MB, 34.7 and 32.0).
+struct AttnPlan { int splits, tiles, groups; size_t lds; bool turn; };
 static AttnPlan attn_plan(const AttnArgs& a, size_t value_bytes) {
   const int rows = a.H / a.Hkv * a.N, tiles = (rows + 15) / 16, steps = (a.P + a.N + 31) / 32;
   const int heads = a.B * a.Hkv;
-  AttnPlan p{1, 8, 1, value_bytes};
+  AttnPlan p{1, 8, 1, value_bytes, false};
   auto part = [&]() { return (steps + p.splits - 1) / p.splits; };  // steps of a part
   auto spread = [&]() {
     p.tiles = 8 / p.splits;
@@ -371,6 +382,12 @@ static AttnPlan attn_plan(const AttnArgs& a, size_t value_bytes) {
   spread();
   if (p.splits > 1) p.lds += exchange_bytes(p.tiles, part());
   p.groups = (tiles + p.tiles - 1) / p.tiles;
+  const int query_tiles = p.groups * p.tiles, waves = p.splits * p.tiles;
+  const size_t with_turn = value_bytes + 512 + p.tiles * 256 + (waves < 4 ? 4 : waves) * kOperandBytes;
+  const size_t window_bytes = static_cast<size_t>(heads) * (a.P + a.N) * a.dh * 4;  // keys and values
+  p.turn = p.splits > 1 && a.dh == 128 && heads * query_tiles * p.splits >= 1024 &&
+           (query_tiles >= 8 || (query_tiles >= 4 && window_bytes <= (48u << 20))) && with_turn <= 160 * 1024;
+  if (p.turn && with_turn > p.lds) p.lds = with_turn;
   return p;
 }
 
@@ -404,8 +421,8 @@ enum AttnForm { kWhole, kWide, kParts, kTwice };
 template <int NKS, int FORM, bool ROWS>
 __global__ __launch_bounds__(512) void attention_core_kernel(AttnArgs a) {
   constexpr int NDT = 2 * NKS;
-  // Queries and keys of wide heads under a cut window may be loaded along their rows (a.turn)
-  const bool along = FORM == kParts && NKS == 4 && a.turn;
+  // Queries and keys of 128-wide heads under a cut window may be loaded along their rows (a.turn)
+  const bool along = FORM == kParts && NKS == 4 && ROWS && a.turn;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   uint16_t* vt = reinterpret_cast<uint16_t*>(smem_raw);  // [ndt * 16][ldv]: values, transposed (unless ROWS)
   const int N = a.N, dh = a.dh, P = a.P, nk = a.P + a.N;
@@ -897,6 +914,21 @@ static void launch_linear(const LinearArgs& a, int kernel_id, hipStream_t st) {
   else pick(linear_tile_kernel<1, 1, 1, 3>, linear_tile_kernel<1, 1, 2, 3>);
 }
 
+static AttnArgs core_args(const des_shape_t& s, const des_attn_shape_t& t) {  // (sizes only)
+  AttnArgs c{};
+  c.B = s.n_seqs; c.N = s.n_tokens; c.H = t.n_heads; c.Hkv = t.n_kv_heads; c.dh = t.head_dim;
+  c.P = attn_cached(t);
+  return c;
+}
+
+void core_plan(const des_shape_t& s, const des_attn_shape_t& t, bool sizes, int32_t* plan) {
+  const AttnPlan p = attn_plan(core_args(s, t), attn_core_lds(s, t));
+  plan[0] = sizes ? static_cast<int32_t>(p.lds) : p.splits;
+  plan[1] = sizes ? static_cast<int32_t>(attn_core_lds(s, t)) : p.tiles;
+  plan[2] = sizes ? 0 : p.groups;
+  plan[3] = sizes ? 0 : p.turn;
+}
+
 int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void* x, const void* wq,
                      const void* wk, const void* wv, const void* wo, const void* k_cache,
                      const void* v_cache, void* y, char* ws, unsigned long long epoch, hipStream_t st) {
@@ -919,30 +951,18 @@ int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void
   p.epoch = epoch;
   launch_linear(p, kKAttnProj, st);
 
-  AttnArgs c{};
+  AttnArgs c = core_args(s, t);
   c.q = p.out[0]; c.k = p.out[1]; c.v = p.out[2];
   c.k_cache = static_cast<const uint16_t*>(k_cache);
   c.v_cache = static_cast<const uint16_t*>(v_cache);
   c.o = reinterpret_cast<uint16_t*>(ws + l.o);
-  c.B = s.n_seqs; c.N = s.n_tokens; c.H = t.n_heads; c.Hkv = t.n_kv_heads; c.dh = t.head_dim;
-  c.P = attn_cached(t);
   c.scale = 1.0f / sqrtf(static_cast<float>(t.head_dim));
   const AttnPlan pl = attn_plan(c, attn_core_lds(s, t));
   c.splits = pl.splits;
   c.tiles = pl.tiles;
-  // Where four wavefronts or more share a compute unit their key loads in operand order queue up (see
-  // operand_write): heads of 128, eight sequences over 496 positions 19.3 -> 16.3 us, 128 tokens over 568
-  // 16.0 -> 14.2, 30 x 17 over 457 49.4 -> 42.4.  With fewer the way through LDS is what counts (one block
-  // over 272 positions, 256 wavefronts: 11.4 and 11.9; whole windows: 64 positions 6.0 and 6.4, 16 x 128 over
-  // 528 level), and so it is for heads up to 96 (30 x 17: 26.6 and 27.9; of 64 16.6 and 20.0) and for one or
-  // two query tiles per key/value head, where the keys come from memory (16 heads on 16, 16 x 16 over 416:
-  // 15.2 and 16.1; 30 x 17 over 457: 39.6 and 40.5).
-  const int query_tiles = pl.groups * pl.tiles;
+  c.turn = pl.turn;
   const int waves = pl.splits * pl.tiles, nks = (t.head_dim + 31) / 32;
-  const size_t with_turn = attn_core_lds(s, t) + 512 + pl.tiles * 256 + (waves < 4 ? 4 : waves) * kOperandBytes;
-  c.turn = pl.splits > 1 && query_tiles >= 4 && s.n_seqs * t.n_kv_heads * query_tiles * pl.splits >= 1024 &&
-           with_turn <= 160 * 1024;
-  const size_t lds = c.turn && with_turn > pl.lds ? with_turn : pl.lds;
+  const size_t lds = pl.lds;
   // (four wavefronts stage faster than one)
   const dim3 grid(s.n_seqs * t.n_kv_heads, pl.groups), block((waves < 4 ? 4 : waves) * kWave);
   auto core = [&](auto kernel) -> int {

@@ -247,6 +247,7 @@ AttnLayout attn_layout(const des_shape_t& s, const des_attn_shape_t& t);
 size_t attn_core_lds(const des_shape_t& s, const des_attn_shape_t& t);
 // Test aids (des_test_plan): the form that a launch of such a call has.
 void projection_plan(const des_shape_t& s, const des_attn_shape_t& t, bool output, int32_t* plan);
+void core_plan(const des_shape_t& s, const des_attn_shape_t& t, bool sizes, int32_t* plan);
 void router_plan(const des_shape_t& s, int32_t* plan);
 int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void* x, const void* wq,
                      const void* wk, const void* wv, const void* wo, const void* k_cache,

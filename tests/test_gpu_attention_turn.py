@@ -1,6 +1,8 @@
 """The attention core of 128-wide heads under a cut window loads queries and keys along their rows where many
 wavefronts share the compute units, in operand order where few do: the same sequences in a batch and alone,
-bit for bit, and against the oracle.  Query rows and windows that do not fill their tiles."""
+bit for bit, and against the oracle.  Query rows and windows that do not fill their tiles; windows in two, four
+and eight parts, in eight the turned keys need more LDS than what the parts exchange.  (test_launch_plans.py holds
+the shapes to those forms.)"""
 import numpy as np
 import pytest
 import torch
@@ -13,8 +15,12 @@ from tests import helpers as H
 pytestmark = pytest.mark.gpu
 
 
-# (sequences, tokens, key/value heads of nine query heads, cached positions)
-@pytest.mark.parametrize("Bn,N,G,P", [(12, 40, 3, 417), (15, 37, 1, 220), (60, 33, 9, 300)])
+# (sequences, tokens, key/value heads of nine query heads, cached positions): parts, tiles of a workgroup
+TURNED = {(12, 40, 3, 417): (4, 1), (15, 37, 1, 220): (4, 1), (22, 40, 3, 417): (4, 2), (52, 33, 3, 267): (2, 4),
+          (7, 33, 1, 452): (8, 1)}
+
+
+@pytest.mark.parametrize("Bn,N,G,P", list(TURNED))
 def test_loads_along_rows(Bn, N, G, P):
     D, Hq, dh = 384, 9, 128  # (the projections add in one order at every size)
     t = W.make_attention(W.AttnConfig("turn", Bn, N, D, Hq, G, dh, P, 0, 97))

@@ -3,6 +3,7 @@ at the sizes where its rule changes, and that the shapes of the GPU tests reach 
 import pytest
 
 from paper_2602_00879_amd import binding as B
+from tests import test_gpu_attention_turn as turn
 from tests import test_gpu_projection_tiles as tiles
 from tests import test_gpu_router_tiles as router
 
@@ -69,3 +70,30 @@ def test_router_test_compares_four_tiles_with_one(M, D, T, part):
         return B.des_test_plan(B.make_shape(1, n, D, M, 32, 1, M, "vanilla", "bf16"), None, 2)
     assert form(T) == (2, 2, 0, 0)
     assert {form(min(part, T - t)) for t in range(0, T, part)} == {(1, 1, 0, 0)}
+
+
+def _core(Bn, N, D, Hq, G, dh, P):
+    """(parts, tiles, workgroups per head, turned), (LDS bytes, of the values among them) of the attention core."""
+    shape, attn = B.make_shape(Bn, N, D, 16, 128, 2, 4, "vanilla", "bf16"), B.make_attn_shape(Hq, G, dh, P, 0)
+    return B.des_test_plan(shape, attn, 3), B.des_test_plan(shape, attn, 4)[:2]
+
+
+@pytest.mark.parametrize("Bn,N,G,P", list(turn.TURNED))
+def test_turn_test_compares_both_orders(Bn, N, G, P):
+    (parts, tiles, _, turned), (lds, values) = _core(Bn, N, 384, 9, G, 128, P)
+    assert (parts, tiles) == turn.TURNED[Bn, N, G, P] and turned == 1
+    assert _core(1, N, 384, 9, G, 128, P)[0][3] == 0
+    ring = 512 + 256 * tiles + 2048 * tiles * -(-((P + N + 31) // 32) // parts)
+    assert lds - values == max(ring, 512 + 256 * tiles + 1024 * max(4, parts * tiles))
+    assert (lds - values > ring) == (parts == 8)
+
+
+@pytest.mark.parametrize("dh", [32, 64, 96, 104, 120])
+def test_only_heads_of_128_are_turned(dh):
+    """Others reserve no LDS for it: 160 tokens, heads of 64 over 570 positions, two workgroups per compute unit."""
+    for Bn, N, P in ((10, 16, 554), (8, 32, 464), (16, 32, 368), (1, 128, 440)):
+        (parts, tiles, _, turned), (lds, values) = _core(Bn, N, 2048, 32, 4, dh, P)
+        assert parts > 1 and turned == 0
+        assert lds - values == 512 + 256 * tiles + 2048 * tiles * -(-((P + N + 31) // 32) // parts)
+        if (dh, Bn) == (64, 10):
+            assert parts == 8 and 2 * lds <= 160 * 1024
