@@ -394,7 +394,10 @@ int des_test_compute_units(int units);
  * router as a launch of its own (attn unused); plan = {expert tiles, token tiles of a workgroup,
  * 0, 0}, all zero in fp32.  launch 3: the attention core; plan = {parts of the window, query tiles of
  * a workgroup, workgroups per key/value head, queries and keys are loaded along their rows}.  launch
- * 4: its LDS; plan = {bytes of a workgroup, bytes of the values among them, 0, 0}.
+ * 4: its LDS; plan = {bytes of a workgroup, bytes of the values among them, 0, 0}.  launch 5: a
+ * layer's routing (attn unused); plan = {one launch, dense block, x is copied into operand order,
+ * selector workgroups per sequence} on the current device (no GPU: as with no compute units, unless
+ * des_test_compute_units gave their number).
  */
 int des_test_plan(const des_shape_t* s, const des_attn_shape_t* attn, int32_t launch, int32_t plan[4]);
 

@@ -145,7 +145,7 @@ struct LayerForm {
   int roles;    // workgroups of the single launch, without those that only copy x
   bool fused;   // all of them can be resident at once: one launch
   bool dense;   // dense_shape, one launch and one selector workgroup
-  bool x_copy;  // at most 32 tokens, bf16, one launch: spare workgroups of it leave x in the order of the
+  bool x_copy;  // at most 32 tokens, bf16: spare workgroups of the launch leave x in the order of the
                 // gate/up projection's operand loads, in the place of O (the down projection writes
                 // that, after gate/up)
 };
@@ -247,6 +247,7 @@ AttnLayout attn_layout(const des_shape_t& s, const des_attn_shape_t& t);
 size_t attn_core_lds(const des_shape_t& s, const des_attn_shape_t& t);
 // Test aids (des_test_plan): the form that a launch of such a call has.
 void projection_plan(const des_shape_t& s, const des_attn_shape_t& t, bool output, int32_t* plan);
+void layer_plan(const des_shape_t& s, int32_t* plan);
 void core_plan(const des_shape_t& s, const des_attn_shape_t& t, bool sizes, int32_t* plan);
 void router_plan(const des_shape_t& s, int32_t* plan);
 int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void* x, const void* wq,

@@ -45,7 +45,7 @@ struct FfnArgs {
   const int32_t* units;         // live units of the routed experts, longest expert first:
                                 // slot | split << 16 | splits of that slot << 24; meta[2] of them
   size_t h_rows;                // routed rows of H (the shared expert's rows follow them)
-  const uint16_t* xo;           // at most 32 tokens: x in operand order (see operand_off), or null
+  const uint16_t* xo;           // x in operand order (see operand_off), or null
   DenseArgs dn;                 // dense short block: stage 2 beside gate/up, see des_common.h
 };
 

@@ -102,7 +102,7 @@ struct RoutingArgs {
                           // and the slot table of the coreset; stage 2 runs beside the gate/up
                           // projection, there is no permutation
   uint32_t* tokmask;      // [n_slots] cleared here for that stage 2
-  uint16_t* xo;           // [D / 8][T][8] x in operand order, by the workgroups from x_first on, or null
+  uint16_t* xo;           // [D / 8][T][8] x in operand order (LayerForm), by the workgroups from x_first on, or null
   int x_first;
 };
 
@@ -1336,8 +1336,21 @@ LayerForm layer_form(const des_shape_t& s) {
   if (n_tiles + s.n_seqs * groups + 1 > fused_limit) groups = 1;
   const int roles = n_tiles + s.n_seqs * groups + (s.n_seqs * groups > 1 ? 1 : 0);
   const bool fused = roles <= fused_limit;
-  return LayerForm{groups, roles, fused, fused && dense_shape(s) && s.n_tokens <= tpp,
-                   fused && s.dtype == DES_BF16 && s.n_seqs * s.n_tokens <= 32};
+  const bool dense = fused && dense_shape(s) && s.n_tokens <= tpp;
+  // x in operand order, against in rows, routing and gate/up of 14 layers.  Dense blocks (gate/up takes all
+  // tokens): 1, 2 and 4 tokens take 1.02, 1.01 and 1.01 of the time (of one token both are the same bytes), 6
+  // to 16 0.99, 17 to 24 0.97, 32 0.94 (3072 x 1536 0.87); 512 wide 0.97 to 1.06.  Elsewhere the pieces of an
+  // expert's few tokens lie further apart than their rows: 20 to 32 tokens of 1024 to 2048 0.93 to 1.01 (64
+  // experts of 2048 x 512, k = 8, vanilla: 1.04), up to 17 tokens 1.01, above 2048 0.98 to 1.08.
+  const int T = s.n_seqs * s.n_tokens;
+  const bool x_copy = fused && s.dtype == DES_BF16 && T <= 32 && s.hidden >= 1024 &&
+                      (dense ? T >= 6 : T >= 20 && s.hidden <= 2048);
+  return LayerForm{groups, roles, fused, dense, x_copy};
+}
+
+void layer_plan(const des_shape_t& s, int32_t* plan) {
+  const LayerForm f = layer_form(s);
+  plan[0] = f.fused; plan[1] = f.dense; plan[2] = f.x_copy; plan[3] = f.groups;
 }
 
 // Four tiles per workgroup read half as much per tile, where one tile each makes more than one

@@ -4,6 +4,7 @@ import pytest
 
 from paper_2602_00879_amd import binding as B
 from tests import test_gpu_attention_turn as turn
+from tests import test_gpu_operand_order as order
 from tests import test_gpu_projection_tiles as tiles
 from tests import test_gpu_router_tiles as router
 
@@ -97,3 +98,33 @@ def test_only_heads_of_128_are_turned(dh):
         assert lds - values == 512 + 256 * tiles + 2048 * tiles * -(-((P + N + 31) // 32) // parts)
         if (dh, Bn) == (64, 10):
             assert parts == 8 and 2 * lds <= 160 * 1024
+
+
+@pytest.fixture
+def routing_form():
+    """Form of a layer's routing as on a device with so many compute units."""
+    def form(case, mode, units=256, dtype="bf16"):
+        Bn, N, D, M, F, Fs, K, C = case
+        B.des_test_compute_units(units)
+        return B.des_test_plan(B.make_shape(Bn, N, D, M, F, K, C, mode, dtype, ffn_shared=Fs), None, 5)
+    return form
+
+
+def test_operand_order_test_has_blocks_that_are_copied(routing_form):
+    for case in order.SHORT:
+        for mode in ("vote", "vanilla"):
+            assert routing_form(case, mode)[2] == (mode in order.COPIED.get(case, ())), (case, mode)
+
+
+def test_routing_form_follows_the_number_of_compute_units(routing_form):
+    """Two expert tiles of 17 tokens make four workgroups, the election one more."""
+    case = (1, 17, 2080, 20, 32, 32, 2, 4)
+    assert routing_form(case, "vote") == (1, 1, 1, 1)
+    assert routing_form(case, "seq", 5) == (1, 1, 1, 1)
+    assert routing_form(case, "vote", 4) == routing_form(case, "vote", 0) == (0, 0, 0, 1)
+    assert routing_form(case, "vanilla") == (1, 0, 0, 1)
+    assert routing_form((3, 9, 2048, 20, 32, 0, 2, 4), "vote") == (1, 0, 1, 1)
+    assert routing_form((3, 9, 2080, 20, 32, 0, 2, 4), "vote") == (1, 0, 0, 1)
+    assert routing_form((3, 9, 992, 20, 32, 0, 2, 4), "vote") == (1, 0, 0, 1)
+    assert routing_form((1, 4, 1024, 20, 32, 0, 2, 4), "vote") == (1, 1, 0, 1)
+    assert routing_form((1, 17, 1024, 20, 32, 0, 2, 4), "vote", dtype="f32") == (1, 0, 0, 1)
