@@ -1186,8 +1186,9 @@ __global__ __launch_bounds__(kRtThreads, 8) void router_kernel(RoutingArgs a) {
   // the element that this thread will finish
   const int tile = threadIdx.x >> 8, er = threadIdx.x & 15, tc = (threadIdx.x >> 4) & 15;
   const int ef = i0 + 16 * (tile / TT) + er, tf = t0 + 16 * (tile % TT) + tc;
-  const bool mine = tile < ET * TT && ef < M && tf < T;
-  const float bias = mine && a.bias ? a.bias[ef] : 0.f;
+  // (its place in one register: two across the loop spill)
+  const int fin = tile < ET * TT && ef < M && tf < T ? tf * M + ef : -1;
+  const float bias = fin >= 0 && a.bias ? a.bias[ef] : 0.f;
   f32x4 acc[ET][TT];
 #pragma unroll
   for (int e = 0; e < ET; ++e)
@@ -1232,11 +1233,11 @@ __global__ __launch_bounds__(kRtThreads, 8) void router_kernel(RoutingArgs a) {
     for (int t = 0; t < TT; ++t)
       *reinterpret_cast<f32x4*>(part + wave * kMine + (e * TT + t) * 256 + r * 16 + 4 * (lane >> 4)) = acc[e][t];
   __syncthreads();
-  if (!mine) return;
+  if (fin < 0) return;
   float s = 0.f;
 #pragma unroll
   for (int w = 0; w < kRtWaves; ++w) s += part[w * kMine + tile * 256 + tc * 16 + er];  // fixed order
-  a.logits[static_cast<size_t>(tf) * M + ef] = s + bias;
+  a.logits[fin] = s + bias;
 }
 
 // probs[t][:] = router weights of token t (softmax of its logits, or their

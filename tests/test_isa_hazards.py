@@ -120,6 +120,13 @@ def test_asm_load_kernels_do_not_spill(ffn_asm):
     assert n > 0
 
 
+def test_router_kernels_do_not_spill():
+    """Two workgroups of 16 wavefronts share a compute unit: 64 registers each."""
+    sizes = {m.group(1): int(m.group(2)) for m in re.finditer(
+        r"\.amdhsa_kernel (\S*router_kernel\S*)\n.*?\.amdhsa_private_segment_fixed_size (\d+)", _asm("des_routing.hip"), re.S)}
+    assert len(sizes) == 2 and set(sizes.values()) == {0}
+
+
 def _regs(operand):
     """Vector registers named by one operand: v7 -> {7}, v[4:7] -> {4..7}."""
     m = re.fullmatch(r"v(\d+)", operand)
