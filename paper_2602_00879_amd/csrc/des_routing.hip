@@ -1354,15 +1354,18 @@ void layer_plan(const des_shape_t& s, int32_t* plan) {
   plan[0] = f.fused; plan[1] = f.dense; plan[2] = f.x_copy; plan[3] = f.groups;
 }
 
-// Four tiles per workgroup read half as much per tile, where one tile each makes more than one
-// round of the chip.  One and four, in us: 128 experts of width 2048, 320 tiles 7.0 and 7.4, 384 8.1 and
-// 7.7, 512 7.8 and 7.4, 1024 12.0 and 8.8; 96 of width 768, 288 5.2 and 5.8, 384 5.9 and 5.8; 128 of width
-// 1024, 320 6.0 and 6.3, 512 6.7 and 5.3; 256 of width 2048, 320 6.6 and 7.6, 512 7.3 and 7.9, 1024 10.5 and
-// 8.9; 64 of width 3072, 256 7.6 and 9.4, 384 11.0 and 9.9.  (Loads in operand order: 128 of width 2048,
-// 256 tiles 6.8, 384 10.2, 1024 11.6 in fours.)
+// Four tiles per workgroup read half as much per tile, where one tile each makes more than one round of
+// the chip.  One and four, in us.  Up to 1024 wide: 128 experts of 1024, 224 tiles 4.0 and 4.6, 288 5.5 and
+// 4.8, 1024 8.9 and 6.1; of 256, 272 tiles level; of 128, where reading counts for little, 512 tiles 3.3 and
+// 3.4, 576 4.0 and 3.4.  Wider, with many token rows: 128 experts of 2048, 256 tiles 5.4 and 6.8, 288 6.7 and
+// 6.9, 320 7.4 and 6.9, 512 8.2 and 7.1; of 3072, 256 tiles 7.2 and 9.2, 264 9.7 and 9.2, 288 10.0 and 9.3.  With
+// few (many experts), one tile each stays ahead up to two rounds: 256 of 2048, 320 tiles 6.2 and 7.0, 512 6.8 and
+// 7.2, 576 7.6 and 7.3, 1024 10.1 and 8.4.  Between, at 160 to 224 experts, fours lose up to 7 % past the lines
+// below (192 of 1536, 444 tiles: 6.5 and 7.0).
 static bool wide_router(const RoutingArgs& a) {
   const int tiles = a.tiles_m * a.tiles_t;
-  return tiles > 352 || (tiles > 256 && a.D > 2048);
+  if (a.D <= 1024) return a.D < 256 ? tiles >= 512 : tiles > 256;
+  return tiles > 512 || (a.D <= 2048 ? tiles > 288 && a.tiles_t > 35 : tiles > 256 && a.tiles_t > 32);
 }
 
 static int launch_router_tiles(const RoutingArgs& a, hipStream_t st) {

@@ -73,6 +73,17 @@ def test_router_test_compares_four_tiles_with_one(M, D, T, part):
     assert {form(min(part, T - t)) for t in range(0, T, part)} == {(1, 1, 0, 0)}
 
 
+# (experts, width): the fewest tokens of the launch with four tiles per workgroup
+@pytest.mark.parametrize("M,D,least", [(128, 1024, 513), (256, 768, 257), (128, 2048, 577), (64, 1280, 1153),
+                                       (256, 2048, 513), (192, 2048, 561), (128, 3072, 513), (24, 4096, 2049),
+                                       (256, 3072, 513), (320, 1536, 401), (128, 256, 513), (128, 224, 1009)])
+def test_rule_of_the_router_tiles(M, D, least):
+    def form(n):
+        return B.des_test_plan(B.make_shape(1, n, D, M, 32, 1, M, "vanilla", "bf16"), None, 2)
+    assert form(least - 1) == (1, 1, 0, 0) and form(least) == (2, 2, 0, 0)
+
+
+
 def _core(Bn, N, D, Hq, G, dh, P):
     """(parts, tiles, workgroups per head, turned), (LDS bytes, of the values among them) of the attention core."""
     shape, attn = B.make_shape(Bn, N, D, 16, 128, 2, 4, "vanilla", "bf16"), B.make_attn_shape(Hq, G, dh, P, 0)
