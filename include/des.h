@@ -397,7 +397,9 @@ int des_test_compute_units(int units);
  * 4: its LDS; plan = {bytes of a workgroup, bytes of the values among them, 0, 0}.  launch 5: a
  * layer's routing (attn unused); plan = {one launch, dense block, x is copied into operand order,
  * selector workgroups per sequence} on the current device (no GPU: as with no compute units, unless
- * des_test_compute_units gave their number).
+ * des_test_compute_units gave their number).  launch 6: the expert launches of an fp32 layer (attn
+ * unused); plan = {gate/up takes the pairs in the order of their experts, choices of a token that down
+ * has in flight together, workgroups of down per token, 0}, all zero in bf16.
  */
 int des_test_plan(const des_shape_t* s, const des_attn_shape_t* attn, int32_t launch, int32_t plan[4]);
 

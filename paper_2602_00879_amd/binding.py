@@ -393,7 +393,7 @@ def des_test_compute_units(units: int) -> None:
 
 def des_test_plan(shape: DesShape, attn: Optional[DesAttnShape], launch: int) -> Tuple[int, ...]:
     """Test aid, host only: the form of a launch (0 q/k/v, 1 output projection, 2 router, 3 attention core, 4 its LDS,
-    5 routing of a layer; see des.h)."""
+    5 routing of a layer, 6 fp32 experts; see des.h)."""
     plan = (ctypes.c_int32 * 4)()
     _check(lib().des_test_plan(ctypes.byref(shape), None if attn is None else ctypes.byref(attn), launch, plan))
     return tuple(plan)

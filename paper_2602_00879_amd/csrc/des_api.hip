@@ -457,11 +457,12 @@ int des_test_compute_units(int units) {
 
 int des_test_plan(const des_shape_t* s, const des_attn_shape_t* t, int32_t launch, int32_t* plan) {
   if (!s || !plan) return DES_ERR_NULL;
-  if (launch < 0 || launch > 5) return DES_ERR_SHAPE;
-  const int rc = launch == 2 || launch == 5 ? check_shape(s, launch == 5) : check_attn(s, t);
+  if (launch < 0 || launch > 6) return DES_ERR_SHAPE;
+  const int rc = launch == 2 || launch >= 5 ? check_shape(s, launch >= 5) : check_attn(s, t);
   if (rc != DES_OK) return rc;
   if (launch == 2) router_plan(*s, plan);
   else if (launch == 5) layer_plan(*s, plan);
+  else if (launch == 6) f32_plan(*s, plan);
   else if (launch > 2) core_plan(*s, *t, launch == 4, plan);
   else projection_plan(*s, *t, launch == 1, plan);
   return DES_OK;

@@ -250,6 +250,7 @@ void projection_plan(const des_shape_t& s, const des_attn_shape_t& t, bool outpu
 void layer_plan(const des_shape_t& s, int32_t* plan);
 void core_plan(const des_shape_t& s, const des_attn_shape_t& t, bool sizes, int32_t* plan);
 void router_plan(const des_shape_t& s, int32_t* plan);
+void f32_plan(const des_shape_t& s, int32_t* plan);
 int launch_attention(const des_shape_t& s, const des_attn_shape_t& t, const void* x, const void* wq,
                      const void* wk, const void* wv, const void* wo, const void* k_cache,
                      const void* v_cache, void* y, char* ws, unsigned long long epoch, hipStream_t st);

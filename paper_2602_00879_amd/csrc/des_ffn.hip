@@ -837,11 +837,12 @@ __global__ __launch_bounds__(kTileThreads, 2) void down_tile_kernel(FfnArgs a) {
 
 // ------------------------------------------------------------------ fp32 path
 // Plain fused-multiply-add kernels for the small fp32 configuration: lanes stride the reduction
-// dimension with 16-byte loads, fixed-order wave reduction.  Launches and dependent loads bound
-// them, so there are two launches, a pair's expert is read straight from the choices (pair
-// t * K + j has row t * K + j of H), and a wavefront of the second one has one output element
-// with all the choices of its token, whose products it adds in slot order as the combine does
-// (8 tokens, 16 experts of 256 x 128: down and combine were 4.4 + 4.2 us, now 4.0; the layer 22.0 -> 19.6).
+// dimension with 16-byte loads, fixed-order wave reduction.  Launches and dependent loads bound small
+// blocks, reading the weights again for every pair large ones.  So there are two launches, a pair's expert
+// is read straight from the choices (pair t * K + j has row t * K + j of H), and a wavefront of the second
+// one has one output element with all the choices of its token, whose products it adds in slot order as the
+// combine does (8 tokens, 16 experts of 256 x 128: down and combine were 4.4 + 4.2 us, now 4.0; the layer
+// 22.0 -> 19.6).  F32Form has the rest.
 __device__ __forceinline__ float dot_f32(const float* a, const float* b, int n, int lane) {
   const float4* pa = reinterpret_cast<const float4*>(a);
   const float4* pb = reinterpret_cast<const float4*>(b);
@@ -864,10 +865,20 @@ __device__ __forceinline__ int f32_expert(const FfnArgs& a, int p) {
 }
 
 // grid.x = pair, then the shared expert's tokens; grid.y tiles the F rows.
+// SORTED: pairs in the order of their experts, so that workgroups that run together read the same rows.
+template <bool SORTED>
 __global__ __launch_bounds__(256) void gateup_f32_kernel(FfnArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r = blockIdx.x, TK = a.T * a.K;
-  const bool sh = r >= TK;
+  const int TK = a.T * a.K;
+  const bool sh = static_cast<int>(blockIdx.x) >= TK;
+  int r = blockIdx.x;
+  if (SORTED && !sh) {
+    if (r >= a.meta[1]) return;  // (fewer pairs than choices)
+    const int p0 = a.pair_tok[r] * a.K;
+    int j = 0;
+    while (j < a.K - 1 && a.pos[p0 + j] != r) ++j;
+    r = p0 + j;
+  }
   const int e = sh ? 0 : f32_expert(a, r);
   if (e < 0) return;
   const int F = sh ? a.Fs : a.F, tok = sh ? r - TK : r / a.K;
@@ -885,10 +896,10 @@ __global__ __launch_bounds__(256) void gateup_f32_kernel(FfnArgs a) {
   }
 }
 
-// y[t][d]: grid.x = token, grid.y tiles the D rows.  Four choices at a time: their rows of H and
+// y[t][d]: grid.x = token, grid.y tiles the D rows.  J choices at a time: their rows of H and
 // of the weights are in flight together.
+template <int J>
 __global__ __launch_bounds__(256) void down_combine_f32_kernel(FfnArgs a) {
-  constexpr int J = 4;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int t = blockIdx.x, K = a.K, D = a.D, n4 = a.F / 4;
   const size_t TK = static_cast<size_t>(a.T) * K;
@@ -910,6 +921,11 @@ __global__ __launch_bounds__(256) void down_combine_f32_kernel(FfnArgs a) {
         ph[u] = reinterpret_cast<const float4*>(h + static_cast<size_t>(p) * a.F);
         pw[u] = reinterpret_cast<const float4*>(static_cast<const float*>(a.wd) +
                                                 (static_cast<size_t>(max(e[u], 0)) * D + d) * a.F);
+      }
+      if (J == 1) {
+        const float *hr = reinterpret_cast<const float*>(ph[0]), *wr = reinterpret_cast<const float*>(pw[0]);
+        if (e[0] >= 0) acc = fmaf(g[0], dot_f32(hr, wr, a.F, lane), acc);
+        continue;
       }
       for (int v = lane; v < n4; v += 64) {
         float4 q[J], w[J];
@@ -1071,6 +1087,39 @@ int launch_read_probe(const void* src, size_t bytes, void* sink, hipStream_t st)
 }
 
 // ------------------------------------------------------------------ launcher
+// How an fp32 layer's two launches run (times are of the launch concerned, in us).
+struct F32Form {
+  bool sorted;     // gate/up takes the pairs in the order of their experts
+  int at_once;     // choices of a token whose rows down has in flight together
+  int down_tiles;  // workgroups of down per token
+};
+static F32Form f32_form(const des_shape_t& s) {
+  const int TK = s.n_seqs * s.n_tokens * s.top_k;
+  // The order of the experts costs dependent loads and spreads a token's row of x, and it pays where an
+  // expert is large and the pairs are more than run together: 128 experts of 2048 x 768, k = 8, vanilla, 128
+  // tokens 1088 in the order of the tokens and 974 in that of the experts, 512 tokens 4444 and 3579; a coreset
+  // of 32 of them, 8 tokens 106 and 130, 128 level, 256 2126 and 1851; 16 of 4096 x 1024, 128 pairs 293 and 269,
+  // 1024 pairs 2109 and 1923.  Experts of 1024 x 512 and less stay ahead in token order up to 4096 pairs
+  // (1029 and 1174; of 512 x 256 270 and 341).  At 96 to 192 pairs without a coreset the line costs up to 7 %.
+  const size_t expert = static_cast<size_t>(s.ffn) * s.hidden;
+  const int pairs = expert >= (4u << 20) ? 128 : 2 * max_live_experts(s) > s.n_experts ? 256 : 1024;
+  // Choices side by side hide the loads of few tokens (16 tokens: 16 experts of 4096 x 1024, k = 4, 81 and one
+  // after the other 104; 32 of 1536 x 1408 58 and 69); with more the chip is full without (64 tokens, 128 of
+  // 2048 x 768, k = 8: 270 and 248).
+  const int at_once = s.top_k == 1 || TK > 128 ? 1 : 4;
+  // A wavefront per output element: one token of width 2048, k = 8, takes 10 us so, 38 in 64 workgroups.  With
+  // one choice per token what leads to the first product is worth sharing among several elements: 512 tokens,
+  // 16 experts of 512 x 256, 45 and 34.
+  const int most = s.top_k == 1 && s.n_seqs * s.n_tokens >= 64 ? 64 : 1024, d4 = (s.hidden + 3) / 4;
+  return F32Form{expert >= (1u << 20) && TK >= pairs, at_once, d4 < most ? d4 : most};
+}
+
+void f32_plan(const des_shape_t& s, int32_t* plan) {
+  const F32Form f = f32_form(s);
+  const bool on = s.dtype == DES_F32;
+  plan[0] = on && f.sorted; plan[1] = on ? f.at_once : 0; plan[2] = on ? f.down_tiles : 0; plan[3] = 0;
+}
+
 int launch_ffn(const des_shape_t& s, const LayerForm& form, const void* x, const void* w_gate,
                const void* w_up, const void* w_down, const void* ws_gate, const void* ws_up,
                const void* ws_down, const float* logits, int32_t* topk_idx, float* topk_w, int32_t* expert_counts,
@@ -1274,10 +1323,12 @@ int launch_ffn(const des_shape_t& s, const LayerForm& form, const void* x, const
   } else {
     const int rows = TK + (a.Fs > 0 ? a.T : 0);
     const int Fm = a.F > a.Fs ? a.F : a.Fs;
-    launch(kKGateUp, gateup_f32_kernel, dim3(rows, (Fm + 3) / 4 > 64 ? 64 : (Fm + 3) / 4),
-           dim3(256), 0, st, a);
-    launch(kKDown, down_combine_f32_kernel, dim3(a.T, (a.D + 3) / 4 > 64 ? 64 : (a.D + 3) / 4),
-           dim3(256), 0, st, a);
+    const F32Form f = f32_form(s);
+    const dim3 gu(rows, (Fm + 3) / 4 > 64 ? 64 : (Fm + 3) / 4), gd(a.T, f.down_tiles), block(256);
+    if (f.sorted) launch(kKGateUp, gateup_f32_kernel<true>, gu, block, 0, st, a);
+    else launch(kKGateUp, gateup_f32_kernel<false>, gu, block, 0, st, a);
+    if (f.at_once == 1) launch(kKDown, down_combine_f32_kernel<1>, gd, block, 0, st, a);
+    else launch(kKDown, down_combine_f32_kernel<4>, gd, block, 0, st, a);
   }
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? DES_OK : hip_fail(e, "ffn launch");

@@ -4,6 +4,7 @@ import pytest
 
 from paper_2602_00879_amd import binding as B
 from tests import test_gpu_attention_turn as turn
+from tests import test_gpu_f32_forms as f32
 from tests import test_gpu_operand_order as order
 from tests import test_gpu_projection_tiles as tiles
 from tests import test_gpu_router_tiles as router
@@ -83,7 +84,6 @@ def test_rule_of_the_router_tiles(M, D, least):
     assert form(least - 1) == (1, 1, 0, 0) and form(least) == (2, 2, 0, 0)
 
 
-
 def _core(Bn, N, D, Hq, G, dh, P):
     """(parts, tiles, workgroups per head, turned), (LDS bytes, of the values among them) of the attention core."""
     shape, attn = B.make_shape(Bn, N, D, 16, 128, 2, 4, "vanilla", "bf16"), B.make_attn_shape(Hq, G, dh, P, 0)
@@ -139,3 +139,27 @@ def test_routing_form_follows_the_number_of_compute_units(routing_form):
     assert routing_form((3, 9, 992, 20, 32, 0, 2, 4), "vote") == (1, 0, 0, 1)
     assert routing_form((1, 4, 1024, 20, 32, 0, 2, 4), "vote") == (1, 1, 0, 1)
     assert routing_form((1, 17, 1024, 20, 32, 0, 2, 4), "vote", dtype="f32") == (1, 0, 0, 1)
+
+
+def _f32(case, mode, dtype="f32"):
+    Bn, N, D, M, F, Fs, K, C = case
+    return B.des_test_plan(B.make_shape(Bn, N, D, M, F, K, C, mode, dtype, ffn_shared=Fs), None, 6)
+
+
+def test_f32_test_reaches_its_forms():
+    for case, forms in f32.FORMS.items():
+        for mode, form in forms.items():
+            assert _f32(case, mode) == (*form, 0), (case, mode)
+
+
+@pytest.mark.parametrize("D,F,M,C,K,least", [(2048, 768, 128, 32, 8, 128), (2048, 768, 64, 40, 8, 32),
+                                             (4096, 1024, 16, 4, 4, 32), (1024, 512, 64, 64, 8, 4097)])
+def test_rule_of_the_f32_pairs_order(D, F, M, C, K, least):
+    """Fewest tokens whose pairs gate/up takes in the order of the experts (none of a small expert's)."""
+    assert _f32((1, least - 1, D, M, F, 0, K, C), "vote")[0] == 0
+    assert least > 4096 or _f32((1, least, D, M, F, 0, K, C), "vote")[0] == 1
+
+
+def test_f32_down_fills_the_chip_with_one_token():
+    assert _f32((1, 1, 2048, 128, 768, 0, 8, 32), "vote")[1:3] == (4, 512)
+    assert _f32((1, 1, 2048, 128, 768, 0, 8, 32), "vote", "bf16") == (0, 0, 0, 0)
