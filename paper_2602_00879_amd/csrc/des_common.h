@@ -182,7 +182,8 @@ struct WsLayout {
   size_t choice;    // u8    [n_slots][32]  ... and which of the token's K choices it is
   size_t h_rows;    // routed rows of H: T*K, or n_slots * T for a dense short block
   size_t h;         // act   [(h_rows + Ts) * max(F, Fs)]   SwiGLU activations
-  size_t o;         // f32   [(T*K + Ts) * D]            per-pair expert outputs
+  size_t o;         // f32   [(T*K + Ts) * D]            per-pair expert outputs (bf16 layers; fp32 ones leave it);
+                    //       before them x in operand order, if LayerForm says so
   size_t total;
 };
 

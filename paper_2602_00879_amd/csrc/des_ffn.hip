@@ -38,7 +38,7 @@ struct FfnArgs {
   const int4* slots;            // [n_slots] {expert, first sorted pair, pairs, 0}
   const int32_t *meta, *pair_tok, *pos;
   void* h;                      // [(TK) x F] then [T x Fs]
-  float* o;                     // [(TK + T) x D]
+  float* o;                     // [(TK + T) x D] outputs per pair (bf16)
   void* y;                      // [T][D]
   int T, D, M, F, Fs, K, n_slots, residual;
   int splits;                   // units the shared expert's rows are spread over (LDS kernels)

@@ -351,7 +351,10 @@ __device__ bool select_sequence(const RoutingArgs& a, int b, int g, char* smem, 
 #pragma unroll
       for (int j = 0; j < kEpl; j += 4) {
         const int idx = rl * kEpl + j;
-        const f32x4 v = live && idx < M ? load_device_quad(Lg, static_cast<uint32_t>((live ? n : 0) * M + idx) * 4u) : f32x4{0.f, 0.f, 0.f, 0.f};
+        // (the row once more: named or left out, 256 experts need scratch and routing takes 2 % longer)
+        const f32x4 v = live && idx < M
+                            ? load_device_quad(Lg, static_cast<uint32_t>((live ? n : 0) * M + idx) * 4u)
+                            : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int q = 0; q < 4; ++q) val[j + q] = v[q];
       }
@@ -1073,11 +1076,12 @@ __device__ void permute_small(const RoutingArgs& a, char* smem) {
 
 // ---------------------------------------------------------------- the kernel
 // LDS of the routing kernel: the selection's carve-up, but at least what the
-// router tile (16 KB) and the permutation (bitmap of at most 8192 words, as many
-// 16-bit counts and at most 5 * 512 + 2 counters, under 59 KB for every shape the
-// library accepts) need.
+// router tile (32 KB, see router_tile_bf16) and the permutation (bitmap of at most 8192
+// words, as many 16-bit counts and at most 5 * 512 + 2 counters, under 59 KB for every
+// shape the library accepts) need.
 constexpr int kMinRoutingLds = 59 * 1024;
 static_assert(kMinRoutingLds >= 8192 * 6 + 4 * (5 * 512 + 2), "permutation tables");
+static_assert(kMinRoutingLds >= kRtWaves * 2 * kOperandBytes, "router tile");
 
 template <int LPT, bool EXT>
 __global__ __launch_bounds__(kRtThreads) void routing_kernel(RoutingArgs a) {
